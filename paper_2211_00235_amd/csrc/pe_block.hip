@@ -151,16 +151,20 @@ template <typename T> static void carve_trans_ctx(Carver& cv, TransCtx<T>& a, co
   a.h = cv.take<T>(N("h"), M * n * C, dtype_tag<T>());
   a.hbits = trans_bits_ok(C, n) ? cv.take<unsigned char>(nullptr, M * ((n * C) / 8), 0) : nullptr;   // not listed in the ctx table
 }
-template <typename T> static void carve_trimul_ctx(Carver& cv, TriMulCtx<T>& a, const char* pre, long long Mz, int cz, int ct) {
+// Row pitch of the triangle multiplication's channel-major planes [c][r][pitch]: r rounded up to 8 elements (the padding is
+// kept at zero), so that the vector kernels take every residue count.  r itself where the fused projection + gating
+// epilogue, which writes the padding, does not apply (c_tri not a multiple of 32).
+static int tm_pitch(const pe_dims& d) { return d.c_tri % 32 == 0 ? (d.r + 7) / 8 * 8 : d.r; }
+template <typename T> static void carve_trimul_ctx(Carver& cv, TriMulCtx<T>& a, const char* pre, long long Mz, long long Pz, int cz, int ct) {
   char nm[32];
   auto N = [&](const char* s) { snprintf(nm, sizeof(nm), "%s.%s", pre, s); return nm; };
   a.zhat = cv.take<T>(N("zhat"), Mz * cz, dtype_tag<T>());
   a.stats = cv.take<float>(N("stats"), Mz * 2, PE_F32);
-  a.proj_t = cv.take<T>(N("proj_t"), Mz * 4 * ct, dtype_tag<T>());
-  a.a_t = cv.take<T>(N("a_t"), Mz * ct, dtype_tag<T>());
-  a.b_t = cv.take<T>(N("b_t"), Mz * ct, dtype_tag<T>());
+  a.proj_t = cv.take<T>(N("proj_t"), Pz * 4 * ct, dtype_tag<T>());
+  a.a_t = cv.take<T>(N("a_t"), Pz * ct, dtype_tag<T>());
+  a.b_t = cv.take<T>(N("b_t"), Pz * ct, dtype_tag<T>());
   a.g = cv.take<T>(N("g"), Mz * cz, dtype_tag<T>());
-  a.x_t = cv.take<T>(N("x_t"), Mz * ct, dtype_tag<T>());
+  a.x_t = cv.take<T>(N("x_t"), Pz * ct, dtype_tag<T>());
   a.stats_out = cv.take<float>(N("stats_out"), Mz * 2, PE_F32);
   a.xhat = cv.take<T>(N("xhat"), Mz * ct, dtype_tag<T>());
   a.u = cv.take<T>(N("u"), Mz * cz, dtype_tag<T>());
@@ -197,10 +201,10 @@ template <typename T> static size_t carve_ctx(char* base, const pe_dims& d, Ctx<
   C.opm.b = C.opm.a + Mm * d.c_opm;
   C.opm.inv_norm = cv.take<float>("opm.inv_norm", Mz, PE_F32);
   C.opm.O = cv.take<T>("opm.O", Mz * d.c_opm * d.c_opm, dtype_tag<T>());
-  carve_trimul_ctx<T>(cv, C.tmo, "tmo", Mz, d.c_z, d.c_tri);
+  carve_trimul_ctx<T>(cv, C.tmo, "tmo", Mz, r * tm_pitch(d), d.c_z, d.c_tri);
   C.z0 = d.variant != PE_VARIANT_PARALLEL ? cv.take<T>("z0", Mz * d.c_z, dtype_tag<T>()) : nullptr;
   C.z1 = cv.take<T>("z1", Mz * d.c_z, dtype_tag<T>());
-  carve_trimul_ctx<T>(cv, C.tmi, "tmi", Mz, d.c_z, d.c_tri);
+  carve_trimul_ctx<T>(cv, C.tmi, "tmi", Mz, r * tm_pitch(d), d.c_z, d.c_tri);
   C.z2 = cv.take<T>("z2", Mz * d.c_z, dtype_tag<T>());
   carve_attn_ctx<T>(cv, C.tas, "tas", Mz, d.c_z, HDz, d.h_pair, r, r, true, Mz);
   C.z3 = cv.take<T>("z3", Mz * d.c_z, dtype_tag<T>());
@@ -319,12 +323,15 @@ template <typename T> struct Runner {
   Arena pm, pp;   // partial sums of the parameter gradients: kept until the end of the backward pass
   long long Mm, Mz;
   int HDm, HDz;
+  int rp; long long Pz;   // row pitch and plane size of the channel-major tensors
 
   void init(const pe_dims& dd) {
     d = dd;
     build_param_layout(d, PL);
     Mm = (long long)d.s * d.r;
     Mz = (long long)d.r * d.r;
+    rp = tm_pitch(d);
+    Pz = (long long)d.r * rp;
     HDm = d.h_msa * d.d_msa;
     HDz = d.h_pair * d.d_pair;
   }
@@ -624,7 +631,7 @@ template <typename T> struct Runner {
     }
   }
   void gemm(hipStream_t st, const Operand& A, bool akc, const Operand& B, bool bkc, int M, int N, int K, int batch,
-            const EpiGeneric<T>& e, const char* what, Arena* split_arena = nullptr) {
+            const EpiGeneric<T>& e, const char* what, Arena* split_arena = nullptr, int b_rows = 0) {
     // A grid too small to fill the chip with a long contraction: split K, fp32 partials,
     // fixed-order finish kernel that applies the epilogue.
     const int tiles = ((M + 127) / 128) * ((N + 127) / 128);
@@ -655,7 +662,7 @@ template <typename T> struct Runner {
       return;
     }
     if (dry || err) return;
-    GemmShape sh{M, N, K, batch, 0};
+    GemmShape sh{M, N, K, batch, 0, 0, b_rows};
     prof_begin(st);
     bool al = false, narrow = false;
     int rc = launch_gemm<T, EpiGeneric<T>>(st, A, akc, B, bkc, sh, e, &al, &narrow);
@@ -663,7 +670,7 @@ template <typename T> struct Runner {
       err = PE_ERR_DIMS;
       if (h) h->last_error = std::string("ReLU bit mask without the vector epilogue: ") + what;
     }
-    // the exact instantiation (operand layouts, epilogue path, feature mask F; F = 8191 is the general kernel)
+    // the exact instantiation (operand layouts, epilogue path, feature mask F; F = 16383 is the general kernel)
     char kn[64];
     if (narrow) snprintf(kn, sizeof(kn), "gemm64_kernel<EpiGeneric,F=%d>", g_gemm_last_features);
     else snprintf(kn, sizeof(kn), "gemm_kernel<%s,%s,%s,EpiGeneric,F=%d>", akc ? "kc" : "xc", bkc ? "kc" : "xc", al ? "vec" : "elem",
@@ -1006,6 +1013,17 @@ template <typename T> struct Runner {
     }
   }
 
+  // channel-major operands of the triangle multiplication: a plane's rows along the contraction (kc) or its columns (xc);
+  // the rows [first residue][second residue] of the channel-last pair tensor as seen from plane positions, and the
+  // number of positions up to the last one that is not padding
+  Operand op_tm(const T* p, bool kc) const { return op_padded(kc ? op_plain(p, rp, Pz) : op_trans(p, rp, Pz)); }
+  Operand op_zrows(const T* p, int ch) const {
+    Operand o = op_plain(p, ch);
+    if (rp != d.r) { o.x_in = rp; o.x_outer = (long long)d.r * ch; }
+    return o;
+  }
+  int zrows_end() const { return (d.r - 1) * rp + d.r; }
+  PlanePos plane_pos() const { return PlanePos{d.r, rp}; }
   void trimul_sub_fwd(hipStream_t st, const TriMulP& p, const TriMulW<T>& w, TriMulCtx<T>& c, const T* z, T* zout,
                       bool outgoing) {
     const int cz = d.c_z, ct = d.c_tri, r = d.r;
@@ -1013,10 +1031,10 @@ template <typename T> struct Runner {
     bool gated = false;   // projection, gate pre-activation and gated operands from one kernel
     if (!dry && !err && w.wt_pi) {
       EpiTmGate<T> eg;
-      eg.proj_t = c.proj_t; eg.a_t = c.a_t; eg.b_t = c.b_t; eg.bias = w.bias_p; eg.mask = pair_mask; eg.ct = ct; eg.Mz = Mz;
-      const Operand A = op_plain(w.wt_pi, cz), B = op_plain(c.zhat, cz);
-      GemmShape sh{4 * ct, (int)Mz, cz, 1, 0, 0};
-      if (eg.vec_ok((int)Mz) && gemm_operand_ok<T>(A, true, 4 * ct, sh) && gemm_operand_ok<T>(B, true, (int)Mz, sh)) {
+      eg.proj_t = c.proj_t; eg.a_t = c.a_t; eg.b_t = c.b_t; eg.bias = w.bias_p; eg.mask = pair_mask; eg.ct = ct; eg.Mz = Pz; eg.r = r; eg.pitch = rp;
+      const Operand A = op_plain(w.wt_pi, cz), B = op_zrows(c.zhat, cz);
+      GemmShape sh{4 * ct, (int)Pz, cz, 1, 0, 0, zrows_end()};
+      if (eg.vec_ok((int)Pz) && gemm_operand_ok<T>(A, true, 4 * ct, sh) && gemm_operand_ok<T>(B, true, (int)Pz, sh)) {
         prof_begin(st);
         int rc = launch_gemm<T, EpiTmGate<T>>(st, A, true, B, true, sh, eg);
         prof_end(st, "trimul proj+gate", "gemm_kernel<kc,kc,vec,EpiTmGate>", 2.0 * 4 * ct * Mz * cz,
@@ -1026,6 +1044,7 @@ template <typename T> struct Runner {
         gated = true;
       }
     }
+    if (!gated && rp != r && !dry && !err) { err = PE_ERR_DIMS; if (h) h->last_error = "trimul: padded planes without the fused projection"; }
     if (!gated) {  // channel-major projections: proj_t[4ct][Mz] = W_p^T[4ct][cz] . zhat^T
       EpiGeneric<T> e = epi_plain<T>(c.proj_t, Mz);
       e.bias_m = w.bias_p;
@@ -1042,28 +1061,29 @@ template <typename T> struct Runner {
     }
     {  // per-channel contraction over the third residue
       EpiGeneric<T> e = epi_plain<T>(c.x_t, r);
-      e.out_batch = Mz;
-      if (outgoing) gemm(st, op_plain(c.a_t, r, Mz), true, op_plain(c.b_t, r, Mz), true, r, r, r, ct, e, "trimul out");
-      else gemm(st, op_trans(c.a_t, r, Mz), false, op_trans(c.b_t, r, Mz), false, r, r, r, ct, e, "trimul in");
+      e.om_stride = rp;
+      e.out_batch = Pz;
+      if (outgoing) gemm(st, op_tm(c.a_t, true), true, op_tm(c.b_t, true), true, r, rp, r, ct, e, "trimul out", nullptr, r);
+      else gemm(st, op_tm(c.a_t, false), false, op_tm(c.b_t, false), false, r, rp, r, ct, e, "trimul in");
     }
     bool lnc_t = false;   // bf16, 64 or 128 channels: the kernels that move 256-byte runs
     if constexpr (std::is_same<T, bf16>::value)
-      lnc_t = (ct == 64 || ct == 128) && Mz % 8 == 0 && al16(c.x_t) && al16(c.xhat);
+      lnc_t = (ct == 64 || ct == 128) && Pz % 8 == 0 && al16(c.x_t) && al16(c.xhat);
     if (!dry && !err && lnc_t) {
       if constexpr (std::is_same<T, bf16>::value) {
-        const unsigned g128 = (unsigned)((Mz + 127) / 128);
+        const unsigned g128 = (unsigned)((Pz + 127) / 128);
         if (ct == 128)
           PE_LAUNCH("ln_cmajor_fwd", 0, 2.0 * Mz * ct * sizeof(T), st, ln_cmajor_fwd_t_kernel<16>, dim3(g128), dim3(256), 0, c.x_t, P(p.ln_out_g),
-                    P(p.ln_out_b), c.xhat, c.stats_out, Mz, d.ln_eps);
+                    P(p.ln_out_b), c.xhat, c.stats_out, Pz, d.ln_eps, plane_pos());
         else
           PE_LAUNCH("ln_cmajor_fwd", 0, 2.0 * Mz * ct * sizeof(T), st, ln_cmajor_fwd_t_kernel<8>, dim3(g128), dim3(256), 0, c.x_t, P(p.ln_out_g),
-                    P(p.ln_out_b), c.xhat, c.stats_out, Mz, d.ln_eps);
+                    P(p.ln_out_b), c.xhat, c.stats_out, Pz, d.ln_eps, plane_pos());
       }
     }
     if (!dry && !err && !lnc_t) {
       size_t lds = (size_t)64 * (ct + 1) * sizeof(float);
-#define PE_LNC_FWD(N) PE_LAUNCH("ln_cmajor_fwd", 0, 2.0 * Mz * ct * sizeof(T), st, (ln_cmajor_fwd_fast_kernel<T, N>), dim3((unsigned)((Mz + 63) / 64)), dim3(256), lds, c.x_t, P(p.ln_out_g), P(p.ln_out_b), c.xhat, c.stats_out, Mz, ct, d.ln_eps)
-      if (Mz % 4 == 0 && ct % 8 == 0) {
+#define PE_LNC_FWD(N) PE_LAUNCH("ln_cmajor_fwd", 0, 2.0 * Mz * ct * sizeof(T), st, (ln_cmajor_fwd_fast_kernel<T, N>), dim3((unsigned)((Pz + 63) / 64)), dim3(256), lds, c.x_t, P(p.ln_out_g), P(p.ln_out_b), c.xhat, c.stats_out, Pz, ct, d.ln_eps, plane_pos())
+      if (Pz % 4 == 0 && ct % 8 == 0) {
         const int nit = (ct + 15) / 16;   // c_tri <= 192
         if (nit <= 2) PE_LNC_FWD(2); else if (nit <= 4) PE_LNC_FWD(4); else if (nit <= 8) PE_LNC_FWD(8); else PE_LNC_FWD(12);
       }
@@ -1356,10 +1376,10 @@ template <typename T> struct Runner {
     T* du = (T*)ar.alloc((size_t)Mz * cz * sizeof(T));
     T* dgraw = (T*)ar.alloc((size_t)Mz * cz * sizeof(T));
     T* dxh_o = (T*)ar.alloc((size_t)Mz * ct * sizeof(T));
-    T* dx_t = (T*)ar.alloc((size_t)Mz * ct * sizeof(T));
-    T* da_t = (T*)ar.alloc((size_t)Mz * ct * sizeof(T));
-    T* db_t = (T*)ar.alloc((size_t)Mz * ct * sizeof(T));
-    T* dproj_t = (T*)ar.alloc((size_t)Mz * 4 * ct * sizeof(T));
+    T* dx_t = (T*)ar.alloc((size_t)Pz * ct * sizeof(T));
+    T* da_t = (T*)ar.alloc((size_t)Pz * ct * sizeof(T));
+    T* db_t = (T*)ar.alloc((size_t)Pz * ct * sizeof(T));
+    T* dproj_t = (T*)ar.alloc((size_t)Pz * 4 * ct * sizeof(T));
     T* dzh = (T*)ar.alloc((size_t)Mz * cz * sizeof(T));
     if (!dry && !err) {
       long long n = Mz * cz;
@@ -1375,25 +1395,25 @@ template <typename T> struct Runner {
     {  // LayerNorm (channel-major input) backward
       bool lnc_t = false;   // bf16, 64 or 128 channels: the kernel that moves 256-byte runs (128 positions per workgroup)
       if constexpr (std::is_same<T, bf16>::value)
-        lnc_t = (ct == 64 || ct == 128) && Mz % 8 == 0 && al16(c.x_t) && al16(dxh_o) && al16(dx_t);
-      int grid = lnc_t ? (int)((Mz + 127) / 128) : (int)((Mz + 63) / 64);
+        lnc_t = (ct == 64 || ct == 128) && Pz % 8 == 0 && al16(c.x_t) && al16(dxh_o) && al16(dx_t);
+      int grid = lnc_t ? (int)((Pz + 127) / 128) : (int)((Pz + 63) / 64);
       float* part = (float*)part_arena(ar).alloc((size_t)grid * 2 * ct * sizeof(float));
       if (!dry && !err && lnc_t) {
         if constexpr (std::is_same<T, bf16>::value) {
           if (ct == 128)
             PE_LAUNCH("ln_cmajor_bwd", 0, 3.0 * Mz * ct * sizeof(T), st, ln_cmajor_bwd_t_kernel<16>, dim3(grid), dim3(256), 0, dxh_o, c.x_t, c.stats_out,
-                      P(p.ln_out_g), dx_t, part, Mz);
+                      P(p.ln_out_g), dx_t, part, Pz, plane_pos());
           else
             PE_LAUNCH("ln_cmajor_bwd", 0, 3.0 * Mz * ct * sizeof(T), st, ln_cmajor_bwd_t_kernel<8>, dim3(grid), dim3(256), 0, dxh_o, c.x_t, c.stats_out,
-                      P(p.ln_out_g), dx_t, part, Mz);
+                      P(p.ln_out_g), dx_t, part, Pz, plane_pos());
           ReduceSeg sg[2] = {{0, ct, p.ln_out_g, 0}, {ct, ct, p.ln_out_b, 0}};
           reduce_to(ar, part, grid, 2LL * ct, 1, 2 * ct, 2, sg);
         }
       }
       if (!dry && !err && !lnc_t) {
         size_t lds = (size_t)64 * (ct + 1) * sizeof(float);
-#define PE_LNC_BWD(N) PE_LAUNCH("ln_cmajor_bwd", 0, 3.0 * Mz * ct * sizeof(T), st, (ln_cmajor_bwd_fast_kernel<T, N>), dim3(grid), dim3(256), lds, dxh_o, c.x_t, c.stats_out, P(p.ln_out_g), dx_t, part, Mz, ct)
-        if (Mz % 4 == 0 && ct % 8 == 0) {
+#define PE_LNC_BWD(N) PE_LAUNCH("ln_cmajor_bwd", 0, 3.0 * Mz * ct * sizeof(T), st, (ln_cmajor_bwd_fast_kernel<T, N>), dim3(grid), dim3(256), lds, dxh_o, c.x_t, c.stats_out, P(p.ln_out_g), dx_t, part, Pz, ct, plane_pos())
+        if (Pz % 4 == 0 && ct % 8 == 0) {
           const int nit = (ct + 15) / 16;   // c_tri <= 192
           if (nit <= 2) PE_LNC_BWD(2); else if (nit <= 4) PE_LNC_BWD(4); else if (nit <= 8) PE_LNC_BWD(8); else PE_LNC_BWD(12);
         }
@@ -1408,23 +1428,25 @@ template <typename T> struct Runner {
     // contraction backward, per channel; where the vector path applies the gating backward is the epilogue of these
     // GEMMs (da_t / db_t are never stored), else they are followed by the gating kernel
     bool gate_fused = false;
+    Operand A1, B1, A2, B2;
+    bool a1k, b1k, a2k, b2k;
     {
-      Operand A1, B1, A2, B2;
-      bool a1k, b1k, a2k, b2k;
       if (outgoing) {
-        A1 = op_plain(dx_t, r, Mz); a1k = true; B1 = op_trans(c.b_t, r, Mz); b1k = false;
-        A2 = op_trans(dx_t, r, Mz); a2k = false; B2 = op_trans(c.a_t, r, Mz); b2k = false;
+        // da[i,k] = sum_j dx[i,j] b[j,k];  db[j,k] = sum_i dx[i,j] a[i,k]
+        A1 = op_tm(dx_t, true); a1k = true; B1 = op_tm(c.b_t, false); b1k = false;
+        A2 = op_tm(dx_t, false); a2k = false; B2 = op_tm(c.a_t, false); b2k = false;
       } else {
-        A1 = op_plain(c.b_t, r, Mz); a1k = true; B1 = op_plain(dx_t, r, Mz); b1k = true;
-        A2 = op_plain(c.a_t, r, Mz); a2k = true; B2 = op_trans(dx_t, r, Mz); b2k = false;
+        // da[k,i] = sum_j b[k,j] dx[i,j];  db[k,j] = sum_i a[k,i] dx[i,j]
+        A1 = op_tm(c.b_t, true); a1k = true; B1 = op_tm(dx_t, true); b1k = true;
+        A2 = op_tm(c.a_t, true); a2k = true; B2 = op_tm(dx_t, false); b2k = false;
       }
       EpiTmGateBwd<T> ga;
-      ga.proj_t = c.proj_t; ga.mask = pair_mask; ga.dproj_t = dproj_t; ga.ct = ct; ga.r = r; ga.side = 0; ga.Mz = Mz;
+      ga.proj_t = c.proj_t; ga.mask = pair_mask; ga.dproj_t = dproj_t; ga.ct = ct; ga.r = r; ga.side = 0; ga.Mz = Pz; ga.pitch = rp;
       EpiTmGateBwd<T> gb = ga;
       gb.side = 1;
-      GemmShape sh{r, r, r, ct, 0, 0};
-      if (!dry && !err && ga.vec_ok(r) && gemm_operand_ok<T>(A1, a1k, r, sh) && gemm_operand_ok<T>(B1, b1k, r, sh) &&
-          gemm_operand_ok<T>(A2, a2k, r, sh) && gemm_operand_ok<T>(B2, b2k, r, sh)) {
+      GemmShape sh{r, rp, r, ct, 0, 0, r};
+      if (!dry && !err && ga.vec_ok(rp) && gemm_operand_ok<T>(A1, a1k, r, sh) && gemm_operand_ok<T>(B1, b1k, rp, sh) &&
+          gemm_operand_ok<T>(A2, a2k, r, sh) && gemm_operand_ok<T>(B2, b2k, rp, sh)) {
         gate_fused = true;
         const double fl = 2.0 * r * r * r * ct, by = (2.0 * r * r + 5.0 * r * r) * ct * sizeof(T);
         prof_begin(st);
@@ -1444,15 +1466,9 @@ template <typename T> struct Runner {
     if (!gate_fused) {
       EpiGeneric<T> ea = epi_plain<T>(da_t, r); ea.out_batch = Mz;
       EpiGeneric<T> eb = epi_plain<T>(db_t, r); eb.out_batch = Mz;
-      if (outgoing) {
-        // da[i,k] = sum_j dx[i,j] b[j,k];  db[j,k] = sum_i dx[i,j] a[i,k]
-        gemm(st, op_plain(dx_t, r, Mz), true, op_trans(c.b_t, r, Mz), false, r, r, r, ct, ea, "trimul da");
-        gemm(st, op_trans(dx_t, r, Mz), false, op_trans(c.a_t, r, Mz), false, r, r, r, ct, eb, "trimul db");
-      } else {
-        // da[k,i] = sum_j b[k,j] dx[i,j];  db[k,j] = sum_i a[k,i] dx[i,j]
-        gemm(st, op_plain(c.b_t, r, Mz), true, op_plain(dx_t, r, Mz), true, r, r, r, ct, ea, "trimul da");
-        gemm(st, op_plain(c.a_t, r, Mz), true, op_trans(dx_t, r, Mz), false, r, r, r, ct, eb, "trimul db");
-      }
+      if (rp != r && !dry && !err) { err = PE_ERR_DIMS; if (h) h->last_error = "trimul: padded planes without the fused gating backward"; }
+      gemm(st, A1, a1k, B1, b1k, r, r, r, ct, ea, "trimul da");
+      gemm(st, A2, a2k, B2, b2k, r, r, r, ct, eb, "trimul db");
     }
     if (!dry && !err && !gate_fused) {
       long long n = (long long)ct * Mz;
@@ -1465,11 +1481,14 @@ template <typename T> struct Runner {
     }
     { ReduceSeg sg[4] = {{0, ct, p.w_ap, ct}, {ct, ct, p.w_ag, ct}, {2 * ct, ct, p.w_bp, ct}, {3 * ct, ct, p.w_bg, ct}};
       ReduceSeg cb[4] = {{0, ct, p.b_ap, 0}, {ct, ct, p.b_ag, 0}, {2 * ct, ct, p.b_bp, 0}, {3 * ct, ct, p.b_bg, 0}};
-      gemm_dw(st, ar, op_trans(c.zhat, cz), false, op_plain(dproj_t, Mz), true, cz, 4 * ct, Mz, 4, sg, "trimul dWp", 4, cb); }
+      Operand X = op_trans(c.zhat, cz);   // contraction over plane positions (padding: zeros in dproj_t)
+      if (rp != r) { X.k_in = rp; X.k_outer = (long long)r * cz; }
+      gemm_dw(st, ar, X, false, op_padded(op_plain(dproj_t, Pz)), true, cz, 4 * ct, zrows_end(), 4, sg, "trimul dWp", 4, cb); }
     { ReduceSeg sg[1] = {{0, cz, p.w_g, cz}}, cb = {0, cz, p.b_g, 0};
       gemm_dw(st, ar, op_trans(c.zhat, cz), false, op_trans(dgraw, cz), false, cz, cz, Mz, 1, sg, "trimul dWg", 1, &cb); }
     { EpiGeneric<T> e = epi_plain<T>(dzh, cz);
-      gemm(st, op_trans(dproj_t, Mz), false, op_plain(w.wn_p, 4 * ct), true, (int)Mz, cz, 4 * ct, 1, e, "trimul dzhat p"); }
+      if (rp != r) { e.om_in = rp; e.om_used = r; e.om_outer = (long long)r * cz; }
+      gemm(st, op_trans(dproj_t, Pz), false, op_plain(w.wn_p, 4 * ct), true, (int)Pz, cz, 4 * ct, 1, e, "trimul dzhat p"); }
     gemm_ln_bwd(st, ar, op_plain(dgraw, cz), op_plain(w.wn_g, cz), Mz, cz, cz, dzh, true, z, c.stats, p.ln_in_g, p.ln_in_b, g, g,
                 "trimul dzhat g");
     end_subop(ar);

@@ -393,6 +393,19 @@ __global__ __launch_bounds__(256) void ln_cmajor_bwd_kernel(const T* dy, const T
   }
 }
 
+// Channel-major planes hold M = r * pitch positions, position p = (p / pitch, p % pitch); with pitch > r (odd residue
+// counts: every plane row starts on a 16-byte boundary) the positions p % pitch >= r are padding, zeros in every plane.
+struct PlanePos {
+  int r, pitch;
+  // channel-last row of position p; ok is cleared for padding
+  PE_DEV long long row(long long p, bool& ok) const {
+    if (pitch == r) return p;
+    const unsigned q = (unsigned)p / (unsigned)pitch, j = (unsigned)p - q * (unsigned)pitch;
+    ok = ok && j < (unsigned)r;
+    return (long long)q * r + j;
+  }
+};
+
 // Fast forms for M % 4 == 0 and C % 8 == 0: thread (pl = tid%16, cl = tid/16) moves 4
 // consecutive positions of channel cl, cl+16, .. per load (8 / 16 bytes per lane, 128 / 256
 // bytes per 16 lanes); the channel-last side moves 8 channels per lane.
@@ -401,7 +414,7 @@ __global__ __launch_bounds__(256) void ln_cmajor_bwd_kernel(const T* dy, const T
 // trip count waits for memory once per channel) and the backward pass keeps x in registers.
 template <typename T, int NIT>
 __global__ __launch_bounds__(256) void ln_cmajor_fwd_fast_kernel(const T* xt, const float* gamma, const float* beta,
-                                                                 T* y, float* stats, long long M, int C, float eps) {
+                                                                 T* y, float* stats, long long M, int C, float eps, PlanePos pos) {
   extern __shared__ float tile[];   // [64][C+1]
   __shared__ float rs[16][65], smu[64], srstd[64];
   const int pl = threadIdx.x & 15, cl = threadIdx.x >> 4, ld = C + 1;
@@ -453,15 +466,17 @@ __global__ __launch_bounds__(256) void ln_cmajor_fwd_fast_kernel(const T* xt, co
     for (int k = 0; k < 16; k++) t += rs[k][threadIdx.x];
     float rstd = rsqrtf(t / C + eps);
     srstd[threadIdx.x] = rstd;
-    long long m = m0 + threadIdx.x;
-    if (m < M) { stats[m * 2] = smu[threadIdx.x]; stats[m * 2 + 1] = rstd; }
+    bool used = m0 + threadIdx.x < M;
+    const long long m = pos.row(m0 + threadIdx.x, used);
+    if (used) { stats[m * 2] = smu[threadIdx.x]; stats[m * 2 + 1] = rstd; }
   }
   __syncthreads();
   const int C8 = C >> 3;
   for (int idx = threadIdx.x; idx < 64 * C8; idx += 256) {
     const int pp = idx / C8, c0 = (idx - pp * C8) * 8;
-    const long long mm = m0 + pp;
-    if (mm < M) {
+    bool used = m0 + pp < M;
+    const long long mm = pos.row(m0 + pp, used);
+    if (used) {
       const float mu = smu[pp], rstd = srstd[pp];
       float o[8];
 #pragma unroll
@@ -474,7 +489,7 @@ __global__ __launch_bounds__(256) void ln_cmajor_fwd_fast_kernel(const T* xt, co
 template <typename T, int NIT>
 __global__ __launch_bounds__(256) void ln_cmajor_bwd_fast_kernel(const T* dy, const T* xt, const float* stats,
                                                                  const float* gamma, T* dxt, float* partial,
-                                                                 long long M, int C) {
+                                                                 long long M, int C, PlanePos pos) {
   extern __shared__ float tile[];   // dy tile [64][C+1]
   __shared__ float r1[16][65], r2[16][65], t1[64], t2[64];
   const int pl = threadIdx.x & 15, cl = threadIdx.x >> 4, ld = C + 1;
@@ -494,14 +509,17 @@ __global__ __launch_bounds__(256) void ln_cmajor_bwd_fast_kernel(const T* dy, co
   float mu[4], rstd[4];
 #pragma unroll
   for (int k = 0; k < 4; k++) {
-    mu[k] = ok ? stats[(mb + k) * 2] : 0.0f;
-    rstd[k] = ok ? stats[(mb + k) * 2 + 1] : 0.0f;
+    bool used = ok;
+    const long long row = pos.row(mb + k, used);
+    mu[k] = used ? stats[row * 2] : 0.0f;
+    rstd[k] = used ? stats[row * 2 + 1] : 0.0f;   // padding: everything below comes out as zero
   }
   for (int idx = threadIdx.x; idx < 64 * C8; idx += 256) {
     const int pp = idx / C8, c0 = (idx - pp * C8) * 8;
-    const long long mm = m0 + pp;
+    bool used = m0 + pp < M;
+    const long long mm = pos.row(m0 + pp, used);
     float v[8];
-    if (mm < M) ld8<T>(dy + mm * C + c0, v);
+    if (used) ld8<T>(dy + mm * C + c0, v);
     else {
 #pragma unroll
       for (int e = 0; e < 8; e++) v[e] = 0.0f;
@@ -599,7 +617,7 @@ PE_DEV void lncm_store_tile(const bf16x8 (&xr)[LnCmT<LPR>::NV], bf16* tile) {
 
 template <int LPR>
 __global__ __launch_bounds__(256) void ln_cmajor_fwd_t_kernel(const bf16* xt, const float* gamma, const float* beta,
-                                                              bf16* y, float* stats, long long M, float eps) {
+                                                              bf16* y, float* stats, long long M, float eps, PlanePos pos) {
   typedef LnCmT<LPR> K;
   constexpr int C = K::C;
   __shared__ __attribute__((aligned(16))) bf16 tile[K::PT * C];
@@ -615,7 +633,8 @@ __global__ __launch_bounds__(256) void ln_cmajor_fwd_t_kernel(const bf16* xt, co
 #pragma unroll
   for (int it = 0; it < K::NIT; it++) {
     const int p = it * K::RPI + rr;
-    const long long row = m0 + p;
+    bool used = m0 + p < M;
+    const long long row = pos.row(m0 + p, used);
     const bf16x8 xb = *reinterpret_cast<const bf16x8*>(tile + K::off(p, c0));
     float xv[8], s = 0.0f;
 #pragma unroll
@@ -625,7 +644,7 @@ __global__ __launch_bounds__(256) void ln_cmajor_fwd_t_kernel(const bf16* xt, co
 #pragma unroll
     for (int e = 0; e < 8; e++) { const float t = xv[e] - mu; q += t * t; }
     const float rstd = rsqrtf(group_sum<LPR>(q) * (1.0f / C) + eps);
-    if (row < M) {
+    if (used) {
       float o[8];
 #pragma unroll
       for (int e = 0; e < 8; e++) o[e] = (xv[e] - mu) * rstd * gm[e] + bt[e];
@@ -637,7 +656,8 @@ __global__ __launch_bounds__(256) void ln_cmajor_fwd_t_kernel(const bf16* xt, co
 
 template <int LPR>
 __global__ __launch_bounds__(256) void ln_cmajor_bwd_t_kernel(const bf16* dy, const bf16* xt, const float* stats,
-                                                              const float* gamma, bf16* dxt, float* partial, long long M) {
+                                                              const float* gamma, bf16* dxt, float* partial, long long M,
+                                                              PlanePos pos) {
   typedef LnCmT<LPR> K;
   constexpr int C = K::C;
   __shared__ __attribute__((aligned(16))) bf16 tile[K::PT * C];
@@ -652,8 +672,8 @@ __global__ __launch_bounds__(256) void ln_cmajor_bwd_t_kernel(const bf16* dy, co
   float mu[K::NIT], rstd[K::NIT];
 #pragma unroll
   for (int it = 0; it < K::NIT; it++) {
-    const long long row = m0 + it * K::RPI + rr;
-    const bool ok = row < M;
+    bool ok = m0 + it * K::RPI + rr < M;
+    const long long row = pos.row(m0 + it * K::RPI + rr, ok);
 #pragma unroll
     for (int k = 0; k < 8; k++) dyr[it][k] = (bf16)0.0f;
     if (ok) dyr[it] = *reinterpret_cast<const bf16x8*>(dy + row * C + c0);

@@ -25,7 +25,10 @@
 struct Operand {
   const void* ptr;
   long long batch_stride;
-  int x_in; long long x_outer, x_stride;
+  int x_in;
+  int padded = 0;   // 1: rows of the contiguous index are followed by zeros up to a multiple of 8 elements, so 16-byte loads
+                    // may run past an extent (x or k, whichever is contiguous) that is not one
+  long long x_outer, x_stride;
   int k_in; long long k_outer, k_stride;
 };
 
@@ -35,6 +38,7 @@ static inline Operand op_plain(const void* p, long long ld /*row stride, k conti
   o.k_in = 1 << 30; o.k_outer = 0; o.k_stride = 1;
   return o;
 }
+static inline Operand op_padded(Operand o) { o.padded = 1; return o; }
 // operand stored [k][x] (x contiguous): contraction index strided by ld
 static inline Operand op_trans(const void* p, long long ld, long long batch = 0) {
   Operand o; o.ptr = p; o.batch_stride = batch;
@@ -47,6 +51,7 @@ struct GemmShape {
   int M, N, K, batch;
   int k_chunk;  // > 0: split-K; batch index selects the k range [b*k_chunk, min(K,(b+1)*k_chunk))
   int unit_n;   // block mapping: 0 = an XCD owns (batch, m-tile) units, 1 = (batch, n-tile) units (set by the launcher)
+  int n_rows;   // rows of B (gemm_kernel; 0 = N, filled in by the launcher): columns n_rows..N-1 are computed from zeros
 };
 
 // 8 consecutive storage elements <-> 8 floats (one or two 16-byte accesses)
@@ -108,13 +113,15 @@ template <> struct Raw8<float> {
 // code (and the run-time checks) of the features in F only; EF_ALL is the fully general kernel.
 enum : int { EF_BIASN = 1, EF_BIASM = 2, EF_ACT = 4, EF_RELUMASK = 8, EF_AUX = 16, EF_MUL = 32, EF_ROWSCALE = 64,
              EF_SCALE2D = 128, EF_RES = 256, EF_ACC = 512, EF_OM2 = 1024, EF_ON2 = 2048, EF_ALPHA = 4096,
-             EF_ALL = 8191 };
+             EF_ROWPAD = 8192, EF_ALL = 16383 };
 
 template <typename T> struct EpiGeneric {
   static constexpr bool HAS_COLSUM = false;
   static constexpr bool TM_GATE = false;
   T* out; long long out_batch;
-  int om_in; long long om_outer, om_stride;
+  int om_in;
+  int om_used;                   // > 0: rows m with m % om_in >= om_used are padding and not stored (plain outputs only)
+  long long om_outer, om_stride;
   int on_in; long long on_outer, on_stride;
   const float* bias_n; int bn_begin;     // v += bias_n[n] for n >= bn_begin
   const float* bias_m;
@@ -165,6 +172,7 @@ template <typename T> struct EpiGeneric {
     if (res) v += to_f(res[(long long)m * ld_res + n]);
     long long o = r.o + c.o;
     if (accumulate) v += to_f(out[o]);
+    if (om_used > 0 && m % om_in >= om_used) return;
     out[o] = from_f<T>(v);
   }
   // Vector epilogue: 8 consecutive columns n..n+7 of row m at once (host checked vec_ok).  The
@@ -184,6 +192,7 @@ template <typename T> struct EpiGeneric {
     if (om_in < (1 << 30)) f |= EF_OM2;
     if (on_in < (1 << 30)) f |= EF_ON2;
     if (alpha != 1.0f) f |= EF_ALPHA;
+    if (om_used > 0) f |= EF_ROWPAD;
     return f;
   }
   struct ColV { long long o; int s2; float bn[8]; };
@@ -279,6 +288,7 @@ template <typename T> struct EpiGeneric {
 #pragma unroll
       for (int e = 0; e < 8; e++) v[e] += t[e];
     }
+    if ((F & EF_ROWPAD) && om_used > 0 && (int)((unsigned)m % (unsigned)om_in) >= om_used) return;
     store8<T>(out + out_off<F>(b, m, c), v);
   }
   template <int F> PE_DEV void vec8(int b, int m, int n, const ColV& c, float (&v)[8]) const {
@@ -419,8 +429,9 @@ template <typename T> struct EpiTmGate {
   static constexpr bool TM_GATE = true;
   T* proj_t; T* a_t; T* b_t;
   const float* bias;     // [4 ct] in the order of proj_t's rows
-  const float* mask;     // [Mz]
-  int ct; long long Mz;
+  const float* mask;     // [r][r]
+  int ct; long long Mz;  // Mz: elements of a channel plane, r * pitch
+  int r, pitch;          // column n is pair position (n / pitch, n % pitch); columns n % pitch >= r are padding, stored as zeros
   struct Row { long long o; };
   struct Col { long long o; };
   PE_DEV Row row(int, int) const { return Row{0}; }
@@ -441,7 +452,7 @@ template <typename T> struct EpiTmGate {
 
 // Epilogue of the triangle multiplication's backward contractions with the gating backward folded in.  The batched
 // GEMM (batch index = channel) produces the cotangent d of the gated operand a (side 0) or b (side 1) at pair
-// position m * r + n; with p and g the stored projection and gate pre-activation at that (channel, position),
+// position (m, n), element m * pitch + n of a channel plane (columns n >= r are padding and get zeros); with p and g the stored projection and gate pre-activation at that (channel, position),
 //   d' = round(d) * mask,   dproj = d' * sigmoid(g),   dgate = d' * p * sigmoid(g) * (1 - sigmoid(g)),
 // written to the projection and gate rows of dproj_t ([a proj | a gate | b proj | b gate] x ct rows of Mz).  d is
 // rounded to the storage type first, so the results equal those of a separate pass over a stored d.
@@ -449,7 +460,8 @@ template <typename T> struct EpiTmGateBwd {
   static constexpr bool HAS_COLSUM = false;
   static constexpr bool TM_GATE = false;
   const T* proj_t; const float* mask; T* dproj_t;
-  int ct, r, side; long long Mz;
+  int ct, r, side; long long Mz;   // Mz = r * pitch
+  int pitch;
   struct Row { long long o; };
   struct Col { long long o; };
   PE_DEV Row row(int, int) const { return Row{0}; }
@@ -460,19 +472,27 @@ template <typename T> struct EpiTmGateBwd {
   template <int F> PE_DEV void colv(int, ColV&) const {}
   struct Pre8 { Raw8<T> p, g; Raw8<float> mk; };
   template <int F> PE_DEV void pre8(int b, int m, int n, const ColV&, Pre8& q) const {
-    const long long pos = (long long)m * r + n;
+    const long long pos = (long long)m * pitch + n;
     q.p.ld(proj_t + ((long long)(side * 2) * ct + b) * Mz + pos);
     q.g.ld(proj_t + ((long long)(side * 2 + 1) * ct + b) * Mz + pos);
-    q.mk.ld(mask + pos);
+    if (pitch == r) {
+      q.mk.ld(mask + pos);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; e++) {
+        q.mk.lo[e] = n + e < r ? mask[(long long)m * r + n + e] : 0.0f;
+        q.mk.hi[e] = n + 4 + e < r ? mask[(long long)m * r + n + 4 + e] : 0.0f;
+      }
+    }
   }
   template <int F> PE_DEV void apply8(int b, int m, int n, const ColV&, float (&v)[8], const Pre8& q) const {
-    const long long pos = (long long)m * r + n;
+    const long long pos = (long long)m * pitch + n;
     float pv[8], gv[8], mk[8], o0[8], o1[8];
     q.p.get(pv); q.g.get(gv); q.mk.get(mk);
 #pragma unroll
     for (int e = 0; e < 8; e++) {
       const float s = sigmoidf_(gv[e]);
-      const float dd = to_f(from_f<T>(v[e])) * mk[e];
+      const float dd = to_f(from_f<T>(v[e])) * mk[e];   // a padding column: v and mk are zero
       o0[e] = dd * s;
       o1[e] = dd * pv[e] * s * (1.0f - s);
     }
@@ -486,7 +506,7 @@ template <typename T> struct EpiTmGateBwd {
   }
   bool vec_ok(int N) const {
     auto p16 = [](const void* p) { return ((uintptr_t)p) % 16 == 0; };
-    return N % 8 == 0 && r % 8 == 0 && Mz % 8 == 0 && p16(proj_t) && p16(dproj_t) && p16(mask);
+    return N % 8 == 0 && pitch % 8 == 0 && p16(proj_t) && p16(dproj_t) && (pitch != r || p16(mask));
   }
 };
 
@@ -684,10 +704,10 @@ __global__ __launch_bounds__(256) void gemm_kernel(Operand A, Operand B, GemmSha
   RowAddr<T, A_KC> rowa;
   RowAddr<T, B_KC> rowb;
   rowa.init(A, m0, sh.M, tid);
-  rowb.init(B, n0, sh.N, tid);
+  rowb.init(B, n0, sh.n_rows, tid);
   if (kbeg < kend) {
     gemm_load_tile<T, A_KC, AL>(ra, pa, A, rowa, sh.M, kbeg, kend, tid);
-    gemm_load_tile<T, B_KC, AL>(rb, pb, B, rowb, sh.N, kbeg, kend, tid);
+    gemm_load_tile<T, B_KC, AL>(rb, pb, B, rowb, sh.n_rows, kbeg, kend, tid);
   }
   for (int k0 = kbeg; k0 < kend; k0 += C::BK) {
     __syncthreads();  // previous tile fully consumed
@@ -696,7 +716,7 @@ __global__ __launch_bounds__(256) void gemm_kernel(Operand A, Operand B, GemmSha
     __syncthreads();
     if (k0 + C::BK < kend) {
       gemm_load_tile<T, A_KC, AL>(ra, pa, A, rowa, sh.M, k0 + C::BK, kend, tid);
-      gemm_load_tile<T, B_KC, AL>(rb, pb, B, rowb, sh.N, k0 + C::BK, kend, tid);
+      gemm_load_tile<T, B_KC, AL>(rb, pb, B, rowb, sh.n_rows, k0 + C::BK, kend, tid);
     }
     if constexpr (Epi::HAS_COLSUM) {
       if (do_cs) {
@@ -742,10 +762,18 @@ __global__ __launch_bounds__(256) void gemm_kernel(Operand A, Operand B, GemmSha
       const int strip = (m0 >> 6) + wm, nside = epi.ct >> 5;
       const int side = strip / nside, ch0 = (strip % nside) * 32;
       float mk[2];
+      bool used[2];
 #pragma unroll
       for (int j = 0; j < 2; j++) {
         const int col = n0 + wn * 64 + j * 32 + l32;
-        mk[j] = col < sh.N ? epi.mask[col] : 0.0f;
+        int pad = 0;   // padding columns before this one
+        used[j] = col < sh.N;
+        if (epi.pitch != epi.r) {
+          const int row = (int)((unsigned)col / (unsigned)epi.pitch);
+          used[j] = used[j] && col - row * epi.pitch < epi.r;
+          pad = row * (epi.pitch - epi.r);
+        }
+        mk[j] = used[j] ? epi.mask[col - pad] : 0.0f;
       }
 #pragma unroll
       for (int a = 0; a < 16; a++) {
@@ -756,6 +784,13 @@ __global__ __launch_bounds__(256) void gemm_kernel(Operand A, Operand B, GemmSha
           acc[0][j][a] = to_f(from_f<T>(acc[0][j][a] + bp));   // as stored
           acc[1][j][a] = to_f(from_f<T>(acc[1][j][a] + bg));
         }
+      }
+      if (epi.pitch != epi.r) {
+#pragma unroll
+        for (int j = 0; j < 2; j++)
+#pragma unroll
+          for (int a = 0; a < 16; a++)
+            if (!used[j]) acc[0][j][a] = acc[1][j][a] = 0.0f;
       }
       __syncthreads();   // all waves are done with the operand tiles
 #pragma unroll
@@ -886,14 +921,14 @@ template <typename T> static inline bool gemm_operand_ok(const Operand& o, bool 
   if (kc) {
     if (o.k_stride != 1) return false;
     if (o.k_in % VEC && o.k_in < sh.K) return false;
-    if (sh.K % VEC) return false;
+    if (sh.K % VEC && !o.padded) return false;
     if (o.x_outer % VEC || (o.x_stride % VEC)) return false;
     if (o.k_outer % VEC) return false;
     if (sh.k_chunk > 0 && sh.k_chunk % GemmCfg<T>::BK) return false;
   } else {
     if (o.x_stride != 1) return false;
     if (o.x_in % VEC && o.x_in < X) return false;
-    if (X % VEC) return false;
+    if (X % VEC && !o.padded) return false;
     if (o.x_outer % VEC || o.k_outer % VEC || o.k_stride % VEC) return false;
   }
   return true;
@@ -2138,6 +2173,11 @@ static inline void launch_gemm_al(hipStream_t st, dim3 grid, const Operand& A, b
     if (!(a_kc && b_kc)) {
       PE_GEMM_SPEC_L(0)
       PE_GEMM_SPEC_L(EF_SCALE2D)
+      if (!a_kc && b_kc && (f & ~(EF_OM2 | EF_ROWPAD)) == 0) {   // channel-major planes with a padded pitch -> channel-last rows
+        hipLaunchKernelGGL((gemm_kernel<T, false, true, true, true, Epi, (EF_OM2 | EF_ROWPAD)>), grid, block, 0, st, A, B, sh, epi);
+        g_gemm_last_features = EF_OM2 | EF_ROWPAD;
+        return;
+      }
     }
 #undef PE_GEMM_SPEC_L
   }
@@ -2156,6 +2196,7 @@ static inline int launch_gemm(hipStream_t st, const Operand& A, bool a_kc, const
   GemmShape sh = shape;
   g_gemm_last_features = EF_ALL;
   if (sh.M <= 0 || sh.N <= 0 || sh.batch <= 0) return 0;
+  if (sh.n_rows <= 0) sh.n_rows = sh.N;
   if (a_kc ? A.k_stride != 1 : A.x_stride != 1) return -1;
   if (b_kc ? B.k_stride != 1 : B.x_stride != 1) return -1;
   if (sh.k_chunk > 0 && sh.k_chunk % GemmCfg<T>::BK) return -1;
@@ -2169,7 +2210,7 @@ static inline int launch_gemm(hipStream_t st, const Operand& A, bool a_kc, const
   sh.unit_n = gn_ < gm_ ? 1 : 0;
   dim3 grid((unsigned)(sh.unit_n ? gn_ : gm_));
   // narrow outputs of tall GEMMs: 64-row tiles (twice the workgroups)
-  const bool narrow = ve && a_kc && b_kc && sh.batch == 1 && sh.k_chunk == 0 && sh.N <= 128 && sh.M >= 128 * 256;
+  const bool narrow = ve && a_kc && b_kc && sh.n_rows == sh.N && sh.batch == 1 && sh.k_chunk == 0 && sh.N <= 128 && sh.M >= 128 * 256;
   if (used_narrow) *used_narrow = false;
   if (narrow && launch_gemm64<T, Epi>(st, A, B, sh, epi)) {
     if (used_narrow) *used_narrow = true;

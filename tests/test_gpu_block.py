@@ -86,6 +86,19 @@ def test_triangle_channel_major_layernorm_bf16(c_tri, r):
     _assert_small(errs, tol, stats)
 
 
+@pytest.mark.parametrize("dtype", [0, 1])
+@pytest.mark.parametrize("c_tri,r", [(32, 1), (32, 7), (64, 9), (128, 67), (96, 130), (32, 133)])
+def test_triangle_planes_with_padded_pitch(c_tri, r, dtype):
+    """Residue counts that are not multiples of 8: the channel-major planes get a row pitch of r rounded up to 8 with
+    zeros in the padding.  One row short of a multiple, one row beyond one, more than one 128-row tile; channel counts
+    of both channel-major LayerNorm kernels; nothing of the padding may reach an output or a gradient."""
+    dims, table, inp = _case("tiny", dtype=dtype, s=5, r=r, c_tri=c_tri, c_z=32)
+    table, n = param_table(dims)
+    inp = make_inputs(dims, table, n, ("random_residues", 0.1), 23)
+    errs, worst, tol, stats = check_case(dims, table, inp)
+    _assert(errs, worst, tol, stats)
+
+
 @pytest.mark.parametrize("use_ctx", [True, False])
 @pytest.mark.parametrize("dtype,r", [(0, 19), (1, 19), (1, 40), (0, 32), (1, 32)])
 def test_row_complete_layernorm_epilogues(dtype, r, use_ctx):
