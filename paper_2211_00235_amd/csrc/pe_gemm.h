@@ -525,6 +525,12 @@ template <typename T> struct GemmCfg {
   template <bool SW> static PE_DEV int off(int row, int c, int w) {
     return SW ? row * LDSS + ((c ^ ((row >> 3) & 7)) * VEC) + w : row * LDSS + c * VEC + w;
   }
+  // fp32: a fragment is one element per lane (32 rows at k, 32 rows at k + 1), so the tile of an x-contiguous operand
+  // needs no transpose.  It stays in memory order [k][128 rows] (16-byte stores of what was loaded, 32 consecutive
+  // words per half wave on a read) with the row index XOR-ed by 32 at odd k: the two halves of a wave read disjoint
+  // banks.  With the transposing store the fp32 parameter-gradient GEMMs ran at 43 TFLOP/s (256 x 1024 x 32768: 301 us).
+  static constexpr bool XMEM = sizeof(T) == 4;
+  static PE_DEV int xoff(int k, int row) { return k * 128 + (row ^ ((k & 1) << 5)); }
 };
 
 // element-wise (unaligned) variant of one 16-byte vector load: elements e = 0..VEC-1 along k (KC) or x
@@ -642,6 +648,11 @@ PE_DEV void gemm_store_tile(const typename Vec16<T>::type (&regs)[4], T* lds, in
   } else {
     constexpr int XB = 128 / VEC;
     int xb = tid % XB, kb = tid / XB;
+    if constexpr (GemmCfg<T>::XMEM) {
+#pragma unroll
+      for (int j = 0; j < 4; j++) *reinterpret_cast<V*>(lds + GemmCfg<T>::xoff(kb * 4 + j, xb * VEC)) = regs[j];
+      return;
+    }
     typedef T V4 __attribute__((ext_vector_type(4)));
 #pragma unroll
     for (int e = 0; e < VEC; e++) {
@@ -719,7 +730,10 @@ __global__ __launch_bounds__(256) void gemm_kernel(Operand A, Operand B, GemmSha
       gemm_load_tile<T, B_KC, AL>(rb, pb, B, rowb, sh.n_rows, k0 + C::BK, kend, tid);
     }
     if constexpr (Epi::HAS_COLSUM) {
-      if (do_cs) {
+      if (do_cs && C::XMEM && !B_KC) {
+#pragma unroll
+        for (int k = 0; k < C::BK; k++) cs += to_f(lds_b[C::xoff(k, tid)]);
+      } else if (do_cs) {
 #pragma unroll
         for (int ch = 0; ch < C::BK / C::VEC; ch++) {
           V v = *reinterpret_cast<const V*>(lds_b + C::template off<!B_KC>(tid, ch, 0));
@@ -734,8 +748,9 @@ __global__ __launch_bounds__(256) void gemm_kernel(Operand A, Operand B, GemmSha
 #pragma unroll
       for (int t = 0; t < 2; t++) {
         const int eo = kk * MM::KSTEP + g * MM::KP;
-        af[t] = MM::load(lds_a + C::template off<!A_KC>(wm * 64 + t * 32 + l32, eo / C::VEC, eo % C::VEC));
-        bf[t] = MM::load(lds_b + C::template off<!B_KC>(wn * 64 + t * 32 + l32, eo / C::VEC, eo % C::VEC));
+        const int ar = wm * 64 + t * 32 + l32, br = wn * 64 + t * 32 + l32;
+        af[t] = MM::load(lds_a + (C::XMEM && !A_KC ? C::xoff(eo, ar) : C::template off<!A_KC>(ar, eo / C::VEC, eo % C::VEC)));
+        bf[t] = MM::load(lds_b + (C::XMEM && !B_KC ? C::xoff(eo, br) : C::template off<!B_KC>(br, eo / C::VEC, eo % C::VEC)));
       }
 #pragma unroll
       for (int i = 0; i < 2; i++)
