@@ -125,7 +125,7 @@ template <typename T> constexpr int dtype_tag() { return sizeof(T) == 2 ? PE_BF1
 template <typename T> static void carve_attn_ctx(Carver& cv, AttnCtx<T>& a, const char* pre, long long M, int C, int HD,
                                                  int H, long long B, long long L, bool has_bias, long long Mz) {
   char nm[32];
-  auto N = [&](const char* s) { snprintf(nm, sizeof(nm), "%s.%s", pre, s); return nm; };
+  auto N = [&](const char* s) { if (cv.rec) snprintf(nm, sizeof(nm), "%s.%s", pre, s); return nm; };
   a.xhat = cv.take<T>(N("xhat"), M * C, dtype_tag<T>());
   a.stats = cv.take<float>(N("stats"), M * 2, PE_F32);
   a.qkvg = cv.take<T>(N("qkvg"), M * 4 * HD, dtype_tag<T>());
@@ -145,7 +145,7 @@ template <typename T> static void carve_attn_ctx(Carver& cv, AttnCtx<T>& a, cons
 static bool trans_bits_ok(int C, int n) { return C % 8 == 0 && (n * C) % 8 == 0; }
 template <typename T> static void carve_trans_ctx(Carver& cv, TransCtx<T>& a, const char* pre, long long M, int C, int n) {
   char nm[32];
-  auto N = [&](const char* s) { snprintf(nm, sizeof(nm), "%s.%s", pre, s); return nm; };
+  auto N = [&](const char* s) { if (cv.rec) snprintf(nm, sizeof(nm), "%s.%s", pre, s); return nm; };
   a.xhat = cv.take<T>(N("xhat"), M * C, dtype_tag<T>());
   a.stats = cv.take<float>(N("stats"), M * 2, PE_F32);
   a.h = cv.take<T>(N("h"), M * n * C, dtype_tag<T>());
@@ -157,7 +157,7 @@ template <typename T> static void carve_trans_ctx(Carver& cv, TransCtx<T>& a, co
 static int tm_pitch(const pe_dims& d) { return d.c_tri % 32 == 0 ? (d.r + 7) / 8 * 8 : d.r; }
 template <typename T> static void carve_trimul_ctx(Carver& cv, TriMulCtx<T>& a, const char* pre, long long Mz, long long Pz, int cz, int ct) {
   char nm[32];
-  auto N = [&](const char* s) { snprintf(nm, sizeof(nm), "%s.%s", pre, s); return nm; };
+  auto N = [&](const char* s) { if (cv.rec) snprintf(nm, sizeof(nm), "%s.%s", pre, s); return nm; };
   a.zhat = cv.take<T>(N("zhat"), Mz * cz, dtype_tag<T>());
   a.stats = cv.take<float>(N("stats"), Mz * 2, PE_F32);
   a.proj_t = cv.take<T>(N("proj_t"), Pz * 4 * ct, dtype_tag<T>());
@@ -359,6 +359,7 @@ template <typename T> struct Runner {
     if (hipEventCreate(&e) != hipSuccess) return nullptr;
     return e;
   }
+  bool timed() const { return h && h->timing; }
   hipEvent_t prof_e0 = nullptr;
   void prof_begin(hipStream_t st) {
     if (dry || err || !h || !h->timing) return;
@@ -649,8 +650,9 @@ template <typename T> struct Runner {
       bool al = false, dwx = false;
       int depth = 0;
       int rc = launch_gemm<T, EpiPartial>(st, A, akc, B, bkc, sh, ep, &al, &dwx, dw_groups(), &depth);
-      char kn[64];
-      if (dwx && depth) snprintf(kn, sizeof(kn), "gemm_dwp_kernel<%d>", depth);
+      char kn[64] = "";
+      if (!timed()) {}
+      else if (dwx && depth) snprintf(kn, sizeof(kn), "gemm_dwp_kernel<%d>", depth);
       else if (dwx) snprintf(kn, sizeof(kn), "gemm_dwx_kernel<%d>", dw_groups());
       else snprintf(kn, sizeof(kn), "gemm_kernel<%s,%s,%s,EpiPartial>", akc ? "kc" : "xc", bkc ? "kc" : "xc", al ? "vec" : "elem");
       prof_end(st, what, kn, 2.0 * M * N * K, ((double)M * K + (double)N * K) * sizeof(T));
@@ -671,8 +673,9 @@ template <typename T> struct Runner {
       if (h) h->last_error = std::string("ReLU bit mask without the vector epilogue: ") + what;
     }
     // the exact instantiation (operand layouts, epilogue path, feature mask F; F = 16383 is the general kernel)
-    char kn[64];
-    if (narrow) snprintf(kn, sizeof(kn), "gemm64_kernel<EpiGeneric,F=%d>", g_gemm_last_features);
+    char kn[64] = "";
+    if (!timed()) {}
+    else if (narrow) snprintf(kn, sizeof(kn), "gemm64_kernel<EpiGeneric,F=%d>", g_gemm_last_features);
     else snprintf(kn, sizeof(kn), "gemm_kernel<%s,%s,%s,EpiGeneric,F=%d>", akc ? "kc" : "xc", bkc ? "kc" : "xc", al ? "vec" : "elem",
                   g_gemm_last_features);
     prof_end(st, what, kn, 2.0 * M * N * K * batch, ((double)M * K + (double)N * K + (double)M * N) * batch * sizeof(T));
@@ -692,8 +695,8 @@ template <typename T> struct Runner {
       GemmShape sh{M, N, K, 1, 0, 0};
       prof_begin(st);
       if (launch_gemm64r<T, 1>(st, A, B, sh, e, ln)) {
-        char kn[64];
-        snprintf(kn, sizeof(kn), "gemm64r_kernel<F=%d,MODE=1,HB=%d>", g_gemm_last_features, nxt.direct ? (nxt.H <= 4 ? 4 : 8) : 0);
+        char kn[64] = "";
+        if (timed()) snprintf(kn, sizeof(kn), "gemm64r_kernel<F=%d,MODE=1,HB=%d>", g_gemm_last_features, nxt.direct ? (nxt.H <= 4 ? 4 : 8) : 0);
         prof_end(st, what, kn, 2.0 * M * N * K, ((double)M * K + (double)N * K + 2.0 * M * N) * sizeof(T));
         check(what);
         ln_done_set(nxt.y);
@@ -758,8 +761,9 @@ template <typename T> struct Runner {
       join_side(st);   // gout may alias a buffer the side stream is still reading
       prof_begin(st);
       if (launch_gemm64r<T, 2>(st, A, B, sh, e, ln)) {
-        char kn[64];
-        if (Cc == 256) snprintf(kn, sizeof(kn), "gemm64w_kernel<F=0,MODE=2>");
+        char kn[64] = "";
+        if (!timed()) {}
+        else if (Cc == 256) snprintf(kn, sizeof(kn), "gemm64w_kernel<F=0,MODE=2>");
         else snprintf(kn, sizeof(kn), "gemm64r_kernel<F=0,MODE=2,HB=%d,G2=%d>", bias_db ? (bias_H <= 4 ? 4 : 8) : 0, fin ? 1 : 0);
         prof_end(st, what, kn, 2.0 * M * Cc * K,
                  ((double)M * K + (double)Cc * K + (gin ? 3.0 : 2.0) * M * Cc + (acc ? 1.0 : 0.0) * M * Cc) * sizeof(T));
@@ -798,8 +802,9 @@ template <typename T> struct Runner {
       bool al = false, dwx = false;
       int depth = 0;
       int rc = launch_gemm<T, EpiPartial>(st, X, xkc, Y, ykc, sh, ep, &al, &dwx, dw_groups(), &depth);
-      char kn[64];
-      if (dwx && depth) snprintf(kn, sizeof(kn), "gemm_dwp_kernel<%d>", depth);
+      char kn[64] = "";
+      if (!timed()) {}
+      else if (dwx && depth) snprintf(kn, sizeof(kn), "gemm_dwp_kernel<%d>", depth);
       else if (dwx) snprintf(kn, sizeof(kn), "gemm_dwx_kernel<%d>", dw_groups());
       else snprintf(kn, sizeof(kn), "gemm_kernel<%s,%s,%s,EpiPartial>", xkc ? "kc" : "xc", ykc ? "kc" : "xc", al ? "vec" : "elem");
       prof_end(st, what, kn, 2.0 * rows * cols * K, ((double)rows * K + (double)cols * K) * sizeof(T));
@@ -1648,7 +1653,23 @@ template <typename T> static Plan make_plan(const pe_dims& d) {
   pl.part_p = (R.pp.high + 255) & ~(size_t)255;
   return pl;
 }
-static Plan plan_for(const pe_dims& d) { return d.dtype == PE_BF16 ? make_plan<bf16>(d) : make_plan<float>(d); }
+// The last few plans of this host thread, by dims.  A plan is a dry run of both passes' host code (about 20 us) and a
+// compute call asks for it two or three times; at the smallest blocks that was a third of the call's time.
+static Plan plan_for(const pe_dims& d) {
+  struct Slot { pe_dims d; Plan pl; };
+  constexpr int N = 8;
+  static thread_local Slot slots[N];
+  static thread_local int used = 0, next = 0;
+  static_assert(sizeof(pe_dims) == 4 * 16, "all 4-byte fields: compared as bytes");
+  for (int i = 0; i < used; i++)
+    if (!memcmp(&slots[i].d, &d, sizeof(d))) return slots[i].pl;
+  Slot& s = slots[next];
+  s.pl = d.dtype == PE_BF16 ? make_plan<bf16>(d) : make_plan<float>(d);
+  s.d = d;
+  if (used < N) used++;
+  next = (next + 1) % N;
+  return s.pl;
+}
 
 template <typename T> static void setup_runner(Runner<T>& R, pe_handle* h, const pe_dims& d, const Plan& pl, char* ws,
                                                char* ctx, hipStream_t sm, hipStream_t sp) {
@@ -2110,7 +2131,7 @@ int pe_param_table(const pe_dims* d, pe_param_entry* out, int cap) {
   int rc = pe_check_dims_impl(d);
   if (rc) return rc;
   ParamLayout L;
-  build_param_layout(*d, L);
+  build_param_layout(*d, L, true);
   int n = (int)L.entries.size();
   if (out) {
     if (cap < n) return PE_ERR_ARG;

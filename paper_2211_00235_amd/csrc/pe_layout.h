@@ -53,21 +53,23 @@ inline int pe_check_dims_impl(const pe_dims* d, const char** why = nullptr) {
 
 struct ParamBuilder {
   ParamLayout& L;
+  bool list;      // fill L.entries (the parameter table); a compute call needs the offsets only
   long long off = 0;
-  explicit ParamBuilder(ParamLayout& l) : L(l) {}
+  ParamBuilder(ParamLayout& l, bool list_) : L(l), list(list_) {}
   long long add(const char* pre, const char* nm, int a, int b, int kind) {
+    long long o = off;
+    off += (long long)a * (b ? b : 1);
+    if (!list) return o;
     pe_param_entry e;
     memset(&e, 0, sizeof(e));
     snprintf(e.name, sizeof(e.name), "%s.%s", pre, nm);
-    e.offset = off;
+    e.offset = o;
     e.ndim = b ? 2 : 1;
     e.shape[0] = a;
     e.shape[1] = b;
     e.fan_in = (kind == 0) ? a : 0;
     e.kind = kind;
     L.entries.push_back(e);
-    long long o = off;
-    off += (long long)a * (b ? b : 1);
     return o;
   }
 };
@@ -116,9 +118,9 @@ inline void build_trimul(ParamBuilder& B, TriMulP& p, const char* pre, int cz, i
   p.w_o = B.add(pre, "w_o", ct, cz, 0); p.b_o = B.add(pre, "b_o", cz, 0, 3);
 }
 
-inline void build_param_layout(const pe_dims& d, ParamLayout& L) {
+inline void build_param_layout(const pe_dims& d, ParamLayout& L, bool with_entries = false) {
   L.entries.clear();
-  ParamBuilder B(L);
+  ParamBuilder B(L, with_entries);
   build_attn(B, L.row, "row", d.c_m, d.h_msa, d.d_msa, d.c_z, true, false);
   build_attn(B, L.col, "col", d.c_m, d.h_msa, d.d_msa, 0, false, d.col_global != 0);
   build_trans(B, L.mtrans, "mtrans", d.c_m, d.n_trans);
