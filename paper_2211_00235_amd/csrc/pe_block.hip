@@ -17,6 +17,7 @@
 #include "pe_gcol.h"
 #include "pe_gemm.h"
 #include "pe_layout.h"
+#include "pe_small.h"
 
 // Scratch of pe_block_fwd_static: one array per device, held from the load of the library's code object
 // until the process ends.  Host code never uses the array's name as an address: pe_create looks the
@@ -107,7 +108,7 @@ template <typename T> struct Ctx {
 
 template <typename T> struct AttnW { T *wt_qkvg, *wn_qkvg, *wt_o, *wn_o; };
 template <typename T> struct TransW { T *wt_1, *wn_1, *wt_2, *wn_2; };
-template <typename T> struct OpmW { T *wt_ab, *wn_ab, *wt_o, *wn_o; };
+template <typename T> struct OpmW { T *wt_ab, *wn_ab, *wt_o, *wn_o; float* bias_ab; };
 // wt_pi: the rows of wt_p in 64-row strips of 32 projection rows followed by the 32 gate rows of the same channels
 // (a-side strips, then b-side), nullptr unless c_tri is a multiple of 32
 template <typename T> struct TriMulW { T *wt_p, *wn_p, *wt_g, *wn_g, *wt_o, *wn_o; float* bias_p; T* wt_pi; };
@@ -389,7 +390,7 @@ template <typename T> struct Runner {
     auto region = [&](size_t bytes) { size_t o = (off + 255) & ~(size_t)255; off = o + bytes; return base + o; };
     // sizes: generous upper bounds (2 copies of every weight + padding)
     size_t tbytes = (size_t)(2 * PL.total + 128 * 64 + 2LL * 4 * d.c_tri * d.c_z) * sizeof(T);   // + the interleaved projection weights
-    size_t fbytes = (size_t)(16 * d.c_tri + 1024) * sizeof(float);
+    size_t fbytes = (size_t)(16 * d.c_tri + 2 * d.c_opm + 1024) * sizeof(float);
     prep_tbase_m = (T*)region(tbytes); prep_fbase_m = (float*)region(fbytes);
     prep_tbase_p = (T*)region(tbytes); prep_fbase_p = (float*)region(fbytes);
     prep_msa.t.clear(); prep_msa.f.clear(); prep_pair.t.clear(); prep_pair.f.clear();
@@ -414,6 +415,9 @@ template <typename T> struct Runner {
       int co = d.c_opm, cm = d.c_m, cz = d.c_z;
       W.opm.wt_ab = pm.region((long long)2 * co * cm); W.opm.wn_ab = pm.region((long long)2 * co * cm);
       W.opm.wt_o = pm.region((long long)co * co * cz); W.opm.wn_o = pm.region((long long)co * co * cz);
+      W.opm.bias_ab = pm.fregion(2 * co);
+      pm.addf(W.opm.bias_ab, PL.opm.b_a, co);
+      pm.addf(W.opm.bias_ab + co, PL.opm.b_b, co);
       pm.add(W.opm.wt_ab, PL.opm.w_a, cm, co, 1, cm);
       pm.add(W.opm.wt_ab + (long long)co * cm, PL.opm.w_b, cm, co, 1, cm);
       pm.add(W.opm.wn_ab, PL.opm.w_a, cm, co, 2 * co, 1);
@@ -475,6 +479,11 @@ template <typename T> struct Runner {
     for (int i = 0; i < 4; i++)
       if (!ln_done_y[i]) { ln_done_y[i] = y; return; }
     ln_done_y[0] = y;
+  }
+  bool ln_done_has(const T* y) const {
+    for (int i = 0; i < 4; i++)
+      if (ln_done_y[i] == y && y) return true;
+    return false;
   }
   bool ln_done_take(const T* y) {
     for (int i = 0; i < 4; i++)
@@ -637,7 +646,7 @@ template <typename T> struct Runner {
     // fixed-order finish kernel that applies the epilogue.
     const int tiles = ((M + 127) / 128) * ((N + 127) / 128);
     const int BK = GemmCfg<T>::BK;
-    if (split_arena && batch == 1 && tiles <= 96 && K >= 16 * BK && N % 8 == 0) {
+    if (split_arena && batch == 1 && !small_gemm_fits<T>(M, N, K, 1, akc, bkc) && tiles <= 96 && K >= 16 * BK && N % 8 == 0) {
       int want = std::max(2, 256 / tiles);
       long long kc = ((K + want - 1) / want + BK - 1) / BK * BK;
       int nsplit = (int)((K + kc - 1) / kc);
@@ -652,6 +661,7 @@ template <typename T> struct Runner {
       int rc = launch_gemm<T, EpiPartial>(st, A, akc, B, bkc, sh, ep, &al, &dwx, dw_groups(), &depth);
       char kn[64] = "";
       if (!timed()) {}
+      else if (g_gemm_last_small) snprintf(kn, sizeof(kn), "gemm_small_kernel<%s,%s>", akc ? "kc" : "xc", bkc ? "kc" : "xc");
       else if (dwx && depth) snprintf(kn, sizeof(kn), "gemm_dwp_kernel<%d>", depth);
       else if (dwx) snprintf(kn, sizeof(kn), "gemm_dwx_kernel<%d>", dw_groups());
       else snprintf(kn, sizeof(kn), "gemm_kernel<%s,%s,%s,EpiPartial>", akc ? "kc" : "xc", bkc ? "kc" : "xc", al ? "vec" : "elem");
@@ -675,12 +685,29 @@ template <typename T> struct Runner {
     // the exact instantiation (operand layouts, epilogue path, feature mask F; F = 16383 is the general kernel)
     char kn[64] = "";
     if (!timed()) {}
+    else if (g_gemm_last_small) snprintf(kn, sizeof(kn), "gemm_small_kernel<%s,%s>", akc ? "kc" : "xc", bkc ? "kc" : "xc");
     else if (narrow) snprintf(kn, sizeof(kn), "gemm64_kernel<EpiGeneric,F=%d>", g_gemm_last_features);
     else snprintf(kn, sizeof(kn), "gemm_kernel<%s,%s,%s,EpiGeneric,F=%d>", akc ? "kc" : "xc", bkc ? "kc" : "xc", al ? "vec" : "elem",
                   g_gemm_last_features);
     prof_end(st, what, kn, 2.0 * M * N * K * batch, ((double)M * K + (double)N * K + (double)M * N) * batch * sizeof(T));
     if (rc == -1) { err = PE_ERR_DIMS; if (h) h->last_error = std::string("gemm operand alignment: ") + what; return; }
     check(what);
+  }
+  // LayerNorm of x into y (with its statistics), then the GEMM of y with B: one launch where the small-problem kernel applies
+  void gemm_ln(hipStream_t st, const T* x, long long g_off, long long b_off, T* y, float* stats, long long M, int Cc, const Operand& B,
+               int N, const EpiGeneric<T>& e, const char* what) {
+    if (!dry && !err && !ln_done_has(y)) {
+      GemmShape sh{(int)M, N, Cc, 1, 0, 0, N};
+      prof_begin(st);
+      if (launch_gemm_small_ln<T>(st, op_plain(x, Cc), B, sh, e, SmallLn<T>{P(g_off), P(b_off), y, stats, d.ln_eps})) {
+        prof_end(st, what, "gemm_small_kernel<LayerNorm>", 2.0 * M * N * Cc, (2.0 * M * Cc + (double)N * Cc + (double)M * N) * sizeof(T));
+        check(what);
+        return;
+      }
+      prof_cancel();
+    }
+    k_ln_fwd(st, x, g_off, b_off, y, stats, M, Cc);
+    gemm(st, op_plain(y, Cc), true, B, true, (int)M, N, Cc, 1, e, what);
   }
   // last GEMM of a sub-operation (output projection + residual): where the row-complete kernel applies it also
   // writes the next sub-operation's LayerNorm (nxt), else the plain GEMM
@@ -775,6 +802,26 @@ template <typename T> struct Runner {
       }
       prof_cancel();
     }
+    if (Cc <= 32 && small_gemm_fits<T>(M, Cc, K, 1, true, true)) {   // narrow rows of a small block: the same fusion on 32-row tiles
+      const long long grids = (M + 31) / 32;
+      float* sp_ = (float*)part_arena(ar).alloc((size_t)grids * 2 * Cc * sizeof(float));
+      if (!dry && !err) {
+        RowLn<T> ln;
+        memset(&ln, 0, sizeof(ln));
+        ln.gamma = P(g_off); ln.prev = acc ? dxh : nullptr; ln.x = x; ln.stats_in = stats; ln.gin = gin; ln.gout = gout; ln.partial = sp_;
+        GemmShape sh{(int)M, Cc, K, 1, 0, 0, Cc};
+        join_side(st);
+        prof_begin(st);
+        if (launch_gemm_small_lnb<T>(st, A, true, B, sh, ln)) {
+          prof_end(st, what, "gemm_small_kernel<EpiLnBwd>", 2.0 * M * Cc * K, ((double)M * K + (double)Cc * K + 3.0 * M * Cc) * sizeof(T));
+          check(what);
+          ReduceSeg sg[2] = {{0, Cc, g_off, 0}, {Cc, Cc, b_off, 0}};
+          reduce_to(ar, sp_, (int)grids, 2LL * Cc, 1, 2 * Cc, 2, sg);
+          return false;
+        }
+        prof_cancel();
+      }
+    }
     EpiGeneric<T> e = epi_plain<T>(dxh, Cc);
     e.accumulate = acc ? 1 : 0;
     gemm(st, A, true, B, true, (int)M, Cc, K, 1, e, what);
@@ -804,6 +851,7 @@ template <typename T> struct Runner {
       int rc = launch_gemm<T, EpiPartial>(st, X, xkc, Y, ykc, sh, ep, &al, &dwx, dw_groups(), &depth);
       char kn[64] = "";
       if (!timed()) {}
+      else if (g_gemm_last_small) snprintf(kn, sizeof(kn), "gemm_small_kernel<%s,%s>", xkc ? "kc" : "xc", ykc ? "kc" : "xc");
       else if (dwx && depth) snprintf(kn, sizeof(kn), "gemm_dwp_kernel<%d>", depth);
       else if (dwx) snprintf(kn, sizeof(kn), "gemm_dwx_kernel<%d>", dw_groups());
       else snprintf(kn, sizeof(kn), "gemm_kernel<%s,%s,%s,EpiPartial>", xkc ? "kc" : "xc", ykc ? "kc" : "xc", al ? "vec" : "elem");
@@ -849,12 +897,11 @@ template <typename T> struct Runner {
   void attn_sub_fwd_pre(hipStream_t st, const AttnP& p, const AttnW<T>& w, AttnCtx<T>& c, const T* x, long long M, int Cc,
                         int H, int dh, const AttnGeom& g) {
     const int HD = H * dh;
-    k_ln_fwd(st, x, p.ln_g, p.ln_b, c.xhat, c.stats, M, Cc);
     EpiGeneric<T> e = epi_plain<T>(c.qkvg, 4 * HD);
     epi_heads(e, g, dh, M * dh);
     e.bias_n = P(p.b_g) - 3 * HD;   // only columns >= 3HD carry a bias (see bn_begin)
     e.bn_begin = 3 * HD;
-    gemm(st, op_plain(c.xhat, Cc), true, op_plain(w.wt_qkvg, Cc), true, (int)M, 4 * HD, Cc, 1, e, "attn qkvg");
+    gemm_ln(st, x, p.ln_g, p.ln_b, c.xhat, c.stats, M, Cc, op_plain(w.wt_qkvg, Cc), 4 * HD, e, "attn qkvg");
   }
   void attn_sub_fwd(hipStream_t st, Arena& ar, const AttnP& p, const AttnW<T>& w, AttnCtx<T>& c, const T* x, T* xout,
                     long long M, int Cc, int H, int dh, const AttnGeom& g, const T* bias_src, long long bias_ln_g,
@@ -930,12 +977,11 @@ template <typename T> struct Runner {
     const AttnP& p = PL.col;
     GlobCtx<T>& c = C.gcol;
     const int Cc = d.c_m, HD = HDm, dd = d.d_msa, Wg = 2 * HD + 2 * dd;
-    k_ln_fwd(st, x, p.ln_g, p.ln_b, c.xhat, c.stats, Mm, Cc);
     {
       EpiGeneric<T> e = epi_plain<T>(c.proj, Wg);
       e.bias_n = P(p.b_g) - (HD + 2 * dd);
       e.bn_begin = HD + 2 * dd;
-      gemm(st, op_plain(c.xhat, Cc), true, op_plain(W.gcol.wt_proj, Cc), true, (int)Mm, Wg, Cc, 1, e, "gcol proj");
+      gemm_ln(st, x, p.ln_g, p.ln_b, c.xhat, c.stats, Mm, Cc, op_plain(W.gcol.wt_proj, Cc), Wg, e, "gcol proj");
     }
     size_t mk = ar.mark();
     const int chunks = (d.s + gc_chunk_len(HD) - 1) / gc_chunk_len(HD);
@@ -1004,12 +1050,11 @@ template <typename T> struct Runner {
   void trans_sub_fwd(hipStream_t st, const TransP& p, const TransW<T>& w, TransCtx<T>& c, const T* x, T* xout, long long M,
                      int Cc) {
     const int nC = d.n_trans * Cc;
-    k_ln_fwd(st, x, p.ln_g, p.ln_b, c.xhat, c.stats, M, Cc);
     {
       EpiGeneric<T> e = epi_plain<T>(c.h, nC);
       e.bias_n = P(p.b1); e.act = 1;
       if (c.hbits) { e.bits_out = c.hbits; e.ld_bits = nC / 8; }
-      gemm(st, op_plain(c.xhat, Cc), true, op_plain(w.wt_1, Cc), true, (int)M, nC, Cc, 1, e, "trans 1");
+      gemm_ln(st, x, p.ln_g, p.ln_b, c.xhat, c.stats, M, Cc, op_plain(w.wt_1, Cc), nC, e, "trans 1");
     }
     {
       EpiGeneric<T> e = epi_plain<T>(xout, Cc);
@@ -1032,7 +1077,16 @@ template <typename T> struct Runner {
   void trimul_sub_fwd(hipStream_t st, const TriMulP& p, const TriMulW<T>& w, TriMulCtx<T>& c, const T* z, T* zout,
                       bool outgoing) {
     const int cz = d.c_z, ct = d.c_tri, r = d.r;
-    k_ln_fwd(st, z, p.ln_in_g, p.ln_in_b, c.zhat, c.stats, Mz, cz);
+    auto gate = [&](bool with_ln) {
+      EpiGeneric<T> e = epi_plain<T>(c.g, cz);
+      e.bias_n = P(p.b_g); e.act = 2;
+      if (with_ln) gemm_ln(st, z, p.ln_in_g, p.ln_in_b, c.zhat, c.stats, Mz, cz, op_plain(w.wt_g, cz), cz, e, "trimul gate");
+      else gemm(st, op_plain(c.zhat, cz), true, op_plain(w.wt_g, cz), true, (int)Mz, cz, cz, 1, e, "trimul gate");
+    };
+    // small blocks: the input LayerNorm is the gate GEMM's prologue and the projections read what it wrote
+    const bool gate_first = cz <= small_ln_k<T>() && small_gemm_fits<T>(Mz, cz, cz, 1, true, true);
+    if (gate_first) gate(true);
+    else k_ln_fwd(st, z, p.ln_in_g, p.ln_in_b, c.zhat, c.stats, Mz, cz);
     bool gated = false;   // projection, gate pre-activation and gated operands from one kernel
     if (!dry && !err && w.wt_pi) {
       EpiTmGate<T> eg;
@@ -1097,11 +1151,7 @@ template <typename T> struct Runner {
         PE_LAUNCH("ln_cmajor_fwd", 0, 2.0 * Mz * ct * sizeof(T), st, ln_cmajor_fwd_kernel<T>, dim3((unsigned)((Mz + 63) / 64)), dim3(256), lds, c.x_t,
                   P(p.ln_out_g), P(p.ln_out_b), c.xhat, c.stats_out, Mz, ct, d.ln_eps);
     }
-    {
-      EpiGeneric<T> e = epi_plain<T>(c.g, cz);
-      e.bias_n = P(p.b_g); e.act = 2;
-      gemm(st, op_plain(c.zhat, cz), true, op_plain(w.wt_g, cz), true, (int)Mz, cz, cz, 1, e, "trimul gate");
-    }
+    if (!gate_first) gate(false);
     {
       EpiGeneric<T> e = epi_plain<T>(zout, cz);
       e.bias_n = P(p.b_o);
@@ -1155,13 +1205,12 @@ template <typename T> struct Runner {
   void fwd_opm_outer(const T* x) {
     const int co = d.c_opm, r = d.r;
     const long long Wd = (long long)r * co;
-    k_ln_fwd(sm, x, PL.opm.ln_g, PL.opm.ln_b, C.opm.mhat, C.opm.stats, Mm, d.c_m);
-    for (int k = 0; k < 2; k++) {
-      EpiGeneric<T> e = epi_plain<T>(k ? C.opm.b : C.opm.a, co);
-      e.bias_n = P(k ? PL.opm.b_b : PL.opm.b_a);
+    {  // both projections in one GEMM: column n = (which, c), the two halves Mm * co apart
+      EpiGeneric<T> e = epi_plain<T>(C.opm.a, co);
+      e.on_in = co; e.on_outer = Mm * co; e.on_stride = 1;
+      e.bias_n = W.opm.bias_ab;
       e.rowscale = msa_mask;
-      gemm(sm, op_plain(C.opm.mhat, d.c_m), true, op_plain(W.opm.wt_ab + (long long)k * co * d.c_m, d.c_m), true, (int)Mm,
-           co, d.c_m, 1, e, "opm ab");
+      gemm_ln(sm, x, PL.opm.ln_g, PL.opm.ln_b, C.opm.mhat, C.opm.stats, Mm, d.c_m, op_plain(W.opm.wt_ab, d.c_m), 2 * co, e, "opm ab");
     }
     if (!dry && !err) {
       PE_LAUNCH("opm_norm", 2.0 * Mz * d.s, 4.0 * (Mz + Mm), sm, opm_norm_kernel, dim3((unsigned)((Mz + 255) / 256)), dim3(256), 0, msa_mask, C.opm.inv_norm,
@@ -1491,6 +1540,35 @@ template <typename T> struct Runner {
       gemm_dw(st, ar, X, false, op_padded(op_plain(dproj_t, Pz)), true, cz, 4 * ct, zrows_end(), 4, sg, "trimul dWp", 4, cb); }
     { ReduceSeg sg[1] = {{0, cz, p.w_g, cz}}, cb = {0, cz, p.b_g, 0};
       gemm_dw(st, ar, op_trans(c.zhat, cz), false, op_trans(dgraw, cz), false, cz, cz, Mz, 1, sg, "trimul dWg", 1, &cb); }
+    // small blocks: both shares of the input LayerNorm's cotangent and its backward in one launch
+    if (cz <= 32 && rp == r && small_gemm_fits<T>(Mz, cz, 4 * ct, 1, false, true)) {
+      const long long grids = (Mz + 31) / 32;
+      float* part = (float*)part_arena(ar).alloc((size_t)grids * 2 * cz * sizeof(float));
+      bool done = false;
+      if (!dry && !err) {
+        RowLn<T> ln;
+        memset(&ln, 0, sizeof(ln));
+        ln.gamma = P(p.ln_in_g); ln.x = z; ln.stats_in = c.stats; ln.gin = g; ln.gout = g; ln.partial = part;
+        GemmShape sh{(int)Mz, cz, 4 * ct, 1, 0, 0, cz};
+        const Operand A2 = op_plain(dgraw, cz), B2 = op_plain(w.wn_g, cz);
+        join_side(st);
+        prof_begin(st);
+        done = launch_gemm_small_lnb<T>(st, op_trans(dproj_t, Pz), false, op_plain(w.wn_p, 4 * ct), sh, ln, &A2, &B2, cz);
+        if (done) {
+          prof_end(st, "trimul dzhat", "gemm_small_kernel<EpiLnBwd>", 2.0 * Mz * cz * (4 * ct + cz), (4.0 * ct + 4.0 * cz) * Mz * sizeof(T));
+          check("trimul dzhat");
+          ReduceSeg sg[2] = {{0, cz, p.ln_in_g, 0}, {cz, cz, p.ln_in_b, 0}};
+          reduce_to(ar, part, (int)grids, 2LL * cz, 1, 2 * cz, 2, sg);
+        } else {
+          prof_cancel();
+        }
+      }
+      if (done) {
+        end_subop(ar);
+        ar.release(mk);
+        return;
+      }
+    }
     { EpiGeneric<T> e = epi_plain<T>(dzh, cz);
       if (rp != r) { e.om_in = rp; e.om_used = r; e.om_outer = (long long)r * cz; }
       gemm(st, op_trans(dproj_t, Pz), false, op_plain(w.wn_p, 4 * ct), true, (int)Pz, cz, 4 * ct, 1, e, "trimul dzhat p"); }

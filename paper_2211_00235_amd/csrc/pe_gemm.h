@@ -118,6 +118,7 @@ enum : int { EF_BIASN = 1, EF_BIASM = 2, EF_ACT = 4, EF_RELUMASK = 8, EF_AUX = 1
 template <typename T> struct EpiGeneric {
   static constexpr bool HAS_COLSUM = false;
   static constexpr bool TM_GATE = false;
+  static constexpr bool ELEM = true;      // has an element-wise path
   T* out; long long out_batch;
   int om_in;
   int om_used;                   // > 0: rows m with m % om_in >= om_used are padding and not stored (plain outputs only)
@@ -326,6 +327,7 @@ template <typename T> static inline EpiGeneric<T> epi_plain(void* out, long long
 struct EpiPartial {
   static constexpr bool HAS_COLSUM = true;
   static constexpr bool TM_GATE = false;
+  static constexpr bool ELEM = true;      // has an element-wise path
   float* out; long long mn; int ldn;
   float* colsum;   // nullable: [batch][N] sums over k of the B operand (bias gradients ride on the dW GEMM)
   struct Row { long long o; };
@@ -342,6 +344,8 @@ struct EpiPartial {
   struct Pre8 {};
   template <int F> PE_DEV void pre8(int, int, int, const ColV&, Pre8&) const {}
   template <int F> PE_DEV void apply8(int b, int m, int n, const ColV& c, float (&v)[8], const Pre8&) const { vec8<F>(b, m, n, c, v); }
+  PE_DEV bool want_colsum() const { return colsum != nullptr; }
+  PE_DEV void put_colsum(int b, int n, int N, float t) const { colsum[(long long)b * N + n] = t; }
   bool vec_ok(int N) const { return N % 8 == 0 && ldn % 8 == 0 && mn % 8 == 0 && ((uintptr_t)out) % 16 == 0; }
 };
 
@@ -357,6 +361,7 @@ struct EpiPartial {
 template <typename T> struct EpiAttnPre {
   static constexpr bool HAS_COLSUM = false;
   static constexpr bool TM_GATE = false;
+  static constexpr bool ELEM = false;      // has an element-wise path
   const T* gate;       // gate pre-activation plane group: qkvg + 3*H*plane
   const T* o;
   T* dO;
@@ -427,6 +432,7 @@ template <typename T> struct EpiAttnPre {
 template <typename T> struct EpiTmGate {
   static constexpr bool HAS_COLSUM = false;
   static constexpr bool TM_GATE = true;
+  static constexpr bool ELEM = false;      // has an element-wise path
   T* proj_t; T* a_t; T* b_t;
   const float* bias;     // [4 ct] in the order of proj_t's rows
   const float* mask;     // [r][r]
@@ -459,6 +465,7 @@ template <typename T> struct EpiTmGate {
 template <typename T> struct EpiTmGateBwd {
   static constexpr bool HAS_COLSUM = false;
   static constexpr bool TM_GATE = false;
+  static constexpr bool ELEM = false;      // has an element-wise path
   const T* proj_t; const float* mask; T* dproj_t;
   int ct, r, side; long long Mz;   // Mz = r * pitch
   int pitch;
@@ -2125,7 +2132,7 @@ static inline bool launch_gemm64(hipStream_t st, const Operand& A, const Operand
   PE_GEMM64_SPEC(EF_ACC | EF_BIASM)
   PE_GEMM64_SPEC(EF_OM2 | EF_ON2 | EF_BIASN)
   PE_GEMM64_SPEC(EF_BIASN | EF_AUX | EF_MUL | EF_RES)
-  PE_GEMM64_SPEC(EF_BIASN | EF_ROWSCALE)
+  PE_GEMM64_SPEC(EF_BIASN | EF_ROWSCALE | EF_ON2)
 #undef PE_GEMM64_SPEC
   return false;
   }
@@ -2160,7 +2167,7 @@ static inline bool launch_gemm_spec(hipStream_t st, dim3 grid, const Operand& A,
   PE_GEMM_SPEC(EF_RELUMASK)
   PE_GEMM_SPEC(EF_OM2 | EF_ON2 | EF_BIASN)
   PE_GEMM_SPEC(EF_ACC | EF_BIASM)
-  PE_GEMM_SPEC(EF_BIASN | EF_ROWSCALE)
+  PE_GEMM_SPEC(EF_BIASN | EF_ROWSCALE | EF_ON2)
   PE_GEMM_SPEC(EF_BIASN | EF_AUX | EF_MUL | EF_RES)
   PE_GEMM_SPEC(EF_OM2 | EF_ON2 | EF_ROWSCALE)
 #undef PE_GEMM_SPEC
@@ -2202,6 +2209,13 @@ static inline void launch_gemm_al(hipStream_t st, dim3 grid, const Operand& A, b
   else hipLaunchKernelGGL((gemm_kernel<T, false, false, AL, VE, Epi>), grid, block, 0, st, A, B, sh, epi);
 }
 
+// small problems (pe_small.h): few output tiles
+template <typename T> static inline bool small_gemm_fits(long long M, long long N, long long K, long long batch, bool a_kc, bool b_kc);
+template <typename T, class Epi>
+static inline void launch_gemm_small(hipStream_t st, const Operand& A, bool a_kc, const Operand& B, bool b_kc, const GemmShape& sh, const Epi& epi);
+// true after a launch_gemm call of this host thread that took the small-problem kernel
+static thread_local bool g_gemm_last_small = false;
+
 // Operands that break the 16-byte vector rules (odd leading dimensions) take the
 // element-wise loader and the per-element epilogue: same tiles, same arithmetic, slower.
 template <typename T, class Epi>
@@ -2216,6 +2230,19 @@ static inline int launch_gemm(hipStream_t st, const Operand& A, bool a_kc, const
   if (b_kc ? B.k_stride != 1 : B.x_stride != 1) return -1;
   if (sh.k_chunk > 0 && sh.k_chunk % GemmCfg<T>::BK) return -1;
   bool al = gemm_operand_ok<T>(A, a_kc, sh.M, sh) && gemm_operand_ok<T>(B, b_kc, sh.N, sh);
+  g_gemm_last_small = false;
+  if constexpr (!Epi::TM_GATE) {
+    const bool sve = epi.vec_ok(sh.N);
+    // bf16 parameter gradients have a kernel that is faster even there (gemm_dwx_kernel)
+    const bool dwx = std::is_same<Epi, EpiPartial>::value && std::is_same<T, bf16>::value && wave_groups && !a_kc && !b_kc;
+    if (!dwx && (sve || Epi::ELEM) && small_gemm_fits<T>(sh.M, sh.N, sh.k_chunk > 0 ? sh.k_chunk : sh.K, sh.batch, a_kc, b_kc)) {
+      launch_gemm_small<T, Epi>(st, A, a_kc, B, b_kc, sh, epi);
+      g_gemm_last_small = true;
+      if (used_vec) *used_vec = sve;
+      if (used_narrow) *used_narrow = false;
+      return hipGetLastError() == hipSuccess ? 0 : -2;
+    }
+  }
   bool ve = al && epi.vec_ok(sh.N);
   if (used_vec) *used_vec = ve;
   const int NTm_ = (sh.M + 127) / 128, NTn_ = (sh.N + 127) / 128;

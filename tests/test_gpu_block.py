@@ -99,6 +99,21 @@ def test_triangle_planes_with_padded_pitch(c_tri, r, dtype):
     _assert(errs, worst, tol, stats)
 
 
+@pytest.mark.parametrize("dtype", [0, 1])
+@pytest.mark.parametrize("s,r,c_m,c_z", [(1, 31, 32, 16), (33, 33, 24, 32), (7, 65, 64, 16), (3, 34, 128, 16)])
+def test_small_problem_gemms(s, r, c_m, c_z, dtype):
+    """The 32 x 32-tile GEMM kernel: row counts one short of and one beyond its tiles, unaligned contractions (odd r),
+    channel counts at and beyond the limits of its LayerNorm prologue (64 fp32, 128 bf16) and of its LayerNorm-backward
+    epilogue (32), a channel count that leaves half a k-chunk (24), a half-empty column tile.  (Not fewer than 16 pair channels: the bf16
+    pre-activation bound of tests/parity.py was measured from 32 channels up, and the error of a LayerNorm over n channels
+    relative to its own spread grows like n^-1/2: 8 channels reach 4.9e-2 against its 4e-2.)"""
+    dims, table, inp = _case("tiny", dtype=dtype, s=s, r=r, c_m=c_m, c_z=c_z)
+    table, n = param_table(dims)
+    inp = make_inputs(dims, table, n, ("random_residues", 0.1), 29)
+    errs, worst, tol, stats = check_case(dims, table, inp)
+    _assert(errs, worst, tol, stats)
+
+
 @pytest.mark.parametrize("use_ctx", [True, False])
 @pytest.mark.parametrize("dtype,r", [(0, 19), (1, 19), (1, 40), (0, 32), (1, 32)])
 def test_row_complete_layernorm_epilogues(dtype, r, use_ctx):
