@@ -887,6 +887,264 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(PE_DKV_WAVE
   }
 }
 
+// ---------------------------------------------------------------------------
+// Backward of the biased attention at head dimension 8 over many batch rows (bf16): dQ, dK, dV and the bias gradient in
+// one kernel.  A workgroup owns (head, 128 keys) and WALKS through the batch rows of its split; a wave owns 32 keys
+// and up to four query tiles, whose dS sums over those rows stay in its registers until the end.
+//
+// At d = 8 a row's q, k, v, dO are 16 bytes per position while its 32 x 32 logit tiles cost as much as at d = 32: the
+// separate dQ and dK / dV kernels evaluated every tile twice (vector unit), read a 96 KB bias slab per workgroup for 24 KB
+// of operands, and passed the bias gradient through memory once per pair of batch rows.  Here a tile is evaluated
+// once:
+//   * scores with a key per lane (as in the dK / dV kernel): dK and dV are contractions over accumulator rows; they share
+//     one accumulator (rows 0-7 dV, 8-15 dK: the A operands are [dO^T; 0] and [0; Q^T]);
+//   * -lse, -D and the key mask are contraction slots 8..: at d = 8 half of the K = 16 MFMA step is free, so S - lse + mask
+//     and dP - D come out of the matrix unit.  lse and D enter as three bf16 pieces each, 24 bits: exact in fp32;
+//   * dS goes to LDS [query][key] in bf16, as which it is an operand of dQ anyway; after a barrier a wave contracts one query
+//     tile with the workgroup's 128 keys.  With more than 128 keys dQ is a sum of fp32 partials per key block.
+// 768 threads: 12 waves x 4 tiles are the 12 x 4 tiles of L = 384, three waves per SIMD leave 168 registers (64 of them
+// the dS sums); 156 KB of LDS, one workgroup per CU.
+// Measured at B = 5120, L = 384, H = 8: 3.13 ms + 0.34 ms for the dQ sum, before it dQ 3.7 + dK / dV 2.86 + reduction
+// 0.85 ms; at B = 1024, L = 256: 0.30 ms instead of 0.83 ms.
+struct AttnWalk {
+  static constexpr int LMAX = 384, KB = 128, THREADS = 768, NTILE = 4;
+  static constexpr int SD = KB + 8, ST = LMAX + 8;    // row strides of the dS and the transposed tiles
+};
+// x as a sum of three bf16 pieces in slots 0..2
+PE_DEV void attn_split3(float x, bf16x8& v) {
+  v[0] = (bf16)x;
+  const float r1 = x - (float)v[0];
+  v[1] = (bf16)r1;
+  v[2] = (bf16)(r1 - (float)v[1]);
+}
+// 16 bytes at a uniform base and a 32-bit byte offset per lane: one address register
+PE_DEV bf16x8 attn_ld8(const bf16* base, unsigned off) {
+  return *reinterpret_cast<const bf16x8*>(reinterpret_cast<const char*>(base) + off);
+}
+// grid H * ceil(L / 128) * nsplit.  dqp: fp32 [key block][H][B L][8], used when L > 128.  dSp: fp32 [nsplit][H] planes in the
+// layout of dS.  Heads cycle fastest over the workgroups, i.e. over the XCDs, so an L2 holds the bias planes of few heads.
+__global__ __launch_bounds__(AttnWalk::THREADS) void attn_bwd_walk_kernel(AttnArgs a, float* dqp, float* dSp, int nsplit) {
+  typedef AttnWalk W;
+  typedef Mma<bf16> MM;
+  __shared__ __attribute__((aligned(16))) bf16 lds_ds[W::LMAX * W::SD];    // [query][key]
+  __shared__ __attribute__((aligned(16))) bf16 lds_rm[2 * W::LMAX * 16];   // rows of q, then of dO: 8 channels, 8 extra slots
+  __shared__ __attribute__((aligned(16))) bf16 lds_t[24 * W::ST];          // rows: dO^T (8), zeros (8), Q^T (8)
+  __shared__ __attribute__((aligned(16))) bf16 lds_kv[2 * W::KB * 16];     // rows of K, then of V, with extra slots
+  __shared__ __attribute__((aligned(16))) bf16 lds_kt[8 * W::SD];          // K^T
+  __shared__ __attribute__((aligned(16))) bf16 lds_id[2 * 64 * 8];         // the identity operand of the bias step
+  float* lds_x = reinterpret_cast<float*>(lds_rm);   // dK / dV of 8 waves, 16 KB: the rows are free by then
+
+  // everything that is the same in a wave is in scalar registers: the vector registers are full
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, g = lane >> 5;
+  const int L = a.L, H = a.H, nqt = (L + 31) >> 5, nkb = (L + W::KB - 1) / W::KB;
+  const int h = blockIdx.x % H, kb = (blockIdx.x / H) % nkb, split = blockIdx.x / (H * nkb);
+  const int b0 = (int)((long long)split * a.B / nsplit), b1 = (int)((long long)(split + 1) * a.B / nsplit);
+  const int kt = wave & 3, qg = wave >> 2;
+  const int k0 = kb * W::KB;
+  const bool kactive = k0 + kt * 32 < L;
+  const int nks = min(W::KB / 16, ((L - k0 + 31) >> 5) * 2);   // 16-key steps of this key block
+  const long long HP = (long long)H * a.plane;
+  const bf16* qbase = (const bf16*)a.qkvg + h * a.plane;
+  const bf16* dobase = (const bf16*)a.dO + h * a.plane;
+  const bf16* bplane = (const bf16*)a.biasK + (long long)h * nqt * L * 32;
+  unsigned boff = (unsigned)(g * L + min(k0 + kt * 32 + l32, L - 1)) * 16;   // this lane's place in a bias chunk, bytes
+  // staging: thread tid < 384 brings q row tid, the others dO row tid - 384; threads 0..127 also a K row, 128..255 a V row
+  const bool isq = wave < W::LMAX / 64, isk = wave < W::KB / 64, iskv = wave < 2 * W::KB / 64;
+  unsigned srow = isq ? tid : tid - W::LMAX, krow = tid & (W::KB - 1);
+  const bf16* const ssrc = isq ? qbase : dobase;
+  const float* const fsrc = (isq ? a.lse : a.D) + (long long)h * L;
+  const bf16* const ksrc = qbase + (isk ? HP : 2 * HP) + k0 * 8;
+  const unsigned nkey = L - k0;
+  bf16x8 sv, kv;
+  float sf = 0.0f, mk = 0.0f;
+#define PE_WALK_LOAD(b)                                                                                              \
+  do {                                                                                                               \
+    sv = MM::zero(); kv = MM::zero(); sf = 0.0f; mk = 0.0f;                                                          \
+    if (srow < (unsigned)L) {                                                                                        \
+      sv = attn_ld8(ssrc + (long long)(b) * L * 8, srow * 16u);                                                      \
+      sf = (fsrc + (long long)(b) * H * L)[srow];                                                                    \
+    }                                                                                                                \
+    if (iskv && krow < nkey) {                                                                                       \
+      kv = attn_ld8(ksrc + (long long)(b) * L * 8, krow * 16u);                                                      \
+      if (isk) mk = a.mask[(long long)(b) * a.mask_bs + (long long)(k0 + krow) * a.mask_ks];                         \
+    }                                                                                                                \
+  } while (0)
+// bias of query tile qt (uniform), as attn_load_bias
+#define PE_WALK_BIAS(qt)                                                                                             \
+  do {                                                                                                               \
+    const bf16* tp = bplane + (long long)(qt) * L * 32;                                                              \
+    asm volatile("" : "+v"(boff));   /* base + offset is not kept across the loop */                                 \
+    bt.v[0] = attn_ld8(tp, boff);                                                                                    \
+    bt.v[1] = attn_ld8(tp + (long long)L * 16, boff);                                                                \
+  } while (0)
+
+  if (wave == 0) {
+    IdFrag<bf16> idf;
+    idf.init(l32, g);
+#pragma unroll
+    for (int c = 0; c < 2; c++) *reinterpret_cast<bf16x8*>(lds_id + (c * 64 + lane) * 8) = idf.f[c];
+  }
+  for (int i = tid; i < 8 * W::ST; i += W::THREADS) lds_t[8 * W::ST + i] = (bf16)0.0f;
+  f32x16 acc[W::NTILE];
+#pragma unroll
+  for (int t = 0; t < W::NTILE; t++) acc[t] = splat16(0.0f);
+  BiasTile<bf16> bt;
+  PE_WALK_BIAS(min(qg, nqt - 1));
+  PE_WALK_LOAD(b0);
+
+  for (int b = b0; b < b1; b++) {
+    // per-lane indices anew for every row: their addresses would otherwise be kept in registers across the loop
+    tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    lane = tid & 63; l32 = lane & 31; g = lane >> 5;
+    srow = isq ? tid : tid - W::LMAX; krow = tid & (W::KB - 1);
+    // ---- this row's operands to LDS ----
+    if (srow < nqt * 32u) {
+#pragma unroll
+      for (int e = 0; e < 8; e++) lds_t[((isq ? 16 : 0) + e) * W::ST + srow] = sv[e];
+    }
+    if (iskv) {
+      bf16x8 x = MM::zero();
+      x[0] = x[1] = x[2] = (bf16)1.0f;
+      if (isk) {
+        x[3] = (bf16)((mk > 0.0f) ? 0.0f : -INFINITY);
+#pragma unroll
+        for (int e = 0; e < 8; e++) lds_kt[e * W::SD + krow] = kv[e];
+      }
+      *reinterpret_cast<bf16x8*>(lds_kv + tid * 16) = kv;
+      *reinterpret_cast<bf16x8*>(lds_kv + tid * 16 + 8) = x;
+    }
+    __syncthreads();   // lds_x (the previous row's dK / dV) has been read
+    if (srow < nqt * 32u) {
+      bf16x8 x = MM::zero();
+      if (srow < (unsigned)L) attn_split3(isq ? -sf * PE_LOG2E : -sf, x);
+      else if (isq) x[0] = (bf16)-INFINITY;          // probability 0 for the queries beyond L
+      if (isq) x[3] = (bf16)1.0f;                    // takes the key mask
+      *reinterpret_cast<bf16x8*>(lds_rm + tid * 16) = sv;
+      *reinterpret_cast<bf16x8*>(lds_rm + tid * 16 + 8) = x;
+    }
+    __syncthreads();
+    if (b + 1 < b1) PE_WALK_LOAD(b + 1);
+
+    // ---- score tiles: dS to registers (sum over rows) and LDS, dK and dV ----
+    f32x16 dkv = splat16(0.0f);
+    if (kactive) {
+      const bf16x8 kf = MM::load(lds_kv + (kt * 32 + l32) * 16 + g * 8);
+      const bf16x8 vf = MM::load(lds_kv + (W::KB + kt * 32 + l32) * 16 + g * 8);
+#pragma unroll
+      for (int t = 0; t < W::NTILE; t++) {
+        const int qt = qg + 3 * t;
+        if (qt < nqt) {
+          const bf16* qrow = lds_rm + (qt * 32 + l32) * 16 + g * 8;
+          f32x16 s = mma_c<bf16>(MM::load(qrow), kf, splat16(0.0f));                       // S - lse + mask
+          f32x16 p = mma_c<bf16>(MM::load(qrow + W::LMAX * 16), vf, splat16(0.0f));        // dP - D
+#pragma unroll
+          for (int c = 0; c < 2; c++) s = mma_c<bf16>(MM::load(lds_id + (c * 64 + lane) * 8), bt.v[c], s);
+          const int qn = qt + 3 < nqt && t + 1 < W::NTILE ? qt + 3 : qg;                   // next tile's bias
+          PE_WALK_BIAS(qn);
+#pragma unroll
+          for (int e = 0; e < 16; e++) {
+            s[e] = fast_exp2(s[e]);
+            p[e] *= s[e];                                                                  // dS = P (dP - D)
+            acc[t][e] += p[e];
+          }
+          const bf16* trow = lds_t + (l32 & 15) * W::ST + qt * 32;
+          bf16* drow = lds_ds + (qt * 32 + 4 * g) * W::SD + kt * 32 + l32;
+#pragma unroll
+          for (int u = 0; u < 2; u++) {
+            const bf16x8 sfr = acc_to_frag<bf16>(p, u);
+            MM::mma(dkv, lds_tfrag<bf16>(trow, g, u), acc_to_frag<bf16>(s, u));            // dV^T += dO^T P
+            MM::mma(dkv, lds_tfrag<bf16>(trow + 8 * W::ST, g, u), sfr);                    // dK^T += Q^T dS
+#pragma unroll
+            for (int e = 0; e < 8; e++) drow[(16 * u + 8 * (e >> 2) + (e & 3)) * W::SD] = sfr[e];
+          }
+        }
+        __builtin_amdgcn_sched_barrier(0);   // one tile's operands at a time in registers
+      }
+    }
+    __syncthreads();
+    // ---- dK / dV partial sums of the waves that share keys; dQ of one query tile per wave ----
+    if (qg > 0 && kactive) {
+#pragma unroll
+      for (int e = 0; e < 8; e++) lds_x[(((qg - 1) * 4 + kt) * 8 + e) * 64 + lane] = dkv[e];
+    }
+    if (wave < nqt) {
+      const bf16* drow = lds_ds + (wave * 32 + l32) * W::SD + 8 * g;
+      const bf16* ktrow = lds_kt + (l32 & 7) * W::SD + 8 * g;
+      f32x16 dq = splat16(0.0f);
+      for (int u = 0; u < nks; u++) MM::mma(dq, MM::load(ktrow + 16 * u), MM::load(drow + 16 * u));
+      const int qi = wave * 32 + l32;
+      if (qi < L) {
+        const long long row = h * a.plane + ((long long)b * L + wave * 32) * 8;
+        const unsigned off = l32 * 8 + 4 * g;
+        float v[4];
+        if (nkb == 1) {
+#pragma unroll
+          for (int r = 0; r < 4; r++) v[r] = dq[r] * a.scale;
+          store4<bf16>((bf16*)a.dqkvg + row + off, v);
+        } else {
+#pragma unroll
+          for (int r = 0; r < 4; r++) v[r] = dq[r];
+          store4<float>(dqp + kb * HP + row + off, v);
+        }
+      }
+    }
+    __syncthreads();
+    if (qg == 0 && k0 + kt * 32 + l32 < L) {
+      float dv[4], dk[4];
+#pragma unroll
+      for (int r = 0; r < 4; r++) {
+        dv[r] = (dkv[r] + lds_x[(kt * 8 + r) * 64 + lane]) + lds_x[((4 + kt) * 8 + r) * 64 + lane];
+        dk[r] = ((dkv[4 + r] + lds_x[(kt * 8 + 4 + r) * 64 + lane]) + lds_x[((4 + kt) * 8 + 4 + r) * 64 + lane]) * PE_LN2;   // q' = q scale log2 e
+      }
+      bf16* pdk = (bf16*)a.dqkvg + HP + h * a.plane + ((long long)b * L + k0 + kt * 32) * 8;
+      const unsigned off = l32 * 8 + 4 * g;
+      store4<bf16>(pdk + off, dk);
+      store4<bf16>(pdk + HP + off, dv);
+    }
+  }
+#undef PE_WALK_LOAD
+#undef PE_WALK_BIAS
+  if (!kactive) return;
+  // this lane's key inside the chunk order of dS: accumulator element ek of lane group gk
+  const int ek = 4 * (l32 >> 3) + (l32 & 3), gk = (l32 >> 2) & 1;
+  float* dst = dSp + ((long long)split * H + h) * nqt * L * 32 + (ek & 7);
+#pragma unroll
+  for (int t = 0; t < W::NTILE; t++)
+#pragma unroll
+    for (int e = 0; e < 16; e++) {
+      const int qi = (qg + 3 * t) * 32 + acc_row(g, e);
+      if (qi < L) dst[bias_chunk_off<bf16>((k0 >> 5) + kt, ek >> 3, gk, qi, L)] = acc[t][e];
+    }
+}
+// dQ = scale * sum of the fp32 partials of the key blocks; 8 channels per thread, n8 = H B L
+__global__ __launch_bounds__(256) void attn_dq_sum_kernel(const float* dqp, bf16* dq, int nkb, long long n8, float scale) {
+  const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
+  if (i >= n8) return;
+  float s[8];
+  ld8_once<float>(dqp + i * 8, s);
+  for (int k = 1; k < nkb; k++) {
+    float v[8];
+    ld8_once<float>(dqp + (k * n8 + i) * 8, v);
+#pragma unroll
+    for (int e = 0; e < 8; e++) s[e] += v[e];
+  }
+#pragma unroll
+  for (int e = 0; e < 8; e++) s[e] *= scale;
+  st8<bf16>(dq + i * 8, s);
+}
+// Workgroups along the batch axis of attn_bwd_walk_kernel, 0: the call keeps the kernels per batch row.  A workgroup
+// takes 32 rows or more (it writes one 32-bit dS plane for them) and two rounds of workgroups fill the CUs; below 128 workgroups half
+// of the CUs would idle.  At the line both are close (B 256, L 256, one-stream block: 2.72 ms without, 2.71 ms with it);
+// B 512, L 40: 1.03 -> 0.97 ms; B 5120, L 40: 2.77 -> 2.36 ms; B 1024, L 128: 1.99 -> 1.89 ms.
+static inline int attn_walk_splits(bool bf, bool bias, long long B, int H, long long L, int d) {
+  if (!bf || !bias || d != 8 || L > AttnWalk::LMAX) return 0;
+  const long long units = H * ((L + AttnWalk::KB - 1) / AttnWalk::KB);
+  const long long n = std::min<long long>(B / 32, std::max<long long>(512 / units, 1));
+  return n * units >= 128 ? (int)n : 0;
+}
+
 // The same reduction with 8 consecutive outputs per thread (16-byte loads for bf16) and eight loads in
 // flight: 64 output groups x 4 batch lanes per workgroup.  Needs hll % 8 == 0 and 16-byte aligned buffers.
 template <typename T>

@@ -1308,8 +1308,15 @@ template <typename T> struct Runner {
     float* dbias = nullptr;
     float* dbias_rows = nullptr;
     const long long btile = (long long)H * ((gm.L + 31) / 32) * gm.L * 32;   // elements of one [H] set of chunk-ordered planes
+    // one kernel that walks through the batch rows (walk > 0: that many splits of them), or dQ and dK / dV kernels per row
+    const int walk = attn_walk_splits(sizeof(T) == 2, c.bias != nullptr, gm.B, H, gm.L, dh), nkb = (int)((gm.L + AttnWalk::KB - 1) / AttnWalk::KB);
+    float* dSp = nullptr;
+    float* dqp = nullptr;
     if (c.bias) {
-      dS = (T*)ar.alloc((size_t)((gm.B + 1) / 2) * btile * sizeof(T));
+      if (walk) {
+        dSp = (float*)ar.alloc((size_t)walk * btile * sizeof(float));
+        if (nkb > 1) dqp = (float*)ar.alloc((size_t)nkb * M * HD * sizeof(float));
+      } else dS = (T*)ar.alloc((size_t)((gm.B + 1) / 2) * btile * sizeof(T));
       dbias = (float*)ar.alloc((size_t)btile * sizeof(float));
       dbias_rows = (float*)ar.alloc((size_t)H * Mz * sizeof(float));   // dbias in pair-row order
     }
@@ -1357,20 +1364,32 @@ template <typename T> struct Runner {
       if (!pre_fused)
         PE_LAUNCH("attn_bwd_pre", 0, 5.0 * M * HD * sizeof(T), st, attn_bwd_pre_kernel<T>, dim3((unsigned)((tot * 8 + 255) / 256)), dim3(256), 0, a);
       dim3 grid(attn_grid_size(gm.B, H, gm.L));
-      // biased attention: two batch rows per workgroup, their dS tiles summed before the write
-      const long long Bds = c.bias ? (gm.B + 1) / 2 : gm.B;
-      if (c.bias) PE_LAUNCH(gm.l_dq, 6.0 * gm.B * H * gm.L * gm.L * dh, 5.0 * M * HD * sizeof(T) + 1.0 * Bds * H * gm.L * gm.L * sizeof(T), st, (attn_bwd_dq2_kernel<T>), dim3(attn_grid_size(Bds, H, gm.L)), dim3(512), 0, a);
-      else PE_LAUNCH(gm.l_dq, 6.0 * gm.B * H * gm.L * gm.L * dh, 5.0 * M * HD * sizeof(T) + (c.bias ? 1.0 * gm.B * H * gm.L * gm.L * sizeof(T) : 0.0), st, (attn_bwd_dq_kernel<T, false>), grid, dim3(256), 0, a);
-      if (c.bias) PE_LAUNCH(gm.l_dkv, 8.0 * gm.B * H * gm.L * gm.L * dh, 6.0 * M * HD * sizeof(T), st, (attn_bwd_dkv_kernel<T, true>), grid, dim3(256), 0, a);
-      else PE_LAUNCH(gm.l_dkv, 8.0 * gm.B * H * gm.L * gm.L * dh, 6.0 * M * HD * sizeof(T), st, (attn_bwd_dkv_kernel<T, false>), grid, dim3(256), 0, a);
+      if (walk) {
+        PE_LAUNCH(gm.l_dkv, 10.0 * gm.B * H * gm.L * gm.L * dh, (7.0 * M * HD) * sizeof(T) + 4.0 * walk * btile, st, attn_bwd_walk_kernel, dim3((unsigned)(H * nkb * walk)),
+                  dim3(AttnWalk::THREADS), 0, a, dqp, dSp, walk);
+        const long long n8 = (long long)H * M;
+        if (nkb > 1)
+          PE_LAUNCH(gm.l_dq, 0, (4.0 * nkb + 2.0) * M * HD, st, attn_dq_sum_kernel, dim3((unsigned)((n8 + 255) / 256)), dim3(256), 0, dqp, (bf16*)dqkvg, nkb, n8, a.scale);
+        PE_LAUNCH("attn_dbias_reduce", 0, 4.0 * (walk + 1) * btile, st, attn_dbias_reduce8_kernel<float>, dim3((unsigned)((btile / 8 + 63) / 64)), dim3(256), 0, dSp, dbias, walk,
+                  btile);
+      } else {
+        // biased attention: two batch rows per workgroup, their dS tiles summed before the write
+        const long long Bds = c.bias ? (gm.B + 1) / 2 : gm.B;
+        if (c.bias) PE_LAUNCH(gm.l_dq, 6.0 * gm.B * H * gm.L * gm.L * dh, 5.0 * M * HD * sizeof(T) + 1.0 * Bds * H * gm.L * gm.L * sizeof(T), st, (attn_bwd_dq2_kernel<T>), dim3(attn_grid_size(Bds, H, gm.L)), dim3(512), 0, a);
+        else PE_LAUNCH(gm.l_dq, 6.0 * gm.B * H * gm.L * gm.L * dh, 5.0 * M * HD * sizeof(T), st, (attn_bwd_dq_kernel<T, false>), grid, dim3(256), 0, a);
+        if (c.bias) PE_LAUNCH(gm.l_dkv, 8.0 * gm.B * H * gm.L * gm.L * dh, 6.0 * M * HD * sizeof(T), st, (attn_bwd_dkv_kernel<T, true>), grid, dim3(256), 0, a);
+        else PE_LAUNCH(gm.l_dkv, 8.0 * gm.B * H * gm.L * gm.L * dh, 6.0 * M * HD * sizeof(T), st, (attn_bwd_dkv_kernel<T, false>), grid, dim3(256), 0, a);
+        if (c.bias) {
+          const long long hll = btile;
+          if (hll % 8 == 0 && al16(dS) && al16(dbias))
+            PE_LAUNCH("attn_dbias_reduce", 0, 1.0 * Bds * hll * sizeof(T) + 4.0 * hll, st, attn_dbias_reduce8_kernel<T>, dim3((unsigned)((hll / 8 + 63) / 64)), dim3(256), 0,
+                      dS, dbias, (int)Bds, hll);
+          else
+            PE_LAUNCH("attn_dbias_reduce", 0, 1.0 * Bds * hll * sizeof(T) + 4.0 * hll, st, attn_dbias_reduce_kernel<T>, dim3((unsigned)((hll + 255) / 256)), dim3(256), 0, dS, dbias,
+                      (int)Bds, hll);
+        }
+      }
       if (c.bias) {
-        const long long hll = btile;
-        if (hll % 8 == 0 && al16(dS) && al16(dbias))
-          PE_LAUNCH("attn_dbias_reduce", 0, 1.0 * Bds * hll * sizeof(T) + 4.0 * hll, st, attn_dbias_reduce8_kernel<T>, dim3((unsigned)((hll / 8 + 63) / 64)), dim3(256), 0,
-                    dS, dbias, (int)Bds, hll);
-        else
-          PE_LAUNCH("attn_dbias_reduce", 0, 1.0 * Bds * hll * sizeof(T) + 4.0 * hll, st, attn_dbias_reduce_kernel<T>, dim3((unsigned)((hll + 255) / 256)), dim3(256), 0, dS, dbias,
-                    (int)Bds, hll);
         // dbias is in the chunk order of the query-per-lane bias copy; the fused LayerNorm-backward epilogue gathers from
         // it directly, the kernel of the bias path wants it in pair-row order
         bias_gather = bias_same_ln && gemm_ln_bwd(st, ar, op_heads_rows(dqkvg, gm, dh, M * dh), op_plain(w.wn_qkvg, 4 * HD), M, Cc, 4 * HD, dxh,

@@ -2,9 +2,11 @@
 import numpy as np
 import pytest
 
+from oracle import evoformer as ev
 from oracle.params import param_table
 from pe_inputs import make_inputs, dims_for
-from tests.parity import check_case, worst_scaled
+from tests.gpu_util import BlockRun, to_np, rel_err, param_errors
+from tests.parity import TOL, check_case, relu_decisions, worst_scaled
 
 pytestmark = pytest.mark.gpu
 
@@ -462,6 +464,33 @@ def test_global_column_attention_head_counts_and_sequence_chunks(h_msa, s, r, dt
         _assert_small(errs, tol, stats)
     else:
         _assert(errs, worst, tol, stats)
+
+
+@pytest.mark.parametrize("h_msa,s,r,mask", [(4, 1050, 33, "random_rows"), (8, 600, 128, "random_residues"),
+                                            (8, 271, 130, "random_rows"), (8, 200, 290, "random_residues"),
+                                            (8, 192, 384, "random_rows")])
+def test_row_attention_backward_over_many_rows(h_msa, s, r, mask):
+    """Head dimension 8 and enough rows for the backward kernel that walks through them (attn_walk_splits > 0): one key
+    block and several, ragged last key block / key tile / query tile, splits of unequal length, rows whose keys are all
+    masked and rows with some of them masked.  Gradients only, against the oracle under the path's own ReLU decisions
+    and at the tolerance of the bf16 path; the forward pass and the validity of the decisions are not this test's
+    (the band of tests/parity.py is calibrated on fewer units than a pair transition has here: r^2 x 64 of them put the
+    largest pre-activation error of the 16-channel forward pass at 5e-2 rms)."""
+    dims, table, inp = _case("tiny", dtype=1, s=s, r=r, c_m=32, h_msa=h_msa, d_msa=8, col_global=1)
+    table, n = param_table(dims)
+    inp = make_inputs(dims, table, n, (mask, 0.1), 41 + h_msa)
+    run = BlockRun(dims, inp)
+    run.fwd(use_ctx=True)
+    run.bwd(use_ctx=True)
+    run.sync()
+    args = (dims, inp["params"], inp["msa"], inp["pair"], inp["msa_mask"], inp["pair_mask"])
+    inter = ev.block_fwd(*args, want_cache=False)[3]
+    _, _, cache, _ = ev.block_fwd(*args, relu_on=relu_decisions(dims, run, inter)[0])
+    dm, dz, g, _ = ev.block_bwd(dims, cache, inp["d_msa_out"], inp["d_pair_out"])
+    errs = {"d_msa_in": rel_err(to_np(run.d_msa_in), dm), "d_pair_in": rel_err(to_np(run.d_pair_in), dz)}
+    errs.update({"d_params." + k: v for k, v in param_errors(to_np(run.d_params), g, table).items()})
+    worst, val = worst_scaled(errs, {"d_params." + e["name"]: int(np.prod(e["shape"])) for e in table})
+    assert val <= TOL[1], (worst, errs[worst])
 
 
 @pytest.mark.slow
