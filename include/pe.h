@@ -223,9 +223,9 @@ int pe_block_fwd(pe_handle* h, const pe_dims* dims,
  * ends; its address on the handle's device is looked up once in pe_create.  The call allocates
  * nothing (no hipMalloc / hipFree, no allocating library routine) and only enqueues.
  *   Arguments as pe_block_fwd; the caller still passes inputs and outputs.
- *   Returns PE_ERR_WORKSPACE (sizes in pe_last_error) when pe_workspace_bytes(dims, 1) exceeds
- *   pe_static_scratch_bytes(): e.g. s=24, r=48 at the tiny channel widths fits, s=128, r=256 does
- *   not.  PE_ERR_ARG when the current device is not the one the handle was created on.
+ *   Returns PE_ERR_WORKSPACE (sizes in pe_last_error) when the scratch of the forward pass exceeds
+ *   pe_static_scratch_bytes().  Dims with pe_workspace_bytes(dims, 1) <= pe_static_scratch_bytes()
+ *   always fit: e.g. s=24, r=48 at the tiny channel widths; s=128, r=256 does not.  PE_ERR_ARG when the current device is not the one the handle was created on.
  *   Every call on a device shares that device's array, which keeps the last call's contents
  *   (nothing in it has to start at zero: every kernel writes what it later reads).  Calls that
  *   overlap on one device — two handles, two host threads, or a second call enqueued on other

@@ -1719,6 +1719,13 @@ struct Plan {
   size_t ctx_total() const { return ctx_bytes + prep_bytes; }
   size_t arenas() const { return arena_m + arena_p + part_m + part_p; }
   size_t total(bool with_ctx) const { return arenas() + (with_ctx ? ctx_total() : 0) + 1024; }
+  // what a forward pass alone uses of the two arenas (of the partial-sum arenas, which belong to the backward pass, nothing)
+  size_t fwd_m, fwd_p;
+  Plan forward_only() const {
+    Plan f = *this;
+    f.arena_m = fwd_m; f.arena_p = fwd_p; f.part_m = f.part_p = 0;
+    return f;
+  }
 };
 
 template <typename T> static Plan make_plan(const pe_dims& d) {
@@ -1739,6 +1746,8 @@ template <typename T> static Plan make_plan(const pe_dims& d) {
   R.fwd_msa(nullptr);
   R.fwd_opm_project(nullptr, nullptr);
   R.fwd_pair();
+  pl.fwd_m = (R.am.high + 255) & ~(size_t)255;
+  pl.fwd_p = (R.ap.high + 255) & ~(size_t)255;
   T* gm = (T*)R.am.alloc((size_t)R.Mm * d.c_m * sizeof(T));
   T* dzb = (T*)R.am.alloc((size_t)R.Mz * d.c_z * sizeof(T));
   R.bwd_msa(nullptr, nullptr, gm, dzb);
@@ -1848,8 +1857,8 @@ template <typename T>
 static int block_fwd_impl(pe_handle* h, const pe_dims& d, const void* msa_in, const void* pair_in, const float* msa_mask,
                           const float* pair_mask, const float* params, void* msa_out, void* pair_out, void* ctx,
                           void* workspace, size_t wbytes, hipStream_t sm, hipStream_t sp, bool row_pre_done = false,
-                          const std::function<int()>* early_next = nullptr) {
-  Plan pl = plan_for(d);
+                          const std::function<int()>* early_next = nullptr, bool forward_only = false) {
+  const Plan pl = forward_only ? plan_for(d).forward_only() : plan_for(d);
   if (wbytes < pl.total(ctx == nullptr)) return PE_ERR_WORKSPACE;
   if (d.variant != PE_VARIANT_PARALLEL && h->branches != 3) return PE_ERR_ARG;
   Runner<T> R;
@@ -2258,9 +2267,9 @@ size_t pe_workspace_bytes(const pe_dims* d, int with_ctx) {
   return plan_for(*d).total(with_ctx != 0);
 }
 
-int pe_block_fwd(pe_handle* h, const pe_dims* dims, const void* msa_in, const void* pair_in, const float* msa_mask,
-                 const float* pair_mask, const float* params, void* msa_out, void* pair_out, void* ctx, void* workspace,
-                 size_t workspace_bytes, void* stream_msa, void* stream_pair) {
+static int block_fwd_call(pe_handle* h, const pe_dims* dims, const void* msa_in, const void* pair_in, const float* msa_mask,
+                          const float* pair_mask, const float* params, void* msa_out, void* pair_out, void* ctx, void* workspace,
+                          size_t workspace_bytes, void* stream_msa, void* stream_pair, bool forward_only) {
   if (!h || !dims || !msa_in || !pair_in || !msa_mask || !pair_mask || !params || !msa_out || !pair_out || !workspace)
     return PE_ERR_NULL;
   int rc = pe_check_dims(dims);
@@ -2268,7 +2277,7 @@ int pe_block_fwd(pe_handle* h, const pe_dims* dims, const void* msa_in, const vo
   size_t E = dims->dtype == PE_BF16 ? 2 : 4;
   size_t nm = (size_t)dims->s * dims->r * dims->c_m * E, nz = (size_t)dims->r * dims->r * dims->c_z * E;
   {
-    const Plan pl = plan_for(*dims);
+    const Plan pl = forward_only ? plan_for(*dims).forward_only() : plan_for(*dims);
     const Region rg[] = {{msa_in, nm, false}, {pair_in, nz, false}, {msa_mask, (size_t)dims->s * dims->r * 4, false},
                          {pair_mask, (size_t)dims->r * dims->r * 4, false}, {params, (size_t)pe_param_count(dims) * 4, false},
                          {msa_out, nm, true}, {pair_out, nz, true}, {ctx, ctx ? pl.ctx_total() : 0, true},
@@ -2278,9 +2287,15 @@ int pe_block_fwd(pe_handle* h, const pe_dims* dims, const void* msa_in, const vo
   if (((uintptr_t)workspace) % 256 || (ctx && ((uintptr_t)ctx) % 256)) return PE_ERR_ARG;
   if (dims->dtype == PE_BF16)
     return block_fwd_impl<bf16>(h, *dims, msa_in, pair_in, msa_mask, pair_mask, params, msa_out, pair_out, ctx, workspace,
-                                workspace_bytes, (hipStream_t)stream_msa, (hipStream_t)stream_pair);
+                                workspace_bytes, (hipStream_t)stream_msa, (hipStream_t)stream_pair, false, nullptr, forward_only);
   return block_fwd_impl<float>(h, *dims, msa_in, pair_in, msa_mask, pair_mask, params, msa_out, pair_out, ctx, workspace,
-                               workspace_bytes, (hipStream_t)stream_msa, (hipStream_t)stream_pair);
+                               workspace_bytes, (hipStream_t)stream_msa, (hipStream_t)stream_pair, false, nullptr, forward_only);
+}
+int pe_block_fwd(pe_handle* h, const pe_dims* dims, const void* msa_in, const void* pair_in, const float* msa_mask,
+                 const float* pair_mask, const float* params, void* msa_out, void* pair_out, void* ctx, void* workspace,
+                 size_t workspace_bytes, void* stream_msa, void* stream_pair) {
+  return block_fwd_call(h, dims, msa_in, pair_in, msa_mask, pair_mask, params, msa_out, pair_out, ctx, workspace, workspace_bytes,
+                        stream_msa, stream_pair, false);
 }
 
 size_t pe_static_scratch_bytes(void) { return PE_STATIC_SCRATCH_BYTES; }
@@ -2296,7 +2311,8 @@ int pe_block_fwd_static(pe_handle* h, const pe_dims* dims, const void* msa_in, c
     h->last_error = "pe_block_fwd_static: the handle belongs to another device than the current one";
     return PE_ERR_ARG;
   }
-  const size_t need = plan_for(*dims).total(true);
+  // the array is laid out for a forward pass: the arenas of pe_workspace_bytes cover the backward pass too
+  const size_t need = plan_for(*dims).forward_only().total(true);
   if (need > PE_STATIC_SCRATCH_BYTES) {
     char msg[160];
     snprintf(msg, sizeof(msg), "pe_block_fwd_static: these dims need %zu bytes of scratch, the static array holds %zu",
@@ -2305,8 +2321,8 @@ int pe_block_fwd_static(pe_handle* h, const pe_dims* dims, const void* msa_in, c
     return PE_ERR_WORKSPACE;
   }
   // nothing in the scratch has to start at zero: every kernel writes what it later reads
-  return pe_block_fwd(h, dims, msa_in, pair_in, msa_mask, pair_mask, params, msa_out, pair_out, nullptr, h->static_scratch,
-                      PE_STATIC_SCRATCH_BYTES, stream_msa, stream_pair);
+  return block_fwd_call(h, dims, msa_in, pair_in, msa_mask, pair_mask, params, msa_out, pair_out, nullptr, h->static_scratch,
+                        PE_STATIC_SCRATCH_BYTES, stream_msa, stream_pair, true);
 }
 
 int pe_block_bwd(pe_handle* h, const pe_dims* dims, const void* msa_in, const void* pair_in, const float* msa_mask,

@@ -55,3 +55,25 @@ def test_static_scratch_rejects_large_dims():
     with pytest.raises(pe.PEError, match="static array holds"):
         pe.block_fwd_static(run.h, dims, run.msa, run.pair, run.msa_mask, run.pair_mask, run.params,
                             run.msa_out, run.pair_out, run.sm, run.sp)
+
+
+@pytest.mark.parametrize("name, over", [
+    ("extra_msa", dict(s=13, r=12, dtype=0)), ("extra_msa", dict(s=64, r=9, dtype=0)), ("tiny", dict(s=64, r=73, dtype=1)),
+    ("af2_initial", dict(s=8, r=9, dtype=1)), ("extra_msa", dict(s=32, r=11, dtype=0, variant=1))])
+def test_static_scratch_holds_blocks_with_padded_planes(name, over):
+    """Residue counts that are not multiples of 8, just below the limit without the padding of the channel-major planes:
+    pe_workspace_bytes, which covers the backward pass too, is above it; the forward pass fits."""
+    dims, mask, _ = dims_for(name)
+    dims.update(over)
+    table, n = param_table(dims)
+    run = BlockRun(dims, make_inputs(dims, table, n, mask, 57))
+    run.fwd(use_ctx=False)
+    torch.cuda.synchronize()
+    ref = run.msa_out.clone(), run.pair_out.clone()
+    run.msa_out.zero_()
+    run.pair_out.zero_()
+    torch.cuda.synchronize()
+    pe.block_fwd_static(run.h, run.dims, run.msa, run.pair, run.msa_mask, run.pair_mask, run.params, run.msa_out,
+                        run.pair_out, run.sm, run.sp)
+    torch.cuda.synchronize()
+    assert torch.equal(run.msa_out, ref[0]) and torch.equal(run.pair_out, ref[1])
