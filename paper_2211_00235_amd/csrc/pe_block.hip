@@ -154,8 +154,13 @@ template <typename T> static void carve_trans_ctx(Carver& cv, TransCtx<T>& a, co
 }
 // Row pitch of the triangle multiplication's channel-major planes [c][r][pitch]: r rounded up to 8 elements (the padding is
 // kept at zero), so that the vector kernels take every residue count.  r itself where the fused projection + gating
-// epilogue, which writes the padding, does not apply (c_tri not a multiple of 32).
-static int tm_pitch(const pe_dims& d) { return d.c_tri % 32 == 0 ? (d.r + 7) / 8 * 8 : d.r; }
+// epilogue, which writes the padding, does not apply (c_tri not a multiple of 32), and where the pitch would exceed 2 r
+// (r < 4): kernels that walk over the positions read channel-last row q r + j of position (q, j), padding included, and
+// for q <= r - 2, j < pitch that row is inside the r^2 rows of the pair tensor only up to a pitch of 2 r.
+static int tm_pitch(const pe_dims& d) {
+  const int pitch = (d.r + 7) / 8 * 8;
+  return d.c_tri % 32 == 0 && pitch <= 2 * d.r ? pitch : d.r;
+}
 template <typename T> static void carve_trimul_ctx(Carver& cv, TriMulCtx<T>& a, const char* pre, long long Mz, long long Pz, int cz, int ct) {
   char nm[32];
   auto N = [&](const char* s) { if (cv.rec) snprintf(nm, sizeof(nm), "%s.%s", pre, s); return nm; };

@@ -70,6 +70,22 @@ def test_sizes_are_consistent(L):
     assert pe.param_count(dict(d, variant=2)) == pe.param_count(d)
 
 
+@pytest.mark.parametrize("dtype", [0, 1])
+@pytest.mark.parametrize("c_tri", [24, 32])
+def test_positions_of_padded_planes_stay_inside_the_pair_tensor(L, c_tri, dtype):
+    """The triangle multiplication's kernels walk over the positions of channel-major planes [r][pitch] up to the last one
+    that is not padding, and read row (p // pitch) * r + p % pitch of the channel-last tensors for each of them, padding
+    included: every such row has to exist.  The pitch is read off the ctx table (proj_t holds 4 c_tri planes)."""
+    for r in range(1, 131):
+        d = dict(CONFIGS["tiny"][0], r=r, c_tri=c_tri, dtype=dtype)
+        for e in pe.ctx_table(d):
+            if e["name"] in ("tmo.proj_t", "tmi.proj_t"):
+                pitch, rest = divmod(e["count"], 4 * c_tri * r)
+                assert rest == 0 and pitch in (r, (r + 7) // 8 * 8), (r, pitch)
+                last = max((p // pitch) * r + p % pitch for p in range((r - 1) * pitch + r))
+                assert last < r * r, "r %d: pitch %d reads row %d of %d" % (r, pitch, last, r * r)
+
+
 def test_null_and_error_strings(L):
     assert L.pe_block_fwd(None, None, None, None, None, None, None, None, None, None, None, 0, None, None) == -1
     assert L.pe_block_bwd(None, None, None, None, None, None, None, None, None, None, None, None, None, None, 0,
