@@ -149,6 +149,9 @@ def test_small_problem_gemms(s, r, c_m, c_z, dtype):
     dims, table, inp = _case("tiny", dtype=dtype, s=s, r=r, c_m=c_m, c_z=c_z)
     table, n = param_table(dims)
     inp = make_inputs(dims, table, n, ("random_residues", 0.1), 29)
+    names = _kernel_launches(BlockRun(dims, inp))
+    for form in ("kc,kc", "LayerNorm", "EpiLnBwd"):
+        assert names.get("gemm_small_kernel<%s>" % form, 0) > 0, (form, names)
     errs, worst, tol, stats = check_case(dims, table, inp)
     _assert(errs, worst, tol, stats)
 
@@ -503,20 +506,28 @@ def test_global_column_attention_head_counts_and_sequence_chunks(h_msa, s, r, dt
         _assert(errs, worst, tol, stats)
 
 
-@pytest.mark.parametrize("h_msa,s,r,mask", [(4, 1050, 33, "random_rows"), (8, 600, 128, "random_residues"),
-                                            (8, 271, 130, "random_rows"), (8, 200, 290, "random_residues"),
-                                            (8, 192, 384, "random_rows")])
-def test_row_attention_backward_over_many_rows(h_msa, s, r, mask):
-    """Head dimension 8 and enough rows for the backward kernel that walks through them (attn_walk_splits > 0): one key
-    block and several, ragged last key block / key tile / query tile, splits of unequal length, rows whose keys are all
-    masked and rows with some of them masked.  Gradients only, against the oracle under the path's own ReLU decisions
-    and at the tolerance of the bf16 path; the forward pass and the validity of the decisions are not this test's
-    (the band of tests/parity.py is calibrated on fewer units than a pair transition has here: r^2 x 64 of them put the
-    largest pre-activation error of the 16-channel forward pass at 5e-2 rms)."""
-    dims, table, inp = _case("tiny", dtype=1, s=s, r=r, c_m=32, h_msa=h_msa, d_msa=8, col_global=1)
-    table, n = param_table(dims)
-    inp = make_inputs(dims, table, n, (mask, 0.1), 41 + h_msa)
+def _kernel_launches(run, use_ctx=True):
+    """One forward and backward pass with per-kernel timing on: launches by kernel name."""
+    run.h.set_option(3, 1)      # PE_OPT_KERNEL_TIMING
+    run.fwd(use_ctx=use_ctx)
+    run.bwd(use_ctx=use_ctx)
+    run.sync()
+    out = {}
+    for e in run.h.timing_collect():
+        out[e["kernel"]] = out.get(e["kernel"], 0) + e["launches"]
+    run.h.set_option(3, 0)
+    return out
+
+
+def _check_walking_backward(dims, inp, table, launches):
+    """Gradients only, against the oracle under the path's own ReLU decisions and at the tolerance of the bf16 path; the
+    forward pass and the validity of the decisions are not these tests' (the band of tests/parity.py is calibrated on
+    fewer units than a pair transition has here: r^2 x 64 of them put the largest pre-activation error of the 16-channel
+    forward pass at 5e-2 rms).  launches: how many attentions of the block take the walking kernel."""
     run = BlockRun(dims, inp)
+    assert _kernel_launches(run).get("attn_bwd_walk_kernel", 0) == launches
+    run.d_params.zero_()
+    run.sync()
     run.fwd(use_ctx=True)
     run.bwd(use_ctx=True)
     run.sync()
@@ -528,6 +539,28 @@ def test_row_attention_backward_over_many_rows(h_msa, s, r, mask):
     errs.update({"d_params." + k: v for k, v in param_errors(to_np(run.d_params), g, table).items()})
     worst, val = worst_scaled(errs, {"d_params." + e["name"]: int(np.prod(e["shape"])) for e in table})
     assert val <= TOL[1], (worst, errs[worst])
+
+
+@pytest.mark.parametrize("h_msa,s,r,mask", [(4, 1050, 33, "random_rows"), (8, 600, 128, "random_residues"),
+                                            (8, 271, 130, "random_rows"), (8, 200, 290, "random_residues"),
+                                            (8, 192, 384, "random_rows"), (8, 545, 17, "random_rows")])
+def test_row_attention_backward_over_many_rows(h_msa, s, r, mask):
+    """Head dimension 8 and enough rows for the backward kernel that walks through them (attn_walk_splits > 0): one key
+    block and several, one query tile (two of the three wave groups own none), ragged last key block / key tile / query
+    tile, splits of unequal length, rows whose keys are all masked and rows with some of them masked."""
+    dims, table, inp = _case("tiny", dtype=1, s=s, r=r, c_m=32, h_msa=h_msa, d_msa=8, col_global=1)
+    table, n = param_table(dims)
+    inp = make_inputs(dims, table, n, (mask, 0.1), 41 + h_msa)
+    _check_walking_backward(dims, inp, table, 1)
+
+
+def test_triangle_attention_backward_over_many_rows():
+    """Pair heads of dimension 8 send both triangle attentions through the walking kernel: positions and key mask strided
+    the other way round at the ending node, a ragged third key block, bias gradient in the LayerNorm epilogue's order."""
+    dims, table, inp = _case("tiny", dtype=1, s=4, r=257, c_m=32, c_z=32, h_pair=8, d_pair=8)
+    table, n = param_table(dims)
+    inp = make_inputs(dims, table, n, ("random_residues", 0.1), 43)
+    _check_walking_backward(dims, inp, table, 2)
 
 
 @pytest.mark.slow

@@ -65,6 +65,7 @@ def test_static_scratch_holds_blocks_with_padded_planes(name, over):
     pe_workspace_bytes, which covers the backward pass too, is above it; the forward pass fits."""
     dims, mask, _ = dims_for(name)
     dims.update(over)
+    assert pe.workspace_bytes(dims, 1) > pe.static_scratch_bytes()
     table, n = param_table(dims)
     run = BlockRun(dims, make_inputs(dims, table, n, mask, 57))
     run.fwd(use_ctx=False)
