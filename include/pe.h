@@ -108,7 +108,11 @@ typedef struct pe_param_entry {
 } pe_param_entry;
 
 /* One saved activation inside ctx (introspection for tests and debugging).
- * dtype: PE_F32 or PE_BF16 storage of that entry.                            */
+ * dtype: PE_F32 or PE_BF16 storage of that entry.
+ * tmo / tmi proj_t, a_t, b_t and x_t are channel-major planes [channel][r][pitch] (4 c_tri channels
+ * in proj_t, c_tri in the others).  pitch is r rounded up to a multiple of 8, and columns r..pitch-1
+ * hold zeros, when c_tri is a multiple of 32 and that is at most 2 r (r >= 4); otherwise pitch = r.
+ * So pitch = count / (channels * r).                                         */
 typedef struct pe_ctx_entry {
   char name[32];
   long long offset_bytes;
@@ -225,7 +229,8 @@ int pe_block_fwd(pe_handle* h, const pe_dims* dims,
  *   Arguments as pe_block_fwd; the caller still passes inputs and outputs.
  *   Returns PE_ERR_WORKSPACE (sizes in pe_last_error) when the scratch of the forward pass exceeds
  *   pe_static_scratch_bytes().  Dims with pe_workspace_bytes(dims, 1) <= pe_static_scratch_bytes()
- *   always fit: e.g. s=24, r=48 at the tiny channel widths; s=128, r=256 does not.  PE_ERR_ARG when the current device is not the one the handle was created on.
+ *   always fit: e.g. s=24, r=48 at the tiny channel widths; s=128, r=256 does not.  PE_ERR_ARG
+ *   when the current device is not the one the handle was created on.
  *   Every call on a device shares that device's array, which keeps the last call's contents
  *   (nothing in it has to start at zero: every kernel writes what it later reads).  Calls that
  *   overlap on one device — two handles, two host threads, or a second call enqueued on other

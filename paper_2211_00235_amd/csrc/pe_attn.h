@@ -1137,7 +1137,9 @@ __global__ __launch_bounds__(256) void attn_dq_sum_kernel(const float* dqp, bf16
 // Workgroups along the batch axis of attn_bwd_walk_kernel, 0: the call keeps the kernels per batch row.  A workgroup
 // takes 32 rows or more (it writes one 32-bit dS plane for them) and two rounds of workgroups fill the CUs; below 128 workgroups half
 // of the CUs would idle.  At the line both are close (B 256, L 256, one-stream block: 2.72 ms without, 2.71 ms with it);
-// B 512, L 40: 1.03 -> 0.97 ms; B 5120, L 40: 2.77 -> 2.36 ms; B 1024, L 128: 1.99 -> 1.89 ms.
+// B 512, L 40: 1.03 -> 0.97 ms; B 5120, L 40: 2.77 -> 2.36 ms; B 1024, L 128: 1.99 -> 1.89 ms.  A last key
+// block with one active key tile of four does not change that (one-stream blocks; L 136: B 1024 2.45 -> 2.27 ms, B 512 1.92 -> 1.82,
+// B 256 1.54 -> 1.54; L 264: B 1024 5.16 -> 4.74, B 256 3.29 -> 3.19 ms).
 static inline int attn_walk_splits(bool bf, bool bias, long long B, int H, long long L, int d) {
   if (!bf || !bias || d != 8 || L > AttnWalk::LMAX) return 0;
   const long long units = H * ((L + AttnWalk::KB - 1) / AttnWalk::KB);

@@ -393,8 +393,8 @@ __global__ __launch_bounds__(256) void ln_cmajor_bwd_kernel(const T* dy, const T
   }
 }
 
-// Channel-major planes hold M = r * pitch positions, position p = (p / pitch, p % pitch); with pitch > r (odd residue
-// counts: every plane row starts on a 16-byte boundary) the positions p % pitch >= r are padding, zeros in every plane.
+// Channel-major planes hold M = r * pitch positions, position p = (p / pitch, p % pitch); with pitch > r (residue
+// counts that are not multiples of 8: every plane row starts on a 16-byte boundary) the positions p % pitch >= r are padding, zeros in every plane.
 struct PlanePos {
   int r, pitch;
   // channel-last row of position p; ok is cleared for padding
