@@ -17,6 +17,7 @@
 #include "pe_gcol.h"
 #include "pe_gemm.h"
 #include "pe_layout.h"
+#include "pe_rows.h"
 #include "pe_small.h"
 
 // Scratch of pe_block_fwd_static: one array per device, held from the load of the library's code object
@@ -679,7 +680,7 @@ template <typename T> struct Runner {
       return;
     }
     if (dry || err) return;
-    GemmShape sh{M, N, K, batch, 0, 0, b_rows};
+    GemmShape sh{M, N, K, batch, 0, 0, b_rows, alone() ? 0 : 1};
     prof_begin(st);
     bool al = false, narrow = false;
     int rc = launch_gemm<T, EpiGeneric<T>>(st, A, akc, B, bkc, sh, e, &al, &narrow);
@@ -691,6 +692,7 @@ template <typename T> struct Runner {
     char kn[64] = "";
     if (!timed()) {}
     else if (g_gemm_last_small) snprintf(kn, sizeof(kn), "gemm_small_kernel<%s,%s>", akc ? "kc" : "xc", bkc ? "kc" : "xc");
+    else if (g_gemm_last_rows) snprintf(kn, sizeof(kn), "gemm_rows_kernel<F=%d,K=%d>", g_gemm_last_features, K);
     else if (narrow) snprintf(kn, sizeof(kn), "gemm64_kernel<EpiGeneric,F=%d>", g_gemm_last_features);
     else snprintf(kn, sizeof(kn), "gemm_kernel<%s,%s,%s,EpiGeneric,F=%d>", akc ? "kc" : "xc", bkc ? "kc" : "xc", al ? "vec" : "elem",
                   g_gemm_last_features);

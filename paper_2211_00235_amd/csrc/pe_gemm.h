@@ -52,6 +52,7 @@ struct GemmShape {
   int k_chunk;  // > 0: split-K; batch index selects the k range [b*k_chunk, min(K,(b+1)*k_chunk))
   int unit_n;   // block mapping: 0 = an XCD owns (batch, m-tile) units, 1 = (batch, n-tile) units (set by the launcher)
   int n_rows;   // rows of B (gemm_kernel; 0 = N, filled in by the launcher): columns n_rows..N-1 are computed from zeros
+  int beside = 0;   // 1: another branch's kernels run beside this launch
 };
 
 // 8 consecutive storage elements <-> 8 floats (one or two 16-byte accesses)
@@ -2215,6 +2216,9 @@ template <typename T, class Epi>
 static inline void launch_gemm_small(hipStream_t st, const Operand& A, bool a_kc, const Operand& B, bool b_kc, const GemmShape& sh, const Epi& epi);
 // true after a launch_gemm call of this host thread that took the small-problem kernel
 static thread_local bool g_gemm_last_small = false;
+// tall A, contraction over channels (pe_rows.h): false = not launched
+template <class Epi> static inline bool launch_gemm_rows(hipStream_t st, const Operand& A, const Operand& B, const GemmShape& sh, const Epi& epi);
+static thread_local bool g_gemm_last_rows = false;
 
 // Operands that break the 16-byte vector rules (odd leading dimensions) take the
 // element-wise loader and the per-element epilogue: same tiles, same arithmetic, slower.
@@ -2231,6 +2235,7 @@ static inline int launch_gemm(hipStream_t st, const Operand& A, bool a_kc, const
   if (sh.k_chunk > 0 && sh.k_chunk % GemmCfg<T>::BK) return -1;
   bool al = gemm_operand_ok<T>(A, a_kc, sh.M, sh) && gemm_operand_ok<T>(B, b_kc, sh.N, sh);
   g_gemm_last_small = false;
+  g_gemm_last_rows = false;
   if constexpr (!Epi::TM_GATE) {
     const bool sve = epi.vec_ok(sh.N);
     // bf16 parameter gradients have a kernel that is faster even there (gemm_dwx_kernel)
@@ -2245,6 +2250,13 @@ static inline int launch_gemm(hipStream_t st, const Operand& A, bool a_kc, const
   }
   bool ve = al && epi.vec_ok(sh.N);
   if (used_vec) *used_vec = ve;
+  if (used_narrow) *used_narrow = false;
+  if constexpr (std::is_same<T, bf16>::value) {
+    if (ve && a_kc && b_kc && launch_gemm_rows<Epi>(st, A, B, sh, epi)) {
+      g_gemm_last_rows = true;
+      return hipGetLastError() == hipSuccess ? 0 : -2;
+    }
+  }
   const int NTm_ = (sh.M + 127) / 128, NTn_ = (sh.N + 127) / 128;
   // units over m-tiles unless units over n-tiles leave fewer idle slots on the 8 XCDs
   const long long um = (long long)NTm_ * sh.batch, un = (long long)NTn_ * sh.batch;
@@ -2253,7 +2265,6 @@ static inline int launch_gemm(hipStream_t st, const Operand& A, bool a_kc, const
   dim3 grid((unsigned)(sh.unit_n ? gn_ : gm_));
   // narrow outputs of tall GEMMs: 64-row tiles (twice the workgroups)
   const bool narrow = ve && a_kc && b_kc && sh.n_rows == sh.N && sh.batch == 1 && sh.k_chunk == 0 && sh.N <= 128 && sh.M >= 128 * 256;
-  if (used_narrow) *used_narrow = false;
   if (narrow && launch_gemm64<T, Epi>(st, A, B, sh, epi)) {
     if (used_narrow) *used_narrow = true;
     return hipGetLastError() == hipSuccess ? 0 : -2;

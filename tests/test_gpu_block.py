@@ -563,6 +563,22 @@ def test_triangle_attention_backward_over_many_rows():
     _check_walking_backward(dims, inp, table, 2)
 
 
+@pytest.mark.parametrize("name,s,r,two_streams,ks", [("af2_initial", 81, 131, False, (256, 128)), ("af2_initial", 9, 33, False, (128,)),
+                                                     ("extra_msa", 150, 47, True, (64,))])
+def test_row_streaming_gemms(name, s, r, two_streams, ks):
+    """The GEMMs whose waves walk through 32-row blocks (pe_rows.h) at each contraction length: a ragged last block, more
+    blocks than wave slots (81 x 131 rows over four panels) and fewer, head-major output of 8 and 32 channels, strided rows
+    (column attention, ending node), ReLU decisions on the way out and in."""
+    dims, table, inp = _case(name, s=s, r=r)
+    table, n = param_table(dims)
+    inp = make_inputs(dims, table, n, ("random_residues", 0.1), s + r)
+    run = BlockRun(dims, inp, two_streams=two_streams)
+    seen = {k.split("K=")[1].rstrip(">") for k in _kernel_launches(run) if k.startswith("gemm_rows_kernel")}
+    assert {str(k) for k in ks} <= seen, seen
+    errs, worst, tol, stats = check_case(dims, table, inp, two_streams=two_streams)
+    _assert(errs, worst, tol, stats)
+
+
 @pytest.mark.slow
 def test_extra_msa_bf16():
     """Config 3: extra-MSA-stack block (s=1024, r=256, c_m=64, global column attention), bf16."""
