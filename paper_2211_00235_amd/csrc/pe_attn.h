@@ -32,8 +32,8 @@ struct AttnArgs {
   const void* biasQ;                 // [H][key tile][chunk][g][query][CH]: read by the query-per-lane kernels
   const void* biasK;                 // [H][query tile][chunk][g][key][CH]: read by the key-per-lane kernel
   const float* mask; long long mask_bs, mask_ks;   // key mask value at mask[b*mask_bs + j*mask_ks]
-  void* o; void* og;                 // forward outputs (o ungated, og = sigmoid(g) * o)
-  float* lse;                        // [B][H][L]
+  void* o; void* og;                 // forward outputs (o ungated, og = sigmoid(g) * o); the forward kernel takes o, lse = nullptr:
+  float* lse;                        // [B][H][L]              not stored (only a backward pass reads them)
   float scale;                       // 1/sqrt(d)
   // backward
   const void* dog;                   // cotangent of og
@@ -446,9 +446,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(PE_FWD_WAVE
   const float l_run = l_part + __shfl_xor(l_part, 32, 64);
   if (!qok) return;
   float inv = (l_run > 0.0f) ? 1.0f / l_run : 0.0f;
-  if (g == 0) a.lse[((long long)b * a.H + h) * L + qi] = (l_run > 0.0f) ? (m_ref + log2f(l_run)) * PE_LN2 : 0.0f;
+  if (g == 0 && a.lse) a.lse[((long long)b * a.H + h) * L + qi] = (l_run > 0.0f) ? (m_ref + log2f(l_run)) * PE_LN2 : 0.0f;
   const long long orow = h * a.plane + ((long long)b * L + qi) * d;
-  T* po = (T*)a.o + orow;
+  T* po = a.o ? (T*)a.o + orow : nullptr;
   T* pog = (T*)a.og + orow;
   const T* pg = qrow + 3 * HP;
 #pragma unroll
@@ -462,7 +462,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(PE_FWD_WAVE
         ov[r] = oacc[q4 * 4 + r] * inv;
         ogv[r] = ov[r] * sigmoidf_(gv[r]);
       }
-      store4<T>(po + dd, ov);
+      if (po) store4<T>(po + dd, ov);
       store4<T>(pog + dd, ogv);
     }
   }

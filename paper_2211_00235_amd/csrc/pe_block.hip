@@ -227,6 +227,7 @@ template <typename T> static size_t carve_ctx(char* base, const pe_dims& d, Ctx<
 // ---------------------------------------------------------------------------
 struct PrepList {
   std::vector<PrepDesc> t;   // storage-type destinations (offsets in elements from the T region)
+  std::vector<PrepDesc> tb;  // the same, copies that only a backward pass reads
   std::vector<PrepDesc> f;   // fp32 destinations
 };
 template <typename T> struct PrepCarver {
@@ -236,11 +237,12 @@ template <typename T> struct PrepCarver {
   // weight W[in][out] at params offset src -> transposed copy [out][in] placed at row block `row0` of a [*, in] matrix
   T* region(long long count) { long long o = (toff + 127) & ~127LL; toff = o + count; return tbase + o; }
   float* fregion(long long count) { long long o = (foff + 63) & ~63LL; foff = o + count; return fbase + o; }
-  void add(T* dst, long long src, int rows, int cols, long long ld_r, long long ld_c, float scale = 1.0f, int c_blk = 0, int c_blk_to = 0) {
+  void add(T* dst, long long src, int rows, int cols, long long ld_r, long long ld_c, float scale = 1.0f, int c_blk = 0, int c_blk_to = 0, bool bwd = false) {
     PrepDesc p; p.src_off = src; p.dst_off = dst - tbase; p.rows = rows; p.cols = cols; p.ld_r = ld_r; p.ld_c = ld_c;
     p.scale = scale; p.c_blk = c_blk; p.c_blk_to = c_blk_to;
-    list->t.push_back(p);
+    (bwd ? list->tb : list->t).push_back(p);
   }
+  void add_bwd(T* dst, long long src, int rows, int cols, long long ld_r, long long ld_c) { add(dst, src, rows, cols, ld_r, ld_c, 1.0f, 0, 0, true); }
   void addf(float* dst, long long src, int n) {
     PrepDesc p; p.src_off = src; p.dst_off = dst - fbase; p.rows = 1; p.cols = n; p.ld_r = -1; p.ld_c = 1; p.scale = 1.0f;
     p.c_blk = 0; p.c_blk_to = 0;
@@ -261,18 +263,18 @@ template <typename T> static void prep_attn(PrepCarver<T>& pc, AttnW<T>& w, cons
   const long long src[4] = {p.w_q, p.w_k, p.w_v, p.w_g};
   for (int k = 0; k < 4; k++) {
     pc.add(w.wt_qkvg + (long long)k * HD * C, src[k], C, HD, 1, C, k == 0 ? qscale : 1.0f);   // [out][in]
-    pc.add(w.wn_qkvg + (long long)k * HD, src[k], C, HD, 4 * HD, 1);  // [in][4HD]
+    pc.add_bwd(w.wn_qkvg + (long long)k * HD, src[k], C, HD, 4 * HD, 1);  // [in][4HD]
   }
   pc.add(w.wt_o, p.w_o, HD, C, 1, HD);   // [C][HD]
-  pc.add(w.wn_o, p.w_o, HD, C, C, 1);    // [HD][C]
+  pc.add_bwd(w.wn_o, p.w_o, HD, C, C, 1);    // [HD][C]
 }
 template <typename T> static void prep_trans(PrepCarver<T>& pc, TransW<T>& w, const TransP& p, int C, int n) {
   long long nc = (long long)n * C;
   w.wt_1 = pc.region(nc * C); w.wn_1 = pc.region(nc * C); w.wt_2 = pc.region(nc * C); w.wn_2 = pc.region(nc * C);
   pc.add(w.wt_1, p.w1, C, (int)nc, 1, C);      // [nC][C]
-  pc.add(w.wn_1, p.w1, C, (int)nc, nc, 1);     // [C][nC]
+  pc.add_bwd(w.wn_1, p.w1, C, (int)nc, nc, 1);     // [C][nC]
   pc.add(w.wt_2, p.w2, (int)nc, C, 1, nc);     // [C][nC]
-  pc.add(w.wn_2, p.w2, (int)nc, C, C, 1);      // [nC][C]
+  pc.add_bwd(w.wn_2, p.w2, (int)nc, C, C, 1);      // [nC][C]
 }
 template <typename T> static void prep_trimul(PrepCarver<T>& pc, TriMulW<T>& w, const TriMulP& p, int cz, int ct) {
   w.wt_p = pc.region((long long)4 * ct * cz); w.wn_p = pc.region((long long)4 * ct * cz);
@@ -283,7 +285,7 @@ template <typename T> static void prep_trimul(PrepCarver<T>& pc, TriMulW<T>& w, 
   const long long bsrc[4] = {p.b_ap, p.b_ag, p.b_bp, p.b_bg};
   for (int k = 0; k < 4; k++) {
     pc.add(w.wt_p + (long long)k * ct * cz, src[k], cz, ct, 1, cz);   // [4ct][cz]
-    pc.add(w.wn_p + (long long)k * ct, src[k], cz, ct, 4 * ct, 1);    // [cz][4ct]
+    pc.add_bwd(w.wn_p + (long long)k * ct, src[k], cz, ct, 4 * ct, 1);    // [cz][4ct]
     pc.addf(w.bias_p + k * ct, bsrc[k], ct);
   }
   w.wt_pi = nullptr;
@@ -293,9 +295,9 @@ template <typename T> static void prep_trimul(PrepCarver<T>& pc, TriMulW<T>& w, 
       pc.add(w.wt_pi + ((long long)(k >> 1) * (ct / 32) * 64 + (k & 1) * 32) * cz, src[k], cz, ct, 1, cz, 1.0f, 32, 64);
   }
   pc.add(w.wt_g, p.w_g, cz, cz, 1, cz);
-  pc.add(w.wn_g, p.w_g, cz, cz, cz, 1);
+  pc.add_bwd(w.wn_g, p.w_g, cz, cz, cz, 1);
   pc.add(w.wt_o, p.w_o, ct, cz, 1, ct);   // [cz][ct]
-  pc.add(w.wn_o, p.w_o, ct, cz, cz, 1);   // [ct][cz]
+  pc.add_bwd(w.wn_o, p.w_o, ct, cz, cz, 1);   // [ct][cz]
 }
 
 // ---------------------------------------------------------------------------
@@ -315,6 +317,10 @@ template <typename T> struct Runner {
   pe_dims d;
   ParamLayout PL;
   bool dry = false;
+  // no backward pass reads what this forward pass leaves in its ctx region: what only a backward pass would read is not
+  // written (weights in its orientation, o and lse of the attentions, the bias in its layout, the triangle projections,
+  // the ungated product u, ReLU bits).  The outputs are the same bits.
+  bool lean = false;
   int err = 0;
   const float* params = nullptr;
   float* dparams = nullptr;
@@ -399,7 +405,7 @@ template <typename T> struct Runner {
     size_t fbytes = (size_t)(16 * d.c_tri + 2 * d.c_opm + 1024) * sizeof(float);
     prep_tbase_m = (T*)region(tbytes); prep_fbase_m = (float*)region(fbytes);
     prep_tbase_p = (T*)region(tbytes); prep_fbase_p = (float*)region(fbytes);
-    prep_msa.t.clear(); prep_msa.f.clear(); prep_pair.t.clear(); prep_pair.f.clear();
+    prep_msa = PrepList(); prep_pair = PrepList();
     PrepCarver<T> pm{prep_tbase_m, prep_fbase_m, 0, 0, &prep_msa};
     prep_attn<T>(pm, W.row, PL.row, d.c_m, HDm, d.d_msa);
     if (!d.col_global) prep_attn<T>(pm, W.col, PL.col, d.c_m, HDm, d.d_msa);
@@ -411,10 +417,10 @@ template <typename T> struct Runner {
       const int wd[4] = {HDm, dd, dd, HDm}, c0[4] = {0, HDm, HDm + dd, HDm + 2 * dd};
       for (int k = 0; k < 4; k++) {
         pm.add(W.gcol.wt_proj + (long long)c0[k] * C_, src[k], C_, wd[k], 1, C_);   // [Wg][C]
-        pm.add(W.gcol.wn_proj + c0[k], src[k], C_, wd[k], Wg, 1);                    // [C][Wg]
+        pm.add_bwd(W.gcol.wn_proj + c0[k], src[k], C_, wd[k], Wg, 1);                    // [C][Wg]
       }
       pm.add(W.gcol.wt_o, PL.col.w_o, HDm, C_, 1, HDm);
-      pm.add(W.gcol.wn_o, PL.col.w_o, HDm, C_, C_, 1);
+      pm.add_bwd(W.gcol.wn_o, PL.col.w_o, HDm, C_, C_, 1);
     }
     prep_trans<T>(pm, W.mt, PL.mtrans, d.c_m, d.n_trans);
     {
@@ -426,10 +432,10 @@ template <typename T> struct Runner {
       pm.addf(W.opm.bias_ab + co, PL.opm.b_b, co);
       pm.add(W.opm.wt_ab, PL.opm.w_a, cm, co, 1, cm);
       pm.add(W.opm.wt_ab + (long long)co * cm, PL.opm.w_b, cm, co, 1, cm);
-      pm.add(W.opm.wn_ab, PL.opm.w_a, cm, co, 2 * co, 1);
-      pm.add(W.opm.wn_ab + co, PL.opm.w_b, cm, co, 2 * co, 1);
+      pm.add_bwd(W.opm.wn_ab, PL.opm.w_a, cm, co, 2 * co, 1);
+      pm.add_bwd(W.opm.wn_ab + co, PL.opm.w_b, cm, co, 2 * co, 1);
       pm.add(W.opm.wt_o, PL.opm.w_o, co * co, cz, 1, (long long)co * co);   // [cz][co*co]
-      pm.add(W.opm.wn_o, PL.opm.w_o, co * co, cz, cz, 1);                   // [co*co][cz]
+      pm.add_bwd(W.opm.wn_o, PL.opm.w_o, co * co, cz, cz, 1);                   // [co*co][cz]
     }
     PrepCarver<T> pp{prep_tbase_p, prep_fbase_p, 0, 0, &prep_pair};
     prep_trimul<T>(pp, W.tmo, PL.tmo, d.c_z, d.c_tri);
@@ -445,9 +451,10 @@ template <typename T> struct Runner {
     return (off + 255) & ~(size_t)255;
   }
   // one launch per PREP_MAX descriptors; the storage-type copies and the fp32 copies of a branch go together
-  void run_prep_list(hipStream_t st, const std::vector<PrepDesc>& vt, const std::vector<PrepDesc>& vf, T* tbase, float* fbase) {
-    std::vector<PrepDesc> v(vt);
-    v.insert(v.end(), vf.begin(), vf.end());
+  void run_prep_list(hipStream_t st, const PrepList& list, T* tbase, float* fbase) {
+    std::vector<PrepDesc> v(list.t);
+    if (!lean) v.insert(v.end(), list.tb.begin(), list.tb.end());
+    v.insert(v.end(), list.f.begin(), list.f.end());
     for (size_t i = 0; i < v.size(); i += PREP_MAX) {
       PrepBatch pb;
       pb.n = (int)std::min((size_t)PREP_MAX, v.size() - i);
@@ -460,8 +467,8 @@ template <typename T> struct Runner {
   }
   void run_prep(bool msa_side) {
     if (dry) return;
-    if (msa_side) run_prep_list(sm, prep_msa.t, prep_msa.f, prep_tbase_m, prep_fbase_m);
-    else run_prep_list(sp, prep_pair.t, prep_pair.f, prep_tbase_p, prep_fbase_p);
+    if (msa_side) run_prep_list(sm, prep_msa, prep_tbase_m, prep_fbase_m);
+    else run_prep_list(sp, prep_pair, prep_tbase_p, prep_fbase_p);
   }
 
   // ---- kernel wrappers -----------------------------------------------------
@@ -949,7 +956,7 @@ template <typename T> struct Runner {
         }
         const int NT = (d.r + 31) / 32;
         PE_LAUNCH("bias_tile", 0, (4.0 + 2.0 * sizeof(T)) * H * Mz, st, bias_tile_kernel<T>, dim3(NT, NT, H), dim3(256), 0, direct, c.biasT,
-                  c.bias, d.r, transposed, 1.4426950408889634f);
+                  lean ? nullptr : c.bias, d.r, transposed, 1.4426950408889634f);
       }
       ar.release(mkb);
     }
@@ -959,7 +966,8 @@ template <typename T> struct Runner {
       a.qkvg = c.qkvg; a.plane = M * dh;
       a.B = (int)g.B; a.L = (int)g.L; a.H = H; a.d = dh;
       a.biasK = c.bias; a.biasQ = c.biasT; a.mask = g.mask; a.mask_bs = g.mask_bs; a.mask_ks = g.mask_ks;
-      a.o = c.o; a.og = c.og; a.lse = c.lse; a.scale = 1.0f / sqrtf((float)dh);
+      a.og = c.og; a.scale = 1.0f / sqrtf((float)dh);
+      if (!lean) { a.o = c.o; a.lse = c.lse; }
       dim3 grid(attn_grid_size(g.B, H, g.L));
       if (c.bias) PE_LAUNCH(g.l_fwd, 4.0 * g.B * H * g.L * g.L * dh, (5.0 * M * HD + 1.0 * M * HD) * sizeof(T) + (c.bias ? 4.0 * H * g.L * g.L : 0.0), st, (attn_fwd_kernel<T, true>), grid, dim3(256), 0, a);
       else PE_LAUNCH(g.l_fwd, 4.0 * g.B * H * g.L * g.L * dh, (5.0 * M * HD + 1.0 * M * HD) * sizeof(T) + (c.bias ? 4.0 * H * g.L * g.L : 0.0), st, (attn_fwd_kernel<T, false>), grid, dim3(256), 0, a);
@@ -1060,7 +1068,7 @@ template <typename T> struct Runner {
     {
       EpiGeneric<T> e = epi_plain<T>(c.h, nC);
       e.bias_n = P(p.b1); e.act = 1;
-      if (c.hbits) { e.bits_out = c.hbits; e.ld_bits = nC / 8; }
+      if (c.hbits && !lean) { e.bits_out = c.hbits; e.ld_bits = nC / 8; }
       gemm_ln(st, x, p.ln_g, p.ln_b, c.xhat, c.stats, M, Cc, op_plain(w.wt_1, Cc), nC, e, "trans 1");
     }
     {
@@ -1097,7 +1105,7 @@ template <typename T> struct Runner {
     bool gated = false;   // projection, gate pre-activation and gated operands from one kernel
     if (!dry && !err && w.wt_pi) {
       EpiTmGate<T> eg;
-      eg.proj_t = c.proj_t; eg.a_t = c.a_t; eg.b_t = c.b_t; eg.bias = w.bias_p; eg.mask = pair_mask; eg.ct = ct; eg.Mz = Pz; eg.r = r; eg.pitch = rp;
+      eg.proj_t = lean ? nullptr : c.proj_t; eg.a_t = c.a_t; eg.b_t = c.b_t; eg.bias = w.bias_p; eg.mask = pair_mask; eg.ct = ct; eg.Mz = Pz; eg.r = r; eg.pitch = rp;
       const Operand A = op_plain(w.wt_pi, cz), B = op_zrows(c.zhat, cz);
       GemmShape sh{4 * ct, (int)Pz, cz, 1, 0, 0, zrows_end()};
       if (eg.vec_ok((int)Pz) && gemm_operand_ok<T>(A, true, 4 * ct, sh) && gemm_operand_ok<T>(B, true, (int)Pz, sh)) {
@@ -1162,7 +1170,7 @@ template <typename T> struct Runner {
     {
       EpiGeneric<T> e = epi_plain<T>(zout, cz);
       e.bias_n = P(p.b_o);
-      e.aux = c.u; e.ld_aux = cz;
+      if (!lean) { e.aux = c.u; e.ld_aux = cz; }
       e.mul = c.g; e.ld_mul = cz;
       e.res = z; e.ld_res = cz;
       gemm_out(st, op_plain(c.xhat, ct), op_plain(w.wt_o, ct), (int)Mz, cz, ct, e, "trimul outproj");
@@ -1199,7 +1207,7 @@ template <typename T> struct Runner {
       else attn_sub_fwd(sm, am, PL.col, W.col, C.col, C.m1, C.m2, Mm, d.c_m, d.h_msa, d.d_msa, geom_col(), nullptr, 0, 0);
     } else {
       trans_sub_fwd(sm, PL.mtrans, W.mt, C.mt, C.m2, C.m3, Mm, d.c_m);
-      if (!dry && !err && msa_out) {
+      if (!dry && !err && msa_out && msa_out != C.m3) {
         if (hipMemcpyAsync(msa_out, C.m3, (size_t)Mm * d.c_m * sizeof(T), hipMemcpyDeviceToDevice, sm) != hipSuccess)
           fail("copy msa_out");
       }
@@ -1863,7 +1871,7 @@ static int run_forward(Runner<T>& R, pe_handle* h, const pe_dims& d, T* msa_out,
 template <typename T>
 static int block_fwd_impl(pe_handle* h, const pe_dims& d, const void* msa_in, const void* pair_in, const float* msa_mask,
                           const float* pair_mask, const float* params, void* msa_out, void* pair_out, void* ctx,
-                          void* workspace, size_t wbytes, hipStream_t sm, hipStream_t sp, bool row_pre_done = false,
+                          void* workspace, size_t wbytes, hipStream_t sm, hipStream_t sp, bool lean, bool row_pre_done = false,
                           const std::function<int()>* early_next = nullptr, bool forward_only = false) {
   const Plan pl = forward_only ? plan_for(d).forward_only() : plan_for(d);
   if (wbytes < pl.total(ctx == nullptr)) return PE_ERR_WORKSPACE;
@@ -1874,6 +1882,9 @@ static int block_fwd_impl(pe_handle* h, const pe_dims& d, const void* msa_in, co
   R.msa_in = (const T*)msa_in; R.pair_in = (const T*)pair_in;
   R.msa_mask = msa_mask; R.pair_mask = pair_mask;
   R.row_pre_done = row_pre_done;
+  R.lean = lean;
+  // the MSA stack's result goes straight to the caller's buffer (every kernel that reads it takes 16-byte aligned rows)
+  if (lean && msa_out && Runner<T>::al16(msa_out)) R.C.m3 = (T*)msa_out;
   if (!ev_link(h, 0, sm, sp)) return PE_ERR_HIP;
   return run_forward<T>(R, h, d, (T*)msa_out, (T*)pair_out, early_next);
 }
@@ -1898,7 +1909,7 @@ template <typename T>
 static int block_bwd_impl(pe_handle* h, const pe_dims& d, const void* msa_in, const void* pair_in, const float* msa_mask,
                           const float* pair_mask, const float* params, const void* d_msa_out, const void* d_pair_out,
                           void* d_msa_in, void* d_pair_in, float* d_params, const void* ctx, void* workspace,
-                          size_t wbytes, hipStream_t sm, hipStream_t sp) {
+                          size_t wbytes, hipStream_t sm, hipStream_t sp, bool fwd_done = false) {
   Plan pl = plan_for(d);
   if (wbytes < pl.total(ctx == nullptr)) return PE_ERR_WORKSPACE;
   if (d.variant != PE_VARIANT_PARALLEL && h->branches != 3) return PE_ERR_ARG;
@@ -1909,7 +1920,9 @@ static int block_bwd_impl(pe_handle* h, const pe_dims& d, const void* msa_in, co
   R.msa_in = (const T*)msa_in; R.pair_in = (const T*)pair_in;
   R.msa_mask = msa_mask; R.pair_mask = pair_mask;
   if (!ev_link(h, 0, sm, sp)) return PE_ERR_HIP;
-  if (ctx == nullptr) {   // recompute the forward into the internal ctx (else: ctx also holds the prepared weights)
+  // recompute the forward into the internal ctx (a caller's ctx holds all of it, the prepared weights too; fwd_done: so does the
+  // internal one, the forward pass of the same block has just filled it)
+  if (ctx == nullptr && !fwd_done) {
     if (d.variant == PE_VARIANT_PARALLEL) {
       if (do_p) R.run_prep(false);
       if (do_m) R.run_prep(true);
@@ -2082,7 +2095,7 @@ static int stack_impl(pe_handle* h, int n_extra, const pe_dims* ex, int n_main, 
                                   ctx_of(b + 1), blockws, sm, sp_);
     };
     int rc = block_fwd_impl<T>(h, d, x_in(b), z_in(b), is_e ? extra_mask : msa_mask, pair_mask, params + poff(b), xo, zo,
-                               ctx_of(b), blockws, sp.block_bytes, sm, sp_, pre_done, chain ? &early : nullptr);
+                               ctx_of(b), blockws, sp.block_bytes, sm, sp_, !sp.keep && b + 1 < nb, pre_done, chain ? &early : nullptr);
     if (rc) return rc;
     pre_done = chain;
   }
@@ -2112,7 +2125,7 @@ static int stack_impl(pe_handle* h, int n_extra, const pe_dims* ex, int n_main, 
     else dx_in = (b == n_extra) ? d_msa_in : (void*)dm_pp[b & 1];
     int rc = block_bwd_impl<T>(h, d, x_in(b), z_in(b), is_e ? extra_mask : msa_mask, pair_mask, params + poff(b),
                                is_e ? de : dm, dz, dx_in, dz_in, d_params + poff(b), ctx_of(b), blockws, sp.block_bytes, sm,
-                               sp_);
+                               sp_, b == nb - 1);
     if (rc) return rc;
     dz = dz_in;
     if (is_e) de = dx_in; else dm = dx_in;
@@ -2294,9 +2307,9 @@ static int block_fwd_call(pe_handle* h, const pe_dims* dims, const void* msa_in,
   if (((uintptr_t)workspace) % 256 || (ctx && ((uintptr_t)ctx) % 256)) return PE_ERR_ARG;
   if (dims->dtype == PE_BF16)
     return block_fwd_impl<bf16>(h, *dims, msa_in, pair_in, msa_mask, pair_mask, params, msa_out, pair_out, ctx, workspace,
-                                workspace_bytes, (hipStream_t)stream_msa, (hipStream_t)stream_pair, false, nullptr, forward_only);
+                                workspace_bytes, (hipStream_t)stream_msa, (hipStream_t)stream_pair, ctx == nullptr, false, nullptr, forward_only);
   return block_fwd_impl<float>(h, *dims, msa_in, pair_in, msa_mask, pair_mask, params, msa_out, pair_out, ctx, workspace,
-                               workspace_bytes, (hipStream_t)stream_msa, (hipStream_t)stream_pair, false, nullptr, forward_only);
+                               workspace_bytes, (hipStream_t)stream_msa, (hipStream_t)stream_pair, ctx == nullptr, false, nullptr, forward_only);
 }
 int pe_block_fwd(pe_handle* h, const pe_dims* dims, const void* msa_in, const void* pair_in, const float* msa_mask,
                  const float* pair_mask, const float* params, void* msa_out, void* pair_out, void* ctx, void* workspace,

@@ -1009,7 +1009,7 @@ __global__ __launch_bounds__(256) void bias_tile_kernel(const float* direct, T* 
 #pragma unroll
       for (int i = 0; i < CH; i++) p[i] = from_f<T>(vq[i]);
     }
-    if (k0 + tx < r) {
+    if (biasK && k0 + tx < r) {   // nullptr: no backward pass follows
       T* p = biasK + h * plane + bias_chunk_off<T>(blockIdx.y, c, g, k0 + tx, r);
 #pragma unroll
       for (int i = 0; i < CH; i++) p[i] = from_f<T>(vk[i]);
@@ -1275,23 +1275,30 @@ __global__ __launch_bounds__(256) void prep_params_kernel(const float* params, T
   T* out = dst + d.dst_off;
   for (int t = blockIdx.x; t < ntr * ntc; t += gridDim.x) {
     const int r0 = (t / ntc) * 32, c0 = (t % ntc) * 32;
+    float v[4];   // all four loads of a thread in flight at once (outside the matrix: its first element, never stored)
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+      const int r = r0 + ty + 8 * i, c = c0 + tx;
+      v[i] = src[(r < d.rows && c < d.cols) ? (long long)r * d.cols + c : 0] * d.scale;
+    }
     if (transposed) {
-      for (int k = ty; k < 32; k += 8) {
-        const int r = r0 + k, c = c0 + tx;
-        tile[k][tx] = (r < d.rows && c < d.cols) ? src[(long long)r * d.cols + c] * d.scale : 0.0f;
-      }
+#pragma unroll
+      for (int i = 0; i < 4; i++) tile[ty + 8 * i][tx] = v[i];
       __syncthreads();
-      for (int k = ty; k < 32; k += 8) {
-        const int c = c0 + k, r = r0 + tx;
+#pragma unroll
+      for (int i = 0; i < 4; i++) {
+        const int c = c0 + ty + 8 * i, r = r0 + tx;
         const int cd = d.c_blk > 0 ? (c / d.c_blk) * d.c_blk_to + c % d.c_blk : c;
-        if (r < d.rows && c < d.cols) out[r + cd * d.ld_c] = from_f<T>(tile[tx][k]);
+        if (r < d.rows && c < d.cols) out[r + cd * d.ld_c] = from_f<T>(tile[tx][ty + 8 * i]);
       }
       __syncthreads();
     } else {
-      for (int k = ty; k < 32; k += 8) {
-        const int r = r0 + k, c = c0 + tx;
-        const int cd = d.c_blk > 0 ? (c / d.c_blk) * d.c_blk_to + c % d.c_blk : c;
-        if (r < d.rows && c < d.cols) out[r * d.ld_r + cd * d.ld_c] = from_f<T>(src[(long long)r * d.cols + c] * d.scale);
+      const int c = c0 + tx;
+      const int cd = d.c_blk > 0 ? (c / d.c_blk) * d.c_blk_to + c % d.c_blk : c;
+#pragma unroll
+      for (int i = 0; i < 4; i++) {
+        const int r = r0 + ty + 8 * i;
+        if (r < d.rows && c < d.cols) out[r * d.ld_r + cd * d.ld_c] = from_f<T>(v[i]);
       }
     }
   }

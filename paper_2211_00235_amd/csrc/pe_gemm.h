@@ -434,7 +434,7 @@ template <typename T> struct EpiTmGate {
   static constexpr bool HAS_COLSUM = false;
   static constexpr bool TM_GATE = true;
   static constexpr bool ELEM = false;      // has an element-wise path
-  T* proj_t; T* a_t; T* b_t;
+  T* proj_t; T* a_t; T* b_t;   // proj_t nullptr: not stored (no backward pass follows)
   const float* bias;     // [4 ct] in the order of proj_t's rows
   const float* mask;     // [r][r]
   int ct; long long Mz;  // Mz: elements of a channel plane, r * pitch
@@ -818,6 +818,7 @@ __global__ __launch_bounds__(256) void gemm_kernel(Operand A, Operand B, GemmSha
       __syncthreads();   // all waves are done with the operand tiles
 #pragma unroll
       for (int rnd = 0; rnd < 3; rnd++) {
+        if (rnd < 2 && !epi.proj_t) continue;
         if (rnd == 2) {
 #pragma unroll
           for (int j = 0; j < 2; j++)

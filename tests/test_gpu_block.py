@@ -563,6 +563,32 @@ def test_triangle_attention_backward_over_many_rows():
     _check_walking_backward(dims, inp, table, 2)
 
 
+@pytest.mark.parametrize("name,dtype,over", [("tiny", 0, {}), ("tiny", 1, dict(s=9, r=21, c_tri=24)), ("af2_initial", 1, dict(s=17, r=45)),
+                                             ("af2_initial", 1, dict(s=17, r=45, variant=1)), ("af2_initial", 0, dict(s=9, r=34, variant=2)),
+                                             ("extra_msa", 1, dict(s=70, r=40))])
+def test_forward_without_activations_is_the_same_forward(name, dtype, over):
+    """Without a ctx the forward pass leaves out what only a backward pass reads; its outputs are the same bits, also when the
+    workspace held NaN before, and a recomputing backward pass after it is the same as one on saved activations."""
+    import torch
+    dims, table, inp = _case(name, dtype=dtype, **over)
+    run = BlockRun(dims, inp)
+    run.fwd(use_ctx=True)
+    run.bwd(use_ctx=True)
+    run.sync()
+    outs = ("msa_out", "pair_out", "d_msa_in", "d_pair_in", "d_params")
+    ref = {k: getattr(run, k).clone() for k in outs}
+    for k in outs[:4]:
+        getattr(run, k).fill_(float("nan"))
+    run.d_params.zero_()
+    run.ws.fill_(0xff)
+    run.sync()
+    run.fwd(use_ctx=False)
+    run.bwd(use_ctx=False)
+    run.sync()
+    for k in outs:
+        assert torch.equal(getattr(run, k), ref[k]), k
+
+
 @pytest.mark.parametrize("name,s,r,two_streams,ks", [("af2_initial", 81, 131, False, (256, 128)), ("af2_initial", 9, 33, False, (128,)),
                                                      ("extra_msa", 150, 47, True, (64,))])
 def test_row_streaming_gemms(name, s, r, two_streams, ks):
