@@ -59,12 +59,12 @@ int main(int argc, char** argv) {
   const double e = 2.0;
   const double ll = (double)B * H * L * L;
   printf("B %d L %d H %d d %d masked tail %d\n", B, L, H, d, nmask);
-  timeit("attn_fwd<bias>", reps, 6.0 * H * plane * e, 4.0 * ll * d, [&] { hipLaunchKernelGGL((attn_fwd_kernel<T, true>), grid, dim3(256), 0, 0, a); });
-  timeit("attn_fwd<nobias>", reps, 6.0 * H * plane * e, 4.0 * ll * d, [&] { hipLaunchKernelGGL((attn_fwd_kernel<T, false>), grid, dim3(256), 0, 0, a); });
-  timeit("attn_bwd_dq2", reps, 5.0 * H * plane * e + ll, 6.0 * ll * d, [&] { hipLaunchKernelGGL((attn_bwd_dq2_kernel<T>), dim3(attn_grid_size((B + 1) / 2, H, L)), dim3(512), 0, 0, a); });
-  AttnArgs a0 = a; a0.dS = nullptr;   // the unbiased kernel would write one dS plane per batch row: the buffer holds half of them
-  timeit("attn_bwd_dq<nobias>", reps, 5.0 * H * plane * e, 6.0 * ll * d, [&] { hipLaunchKernelGGL((attn_bwd_dq_kernel<T, false>), grid, dim3(256), 0, 0, a0); });
-  timeit("attn_bwd_dkv<bias>", reps, 6.0 * H * plane * e, 8.0 * ll * d, [&] { hipLaunchKernelGGL((attn_bwd_dkv_kernel<T, true>), grid, dim3(256), 0, 0, a); });
-  timeit("attn_bwd_dkv<nobias>", reps, 6.0 * H * plane * e, 8.0 * ll * d, [&] { hipLaunchKernelGGL((attn_bwd_dkv_kernel<T, false>), grid, dim3(256), 0, 0, a); });
+  timeit("attn_fwd<bias>", reps, 6.0 * H * plane * e, 4.0 * ll * d, [&] { launch_attn_fwd<T>(0, a); });
+  timeit("attn_fwd<nobias>", reps, 6.0 * H * plane * e, 4.0 * ll * d, [&] { AttnArgs an = a; an.biasQ = an.biasK = nullptr; launch_attn_fwd<T>(0, an); });
+  timeit("attn_bwd_dq2", reps, 5.0 * H * plane * e + ll, 6.0 * ll * d, [&] { launch_attn_bwd_dq<T>(0, a); });
+  AttnArgs a0 = a; a0.dS = nullptr; a0.biasQ = a0.biasK = nullptr;   // the unbiased kernel would write one dS plane per batch row: the buffer holds half of them
+  timeit("attn_bwd_dq<nobias>", reps, 5.0 * H * plane * e, 6.0 * ll * d, [&] { launch_attn_bwd_dq<T>(0, a0); });
+  timeit("attn_bwd_dkv<bias>", reps, 6.0 * H * plane * e, 8.0 * ll * d, [&] { launch_attn_bwd_dkv<T>(0, a); });
+  timeit("attn_bwd_dkv<nobias>", reps, 6.0 * H * plane * e, 8.0 * ll * d, [&] { launch_attn_bwd_dkv<T>(0, a0); });
   return 0;
 }

@@ -162,6 +162,46 @@ template <> PE_DEV Mma<float>::frag lds_tfrag<float>(const float* rowp, int g, i
   return rowp[8 * (u >> 2) + 4 * g + (u & 3)];
 }
 
+// The same fragment from a ROW-major LDS tile [position][STRIDE] (bf16, transposing reads): channel l32, the 16 positions from
+// pos0 in the order of acc_row.  No second, transposed copy, whose 2-byte stores were 8 per 16-byte vector.
+template <int STRIDE> PE_DEV bf16x8 lds_rfrag(const bf16* tile, int pos0, int l32, int g) {
+  const bf16* q = tile + (pos0 + 4 * g + ((l32 & 15) >> 2)) * STRIDE + (l32 & 16) + 4 * (l32 & 3);
+  const bf16x4 lo = lds_read_tr(q), hi = lds_read_tr(q + 8 * STRIDE);
+  bf16x8 f;
+#pragma unroll
+  for (int e = 0; e < 4; e++) { f[e] = lo[e]; f[4 + e] = hi[e]; }
+  return f;
+}
+// a lane's position (row) of a [position][d] tensor from a transposed 32 x 32 accumulator tile, times f
+template <typename T> PE_DEV void attn_store_row(T* row, const f32x16& acc, float f, int d, int g) {
+  if constexpr (sizeof(T) == 2) {
+    if (d % 8 == 0) {
+#pragma unroll
+      for (int j = 0; j < 2; j++) {
+        float v[8];
+        rows_unpack(acc, j, v);      // every lane of the wave takes part
+#pragma unroll
+        for (int e = 0; e < 8; e++) v[e] *= f;
+        bf16x8 t;
+#pragma unroll
+        for (int e = 0; e < 8; e++) t[e] = (bf16)v[e];
+        if (row && 16 * j + 8 * g < d) *reinterpret_cast<bf16x8*>(row + 16 * j + 8 * g) = t;
+      }
+      return;
+    }
+  }
+#pragma unroll
+  for (int q4 = 0; q4 < 4; q4++) {
+    const int dd = 8 * q4 + 4 * g;
+    if (row && dd < d) {
+      float v[4];
+#pragma unroll
+      for (int r = 0; r < 4; r++) v[r] = acc[q4 * 4 + r] * f;
+      store4<T>(row + dd, v);
+    }
+  }
+}
+
 // operand fragment straight from global memory: row `p` (nullptr = out of range), channels
 // [kk*KSTEP + g*KP, +KP), zero beyond d
 template <typename T> PE_DEV typename Mma<T>::frag gl_frag(const T* p, int kk, int g, int d) {
@@ -223,6 +263,19 @@ PE_DEV void attn_load_bias(const float* plane, int L, int tile, int col, int g, 
     for (int r = 0; r < 4; r++) b.v[c * 4 + r] = v[r];
   }
 }
+// the same from the lane's own address of chunk 0: chunks are 2 L lanes apart
+PE_DEV void attn_load_bias_at(const bf16* p, int L, BiasTile<bf16>& b) {
+#pragma unroll
+  for (int c = 0; c < 2; c++) b.v[c] = *reinterpret_cast<const bf16x8*>(p + (long long)c * 2 * L * BiasChunk<bf16>::CH);
+}
+PE_DEV void attn_load_bias_at(const float* p, int L, BiasTile<float>& b) {
+#pragma unroll
+  for (int c = 0; c < 4; c++) {
+    const f32x4 v = *reinterpret_cast<const f32x4*>(p + (long long)c * 2 * L * BiasChunk<float>::CH);
+#pragma unroll
+    for (int r = 0; r < 4; r++) b.v[c * 4 + r] = v[r];
+  }
+}
 // identity A operand: lane (row l32, group g) of step c holds [16 c + 8 g + t == l32], t = 0..7
 template <typename T> struct IdFrag;
 template <> struct IdFrag<bf16> {
@@ -260,28 +313,28 @@ PE_DEV void attn_stage_mask(float mk, float* lds_madd, int* lds_flag, int t64) {
   const unsigned long long bal = __ballot(masked);
   if (t64 == 0) { lds_flag[0] = (bal & 0xffffffffull) != 0; lds_flag[1] = (bal >> 32) != 0; }
 }
-// a lane's 16 elements of a score tile (dS) stored in the same chunk order
-template <typename T> PE_DEV void attn_store_tile16(T* plane, int L, int tile, int col, int g, const float (&v)[16]);
-template <> PE_DEV void attn_store_tile16<float>(float* plane, int L, int tile, int col, int g, const float (&v)[16]) {
+// a lane's 16 elements of a score tile (dS) stored in the same chunk order, from its address of chunk 0
+template <typename T> PE_DEV void attn_store_tile16_at(T* p, int L, const float (&v)[16]);
+template <> PE_DEV void attn_store_tile16_at<float>(float* p, int L, const float (&v)[16]) {
 #pragma unroll
   for (int c = 0; c < 4; c++) {
     float t[4];
 #pragma unroll
     for (int r = 0; r < 4; r++) t[r] = v[c * 4 + r];
-    store4<float>(plane + bias_chunk_off<float>(tile, c, g, col, L), t);
+    store4<float>(p + (long long)c * 2 * L * BiasChunk<float>::CH, t);
   }
 }
-template <> PE_DEV void attn_store_tile16<bf16>(bf16* plane, int L, int tile, int col, int g, const float (&v)[16]) {
+template <> PE_DEV void attn_store_tile16_at<bf16>(bf16* p, int L, const float (&v)[16]) {
 #pragma unroll
   for (int c = 0; c < 2; c++) {
-    float t[8];
-#pragma unroll
-    for (int r = 0; r < 8; r++) t[r] = v[c * 8 + r];
     bf16x8 o;   // non-temporal: read once, by the reduction over the batch axis
 #pragma unroll
-    for (int r = 0; r < 8; r++) o[r] = (bf16)t[r];
-    __builtin_nontemporal_store(o, reinterpret_cast<bf16x8*>(plane + bias_chunk_off<bf16>(tile, c, g, col, L)));
+    for (int r = 0; r < 8; r++) o[r] = (bf16)v[c * 8 + r];
+    __builtin_nontemporal_store(o, reinterpret_cast<bf16x8*>(p + (long long)c * 2 * L * BiasChunk<bf16>::CH));
   }
+}
+template <typename T> PE_DEV void attn_store_tile16(T* plane, int L, int tile, int col, int g, const float (&v)[16]) {
+  attn_store_tile16_at<T>(plane + bias_chunk_off<T>(tile, 0, g, col, L), L, v);
 }
 // number of 32-position tiles of an axis of length L
 PE_DEV int attn_tiles32(int L) { return (L + 31) >> 5; }
@@ -345,14 +398,19 @@ PE_DEV void attn_chunk_store(const typename Vec16<T>::type (&r)[AttnChunk<T>::NV
 #ifndef PE_FWD_WAVES
 #define PE_FWD_WAVES 4
 #endif
-template <typename T, bool HAS_BIAS>
+// NK: contraction steps of the score products when known at compile time (bf16: 1 up to d = 16, 2 above), 0: from d.
+// What bounds it: the vector unit, about 9 instructions per logit at d = 32 of which one is an exponential of four times the
+// length.  Hence no transposed copy of V, the partner's maximum by a lane swap instead of through LDS, a bias pointer that
+// steps by a constant; outputs and gate pass through LDS at the end (64-byte runs; a query per lane is a 16-byte access per row).
+template <typename T, bool HAS_BIAS, int NK = 0>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(PE_FWD_WAVES, PE_FWD_WAVES))) void attn_fwd_kernel(AttnArgs a) {
   typedef AttnCfg<T> C;
   typedef Mma<T> MM;
   typedef AttnChunk<T> K;
   typedef typename Vec16<T>::type V;
+  constexpr bool TR = sizeof(T) == 2;
   __shared__ __attribute__((aligned(16))) T lds_k[K::CH * C::RM];
-  __shared__ __attribute__((aligned(16))) T lds_vt[32 * K::TS];
+  __shared__ __attribute__((aligned(16))) T lds_v[TR ? K::CH * 32 : 32 * K::TS];   // [key][32], or transposed [channel][key]
   __shared__ __attribute__((aligned(16))) float lds_madd[K::CH];   // 0 for a valid key, -inf for a masked one
   __shared__ int lds_flag[K::CH / 32];
 
@@ -362,23 +420,27 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(PE_FWD_WAVE
   const int h = wg.h, b = wg.b;
   const int L = a.L, d = a.d;
   const int DP = round_up_i(d, MM::KSTEP);
-  const int NKK = DP / MM::KSTEP;
-  const int qi = wg.tile * 128 + wave * 32 + l32;       // this lane's query
+  const int NKK = NK > 0 ? NK : DP / MM::KSTEP;
+  const int q0 = wg.tile * 128 + wave * 32, qi = q0 + l32;       // this lane's query
   const bool qok = qi < L;
   const long long HP = (long long)a.H * a.plane;            // distance between the q, k, v, gate groups
   const T* base = (const T*)a.qkvg + h * a.plane + (long long)b * L * d;
   const T* qrow = qok ? base + qi * d : nullptr;
 
-  constexpr int MAXKK = 32 / MM::KSTEP;   // 2 (bf16) or 16 (fp32): d <= 32
+  constexpr int MAXKK = NK > 0 ? NK : 32 / MM::KSTEP;   // d <= 32
   typename MM::frag qf[MAXKK];
   f32x16 oacc = splat16(0.0f);
   float m_ref = 0.0f, l_part = 0.0f;     // l_part: this lane's keys only; the two halves of a query are added at the end
-  bool seen = false;                     // a finite logit has been seen
+  float limit = -INFINITY;               // re-base above it: m_ref + TAU once a finite logit has been seen
   constexpr bool has_bias = HAS_BIAS;
-  const T* bplane = has_bias ? (const T*)a.biasQ + (long long)h * attn_tiles32(L) * L * 32 : nullptr;
-  const int bcolq = min(qi, L - 1);
+  const int ntile = attn_tiles32(L);
+  // this lane's bias chunks of the current tile; a tile further is a constant number of elements further
+  constexpr int BCH = BiasChunk<T>::CH;
+  const T* bptr = has_bias ? (const T*)a.biasQ + (long long)h * ntile * L * 32 + ((long long)g * L + min(qi, L - 1)) * BCH : nullptr;
+  const long long bstep = (long long)L * 32;
   IdFrag<T> idf;
   idf.init(l32, g);
+  int tile = 0;
 
   for (int c0 = 0; c0 < L; c0 += K::CH) {
     {
@@ -394,36 +456,50 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(PE_FWD_WAVE
           if (kk < NKK) qf[kk] = gl_frag<T>(qrow, kk, g, d);
       }
       attn_chunk_store<T>(rk, DP, lds_k, (T*)nullptr, tid);
-      attn_chunk_store<T>(rv, DP, (T*)nullptr, lds_vt, tid);
+      if constexpr (TR) {
+#pragma unroll
+        for (int i = 0; i < K::NV; i++) *reinterpret_cast<V*>(lds_v + (tid + i * 256) * C::VEC) = rv[i];   // rows of 32, zeros beyond d
+      } else {
+        attn_chunk_store<T>(rv, DP, (T*)nullptr, lds_v, tid);
+      }
       if (tid < K::CH) attn_stage_mask(mk, lds_madd + 64 * wave, lds_flag + 2 * wave, lane);
       __syncthreads();
     }
     const int jend = min(K::CH, L - c0);
     BiasTile<T> bt;
-    if (has_bias) attn_load_bias(bplane, L, c0 >> 5, bcolq, g, bt);
-    for (int js = 0; js < jend; js += 32) {
+    if (has_bias) attn_load_bias_at(bptr, L, bt);
+    for (int js = 0; js < jend; js += 32, tile++) {
       const int masked = __builtin_amdgcn_readfirstlane(lds_flag[js >> 5]);
       // base-2 logits for (query = lane, keys = acc rows)
       f32x16 sacc = splat16(0.0f);
+      typename MM::frag kf[NK > 0 ? NK : 1];
+      if constexpr (NK > 0) {
 #pragma unroll
-      for (int kk = 0; kk < MAXKK; kk++)
-        if (kk < NKK) MM::mma(sacc, MM::load(lds_k + (js + l32) * C::RM + kk * MM::KSTEP + g * MM::KP), qf[kk]);
+        for (int kk = 0; kk < NK; kk++) kf[kk] = MM::load(lds_k + (js + l32) * C::RM + kk * MM::KSTEP + g * MM::KP);
+#pragma unroll
+        for (int kk = 0; kk < NK; kk++) MM::mma(sacc, kf[kk], qf[kk]);
+      } else {
+#pragma unroll
+        for (int kk = 0; kk < MAXKK; kk++)
+          if (kk < NKK) MM::mma(sacc, MM::load(lds_k + (js + l32) * C::RM + kk * MM::KSTEP + g * MM::KP), qf[kk]);
+      }
       if (has_bias) {
         attn_add_bias(sacc, bt, idf);
-        attn_load_bias(bplane, L, min(((c0 + js) >> 5) + 1, attn_tiles32(L) - 1), bcolq, g, bt);   // next tile's bias
+        if (tile + 1 < ntile) bptr += bstep;
+        attn_load_bias_at(bptr, L, bt);   // next tile's bias
       }
       if (masked) attn_add_row_mask(sacc, lds_madd + js, g);
       float tmax = sacc[0];
 #pragma unroll
       for (int e = 1; e < 16; e++) tmax = fmaxf(tmax, sacc[e]);
-      tmax = fmaxf(tmax, __shfl_xor(tmax, 32, 64));
-      // re-base when the tile's maximum is more than TAU above the reference, and at the first finite logit
-      const bool finite = tmax > -INFINITY;
-      const bool rebase = tmax > m_ref + ATTN_TAU || (!seen && finite);
-      seen = seen || finite;
+      tmax = pair_max(tmax);
+      // re-base when the tile's maximum is more than TAU above the reference, and at the first finite logit (nothing is
+      // accumulated before it)
+      const bool rebase = tmax > limit;
       if (__any(rebase)) {
         const float m_new = rebase ? tmax : m_ref;
-        const float corr = fast_exp2(m_ref - m_new);
+        const float corr = rebase && limit == -INFINITY ? 0.0f : fast_exp2(m_ref - m_new);
+        if (rebase) limit = tmax + ATTN_TAU;
         m_ref = m_new;
         l_part *= corr;
 #pragma unroll
@@ -438,15 +514,54 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(PE_FWD_WAVE
       }
       l_part += psum;
       // O^T[dd, i] += sum_j V^T[dd, j] P^T[j, i]
-      const T* vrow = lds_vt + l32 * K::TS + js;
+      if constexpr (TR) {
 #pragma unroll
-      for (int u = 0; u < 32 / MM::KSTEP; u++) MM::mma(oacc, lds_tfrag<T>(vrow, g, u), acc_to_frag<T>(sacc, u));
+        for (int u = 0; u < 2; u++) MM::mma(oacc, lds_rfrag<32>(lds_v, js + 16 * u, l32, g), acc_to_frag<T>(sacc, u));
+      } else {
+        const T* vrow = lds_v + l32 * K::TS + js;
+#pragma unroll
+        for (int u = 0; u < 32 / MM::KSTEP; u++) MM::mma(oacc, lds_tfrag<T>(vrow, g, u), acc_to_frag<T>(sacc, u));
+      }
     }
   }
   const float l_run = l_part + __shfl_xor(l_part, 32, 64);
+  const float inv = (l_run > 0.0f) ? 1.0f / l_run : 0.0f;
+  if (qok && g == 0 && a.lse) a.lse[((long long)b * a.H + h) * L + qi] = (l_run > 0.0f) ? (m_ref + log2f(l_run)) * PE_LN2 : 0.0f;
+  if constexpr (TR) {
+    if (d == 32) {
+      __syncthreads();   // lds_k becomes the waves' pieces
+      RowsPiece pc;
+      pc.init(reinterpret_cast<bf16*>(lds_k) + wave * 1024, lane);
+      const long long wrow = h * a.plane + ((long long)b * L + q0) * 32 + lane * 8;     // memory layout: 16 rows further is 512 elements further
+      const bool ok0 = q0 + (lane >> 2) < L, ok1 = q0 + (lane >> 2) + 16 < L;
+      bf16x8 gm[2], gf[2], of[2], ogf[2], t0, t1;
+      const T* pg = (const T*)a.qkvg + 3 * HP + wrow;
+      gm[0] = *reinterpret_cast<const bf16x8*>(ok0 ? pg : (const T*)a.qkvg);
+      gm[1] = *reinterpret_cast<const bf16x8*>(ok1 ? pg + 512 : (const T*)a.qkvg);
+      pc.to_frag(gm, gf[0], gf[1]);
+#pragma unroll
+      for (int j = 0; j < 2; j++) {
+        float v[8];
+        rows_unpack(oacc, j, v);
+#pragma unroll
+        for (int e = 0; e < 8; e++) {
+          v[e] *= inv;
+          of[j][e] = (bf16)v[e];
+          ogf[j][e] = (bf16)(v[e] * sigmoidf_((float)gf[j][e]));
+        }
+      }
+      pc.to_mem(ogf, t0, t1);
+      if (ok0) *reinterpret_cast<bf16x8*>((T*)a.og + wrow) = t0;
+      if (ok1) *reinterpret_cast<bf16x8*>((T*)a.og + wrow + 512) = t1;
+      if (a.o) {
+        pc.to_mem(of, t0, t1);
+        if (ok0) *reinterpret_cast<bf16x8*>((T*)a.o + wrow) = t0;
+        if (ok1) *reinterpret_cast<bf16x8*>((T*)a.o + wrow + 512) = t1;
+      }
+      return;
+    }
+  }
   if (!qok) return;
-  float inv = (l_run > 0.0f) ? 1.0f / l_run : 0.0f;
-  if (g == 0 && a.lse) a.lse[((long long)b * a.H + h) * L + qi] = (l_run > 0.0f) ? (m_ref + log2f(l_run)) * PE_LN2 : 0.0f;
   const long long orow = h * a.plane + ((long long)b * L + qi) * d;
   T* po = a.o ? (T*)a.o + orow : nullptr;
   T* pog = (T*)a.og + orow;
@@ -466,6 +581,21 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(PE_FWD_WAVE
       store4<T>(pog + dd, ogv);
     }
   }
+}
+template <typename T>
+static inline void launch_attn_fwd(hipStream_t st, const AttnArgs& a) {
+  const dim3 grid(attn_grid_size(a.B, a.H, a.L)), block(256);
+#define PE_ATTN_FWD(NK)                                                                                   \
+  do {                                                                                                    \
+    if (a.biasQ) hipLaunchKernelGGL((attn_fwd_kernel<T, true, NK>), grid, block, 0, st, a);               \
+    else hipLaunchKernelGGL((attn_fwd_kernel<T, false, NK>), grid, block, 0, st, a);                      \
+  } while (0)
+  if constexpr (sizeof(T) == 2) {
+    if (a.d <= 16) PE_ATTN_FWD(1); else PE_ATTN_FWD(2);
+  } else {
+    PE_ATTN_FWD(0);
+  }
+#undef PE_ATTN_FWD
 }
 
 // ---------------------------------------------------------------------------
@@ -517,12 +647,12 @@ __global__ __launch_bounds__(256) void attn_bwd_pre_kernel(AttnArgs a) {
 // ---------------------------------------------------------------------------
 // Capped at 128 registers (4 waves per SIMD instead of 3 at the 138 the compiler would take; three
 // dwords spill): measured 85 -> 77 us per biased attention at L = 256.
-template <typename T, bool HAS_BIAS>
+template <typename T, bool HAS_BIAS, int NK = 0>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) void attn_bwd_dq_kernel(AttnArgs a) {
   typedef AttnCfg<T> C;
   typedef Mma<T> MM;
   __shared__ __attribute__((aligned(16))) T lds_k[C::KT * C::RM];
-  __shared__ __attribute__((aligned(16))) T lds_kt[32 * C::TS];
+  __shared__ __attribute__((aligned(16))) T lds_kt[sizeof(T) == 2 ? 8 : 32 * C::TS];
   __shared__ __attribute__((aligned(16))) T lds_v[C::KT * C::RM];
   __shared__ __attribute__((aligned(16))) float lds_madd[C::KT];
   __shared__ int lds_flag[2];
@@ -533,7 +663,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
   const int h = wg.h, b = wg.b;
   const int L = a.L, d = a.d;
   const int DP = round_up_i(d, MM::KSTEP);
-  const int NKK = DP / MM::KSTEP;
+  const int NKK = NK > 0 ? NK : DP / MM::KSTEP;
   const int qi = wg.tile * 128 + wave * 32 + l32;
   const bool qok = qi < L;
   const long long HP = (long long)a.H * a.plane;
@@ -542,7 +672,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
   const long long orow = h * a.plane + ((long long)b * L + qi) * d;
   const T* dorow = qok ? (const T*)a.dO + orow : nullptr;
 
-  constexpr int MAXKK = 32 / MM::KSTEP;
+  constexpr int MAXKK = NK > 0 ? NK : 32 / MM::KSTEP;
+  constexpr bool TR = sizeof(T) == 2;     // the transposed fragments come from the row-major tile
   typename MM::frag qf[MAXKK], dof[MAXKK];
 #pragma unroll
   for (int kk = 0; kk < MAXKK; kk++)
@@ -551,8 +682,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
       dof[kk] = gl_frag<T>(dorow, kk, g, d);
     }
   const long long sidx = ((long long)b * a.H + h) * L + qi;
-  const float lse2 = qok ? a.lse[sidx] * PE_LOG2E : 0.0f;
-  const float Di = qok ? a.D[sidx] : 0.0f;
+  const f32x16 negl = splat16(qok ? -a.lse[sidx] * PE_LOG2E : 0.0f), negD = splat16(qok ? -a.D[sidx] : 0.0f);
   constexpr bool has_bias = HAS_BIAS;
   const T* bplane = has_bias ? (const T*)a.biasQ + (long long)h * attn_tiles32(L) * L * 32 : nullptr;
   const int bcolq = min(qi, L - 1);
@@ -567,7 +697,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
 
   for (int j0 = 0; j0 < L; j0 += C::KT) {
     __syncthreads();
-    attn_stage<T>(base + HP, d, j0, L, d, DP, lds_k, lds_kt, tid, 256);
+    attn_stage<T>(base + HP, d, j0, L, d, DP, lds_k, TR ? (T*)nullptr : lds_kt, tid, 256);
     attn_stage<T>(base + 2 * HP, d, j0, L, d, DP, lds_v, (T*)nullptr, tid, 256);
     if (tid < C::KT) {
       const int j = j0 + tid;
@@ -582,7 +712,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
       if (has_bias) attn_load_bias(bplane, L, kt0 >> 5, bcolq, g, bt);
       const int masked = __builtin_amdgcn_readfirstlane(lds_flag[jt]);
       const int off0 = (jt * 32 + l32) * C::RM + g * MM::KP;
-      f32x16 sacc = splat16(0.0f), pacc = splat16(0.0f);
+      f32x16 sacc = TR ? negl : splat16(0.0f), pacc = TR ? negD : splat16(0.0f);     // bf16: S - lse, dP - D from the matrix unit
 #pragma unroll
       for (int kk = 0; kk < MAXKK; kk++)
         if (kk < NKK) {
@@ -592,30 +722,24 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
       if (has_bias) attn_add_bias(sacc, bt, idf);
       if (masked) attn_add_row_mask(sacc, lds_madd + jt * 32, g);
 #pragma unroll
-      for (int e = 0; e < 16; e++) sacc[e] = fast_exp2(sacc[e] - lse2) * (pacc[e] - Di);     // dS = P (dP - D)
+      for (int e = 0; e < 16; e++) sacc[e] = TR ? fast_exp2(sacc[e]) * pacc[e] : fast_exp2(sacc[e] + negl[e]) * (pacc[e] + negD[e]);     // dS = P (dP - D)
       if (dsplane && qok) {
         float v16[16];
 #pragma unroll
         for (int e = 0; e < 16; e++) v16[e] = sacc[e];
         attn_store_tile16<T>(dsplane, L, kt0 >> 5, qi, g, v16);
       }
-      const T* krow = lds_kt + l32 * C::TS + jt * 32;
+      if constexpr (TR) {
 #pragma unroll
-      for (int u = 0; u < 32 / MM::KSTEP; u++) MM::mma(dq, lds_tfrag<T>(krow, g, u), acc_to_frag<T>(sacc, u));
+        for (int u = 0; u < 2; u++) MM::mma(dq, lds_rfrag<C::RM>(lds_k, jt * 32 + 16 * u, l32, g), acc_to_frag<T>(sacc, u));
+      } else {
+        const T* krow = lds_kt + l32 * C::TS + jt * 32;
+#pragma unroll
+        for (int u = 0; u < 32 / MM::KSTEP; u++) MM::mma(dq, lds_tfrag<T>(krow, g, u), acc_to_frag<T>(sacc, u));
+      }
     }
   }
-  if (!qok) return;
-  T* pdq = (T*)a.dqkvg + orow;
-#pragma unroll
-  for (int q4 = 0; q4 < 4; q4++) {
-    int dd = 8 * q4 + 4 * g;
-    if (dd < d) {
-      float v[4];
-#pragma unroll
-      for (int r = 0; r < 4; r++) v[r] = dq[q4 * 4 + r] * a.scale;
-      store4<T>(pdq + dd, v);
-    }
-  }
+  attn_store_row<T>(qok ? (T*)a.dqkvg + orow : nullptr, dq, a.scale, d, g);
 }
 
 // ---------------------------------------------------------------------------
@@ -630,12 +754,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
 #ifndef PE_DQ2_WAVES
 #define PE_DQ2_WAVES 4
 #endif
-template <typename T>
+template <typename T, int NK = 0>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(PE_DQ2_WAVES, PE_DQ2_WAVES))) void attn_bwd_dq2_kernel(AttnArgs a) {
   typedef AttnCfg<T> C;
   typedef Mma<T> MM;
   __shared__ __attribute__((aligned(16))) T lds_k2[2][C::KT * C::RM];
-  __shared__ __attribute__((aligned(16))) T lds_kt2[2][32 * C::TS];
+  __shared__ __attribute__((aligned(16))) T lds_kt2[2][sizeof(T) == 2 ? 8 : 32 * C::TS];
   __shared__ __attribute__((aligned(16))) T lds_v2[2][C::KT * C::RM];
   __shared__ __attribute__((aligned(16))) float lds_madd2[2][C::KT];
   __shared__ int lds_flag2[2][2];
@@ -659,7 +783,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(PE_DQ2_WAVE
 
   const int L = a.L, d = a.d;
   const int DP = round_up_i(d, MM::KSTEP);
-  const int NKK = DP / MM::KSTEP;
+  const int NKK = NK > 0 ? NK : DP / MM::KSTEP;
   const int qi = tile * 128 + wave * 32 + l32;
   const bool qok = qi < L;
   const long long HP = (long long)a.H * a.plane;
@@ -668,7 +792,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(PE_DQ2_WAVE
   const long long orow = h * a.plane + ((long long)b * L + qi) * d;
   const T* dorow = qok ? (const T*)a.dO + orow : nullptr;
 
-  constexpr int MAXKK = 32 / MM::KSTEP;
+  constexpr int MAXKK = NK > 0 ? NK : 32 / MM::KSTEP;
+  constexpr bool TR = sizeof(T) == 2;     // the transposed fragments come from the row-major tile
   typename MM::frag qf[MAXKK], dof[MAXKK];
 #pragma unroll
   for (int kk = 0; kk < MAXKK; kk++)
@@ -679,9 +804,12 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(PE_DQ2_WAVE
   const long long sidx = ((long long)b * a.H + h) * L + qi;
   const float lse2 = qok ? a.lse[sidx] * PE_LOG2E : 0.0f;
   const float Di = qok ? a.D[sidx] : 0.0f;
-  const T* bplane = (const T*)a.biasQ + (long long)h * attn_tiles32(L) * L * 32;
-  const int bcolq = min(qi, L - 1);
-  T* dsplane = (T*)a.dS + ((long long)bp * a.H + h) * attn_tiles32(L) * L * 32;   // summed pair of rows, accumulator order
+  // this lane's chunks of the current tile in the bias planes and (summed pair of rows, accumulator order) in the dS planes: the next
+  // tile's are bstep elements further
+  const int ntile = attn_tiles32(L);
+  const long long bstep = (long long)L * 32, lane_off = ((long long)g * L + min(qi, L - 1)) * BiasChunk<T>::CH;
+  const T* bptr = (const T*)a.biasQ + (long long)h * ntile * bstep + lane_off;
+  T* dsptr = (T*)a.dS + ((long long)bp * a.H + h) * ntile * bstep + lane_off;
   IdFrag<T> idf;
   idf.init(l32, g);
 
@@ -690,9 +818,11 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(PE_DQ2_WAVE
   for (int e = 0; e < 16; e++) dq[e] = 0.0f;
 
   int xb = 0;   // exchange buffer of the current tile
+  BiasTile<T> bt;
+  attn_load_bias_at(bptr, L, bt);
   for (int j0 = 0; j0 < L; j0 += C::KT) {
     __syncthreads();
-    attn_stage<T>(base + HP, d, j0, L, d, DP, lds_k, lds_kt, tg, 256);
+    attn_stage<T>(base + HP, d, j0, L, d, DP, lds_k, TR ? (T*)nullptr : lds_kt, tg, 256);
     attn_stage<T>(base + 2 * HP, d, j0, L, d, DP, lds_v, (T*)nullptr, tg, 256);
     if (tg < C::KT) {
       const int j = j0 + tg;
@@ -703,8 +833,6 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(PE_DQ2_WAVE
     for (int jt = 0; jt < C::KT / 32; jt++) {
       const int kt0 = j0 + jt * 32;
       if (kt0 >= L) break;   // uniform over the workgroup
-      BiasTile<T> bt;
-      attn_load_bias(bplane, L, kt0 >> 5, bcolq, g, bt);
       const int masked = __builtin_amdgcn_readfirstlane(lds_flag[jt]);
       const int off0 = (jt * 32 + l32) * C::RM + g * MM::KP;
       f32x16 sacc = splat16(0.0f), pacc = splat16(0.0f);
@@ -715,6 +843,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(PE_DQ2_WAVE
           MM::mma(pacc, MM::load(lds_v + off0 + kk * MM::KSTEP), dof[kk]);     // dP^T = V dO^T
         }
       attn_add_bias(sacc, bt, idf);
+      if (kt0 + 32 < L) bptr += bstep;
+      attn_load_bias_at(bptr, L, bt);   // next tile's bias
       if (masked) attn_add_row_mask(sacc, lds_madd + jt * 32, g);
 #pragma unroll
       for (int e = 0; e < 16; e++) sacc[e] = fast_exp2(sacc[e] - lse2) * (pacc[e] - Di);     // dS = P (dP - D)
@@ -728,26 +858,21 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(PE_DQ2_WAVE
         float v16[16];
 #pragma unroll
         for (int e = 0; e < 16; e++) v16[e] = sacc[e] + lds_x[xb][wave][e][lane];
-        attn_store_tile16<T>(dsplane, L, kt0 >> 5, qi, g, v16);
+        attn_store_tile16_at<T>(dsptr, L, v16);
       }
       xb ^= 1;
-      const T* krow = lds_kt + l32 * C::TS + jt * 32;
+      dsptr += bstep;
+      if constexpr (TR) {
 #pragma unroll
-      for (int uu = 0; uu < 32 / MM::KSTEP; uu++) MM::mma(dq, lds_tfrag<T>(krow, g, uu), acc_to_frag<T>(sacc, uu));
+        for (int uu = 0; uu < 2; uu++) MM::mma(dq, lds_rfrag<C::RM>(lds_k, jt * 32 + 16 * uu, l32, g), acc_to_frag<T>(sacc, uu));
+      } else {
+        const T* krow = lds_kt + l32 * C::TS + jt * 32;
+#pragma unroll
+        for (int uu = 0; uu < 32 / MM::KSTEP; uu++) MM::mma(dq, lds_tfrag<T>(krow, g, uu), acc_to_frag<T>(sacc, uu));
+      }
     }
   }
-  if (!qok || !bvalid) return;
-  T* pdq = (T*)a.dqkvg + orow;
-#pragma unroll
-  for (int q4 = 0; q4 < 4; q4++) {
-    int dd = 8 * q4 + 4 * g;
-    if (dd < d) {
-      float v[4];
-#pragma unroll
-      for (int r = 0; r < 4; r++) v[r] = dq[q4 * 4 + r] * a.scale;
-      store4<T>(pdq + dd, v);
-    }
-  }
+  attn_store_row<T>(qok && bvalid ? (T*)a.dqkvg + orow : nullptr, dq, a.scale, d, g);
 }
 
 // ---------------------------------------------------------------------------
@@ -757,14 +882,14 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(PE_DQ2_WAVE
 #ifndef PE_DKV_WAVES
 #define PE_DKV_WAVES 3
 #endif
-template <typename T, bool HAS_BIAS>
+template <typename T, bool HAS_BIAS, int NK = 0>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(PE_DKV_WAVES, PE_DKV_WAVES))) void attn_bwd_dkv_kernel(AttnArgs a) {
   typedef AttnCfg<T> C;
   typedef Mma<T> MM;
   __shared__ __attribute__((aligned(16))) T lds_q[C::KT * C::RM];
-  __shared__ __attribute__((aligned(16))) T lds_qt[32 * C::TS];
+  __shared__ __attribute__((aligned(16))) T lds_qt[sizeof(T) == 2 ? 8 : 32 * C::TS];
   __shared__ __attribute__((aligned(16))) T lds_do[C::KT * C::RM];
-  __shared__ __attribute__((aligned(16))) T lds_dot[32 * C::TS];
+  __shared__ __attribute__((aligned(16))) T lds_dot[sizeof(T) == 2 ? 8 : 32 * C::TS];
   __shared__ __attribute__((aligned(16))) float lds_lse[C::KT];   // minus the base-2 log-sum-exp, -inf beyond L
   __shared__ __attribute__((aligned(16))) float lds_D[C::KT];     // minus D
 
@@ -774,7 +899,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(PE_DKV_WAVE
   const int h = wg.h, b = wg.b;
   const int L = a.L, d = a.d;
   const int DP = round_up_i(d, MM::KSTEP);
-  const int NKK = DP / MM::KSTEP;
+  const int NKK = NK > 0 ? NK : DP / MM::KSTEP;
   const int kj = wg.tile * 128 + wave * 32 + l32;       // this lane's key
   const bool kok = kj < L;
   const long long HP = (long long)a.H * a.plane;
@@ -783,7 +908,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(PE_DKV_WAVE
   const T* vrow = kok ? base + 2 * HP + kj * d : nullptr;
   const T* dobase = (const T*)a.dO + h * a.plane + (long long)b * L * d;
 
-  constexpr int MAXKK = 32 / MM::KSTEP;
+  constexpr int MAXKK = NK > 0 ? NK : 32 / MM::KSTEP;
+  constexpr bool TR = sizeof(T) == 2;     // the transposed fragments come from the row-major tile
   typename MM::frag kf[MAXKK], vf[MAXKK];
 #pragma unroll
   for (int kk = 0; kk < MAXKK; kk++)
@@ -795,8 +921,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(PE_DKV_WAVE
   const float madd = (mk > 0.0f) ? 0.0f : -INFINITY;
   const bool wave_masked = __any(!(mk > 0.0f));          // some key of this wave is masked or padded
   constexpr bool has_bias = HAS_BIAS;
-  const T* bplane = has_bias ? (const T*)a.biasK + (long long)h * attn_tiles32(L) * L * 32 : nullptr;
-  const int bcolk = min(kj, L - 1);
+  const int ntile = attn_tiles32(L);
+  const long long bstep = (long long)L * 32;      // elements between this lane's bias chunks of neighbouring tiles
+  const T* bptr = has_bias ? (const T*)a.biasK + (long long)h * ntile * bstep + ((long long)g * L + min(kj, L - 1)) * BiasChunk<T>::CH : nullptr;
   IdFrag<T> idf;
   idf.init(l32, g);
 
@@ -818,13 +945,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(PE_DKV_WAVE
     r_D = ok ? -a.D[sidx] : 0.0f;
   };
   prefetch(0);
-  const int ntile = attn_tiles32(L);
   BiasTile<T> bt;                       // refilled for the next 32-query tile as soon as its MFMAs have taken it
-  if (has_bias) attn_load_bias(bplane, L, 0, bcolk, g, bt);
+  if (has_bias) attn_load_bias_at(bptr, L, bt);
   for (int i0 = 0; i0 < L; i0 += C::KT) {
     __syncthreads();
-    attn_stage_store<T>(rq, DP, lds_q, lds_qt, tid);
-    attn_stage_store<T>(rdo, DP, lds_do, lds_dot, tid);
+    attn_stage_store<T>(rq, DP, lds_q, TR ? (T*)nullptr : lds_qt, tid);
+    attn_stage_store<T>(rdo, DP, lds_do, TR ? (T*)nullptr : lds_dot, tid);
     if (tid < C::KT) { lds_lse[tid] = r_lse; lds_D[tid] = r_D; }
     __syncthreads();
     if (i0 + C::KT < L) prefetch(i0 + C::KT);
@@ -849,7 +975,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(PE_DKV_WAVE
         }
       if (has_bias) {
         attn_add_bias(sacc, bt, idf);
-        attn_load_bias(bplane, L, min((i0 >> 5) + it + 1, ntile - 1), bcolk, g, bt);
+        if ((i0 >> 5) + it + 1 < ntile) bptr += bstep;
+        attn_load_bias_at(bptr, L, bt);
       }
       if (wave_masked) {
 #pragma unroll
@@ -862,29 +989,59 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(PE_DKV_WAVE
         pv[e] = p;
         sacc[e] = p * pacc[e];                                // dS = P (dP - D)
       }
-      const T* dotrow = lds_dot + l32 * C::TS + it * 32;
-      const T* qtrow = lds_qt + l32 * C::TS + it * 32;
+      if constexpr (TR) {
 #pragma unroll
-      for (int u = 0; u < 32 / MM::KSTEP; u++) {
-        MM::mma(dv, lds_tfrag<T>(dotrow, g, u), acc_to_frag<T>(pv, u));     // dV^T += dO^T P
-        MM::mma(dk, lds_tfrag<T>(qtrow, g, u), acc_to_frag<T>(sacc, u));    // dK^T += Q^T dS
+        for (int u = 0; u < 2; u++) {
+          MM::mma(dv, lds_rfrag<C::RM>(lds_do, it * 32 + 16 * u, l32, g), acc_to_frag<T>(pv, u));     // dV^T += dO^T P
+          MM::mma(dk, lds_rfrag<C::RM>(lds_q, it * 32 + 16 * u, l32, g), acc_to_frag<T>(sacc, u));    // dK^T += Q^T dS
+        }
+      } else {
+        const T* dotrow = lds_dot + l32 * C::TS + it * 32;
+        const T* qtrow = lds_qt + l32 * C::TS + it * 32;
+#pragma unroll
+        for (int u = 0; u < 32 / MM::KSTEP; u++) {
+          MM::mma(dv, lds_tfrag<T>(dotrow, g, u), acc_to_frag<T>(pv, u));
+          MM::mma(dk, lds_tfrag<T>(qtrow, g, u), acc_to_frag<T>(sacc, u));
+        }
       }
     }
   }
-  if (!kok) return;
-  T* pdk = (T*)a.dqkvg + HP + h * a.plane + ((long long)b * L + kj) * d;
-  T* pdv = pdk + HP;
-#pragma unroll
-  for (int q4 = 0; q4 < 4; q4++) {
-    int dd = 8 * q4 + 4 * g;
-    if (dd < d) {
-      float v1[4], v2[4];
-#pragma unroll
-      for (int r = 0; r < 4; r++) { v1[r] = dk[q4 * 4 + r] * PE_LN2; v2[r] = dv[q4 * 4 + r]; }   // q' = q scale log2 e
-      store4<T>(pdk + dd, v1);
-      store4<T>(pdv + dd, v2);
-    }
+  T* pdk = kok ? (T*)a.dqkvg + HP + h * a.plane + ((long long)b * L + kj) * d : nullptr;
+  attn_store_row<T>(pdk, dk, PE_LN2, d, g);                       // q' = q scale log2 e
+  attn_store_row<T>(pdk ? pdk + HP : nullptr, dv, 1.0f, d, g);
+}
+
+// dQ (and dS, two batch rows per workgroup, for a biased attention)
+template <typename T>
+static inline void launch_attn_bwd_dq(hipStream_t st, const AttnArgs& a) {
+  const long long B = a.biasQ ? (a.B + 1) / 2 : a.B;
+  const dim3 grid(attn_grid_size(B, a.H, a.L));
+#define PE_ATTN_DQ(NK)                                                                             \
+  do {                                                                                             \
+    if (a.biasQ) hipLaunchKernelGGL((attn_bwd_dq2_kernel<T, NK>), grid, dim3(512), 0, st, a);      \
+    else hipLaunchKernelGGL((attn_bwd_dq_kernel<T, false, NK>), grid, dim3(256), 0, st, a);        \
+  } while (0)
+  if constexpr (sizeof(T) == 2) {
+    if (a.d <= 16) PE_ATTN_DQ(1); else PE_ATTN_DQ(2);
+  } else {
+    PE_ATTN_DQ(0);
   }
+#undef PE_ATTN_DQ
+}
+template <typename T>
+static inline void launch_attn_bwd_dkv(hipStream_t st, const AttnArgs& a) {
+  const dim3 grid(attn_grid_size(a.B, a.H, a.L)), block(256);
+#define PE_ATTN_DKV(NK)                                                                            \
+  do {                                                                                             \
+    if (a.biasK) hipLaunchKernelGGL((attn_bwd_dkv_kernel<T, true, NK>), grid, block, 0, st, a);    \
+    else hipLaunchKernelGGL((attn_bwd_dkv_kernel<T, false, NK>), grid, block, 0, st, a);           \
+  } while (0)
+  if constexpr (sizeof(T) == 2) {
+    if (a.d <= 16) PE_ATTN_DKV(1); else PE_ATTN_DKV(2);
+  } else {
+    PE_ATTN_DKV(0);
+  }
+#undef PE_ATTN_DKV
 }
 
 // ---------------------------------------------------------------------------

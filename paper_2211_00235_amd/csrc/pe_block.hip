@@ -968,9 +968,11 @@ template <typename T> struct Runner {
       a.biasK = c.bias; a.biasQ = c.biasT; a.mask = g.mask; a.mask_bs = g.mask_bs; a.mask_ks = g.mask_ks;
       a.og = c.og; a.scale = 1.0f / sqrtf((float)dh);
       if (!lean) { a.o = c.o; a.lse = c.lse; }
-      dim3 grid(attn_grid_size(g.B, H, g.L));
-      if (c.bias) PE_LAUNCH(g.l_fwd, 4.0 * g.B * H * g.L * g.L * dh, (5.0 * M * HD + 1.0 * M * HD) * sizeof(T) + (c.bias ? 4.0 * H * g.L * g.L : 0.0), st, (attn_fwd_kernel<T, true>), grid, dim3(256), 0, a);
-      else PE_LAUNCH(g.l_fwd, 4.0 * g.B * H * g.L * g.L * dh, (5.0 * M * HD + 1.0 * M * HD) * sizeof(T) + (c.bias ? 4.0 * H * g.L * g.L : 0.0), st, (attn_fwd_kernel<T, false>), grid, dim3(256), 0, a);
+      prof_begin(st);
+      launch_attn_fwd<T>(st, a);
+      prof_end(st, g.l_fwd, c.bias ? "(attn_fwd_kernel<T, true>)" : "(attn_fwd_kernel<T, false>)", 4.0 * g.B * H * g.L * g.L * dh,
+               6.0 * M * HD * sizeof(T) + (c.bias ? 4.0 * H * g.L * g.L : 0.0));
+      check(g.l_fwd);
     }
     {
       EpiGeneric<T> e = epi_plain<T>(xout, Cc);
@@ -1378,7 +1380,6 @@ template <typename T> struct Runner {
       long long tot = gm.B * gm.L * H;
       if (!pre_fused)
         PE_LAUNCH("attn_bwd_pre", 0, 5.0 * M * HD * sizeof(T), st, attn_bwd_pre_kernel<T>, dim3((unsigned)((tot * 8 + 255) / 256)), dim3(256), 0, a);
-      dim3 grid(attn_grid_size(gm.B, H, gm.L));
       if (walk) {
         PE_LAUNCH(gm.l_dkv, 10.0 * gm.B * H * gm.L * gm.L * dh, (7.0 * M * HD) * sizeof(T) + 4.0 * walk * btile, st, attn_bwd_walk_kernel, dim3((unsigned)(H * nkb * walk)),
                   dim3(AttnWalk::THREADS), 0, a, dqp, dSp, walk);
@@ -1390,10 +1391,16 @@ template <typename T> struct Runner {
       } else {
         // biased attention: two batch rows per workgroup, their dS tiles summed before the write
         const long long Bds = c.bias ? (gm.B + 1) / 2 : gm.B;
-        if (c.bias) PE_LAUNCH(gm.l_dq, 6.0 * gm.B * H * gm.L * gm.L * dh, 5.0 * M * HD * sizeof(T) + 1.0 * Bds * H * gm.L * gm.L * sizeof(T), st, (attn_bwd_dq2_kernel<T>), dim3(attn_grid_size(Bds, H, gm.L)), dim3(512), 0, a);
-        else PE_LAUNCH(gm.l_dq, 6.0 * gm.B * H * gm.L * gm.L * dh, 5.0 * M * HD * sizeof(T), st, (attn_bwd_dq_kernel<T, false>), grid, dim3(256), 0, a);
-        if (c.bias) PE_LAUNCH(gm.l_dkv, 8.0 * gm.B * H * gm.L * gm.L * dh, 6.0 * M * HD * sizeof(T), st, (attn_bwd_dkv_kernel<T, true>), grid, dim3(256), 0, a);
-        else PE_LAUNCH(gm.l_dkv, 8.0 * gm.B * H * gm.L * gm.L * dh, 6.0 * M * HD * sizeof(T), st, (attn_bwd_dkv_kernel<T, false>), grid, dim3(256), 0, a);
+        prof_begin(st);
+        launch_attn_bwd_dq<T>(st, a);
+        prof_end(st, gm.l_dq, c.bias ? "(attn_bwd_dq2_kernel<T>)" : "(attn_bwd_dq_kernel<T, false>)", 6.0 * gm.B * H * gm.L * gm.L * dh,
+                 5.0 * M * HD * sizeof(T) + (c.bias ? 1.0 * Bds * H * gm.L * gm.L * sizeof(T) : 0.0));
+        check(gm.l_dq);
+        prof_begin(st);
+        launch_attn_bwd_dkv<T>(st, a);
+        prof_end(st, gm.l_dkv, c.bias ? "(attn_bwd_dkv_kernel<T, true>)" : "(attn_bwd_dkv_kernel<T, false>)", 8.0 * gm.B * H * gm.L * gm.L * dh,
+                 6.0 * M * HD * sizeof(T));
+        check(gm.l_dkv);
         if (c.bias) {
           const long long hll = btile;
           if (hll % 8 == 0 && al16(dS) && al16(dbias))

@@ -16,54 +16,6 @@
 #pragma once
 #include "pe_gemm.h"
 
-// accumulator rows are output columns: elements 8 j + 0..7 of lane (l32, g) -> columns 16 j + 8 g + 0..7 of row l32
-PE_DEV void rows_unpack(const f32x16& acc, int j, float (&v)[8]) {
-#pragma unroll
-  for (int i = 0; i < 4; i++) {
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(acc[8 * j + i]), __float_as_uint(acc[8 * j + 4 + i]), false, false);
-    v[i] = __uint_as_float(r[0]);
-    v[4 + i] = __uint_as_float(r[1]);
-  }
-}
-
-// A piece: 32 rows x 64 bytes, in a wave's own 2 KB of LDS, between the layout in which memory is read and written in 64-byte
-// runs (lane q: chunk q % 4 of rows q / 4 and q / 4 + 16) and the fragment layout (lane (l32, g): chunks g and 2 + g of
-// row l32).  A global access in which neighbouring lanes are rows apart costs the address unit one cycle per lane: with the
-// fragments loaded and the results stored that way these GEMMs were no faster than gemm_kernel.
-// The chunk index is XOR-ed with (row / 2) % 4: both access patterns fall on distinct banks.
-PE_DEV int piece_slot(int row, int c) { return row * 32 + ((c ^ ((row >> 1) & 3)) << 3); }   // element offset
-struct RowsPiece {
-  bf16* lds;      // this wave's
-  int mem[2];     // slots of the memory layout
-  int frag[2];    // slots of the fragment layout
-  PE_DEV void init(bf16* p, int lane) {
-    lds = p;
-    mem[0] = piece_slot(lane >> 2, lane & 3); mem[1] = piece_slot((lane >> 2) + 16, lane & 3);
-    frag[0] = piece_slot(lane & 31, lane >> 5); frag[1] = piece_slot(lane & 31, 2 + (lane >> 5));
-  }
-  // LDS operations of one wave execute in order: only the compiler has to keep the two phases apart
-  static PE_DEV void phase() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  }
-  PE_DEV void to_frag(const bf16x8 (&m)[2], bf16x8& f0, bf16x8& f1) const {
-    phase();
-    *reinterpret_cast<bf16x8*>(lds + mem[0]) = m[0];
-    *reinterpret_cast<bf16x8*>(lds + mem[1]) = m[1];
-    phase();
-    f0 = *reinterpret_cast<const bf16x8*>(lds + frag[0]);
-    f1 = *reinterpret_cast<const bf16x8*>(lds + frag[1]);
-  }
-  PE_DEV void to_mem(const bf16x8 (&f)[2], bf16x8& m0, bf16x8& m1) const {
-    phase();
-    *reinterpret_cast<bf16x8*>(lds + frag[0]) = f[0];
-    *reinterpret_cast<bf16x8*>(lds + frag[1]) = f[1];
-    phase();
-    m0 = *reinterpret_cast<const bf16x8*>(lds + mem[0]);
-    m1 = *reinterpret_cast<const bf16x8*>(lds + mem[1]);
-  }
-};
 PE_DEV long long rows_map(int x, int in, long long outer, long long stride) {
   return in >= (1 << 30) ? (long long)x * stride : (long long)((unsigned)x / (unsigned)in) * outer + (long long)((unsigned)x % (unsigned)in) * stride;
 }

@@ -563,6 +563,33 @@ def test_triangle_attention_backward_over_many_rows():
     _check_walking_backward(dims, inp, table, 2)
 
 
+def test_attention_logits_far_below_zero():
+    """Every logit of the row attention near -300 (a pair bias that is the same for all keys, to which the softmax is
+    indifferent): the first reference maximum is that low, and 2^(0 - reference) is not a finite factor."""
+    dims, table, inp = _case("tiny", dtype=0, s=6, r=70)
+    table, n = param_table(dims)
+    inp = make_inputs(dims, table, n, ("random_residues", 0.1), 51)
+    for name, value in (("row.ln_z.g", 0.0), ("row.ln_z.b", 1.0), ("row.w_bias", -300.0)):
+        e = next(e for e in table if e["name"] == name)
+        w = inp["params"][e["offset"]:e["offset"] + int(np.prod(e["shape"]))].reshape(e["shape"])
+        w[0] = value     # channel 0
+    run = BlockRun(dims, inp)
+    run.fwd()
+    run.sync()
+    m, z, _, _ = ev.block_fwd(dims, inp["params"], inp["msa"], inp["pair"], inp["msa_mask"], inp["pair_mask"], want_cache=False)
+    assert rel_err(to_np(run.msa_out), m) < TOL[0] and rel_err(to_np(run.pair_out), z) < TOL[0]
+
+
+@pytest.mark.parametrize("h_msa,d_msa,s,r,dtype", [(4, 32, 257, 33, 1), (2, 24, 65, 65, 1), (4, 16, 97, 31, 1), (4, 8, 31, 34, 1), (4, 32, 290, 7, 0)])
+def test_attention_tiles_and_head_dimensions(h_msa, d_msa, s, r, dtype):
+    """Head dimensions of one and two contraction steps, one key more than a staged chunk, a ragged last tile, an odd last batch row."""
+    dims, table, inp = _case("tiny", dtype=dtype, s=s, r=r, c_m=64, h_msa=h_msa, d_msa=d_msa)
+    table, n = param_table(dims)
+    inp = make_inputs(dims, table, n, ("random_residues", 0.1), 53 + d_msa)
+    errs, worst, tol, stats = check_case(dims, table, inp)
+    _assert(errs, worst, tol, stats)
+
+
 @pytest.mark.parametrize("name,dtype,over", [("tiny", 0, {}), ("tiny", 1, dict(s=9, r=21, c_tri=24)), ("af2_initial", 1, dict(s=17, r=45)),
                                              ("af2_initial", 1, dict(s=17, r=45, variant=1)), ("af2_initial", 0, dict(s=9, r=34, variant=2)),
                                              ("extra_msa", 1, dict(s=70, r=40))])
