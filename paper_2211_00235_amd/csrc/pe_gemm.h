@@ -9,9 +9,9 @@
 //   addr(x,k) = (x / x_in) * x_outer + (x % x_in) * x_stride
 //             + (k / k_in) * k_outer + (k % k_in) * k_stride
 // An operand is either "k-contiguous" (k_stride == 1, 16-byte loads along k) or
-// "x-contiguous" (x_stride == 1, 16-byte loads along x, transposed in registers
-// on the way into LDS).  LDS always holds k-contiguous rows, which is what the
-// 32x32 MFMA operand fragments want.
+// "x-contiguous" (x_stride == 1, 16-byte loads along x).  LDS holds a tile in memory order
+// either way; the MFMA fragments of an x-contiguous bf16 tile (8 consecutive k of one
+// row) come from transposing LDS reads.
 //
 // Workgroup: 256 threads = 4 waves in a 2x2 grid; block tile 128x128; each wave
 // owns 64x64 = 2x2 MFMA tiles (64 accumulator VGPRs).  Next k-tile is prefetched
@@ -523,23 +523,29 @@ template <typename T> struct GemmCfg {
   static constexpr int BM = 128, BN = 128;
   static constexpr int BK = 8 * VEC;        // 64 (bf16) or 32 (fp32): 128-byte rows
   static constexpr int LDSS = BK + VEC;     // +16 bytes: conflict-free 16-byte fragment reads
-  // LDS element offset of (row, 16-byte chunk c of the row, element w inside the chunk).  For a tile
-  // filled by the transposing store of an x-contiguous operand (SW = true) the chunk index is
-  // XOR-swizzled with the row's 8-row group, so that this store (8 rows apart per lane) does not hit
-  // one bank pair 16 times.  A tile of a k-contiguous operand is stored row by row and keeps the plain
-  // layout, in which the 16 rows that a fragment read touches at once fall on 16 different bank
-  // groups (row stride 144 bytes); with the swizzle rows 8..15 would land on the groups of rows 0..7
-  // (counters: 45 % of the LDS cycles of the k-contiguous GEMMs were bank-conflict cycles).
-  template <bool SW> static PE_DEV int off(int row, int c, int w) {
-    return SW ? row * LDSS + ((c ^ ((row >> 3) & 7)) * VEC) + w : row * LDSS + c * VEC + w;
+  // LDS element offset of (row, 16-byte chunk c of the row, element w inside the chunk) in the tile of a k-contiguous operand:
+  // the 16 rows that a fragment read touches at once fall on 16 different bank groups (row stride 144 bytes)
+  static PE_DEV int off(int row, int c, int w) { return row * LDSS + c * VEC + w; }
+  // The tile of an x-contiguous operand stays in memory order [k][128 rows] (16-byte stores of what was loaded).
+  // fp32: a fragment is one element per lane (32 rows at k, 32 rows at k + 1: 32 consecutive words per half wave on a
+  // read), the row index is XOR-ed by 32 at odd k: the two halves of a wave read disjoint banks.  With a transposing store
+  // the fp32 parameter-gradient GEMMs ran at 43 TFLOP/s (256 x 1024 x 32768: 301 us).
+  // bf16: fragments come from transposing reads (xmem_frag); the 32-byte unit of a row is XOR-ed by 2 (k % 4), so that the four
+  // rows of k and both halves of the 32 rows that a read touches cover every bank once.
+  static PE_DEV int xoff(int k, int row) {
+    return sizeof(T) == 4 ? k * 128 + (row ^ ((k & 1) << 5)) : k * 128 + (row ^ ((k & 3) << 5));
   }
-  // fp32: a fragment is one element per lane (32 rows at k, 32 rows at k + 1), so the tile of an x-contiguous operand
-  // needs no transpose.  It stays in memory order [k][128 rows] (16-byte stores of what was loaded, 32 consecutive
-  // words per half wave on a read) with the row index XOR-ed by 32 at odd k: the two halves of a wave read disjoint
-  // banks.  With the transposing store the fp32 parameter-gradient GEMMs ran at 43 TFLOP/s (256 x 1024 x 32768: 301 us).
-  static constexpr bool XMEM = sizeof(T) == 4;
-  static PE_DEV int xoff(int k, int row) { return k * 128 + (row ^ ((k & 1) << 5)); }
 };
+// MFMA fragment (16 k from k0, 32 rows from r0, lane (l32, g)) of a bf16 tile in memory order
+PE_DEV bf16x8 xmem_frag(const bf16* tile, int k0, int r0, int l32, int g) {
+  const int q = (l32 & 15) >> 2;
+  const bf16* p = tile + GemmCfg<bf16>::xoff(k0 + 8 * g + q, r0 + (l32 & 16) + 4 * (l32 & 3));    // k0 and 8 g are multiples of 4
+  const bf16x4 lo = lds_read_tr(p), hi = lds_read_tr(p + 4 * 128);
+  bf16x8 f;
+#pragma unroll
+  for (int e = 0; e < 4; e++) { f[e] = lo[e]; f[4 + e] = hi[e]; }
+  return f;
+}
 
 // element-wise (unaligned) variant of one 16-byte vector load: elements e = 0..VEC-1 along k (KC) or x
 template <typename T, bool KC>
@@ -651,23 +657,13 @@ PE_DEV void gemm_store_tile(const typename Vec16<T>::type (&regs)[4], T* lds, in
 #pragma unroll
     for (int i = 0; i < 4; i++) {
       int row = (tid >> 3) + 32 * i;
-      *reinterpret_cast<V*>(lds + GemmCfg<T>::template off<false>(row, kv, 0)) = regs[i];
+      *reinterpret_cast<V*>(lds + GemmCfg<T>::off(row, kv, 0)) = regs[i];
     }
   } else {
     constexpr int XB = 128 / VEC;
-    int xb = tid % XB, kb = tid / XB;
-    if constexpr (GemmCfg<T>::XMEM) {
+    const int xb = tid % XB, kb = tid / XB;
 #pragma unroll
-      for (int j = 0; j < 4; j++) *reinterpret_cast<V*>(lds + GemmCfg<T>::xoff(kb * 4 + j, xb * VEC)) = regs[j];
-      return;
-    }
-    typedef T V4 __attribute__((ext_vector_type(4)));
-#pragma unroll
-    for (int e = 0; e < VEC; e++) {
-      V4 w;
-      w[0] = regs[0][e]; w[1] = regs[1][e]; w[2] = regs[2][e]; w[3] = regs[3][e];
-      *reinterpret_cast<V4*>(lds + GemmCfg<T>::template off<true>(xb * VEC + e, (kb * 4) / VEC, (kb * 4) % VEC)) = w;
-    }
+    for (int j = 0; j < 4; j++) *reinterpret_cast<V*>(lds + GemmCfg<T>::xoff(kb * 4 + j, xb * VEC)) = regs[j];
   }
 }
 
@@ -738,13 +734,13 @@ __global__ __launch_bounds__(256) void gemm_kernel(Operand A, Operand B, GemmSha
       gemm_load_tile<T, B_KC, AL>(rb, pb, B, rowb, sh.n_rows, k0 + C::BK, kend, tid);
     }
     if constexpr (Epi::HAS_COLSUM) {
-      if (do_cs && C::XMEM && !B_KC) {
-#pragma unroll
+      if (do_cs && !B_KC) {
+#pragma unroll 8
         for (int k = 0; k < C::BK; k++) cs += to_f(lds_b[C::xoff(k, tid)]);
       } else if (do_cs) {
 #pragma unroll
         for (int ch = 0; ch < C::BK / C::VEC; ch++) {
-          V v = *reinterpret_cast<const V*>(lds_b + C::template off<!B_KC>(tid, ch, 0));
+          V v = *reinterpret_cast<const V*>(lds_b + C::off(tid, ch, 0));
 #pragma unroll
           for (int e = 0; e < C::VEC; e++) cs += to_f(v[e]);
         }
@@ -757,8 +753,12 @@ __global__ __launch_bounds__(256) void gemm_kernel(Operand A, Operand B, GemmSha
       for (int t = 0; t < 2; t++) {
         const int eo = kk * MM::KSTEP + g * MM::KP;
         const int ar = wm * 64 + t * 32 + l32, br = wn * 64 + t * 32 + l32;
-        af[t] = MM::load(lds_a + (C::XMEM && !A_KC ? C::xoff(eo, ar) : C::template off<!A_KC>(ar, eo / C::VEC, eo % C::VEC)));
-        bf[t] = MM::load(lds_b + (C::XMEM && !B_KC ? C::xoff(eo, br) : C::template off<!B_KC>(br, eo / C::VEC, eo % C::VEC)));
+        if constexpr (A_KC) af[t] = MM::load(lds_a + C::off(ar, eo / C::VEC, eo % C::VEC));
+        else if constexpr (sizeof(T) == 4) af[t] = MM::load(lds_a + C::xoff(eo, ar));
+        else af[t] = xmem_frag(lds_a, kk * MM::KSTEP, wm * 64 + t * 32, l32, g);
+        if constexpr (B_KC) bf[t] = MM::load(lds_b + C::off(br, eo / C::VEC, eo % C::VEC));
+        else if constexpr (sizeof(T) == 4) bf[t] = MM::load(lds_b + C::xoff(eo, br));
+        else bf[t] = xmem_frag(lds_b, kk * MM::KSTEP, wn * 64 + t * 32, l32, g);
       }
 #pragma unroll
       for (int i = 0; i < 2; i++)
@@ -1020,7 +1020,7 @@ __global__ __launch_bounds__(256) void gemm64_kernel(Operand A, Operand B, GemmS
   for (int k0 = 0; k0 < sh.K; k0 += C::BK) {
     __syncthreads();  // previous tile fully consumed
 #pragma unroll
-    for (int i = 0; i < 2; i++) *reinterpret_cast<V*>(lds_a + C::template off<false>((tid >> 3) + 32 * i, kv, 0)) = ra[i];
+    for (int i = 0; i < 2; i++) *reinterpret_cast<V*>(lds_a + C::off((tid >> 3) + 32 * i, kv, 0)) = ra[i];
     gemm_store_tile<T, true>(rb, lds_b, tid);
     __syncthreads();
     if (k0 + C::BK < sh.K) {
@@ -1030,10 +1030,10 @@ __global__ __launch_bounds__(256) void gemm64_kernel(Operand A, Operand B, GemmS
 #pragma unroll
     for (int kk = 0; kk < C::BK / MM::KSTEP; kk++) {
       const int eo = kk * MM::KSTEP + g * MM::KP;
-      typename MM::frag bf = MM::load(lds_b + C::template off<false>(wave * 32 + l32, eo / C::VEC, eo % C::VEC));
+      typename MM::frag bf = MM::load(lds_b + C::off(wave * 32 + l32, eo / C::VEC, eo % C::VEC));
 #pragma unroll
       for (int t = 0; t < 2; t++)
-        MM::mma(acc[t], MM::load(lds_a + C::template off<false>(t * 32 + l32, eo / C::VEC, eo % C::VEC)), bf);
+        MM::mma(acc[t], MM::load(lds_a + C::off(t * 32 + l32, eo / C::VEC, eo % C::VEC)), bf);
     }
   }
 
@@ -1171,7 +1171,7 @@ __global__ __launch_bounds__(256) void gemm64r_kernel(Operand A, Operand B, Gemm
   for (int k0 = 0; k0 < sh.K; k0 += C::BK) {
     __syncthreads();  // previous tile fully consumed
 #pragma unroll
-    for (int i = 0; i < 2; i++) *reinterpret_cast<V*>(lds_a + C::template off<false>((tid >> 3) + 32 * i, kv, 0)) = ra[i];
+    for (int i = 0; i < 2; i++) *reinterpret_cast<V*>(lds_a + C::off((tid >> 3) + 32 * i, kv, 0)) = ra[i];
     gemm_store_tile<T, true>(rb, lds_b, tid);
     __syncthreads();
     if (k0 + C::BK < sh.K) {
@@ -1181,10 +1181,10 @@ __global__ __launch_bounds__(256) void gemm64r_kernel(Operand A, Operand B, Gemm
 #pragma unroll
     for (int kk = 0; kk < C::BK / MM::KSTEP; kk++) {
       const int eo = kk * MM::KSTEP + g * MM::KP;
-      typename MM::frag bf = MM::load(lds_b + C::template off<false>(wave * 32 + l32, eo / C::VEC, eo % C::VEC));
+      typename MM::frag bf = MM::load(lds_b + C::off(wave * 32 + l32, eo / C::VEC, eo % C::VEC));
 #pragma unroll
       for (int t = 0; t < 2; t++)
-        MM::mma(acc[t], MM::load(lds_a + C::template off<false>(t * 32 + l32, eo / C::VEC, eo % C::VEC)), bf);
+        MM::mma(acc[t], MM::load(lds_a + C::off(t * 32 + l32, eo / C::VEC, eo % C::VEC)), bf);
     }
   }
 
@@ -1519,7 +1519,7 @@ __global__ __launch_bounds__(256) void gemm64w_kernel(Operand A, Operand B, Gemm
   for (int k0 = 0; k0 < sh.K; k0 += C::BK) {
     __syncthreads();  // previous tile fully consumed
 #pragma unroll
-    for (int i = 0; i < 2; i++) *reinterpret_cast<V*>(lds_a + C::template off<false>((tid >> 3) + 32 * i, kv, 0)) = ra[i];
+    for (int i = 0; i < 2; i++) *reinterpret_cast<V*>(lds_a + C::off((tid >> 3) + 32 * i, kv, 0)) = ra[i];
     gemm_store_tile<T, true>(rb0, lds_b, tid);
     gemm_store_tile<T, true>(rb1, lds_b + 128 * C::LDSS, tid);
     __syncthreads();
@@ -1534,8 +1534,8 @@ __global__ __launch_bounds__(256) void gemm64w_kernel(Operand A, Operand B, Gemm
       typename MM::frag af[2], bf[2];
 #pragma unroll
       for (int t = 0; t < 2; t++) {
-        af[t] = MM::load(lds_a + C::template off<false>(t * 32 + l32, eo / C::VEC, eo % C::VEC));
-        bf[t] = MM::load(lds_b + C::template off<false>(wave * 64 + t * 32 + l32, eo / C::VEC, eo % C::VEC));
+        af[t] = MM::load(lds_a + C::off(t * 32 + l32, eo / C::VEC, eo % C::VEC));
+        bf[t] = MM::load(lds_b + C::off(wave * 64 + t * 32 + l32, eo / C::VEC, eo % C::VEC));
       }
 #pragma unroll
       for (int i = 0; i < 2; i++)
@@ -1713,20 +1713,16 @@ static inline bool launch_gemm64r(hipStream_t st, const Operand& A, const Operan
 // ---------------------------------------------------------------------------
 // Parameter-gradient variant (bf16, both operands x-contiguous and 16-byte aligned, fp32 partials):
 //   part[b][m][n] = sum over the k range of split b of A[k][m] * B[k][n]
-// The operand tiles stay in their memory order in LDS ([k][x], 16-byte stores, no register
-// transpose).  The MFMA fragments (8 consecutive k of one row per lane) are gathered with eight
-// 32-bit reads per pair of MFMA row blocks: lane l reads the rows (2l, 2l+1) of its wave's 64-row
-// strip at eight k and splits the halves, so MFMA row block i of a wave covers the strip's rows
-// 2r + i (r = 0..31) instead of 32 consecutive ones; the accumulator mapping below follows.
-// Rows k and k+8 are read by the two lane halves at once: the 16-byte chunk index of a row is
-// XOR-ed with 8 when (k / 8) is odd, which puts them on disjoint banks.
+// The operand tiles stay in their memory order in LDS ([k][x], 16-byte stores, no register transpose); the MFMA fragments
+// (8 consecutive k of one row per lane) are two transposing reads each (xmem_frag).  Gathering them with eight 32-bit reads and
+// a byte permute per register pair cost 16 LDS reads and 16 permutes per four MFMAs instead of 8 reads.
 // KG wave groups (4 waves each) take alternate k-tiles of the workgroup's range, each with its own
 // tiles in LDS and its own register prefetch, which doubles the bytes in flight per CU without a
 // second set of partials; the groups' accumulators are added through LDS at the end.
 // ---------------------------------------------------------------------------
 // partial sums are read back by the deferred reduction at the end of the backward pass, long after the L2 has
 // turned over: written non-temporally, they do not displace the lines the neighbouring kernels share
-PE_DEV void dw_store_partial(float* p, f32x2 v) { __builtin_nontemporal_store(v, reinterpret_cast<f32x2*>(p)); }
+PE_DEV void dw_store_partial(float* p, float v) { __builtin_nontemporal_store(v, p); }
 struct XAddr {   // per-thread x part of the tile addressing: 8 consecutive x, 4 consecutive k per tile
   long long a; bool ok;
   PE_DEV void init(const Operand& op, int x0, int X, int xb) {
@@ -1799,16 +1795,12 @@ __global__ __launch_bounds__(256 * KG) void gemm_dwx_kernel(Operand A, Operand B
   XAddr xa, xbb;
   xa.init(A, m0, sh.M, xb);
   xbb.init(B, n0, sh.N, xb);
-  const int st_off = kb * 4 * 128 + ((xb ^ (((kb >> 1) & 1) << 3)) * 8);
   // column sums of B (bias gradients): one m-tile workgroup per (batch, n-tile) adds up what it loads
   const bool do_cs = epi.colsum != nullptr && (m0 / BM) == (n0 / BM + b) % NTm;
   float cs[8];
 #pragma unroll
   for (int e = 0; e < 8; e++) cs[e] = 0.0f;
 
-  // fragment role: 32-bit words (rows 2 l32, 2 l32 + 1 of the wave's strip) at k = 16 kk + 8 g + e
-  const uint32_t* fa = reinterpret_cast<const uint32_t*>(lds_a) + (((wm * 64 + 2 * l32) ^ (g * 64)) >> 1) + g * 8 * 64;
-  const uint32_t* fb = reinterpret_cast<const uint32_t*>(lds_b) + (((wn * 64 + 2 * l32) ^ (g * 64)) >> 1) + g * 8 * 64;
 
   bf16x8 ra[4], rb[4];
   const int nt = (kend - kbeg + BK - 1) / BK;          // k-tiles of this workgroup
@@ -1822,8 +1814,8 @@ __global__ __launch_bounds__(256 * KG) void gemm_dwx_kernel(Operand A, Operand B
     __syncthreads();  // previous tile fully consumed
 #pragma unroll
     for (int j = 0; j < 4; j++) {
-      *reinterpret_cast<bf16x8*>(lds_a + st_off + j * 128) = ra[j];
-      *reinterpret_cast<bf16x8*>(lds_b + st_off + j * 128) = rb[j];
+      *reinterpret_cast<bf16x8*>(lds_a + GemmCfg<bf16>::xoff(kb * 4 + j, xb * 8)) = ra[j];
+      *reinterpret_cast<bf16x8*>(lds_b + GemmCfg<bf16>::xoff(kb * 4 + j, xb * 8)) = rb[j];
     }
     if (do_cs) {
 #pragma unroll
@@ -1839,26 +1831,16 @@ __global__ __launch_bounds__(256 * KG) void gemm_dwx_kernel(Operand A, Operand B
     }
 #pragma unroll
     for (int kk = 0; kk < BK / 16; kk++) {
-      uint32_t wa[8], wb[8];
+      bf16x8 af[2], bf[2];
 #pragma unroll
-      for (int e = 0; e < 8; e++) {
-        wa[e] = fa[(kk * 16 + e) * 64];
-        wb[e] = fb[(kk * 16 + e) * 64];
+      for (int i = 0; i < 2; i++) {
+        af[i] = xmem_frag(lds_a, kk * 16, wm * 64 + i * 32, l32, g);
+        bf[i] = xmem_frag(lds_b, kk * 16, wn * 64 + i * 32, l32, g);
       }
-      union { uint32_t u[4]; bf16x8 v; } a0, a1, b0, b1;
 #pragma unroll
-      for (int j = 0; j < 4; j++) {
-        // byte permute of {first operand, second operand}: selectors 0..3 take bytes of the second, 4..7 of the
-        // first: low halves (rows 2l) -> 0x05040100, high halves (rows 2l + 1) -> 0x07060302
-        a0.u[j] = __builtin_amdgcn_perm(wa[2 * j + 1], wa[2 * j], 0x05040100u);
-        a1.u[j] = __builtin_amdgcn_perm(wa[2 * j + 1], wa[2 * j], 0x07060302u);
-        b0.u[j] = __builtin_amdgcn_perm(wb[2 * j + 1], wb[2 * j], 0x05040100u);
-        b1.u[j] = __builtin_amdgcn_perm(wb[2 * j + 1], wb[2 * j], 0x07060302u);
-      }
-      acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0.v, b0.v, acc[0][0], 0, 0, 0);
-      acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0.v, b1.v, acc[0][1], 0, 0, 0);
-      acc[1][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1.v, b0.v, acc[1][0], 0, 0, 0);
-      acc[1][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1.v, b1.v, acc[1][1], 0, 0, 0);
+      for (int i = 0; i < 2; i++)
+#pragma unroll
+        for (int j = 0; j < 2; j++) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[i], bf[j], acc[i][j], 0, 0, 0);
     }
   }
 
@@ -1876,45 +1858,44 @@ __global__ __launch_bounds__(256 * KG) void gemm_dwx_kernel(Operand A, Operand B
       epi.colsum[(long long)b * sh.N + n0 + threadIdx.x] = s;
     }
   }
-  // accumulator element (i, j, a) of lane (l32, g): row 2 acc_row(g, a) + i, column 2 l32 + j of the wave's 64 x 64
 #pragma unroll 1
   for (int og = 1; og < KG; og++) {   // group og hands its 128 x 128 tile to group 0 (64 KB at the start of LDS)
+    float* x = lds_f + (wm * 64 + 4 * g) * 128 + wn * 64 + l32;     // element (i, j, a): row 32 i + acc_row(0, a), column 32 j further
     __syncthreads();
     if (kg == og) {
 #pragma unroll
       for (int i = 0; i < 2; i++)
 #pragma unroll
-        for (int a = 0; a < 16; a++) {
-          f32x2 v; v[0] = acc[i][0][a]; v[1] = acc[i][1][a];
-          *reinterpret_cast<f32x2*>(lds_f + (wm * 64 + 2 * acc_row(g, a) + i) * 128 + wn * 64 + 2 * l32) = v;
-        }
+        for (int a = 0; a < 16; a++)
+#pragma unroll
+          for (int j = 0; j < 2; j++) x[(i * 32 + acc_row(0, a)) * 128 + j * 32] = acc[i][j][a];
     }
     __syncthreads();
     if (kg == 0) {
 #pragma unroll
       for (int i = 0; i < 2; i++)
 #pragma unroll
-        for (int a = 0; a < 16; a++) {
-          f32x2 o = *reinterpret_cast<const f32x2*>(lds_f + (wm * 64 + 2 * acc_row(g, a) + i) * 128 + wn * 64 + 2 * l32);
-          acc[i][0][a] += o[0]; acc[i][1][a] += o[1];
-        }
+        for (int a = 0; a < 16; a++)
+#pragma unroll
+          for (int j = 0; j < 2; j++) acc[i][j][a] += x[(i * 32 + acc_row(0, a)) * 128 + j * 32];
     }
   }
   if (kg != 0) return;
-  const int n = n0 + wn * 64 + 2 * l32;
+  const int n = n0 + wn * 64 + l32;
+  float* out = epi.out + (long long)b * epi.mn + n;
 #pragma unroll
   for (int i = 0; i < 2; i++)
 #pragma unroll
     for (int a = 0; a < 16; a++) {
-      const int rloc = wm * 64 + 2 * acc_row(g, a) + i;
-      const int m = m0 + rloc;
-      f32x2 v; v[0] = acc[i][0][a]; v[1] = acc[i][1][a];
-      if (m < sh.M && n < sh.N) dw_store_partial(epi.out + (long long)b * epi.mn + (long long)m * epi.ldn + n, v);
+      const int m = m0 + wm * 64 + i * 32 + acc_row(g, a);
+#pragma unroll
+      for (int j = 0; j < 2; j++)
+        if (m < sh.M && n + j * 32 < sh.N) dw_store_partial(out + (long long)m * epi.ldn + j * 32, acc[i][j][a]);
     }
 }
 
 // ---------------------------------------------------------------------------
-// Pipelined parameter-gradient kernel: the arithmetic, LDS layout, fragment gather and accumulator mapping of
+// Pipelined parameter-gradient kernel: the arithmetic, LDS layout, fragments and accumulator mapping of
 // gemm_dwx_kernel<1>, with S k-tiles in flight per workgroup instead of one.  Every thread keeps a ring of S
 // register tiles (S x 8 loads of 16 bytes): in step t it stores ring slot t % S to the LDS buffer t % 2, re-issues
 // the slot's loads for tile t + S, passes ONE barrier and multiplies from that buffer; the next store to the
@@ -1969,14 +1950,10 @@ __global__ __launch_bounds__(256) void gemm_dwp_kernel(Operand A, Operand B, Gem
   XAddr xa, xbb;
   xa.init(A, m0, sh.M, xb);
   xbb.init(B, n0, sh.N, xb);
-  const int st_off = kb * 4 * 128 + ((xb ^ (((kb >> 1) & 1) << 3)) * 8);
   const bool do_cs = epi.colsum != nullptr && (m0 / BM) == (n0 / BM + b) % NTm;
   float cs[8];
 #pragma unroll
   for (int e = 0; e < 8; e++) cs[e] = 0.0f;
-  // fragment role (word offsets inside an operand tile): rows 2 l32, 2 l32 + 1 of the wave's strip at k = 16 kk + 8 g + e
-  const int fa_off = (((wm * 64 + 2 * l32) ^ (g * 64)) >> 1) + g * 8 * 64;
-  const int fb_off = (((wn * 64 + 2 * l32) ^ (g * 64)) >> 1) + g * 8 * 64;
 
   bf16x8 ra[S][4], rb[S][4];
   const int nt = (kend - kbeg) / BK;                   // a multiple of S
@@ -1991,8 +1968,8 @@ __global__ __launch_bounds__(256) void gemm_dwp_kernel(Operand A, Operand B, Gem
     bf16* lb = la + TILE;
 #pragma unroll
     for (int q = 0; q < 4; q++) {
-      *reinterpret_cast<bf16x8*>(la + st_off + q * 128) = ra[j][q];
-      *reinterpret_cast<bf16x8*>(lb + st_off + q * 128) = rb[j][q];
+      *reinterpret_cast<bf16x8*>(la + GemmCfg<bf16>::xoff(kb * 4 + q, xb * 8)) = ra[j][q];
+      *reinterpret_cast<bf16x8*>(lb + GemmCfg<bf16>::xoff(kb * 4 + q, xb * 8)) = rb[j][q];
     }
     if (do_cs) {
 #pragma unroll
@@ -2005,28 +1982,18 @@ __global__ __launch_bounds__(256) void gemm_dwp_kernel(Operand A, Operand B, Gem
       dwp_load(rb[j], pb, B, xbb.a, kbeg + (t + S) * BK + kb * 4);
     }
     __syncthreads();
-    const uint32_t* fa = reinterpret_cast<const uint32_t*>(la) + fa_off;
-    const uint32_t* fb = reinterpret_cast<const uint32_t*>(lb) + fb_off;
 #pragma unroll
     for (int kk = 0; kk < BK / 16; kk++) {
-      uint32_t wa[8], wb[8];
+      bf16x8 af[2], bf[2];
 #pragma unroll
-      for (int e = 0; e < 8; e++) {
-        wa[e] = fa[(kk * 16 + e) * 64];
-        wb[e] = fb[(kk * 16 + e) * 64];
+      for (int i = 0; i < 2; i++) {
+        af[i] = xmem_frag(la, kk * 16, wm * 64 + i * 32, l32, g);
+        bf[i] = xmem_frag(lb, kk * 16, wn * 64 + i * 32, l32, g);
       }
-      union { uint32_t u[4]; bf16x8 v; } a0, a1, b0, b1;
 #pragma unroll
-      for (int q = 0; q < 4; q++) {
-        a0.u[q] = __builtin_amdgcn_perm(wa[2 * q + 1], wa[2 * q], 0x05040100u);
-        a1.u[q] = __builtin_amdgcn_perm(wa[2 * q + 1], wa[2 * q], 0x07060302u);
-        b0.u[q] = __builtin_amdgcn_perm(wb[2 * q + 1], wb[2 * q], 0x05040100u);
-        b1.u[q] = __builtin_amdgcn_perm(wb[2 * q + 1], wb[2 * q], 0x07060302u);
-      }
-      acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0.v, b0.v, acc[0][0], 0, 0, 0);
-      acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0.v, b1.v, acc[0][1], 0, 0, 0);
-      acc[1][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1.v, b0.v, acc[1][0], 0, 0, 0);
-      acc[1][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1.v, b1.v, acc[1][1], 0, 0, 0);
+      for (int i = 0; i < 2; i++)
+#pragma unroll
+        for (int j = 0; j < 2; j++) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[i], bf[j], acc[i][j], 0, 0, 0);
     }
   };
   int t = 0;
@@ -2060,15 +2027,14 @@ __global__ __launch_bounds__(256) void gemm_dwp_kernel(Operand A, Operand B, Gem
       epi.colsum[(long long)b * sh.N + n0 + tid] = s;
     }
   }
-  // accumulator element (i, j, a) of lane (l32, g): row 2 acc_row(g, a) + i, column 2 l32 + j of the wave's 64 x 64
-  const int n = n0 + wn * 64 + 2 * l32;
+  float* out = epi.out + (long long)b * epi.mn + n0 + wn * 64 + l32;
 #pragma unroll
   for (int i = 0; i < 2; i++)
 #pragma unroll
     for (int a = 0; a < 16; a++) {
-      const int m = m0 + wm * 64 + 2 * acc_row(g, a) + i;
-      f32x2 v; v[0] = acc[i][0][a]; v[1] = acc[i][1][a];
-      dw_store_partial(epi.out + (long long)b * epi.mn + (long long)m * epi.ldn + n, v);
+      const int m = m0 + wm * 64 + i * 32 + acc_row(g, a);
+#pragma unroll
+      for (int j = 0; j < 2; j++) dw_store_partial(out + (long long)m * epi.ldn + j * 32, acc[i][j][a]);
     }
 }
 
