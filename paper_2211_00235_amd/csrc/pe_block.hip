@@ -14,6 +14,7 @@
 
 #include "pe_attn.h"
 #include "pe_elem.h"
+#include "pe_deep.h"
 #include "pe_gcol.h"
 #include "pe_gemm.h"
 #include "pe_layout.h"
@@ -723,6 +724,7 @@ template <typename T> struct Runner {
     char kn[64] = "";
     if (!timed()) {}
     else if (g_gemm_last_small) snprintf(kn, sizeof(kn), "gemm_small_kernel<%s,%s>", akc ? "kc" : "xc", bkc ? "kc" : "xc");
+    else if (g_gemm_last_deep) snprintf(kn, sizeof(kn), "gemm_deep_kernel<%s,%s>", akc ? "kc" : "xc", bkc ? "kc" : "xc");
     else if (g_gemm_last_rows) snprintf(kn, sizeof(kn), "gemm_rows_kernel<F=%d,K=%d>", g_gemm_last_features, K);
     else if (narrow) snprintf(kn, sizeof(kn), "gemm64_kernel<EpiGeneric,F=%d>", g_gemm_last_features);
     else snprintf(kn, sizeof(kn), "gemm_kernel<%s,%s,%s,EpiGeneric,F=%d>", akc ? "kc" : "xc", bkc ? "kc" : "xc", al ? "vec" : "elem",

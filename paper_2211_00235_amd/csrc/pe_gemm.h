@@ -2138,6 +2138,7 @@ static inline bool launch_gemm_spec(hipStream_t st, dim3 grid, const Operand& A,
   PE_GEMM_SPEC(EF_BIASN | EF_ROWSCALE | EF_ON2)
   PE_GEMM_SPEC(EF_BIASN | EF_AUX | EF_MUL | EF_RES)
   PE_GEMM_SPEC(EF_OM2 | EF_ON2 | EF_ROWSCALE)
+  PE_GEMM_SPEC(EF_SCALE2D)
 #undef PE_GEMM_SPEC
   return false;
   }
@@ -2186,6 +2187,10 @@ static thread_local bool g_gemm_last_small = false;
 // tall A, contraction over channels (pe_rows.h): false = not launched
 template <class Epi> static inline bool launch_gemm_rows(hipStream_t st, const Operand& A, const Operand& B, const GemmShape& sh, const Epi& epi);
 static thread_local bool g_gemm_last_rows = false;
+// large outputs with a long contraction (pe_deep.h): false = not launched
+template <class Epi>
+static inline bool launch_gemm_deep(hipStream_t st, const Operand& A, bool a_kc, const Operand& B, bool b_kc, const GemmShape& sh, const Epi& epi);
+static thread_local bool g_gemm_last_deep = false;
 
 // Operands that break the 16-byte vector rules (odd leading dimensions) take the
 // element-wise loader and the per-element epilogue: same tiles, same arithmetic, slower.
@@ -2203,6 +2208,7 @@ static inline int launch_gemm(hipStream_t st, const Operand& A, bool a_kc, const
   bool al = gemm_operand_ok<T>(A, a_kc, sh.M, sh) && gemm_operand_ok<T>(B, b_kc, sh.N, sh);
   g_gemm_last_small = false;
   g_gemm_last_rows = false;
+  g_gemm_last_deep = false;
   if constexpr (!Epi::TM_GATE) {
     const bool sve = epi.vec_ok(sh.N);
     // bf16 parameter gradients have a kernel that is faster even there (gemm_dwx_kernel)
@@ -2221,6 +2227,10 @@ static inline int launch_gemm(hipStream_t st, const Operand& A, bool a_kc, const
   if constexpr (std::is_same<T, bf16>::value) {
     if (ve && a_kc && b_kc && launch_gemm_rows<Epi>(st, A, B, sh, epi)) {
       g_gemm_last_rows = true;
+      return hipGetLastError() == hipSuccess ? 0 : -2;
+    }
+    if (ve && launch_gemm_deep<Epi>(st, A, a_kc, B, b_kc, sh, epi)) {
+      g_gemm_last_deep = true;
       return hipGetLastError() == hipSuccess ? 0 : -2;
     }
   }

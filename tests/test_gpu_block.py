@@ -632,6 +632,20 @@ def test_row_streaming_gemms(name, s, r, two_streams, ks):
     _assert(errs, worst, tol, stats)
 
 
+def test_outer_product_over_many_rows():
+    """The outer product's contractions on 256 x 256 tiles (pe_deep.h) in their three operand layouts: 3680 = 14 x 256 + 96
+    columns (and a contraction that ends in half a step of 64), a contraction over 3501 rows (an odd tail of 45), ragged last
+    tiles in both directions, a last band of fewer than four m-tiles."""
+    dims, table, inp = _case("tiny", dtype=1, s=3501, r=115, c_m=32, c_z=32, c_opm=32, h_msa=2, d_msa=8, col_global=1)
+    table, n = param_table(dims)
+    inp = make_inputs(dims, table, n, ("random_rows", 0.1), 61)
+    names = _kernel_launches(BlockRun(dims, inp))
+    for form in ("xc,xc", "kc,kc", "kc,xc"):
+        assert names.get("gemm_deep_kernel<%s>" % form, 0) == 1, (form, names)
+    errs, worst, tol, stats = check_case(dims, table, inp)
+    _assert(errs, worst, tol, stats)
+
+
 @pytest.mark.slow
 def test_extra_msa_bf16():
     """Config 3: extra-MSA-stack block (s=1024, r=256, c_m=64, global column attention), bf16."""
