@@ -4,8 +4,8 @@
 // What bounds gemm_kernel there is LDS bandwidth: a wave that owns 64 x 64 of a 128 x 128 tile reads 4 KB of fragments per
 // four MFMAs, 128 cycles of LDS against 128 cycles of MFMA per 16 k of a workgroup with the tile's stores still to come.
 // Here the tile is 256 x 256 and each of eight waves owns 128 x 64 of it: 6 KB per eight MFMAs.  One workgroup per CU, two
-// buffers of 64 KB: a k-step of 64 costs one barrier; the next tile is requested before the products of the current one and
-// stored to the other buffer after them, so a round trip to memory hides under 64 MFMAs of each SIMD.
+// buffers of 64 KB: a k-step of 64 costs one barrier.  A tile is requested a whole step (64 MFMAs of each SIMD) before it is
+// stored to the other buffer, and the fragments of each 16 k are requested ahead of the products of the 16 k before them.
 // Products are summed in gemm_kernel's order: results are bit-identical to it.
 #pragma once
 #include "pe_gemm.h"
@@ -29,30 +29,33 @@ struct DeepCfg {
 };
 
 // one operand's part of the staging: a thread moves four 16-byte vectors of a tile
+// (a uniform base and 32-bit byte offsets: with 64-bit addresses per row the kernel spills)
 template <bool KC> struct DeepTile {
-  const bf16* p[KC ? 4 : 1];
-  long long ld;
+  const char* base;
+  unsigned ro[KC ? 4 : 1];
+  unsigned ld;
   int K, c;
   // rows beyond the operand's extent X repeat the last one (their products are not stored)
   PE_DEV void init(const Operand& op, int x0, int X, int K_, int tid) {
+    base = (const char*)op.ptr;
     K = K_;
     if constexpr (KC) {
       c = (tid & 7) * 8;
-      ld = op.x_stride;
+      ld = (unsigned)op.x_stride * 2;
 #pragma unroll
-      for (int i = 0; i < 4; i++) p[i] = (const bf16*)op.ptr + (long long)min(x0 + (tid >> 3) + 64 * i, X - 1) * ld;
+      for (int i = 0; i < 4; i++) ro[i] = (unsigned)min(x0 + (tid >> 3) + 64 * i, X - 1) * ld;
     } else {
       c = tid >> 5;
-      ld = op.k_stride;
-      p[0] = (const bf16*)op.ptr + min(x0 + (tid & 31) * 8, X - 8);
+      ld = (unsigned)op.k_stride * 2;
+      ro[0] = (unsigned)min(x0 + (tid & 31) * 8, X - 8) * 2;
     }
   }
   // k beyond the contraction: an address inside the operand, and zeros
   PE_DEV void load(bf16x8 (&v)[4], int k0) const {
 #pragma unroll
     for (int i = 0; i < 4; i++) {
-      if constexpr (KC) v[i] = *reinterpret_cast<const bf16x8*>(p[i] + min(k0 + c, K - 8));
-      else v[i] = *reinterpret_cast<const bf16x8*>(p[0] + (long long)min(k0 + c + 16 * i, K - 1) * ld);
+      if constexpr (KC) v[i] = *reinterpret_cast<const bf16x8*>(base + (ro[i] + (unsigned)min(k0 + c, K - 8) * 2));
+      else v[i] = *reinterpret_cast<const bf16x8*>(base + (ro[0] + (unsigned)min(k0 + c + 16 * i, K - 1) * ld));
     }
   }
   PE_DEV void store(bf16x8 (&v)[4], bf16* tile, int k0, int tid) const {
@@ -92,45 +95,54 @@ __global__ __launch_bounds__(512, 2) void gemm_deep_kernel(Operand A, Operand B,
   DeepTile<B_KC> tb;
   ta.init(A, m0, sh.M, sh.K, tid);
   tb.init(B, n0, sh.N, sh.K, tid);
-  bf16x8 ra[4], rb[4];
+  bf16x8 ra[4], rb[4], af[2][4], bf[2][2];
+  auto frags = [&](const bf16* la, int kk, bf16x8 (&fa)[4], bf16x8 (&fb)[2]) {
+    const bf16* lb = la + C::TILE;
+#pragma unroll
+    for (int j = 0; j < 2; j++) {
+      if constexpr (B_KC) fb[j] = *reinterpret_cast<const bf16x8*>(lb + C::koff(wn + j * 32 + l32, 2 * kk + g));
+      else fb[j] = C::xfrag(lb, kk * 16, wn + j * 32, l32, g);
+    }
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+      if constexpr (A_KC) fa[i] = *reinterpret_cast<const bf16x8*>(la + C::koff(wm + i * 32 + l32, 2 * kk + g));
+      else fa[i] = C::xfrag(la, kk * 16, wm + i * 32, l32, g);
+    }
+  };
   ta.load(ra, 0);
   tb.load(rb, 0);
   ta.store(ra, lds_all, 0, tid);
   tb.store(rb, lds_all + C::TILE, 0, tid);
-  int buf = 0;
+  ta.load(ra, C::BK);
+  tb.load(rb, C::BK);
+  __syncthreads();
+  frags(lds_all, 0, af[0], bf[0]);
+  bf16* cur = lds_all;
+  bf16* nxt = lds_all + 2 * C::TILE;
   for (int k0 = 0; k0 < sh.K; k0 += C::BK) {
-    __syncthreads();    // this step's tile is stored, and the other buffer's readers are done
-    const bool more = k0 + C::BK < sh.K;
-    if (more) {
-      ta.load(ra, k0 + C::BK);
-      tb.load(rb, k0 + C::BK);
-    }
-    const bf16* la = lds_all + buf * 2 * C::TILE;
-    const bf16* lb = la + C::TILE;
 #pragma unroll
-    for (int kk = 0; kk < C::BK / 16; kk++) {
-      bf16x8 af[4], bf[2];
-#pragma unroll
-      for (int j = 0; j < 2; j++) {
-        if constexpr (B_KC) bf[j] = *reinterpret_cast<const bf16x8*>(lb + C::koff(wn + j * 32 + l32, 2 * kk + g));
-        else bf[j] = C::xfrag(lb, kk * 16, wn + j * 32, l32, g);
+    for (int kk = 0; kk < 4; kk++) {
+      // The fragments of the next 16 k are requested ahead of this quarter's products.  The last quarter's come from the next
+      // tile: every wave has stored its part of that tile and read its last fragments of this one before the barrier.
+      if (kk < 3) frags(cur, kk + 1, af[(kk + 1) & 1], bf[(kk + 1) & 1]);
+      else {
+        __syncthreads();
+        frags(nxt, 0, af[0], bf[0]);
       }
-#pragma unroll
-      for (int i = 0; i < 4; i++) {
-        if constexpr (A_KC) af[i] = *reinterpret_cast<const bf16x8*>(la + C::koff(wm + i * 32 + l32, 2 * kk + g));
-        else af[i] = C::xfrag(la, kk * 16, wm + i * 32, l32, g);
+      if (kk == 1) {      // beyond the contraction: zeros that no product reads
+        ta.store(ra, nxt, k0 + C::BK, tid);
+        tb.store(rb, nxt + C::TILE, k0 + C::BK, tid);
+        ta.load(ra, k0 + 2 * C::BK);
+        tb.load(rb, k0 + 2 * C::BK);
       }
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int i = 0; i < 4; i++)
 #pragma unroll
-        for (int j = 0; j < 2; j++) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[i], bf[j], acc[i][j], 0, 0, 0);
+        for (int j = 0; j < 2; j++) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[kk & 1][i], bf[kk & 1][j], acc[i][j], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
     }
-    buf ^= 1;
-    if (more) {
-      bf16* ls = lds_all + buf * 2 * C::TILE;
-      ta.store(ra, ls, k0 + C::BK, tid);
-      tb.store(rb, ls + C::TILE, k0 + C::BK, tid);
-    }
+    bf16* t = cur; cur = nxt; nxt = t;
   }
   __syncthreads();      // all waves are done with the operand tiles
   constexpr int WS = 68;
@@ -166,14 +178,22 @@ __global__ __launch_bounds__(512, 2) void gemm_deep_kernel(Operand A, Operand B,
   }
 }
 
+// Measured in the block on one stream, gemm_kernel -> this one (us; tiles of 256 x 256, share of the 256 CUs' rounds that they fill):
+// both x-contiguous: 8192 x 8192, K 128 59 -> 61.5, K 256 79 -> 74, K 512 125 -> 104, K 1024 215 -> 154 (890 TFLOP/s), K 2048
+// 405 -> 267; 12288 x 12288, K 170 138 -> 141, K 512 264 -> 214, K 5120 (beside the other branch) 2130 -> 1350 (1140); 3680 x 3680, K 3501
+// (225 tiles, 0.88) 191 -> 109; 5120 x 5120, K 1024 (400 tiles, 0.78) 102 -> 75.  k-contiguous A: 2048 x 8192, K 8192 (256 tiles) 352 ->
+// 256 and (B x-contiguous) 404 -> 243; 1024 x 9600, K 9600 (152 tiles, 0.59) 273 -> 257 and 300 -> 241; 1024 x 8192 (128 tiles, 0.5) 183 ->
+// 214 and 204 -> 203; 512 x 12288 (96 tiles) 262 -> 322 and 293 -> 311.
 static inline bool deep_fits(const Operand& A, bool a_kc, const Operand& B, bool b_kc, const GemmShape& sh) {
   if (sh.batch != 1 || sh.k_chunk > 0 || sh.n_rows != sh.N) return false;
   if (A.x_in < (1 << 30) || A.k_in < (1 << 30) || B.x_in < (1 << 30) || B.k_in < (1 << 30)) return false;
+  if ((long long)sh.M * A.x_stride + (long long)sh.K * A.k_stride >= (1LL << 30) || (long long)sh.N * B.x_stride + (long long)sh.K * B.k_stride >= (1LL << 30))
+    return false;      // byte offsets of 32 bits
   if ((a_kc || b_kc) && sh.K % 8) return false;
   if ((!a_kc && sh.M % 8) || (!b_kc && sh.N % 8)) return false;
-  if (sh.K < 512) return false;
+  if (sh.K < 256) return false;
   const long long tiles = (long long)((sh.M + 255) / 256) * ((sh.N + 255) / 256), rounds = (tiles + 255) / 256;
-  return tiles < (1 << 20) && tiles * 5 >= rounds * 256 * 4;
+  return tiles < (1 << 20) && tiles * 20 >= rounds * 256 * 11;
 }
 template <class Epi>
 static inline bool launch_gemm_deep(hipStream_t st, const Operand& A, bool a_kc, const Operand& B, bool b_kc, const GemmShape& sh, const Epi& epi) {
