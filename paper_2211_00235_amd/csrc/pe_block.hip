@@ -451,49 +451,25 @@ template <typename T> struct Runner {
     }
     return (off + 255) & ~(size_t)255;
   }
-  // Weight preparation of the MSA branch (with the outer product mean's normaliser) and / or of the pair branch, on st; one launch
-  // per PREP_MAX descriptors: the storage-type copies and the fp32 copies of what is prepared go together
-  void run_prep_on(hipStream_t st, bool msa, bool pair) {
-    if (dry || err) return;
-    T* tbase = msa ? prep_tbase_m : prep_tbase_p;
-    float* fbase = msa ? prep_fbase_m : prep_fbase_p;
-    PrepBatch pb;
-    pb.n = 0;
-    double bytes = 0;
-    bool norm = msa;
-    auto flush = [&]() {
-      if (!pb.n && !norm) return;
-      OpmNorm nq;
-      nq.mask = msa_mask; nq.inv_norm = C.opm.inv_norm; nq.s = d.s; nq.r = d.r; nq.eps = d.opm_eps;
-      const int nt = (d.r + 15) / 16, ny = norm ? (nt * nt + 63) / 64 : 0;
-      PE_LAUNCH("prep_params", norm ? 2.0 * Mz * d.s : 0.0, bytes + (norm ? 4.0 * (Mz + Mm) : 0.0), st, prep_params_kernel<T>, dim3(64, pb.n + ny), dim3(256), 0,
-                params, tbase, fbase, pb, nq);
-      pb.n = 0;
-      bytes = 0;
-      norm = false;
-    };
-    auto add = [&](const std::vector<PrepDesc>& v, long long dt, long long df) {
-      for (const PrepDesc& q : v) {
-        PrepDesc& t = pb.d[pb.n++];
-        t = q;
-        t.dst_off += q.ld_r < 0 ? df : dt;
-        bytes += (double)q.rows * q.cols * (4 + (q.ld_r < 0 ? 4 : sizeof(T)));
-        if (pb.n == PREP_MAX) flush();
-      }
-    };
-    auto add_list = [&](const PrepList& l, long long dt, long long df) {
-      add(l.t, dt, df);
-      if (!lean) add(l.tb, dt, df);
-      add(l.f, dt, df);
-    };
-    if (msa) add_list(prep_msa, 0, 0);
-    if (pair) add_list(prep_pair, prep_tbase_p - tbase, prep_fbase_p - fbase);
-    flush();
+  // one launch per PREP_MAX descriptors; the storage-type copies and the fp32 copies of a branch go together
+  void run_prep_list(hipStream_t st, const PrepList& list, T* tbase, float* fbase) {
+    std::vector<PrepDesc> v(list.t);
+    if (!lean) v.insert(v.end(), list.tb.begin(), list.tb.end());
+    v.insert(v.end(), list.f.begin(), list.f.end());
+    for (size_t i = 0; i < v.size(); i += PREP_MAX) {
+      PrepBatch pb;
+      pb.n = (int)std::min((size_t)PREP_MAX, v.size() - i);
+      for (int k = 0; k < pb.n; k++) pb.d[k] = v[i + k];
+      dim3 grid(64, pb.n);
+      double bytes = 0;
+      for (int k = 0; k < pb.n; k++) bytes += (double)pb.d[k].rows * pb.d[k].cols * (4 + (pb.d[k].ld_r < 0 ? 4 : sizeof(T)));
+      PE_LAUNCH("prep_params", 0, bytes, st, prep_params_kernel<T>, grid, dim3(256), 0, params, tbase, fbase, pb);
+    }
   }
-  void run_prep(bool msa, bool pair) {
-    if (msa && pair && sm == sp) { run_prep_on(sm, true, true); return; }
-    if (pair) run_prep_on(sp, false, true);
-    if (msa) run_prep_on(sm, true, false);
+  void run_prep(bool msa_side) {
+    if (dry) return;
+    if (msa_side) run_prep_list(sm, prep_msa, prep_tbase_m, prep_fbase_m);
+    else run_prep_list(sp, prep_pair, prep_tbase_p, prep_fbase_p);
   }
 
   // ---- kernel wrappers -----------------------------------------------------
@@ -1223,7 +1199,7 @@ template <typename T> struct Runner {
   // and the first part of its row attention (fwd_row_pre) on stream_msa
   bool row_pre_done = false;
   void fwd_row_pre() {
-    run_prep(true, false);
+    run_prep(true);
     attn_sub_fwd_pre(sm, PL.row, W.row, C.row, msa_in, Mm, d.c_m, d.h_msa, d.d_msa, geom_row());
   }
   void fwd_msa_step(int i, const T* bias_pair, T* msa_out) {
@@ -1255,6 +1231,10 @@ template <typename T> struct Runner {
       e.rowscale = msa_mask;
       gemm_ln(sm, x, PL.opm.ln_g, PL.opm.ln_b, C.opm.mhat, C.opm.stats, Mm, d.c_m, op_plain(W.opm.wt_ab, d.c_m), 2 * co, e, "opm ab");
     }
+    if (!dry && !err) {
+      PE_LAUNCH("opm_norm", 2.0 * Mz * d.s, 4.0 * (Mz + Mm), sm, opm_norm_kernel, dim3((unsigned)((Mz + 255) / 256)), dim3(256), 0, msa_mask, C.opm.inv_norm,
+                         d.s, r, d.opm_eps);
+    }
     {
       EpiGeneric<T> e = epi_plain<T>(C.opm.O, Wd);
       e.scale2d = C.opm.inv_norm; e.s2_mdiv = co; e.s2_ndiv = co; e.s2_ld = r;
@@ -1264,7 +1244,7 @@ template <typename T> struct Runner {
   // Parallel block, MSA branch: the stack, then the outer product mean of its output up to the
   // projection (which needs the pair branch's result)
   void fwd_msa(T* msa_out) {
-    run_prep(true, false);
+    run_prep(true);
     fwd_msa_stack(pair_in, msa_out);
     fwd_opm_outer(C.m3);
   }
@@ -1282,7 +1262,7 @@ template <typename T> struct Runner {
     gemm(sm, A, true, op_plain(W.opm.wt_o, (long long)co * co), true, (int)Mz, d.c_z, co * co, 1, e, "opm project");
   }
   void fwd_pair() {
-    run_prep(false, true);
+    run_prep(false);
     fwd_pair_stack(pair_in, C.z5);
   }
   void fwd_pair_step(int i, const T* z_in, T* z_out) {
@@ -1859,7 +1839,8 @@ static int run_forward(Runner<T>& R, pe_handle* h, const pe_dims& d, T* msa_out,
   hipStream_t sm = R.sm, sp = R.sp;
   const bool do_m = h->branches & 1, do_p = h->branches & 2;
   if (d.variant == PE_VARIANT_PARALLEL) {
-    R.run_prep(do_m && !R.row_pre_done, do_p);
+    if (do_p) R.run_prep(false);
+    if (do_m && !R.row_pre_done) R.run_prep(true);
     R.fwd_stacks(do_m, do_p, R.pair_in, R.pair_in, msa_out, R.C.z5, true);
     if (early_next && *early_next) { int rc = (*early_next)(); if (rc) return rc; }
     if (do_p && !ev_link(h, 1, sp, sm)) return PE_ERR_HIP;
@@ -1873,7 +1854,8 @@ static int run_forward(Runner<T>& R, pe_handle* h, const pe_dims& d, T* msa_out,
     if (!ev_link(h, 2, sm, sp)) return PE_ERR_HIP;
     return R.err;
   }
-  R.run_prep(true, true);
+  R.run_prep(true);
+  R.run_prep(false);
   T* z_out = pair_out ? pair_out : R.C.z5;
   if (d.variant == PE_VARIANT_AF2) {
     // MSA stack -> outer product mean of its output added to the pair input -> pair stack
@@ -1951,7 +1933,8 @@ static int block_bwd_impl(pe_handle* h, const pe_dims& d, const void* msa_in, co
   // internal one, the forward pass of the same block has just filled it)
   if (ctx == nullptr && !fwd_done) {
     if (d.variant == PE_VARIANT_PARALLEL) {
-      R.run_prep(do_m, do_p);
+      if (do_p) R.run_prep(false);
+      if (do_m) R.run_prep(true);
       R.fwd_stacks(do_m, do_p, R.pair_in, R.pair_in, nullptr, R.C.z5, true);   // the projection is not needed here
     } else {
       int rc = run_forward<T>(R, h, d, nullptr, nullptr);

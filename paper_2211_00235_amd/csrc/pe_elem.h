@@ -879,8 +879,8 @@ template <typename T, int LPR, int HH>
 __global__ __launch_bounds__(256) void ln_bias_fwd_fast_kernel(const T* z, const float* gamma, const float* beta,
                                                                const float* w, float* direct, float direct_scale,
                                                                float* stats, int r, int H, float eps) {
-  // writes direct[h][row] = (LN(z_row) W)_h * direct_scale in row order (coalesced); bias_tile_kernel makes the tiled copies from it
-  // (written from here, element by element, they cost more than that launch: 3.9 + 3.4 -> 8.3 us at r 48, 8.8 + 4.2 -> 17.6 at r 97)
+  // writes direct[h][row] = (LN(z_row) W)_h * direct_scale in row order (coalesced); the other
+  // orientation is produced by bias_transpose_kernel
   constexpr int C = 8 * LPR, RPW = 64 / LPR;
   __shared__ float sw[LPR][8 * HH + 4];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -1258,42 +1258,11 @@ __global__ __launch_bounds__(256) void reduce_partials_kernel(ReduceBatch rb) {
 struct PrepDesc { long long src_off, dst_off; int rows, cols; long long ld_r, ld_c; float scale; int c_blk, c_blk_to; };
 constexpr int PREP_MAX = 64;   // descriptors per launch (3 KB of kernel arguments)
 struct PrepBatch { PrepDesc d[PREP_MAX]; int n; };
-// The outer product mean's normaliser, inv_norm[i][j] = 1 / (eps + sum_t mask[t][i] mask[t][j]), depends on the mask alone and rides on
-// the weight preparation (the grid's rows from pb.n on).  A workgroup takes 16 x 16 entries; 256 rows of the mask are loaded
-// at once (one round trip) and summed from LDS in the order of t.  As a launch of its own, a thread per entry walking through
-// s in steps of 32: 7.4 us at s 128, r 256, 26 at s 512, r 384, 237 at s 5120, r 384.
-struct OpmNorm { const float* mask; float* inv_norm; int s, r; float eps; };
-PE_DEV void opm_norm_tiles(const OpmNorm& q, float (*ms)[32], int blk, int nblk) {
-  const int nt = (q.r + 15) / 16, ii = threadIdx.x >> 4, jj = threadIdx.x & 15;
-  for (int t16 = blk; t16 < nt * nt; t16 += nblk) {
-    const int i0 = (t16 / nt) * 16, j0 = (t16 % nt) * 16;
-    float acc = 0.0f;
-    for (int t0 = 0; t0 < q.s; t0 += 256) {
-      __syncthreads();
-#pragma unroll
-      for (int u = 0; u < 32; u++) {     // row ii + 16 (u / 2) of the 256; column jj of i0 .. (even u) or j0 .. (odd u)
-        const int t = t0 + ii + 16 * (u >> 1), c = ((u & 1) ? j0 : i0) + jj;
-        const bool in = t < q.s && c < q.r;
-        const float v = q.mask[in ? (long long)t * q.r + c : 0];
-        ms[ii + 16 * (u >> 1)][(u & 1) * 16 + jj] = in ? v : 0.0f;
-      }
-      __syncthreads();
-      const int n = min(256, q.s - t0);
-      for (int t = 0; t < n; t++) acc += ms[t][ii] * ms[t][16 + jj];
-    }
-    if (i0 + ii < q.r && j0 + jj < q.r) q.inv_norm[(long long)(i0 + ii) * q.r + j0 + jj] = 1.0f / (q.eps + acc);
-  }
-}
 template <typename T>
-__global__ __launch_bounds__(256) void prep_params_kernel(const float* params, T* dst, float* fdst, PrepBatch pb, OpmNorm nq) {
+__global__ __launch_bounds__(256) void prep_params_kernel(const float* params, T* dst, float* fdst, PrepBatch pb) {
   // 32 x 32 tiles; a transposed destination (ld_r == 1) goes through LDS so that reads and
   // writes both run along the contiguous index
-  __shared__ float lds[256 * 32];
-  if ((int)blockIdx.y >= pb.n) {      // uniform over the workgroup
-    opm_norm_tiles(nq, reinterpret_cast<float (*)[32]>(lds), ((int)blockIdx.y - pb.n) * gridDim.x + blockIdx.x, ((int)gridDim.y - pb.n) * gridDim.x);
-    return;
-  }
-  float (*tile)[33] = reinterpret_cast<float (*)[33]>(lds);
+  __shared__ float tile[32][33];
   const PrepDesc& d = pb.d[blockIdx.y];
   if (d.ld_r < 0) {   // fp32 copy (biases that a GEMM epilogue reads as one vector)
     for (int c = blockIdx.x * 256 + threadIdx.x; c < d.cols; c += gridDim.x * 256) fdst[d.dst_off + c] = params[d.src_off + c];
@@ -1456,6 +1425,25 @@ __global__ __launch_bounds__(256) void add2x8_kernel(const T* a, const T* b, T* 
 #pragma unroll
   for (int e = 0; e < 8; e++) x[e] += y[e];
   st8<T>(out + idx, x);
+}
+// ---------------------------------------------------------------------------
+// Outer product mean normaliser: inv_norm[i][j] = 1 / (eps + sum_s mask[s][i] mask[s][j])
+// ---------------------------------------------------------------------------
+__global__ void opm_norm_kernel(const float* mask, float* inv_norm, int s, int r, float eps) {
+  long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+  if (idx >= (long long)r * r) return;
+  int i = idx / r, j = idx % r;
+  float acc = 0.0f;   // 0/1 products: any summation order gives the same (exact) count
+  int t = 0;
+  for (; t + 32 <= s; t += 32) {   // 64 independent loads in flight per thread: the loop is a chain of memory round trips
+    float a[32], b[32];
+#pragma unroll
+    for (int u = 0; u < 32; u++) { a[u] = mask[(long long)(t + u) * r + i]; b[u] = mask[(long long)(t + u) * r + j]; }
+#pragma unroll
+    for (int u = 0; u < 32; u++) acc += a[u] * b[u];
+  }
+  for (; t < s; t++) acc += mask[(long long)t * r + i] * mask[(long long)t * r + j];
+  inv_norm[idx] = 1.0f / (eps + acc);
 }
 
 // zero n 16-byte words (buffers are 256-byte multiples)
