@@ -682,7 +682,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
       dof[kk] = gl_frag<T>(dorow, kk, g, d);
     }
   const long long sidx = ((long long)b * a.H + h) * L + qi;
-  const f32x16 negl = splat16(qok ? -a.lse[sidx] * PE_LOG2E : 0.0f), negD = splat16(qok ? -a.D[sidx] : 0.0f);
+  const float lse2 = qok ? a.lse[sidx] * PE_LOG2E : 0.0f;
+  const float Di = qok ? a.D[sidx] : 0.0f;
   constexpr bool has_bias = HAS_BIAS;
   const T* bplane = has_bias ? (const T*)a.biasQ + (long long)h * attn_tiles32(L) * L * 32 : nullptr;
   const int bcolq = min(qi, L - 1);
@@ -712,7 +713,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
       if (has_bias) attn_load_bias(bplane, L, kt0 >> 5, bcolq, g, bt);
       const int masked = __builtin_amdgcn_readfirstlane(lds_flag[jt]);
       const int off0 = (jt * 32 + l32) * C::RM + g * MM::KP;
-      f32x16 sacc = TR ? negl : splat16(0.0f), pacc = TR ? negD : splat16(0.0f);     // bf16: S - lse, dP - D from the matrix unit
+      f32x16 sacc = splat16(0.0f), pacc = splat16(0.0f);
 #pragma unroll
       for (int kk = 0; kk < MAXKK; kk++)
         if (kk < NKK) {
@@ -722,7 +723,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
       if (has_bias) attn_add_bias(sacc, bt, idf);
       if (masked) attn_add_row_mask(sacc, lds_madd + jt * 32, g);
 #pragma unroll
-      for (int e = 0; e < 16; e++) sacc[e] = TR ? fast_exp2(sacc[e]) * pacc[e] : fast_exp2(sacc[e] + negl[e]) * (pacc[e] + negD[e]);     // dS = P (dP - D)
+      for (int e = 0; e < 16; e++) sacc[e] = fast_exp2(sacc[e] - lse2) * (pacc[e] - Di);     // dS = P (dP - D)
       if (dsplane && qok) {
         float v16[16];
 #pragma unroll

@@ -580,6 +580,44 @@ def test_attention_logits_far_below_zero():
     assert rel_err(to_np(run.msa_out), m) < TOL[0] and rel_err(to_np(run.pair_out), z) < TOL[0]
 
 
+def _entry(inp, table, name):
+    """View of one parameter in inp["params"]."""
+    e = next(e for e in table if e["name"] == name)
+    return inp["params"][e["offset"]:e["offset"] + int(np.prod(e["shape"]))].reshape(e["shape"])
+
+
+@pytest.mark.parametrize("h_msa,d_msa,s,r,dtype", [(2, 32, 37, 150, 1), (4, 16, 21, 65, 1), (2, 32, 13, 70, 0)])
+def test_attention_without_a_bias_is_one_with_a_zero_bias(h_msa, d_msa, s, r, dtype):
+    """The column attention of a transposed MSA against the row attention with a bias of zero: forward and backward go through
+    the kernels without and with a bias, which do the same arithmetic, so outputs and cotangents are the same bits (adding an
+    exact zero to a logit changes nothing).  The other sub-operations pass the MSA through: their output weights are zero."""
+    over = dict(c_m=64, h_msa=h_msa, d_msa=d_msa)
+    dims, table, inp = _case("tiny", dtype=dtype, s=s, r=r, **over)
+    table, n = param_table(dims)
+    inp = make_inputs(dims, table, n, ("random_residues", 0.1), 67)
+    for name in ("row.w_bias", "row.b_o", "col.b_o", "mtrans.w2", "mtrans.b2", "opm.w_o"):
+        _entry(inp, table, name)[...] = 0.0
+    tdims, ttable, tinp = _case("tiny", dtype=dtype, s=r, r=s, **over)
+    tinp["params"] = inp["params"].copy()
+    for k in ("msa", "d_msa_out"):
+        tinp[k] = np.ascontiguousarray(inp[k].transpose(1, 0, 2))
+    tinp["msa_mask"] = np.ascontiguousarray(inp["msa_mask"].T)
+    for a, b in (("row.ln_m.g", "col.ln.g"), ("row.ln_m.b", "col.ln.b")) + tuple(("row." + w, "col." + w) for w in ("w_q", "w_k", "w_v", "w_g", "b_g", "w_o")):
+        _entry(tinp, ttable, b)[...] = _entry(inp, table, a)
+    _entry(inp, table, "col.w_o")[...] = 0.0
+    _entry(tinp, ttable, "row.w_o")[...] = 0.0
+    row, col = BlockRun(dims, inp), BlockRun(tdims, tinp)
+    for run in (row, col):
+        run.fwd()
+        run.bwd()
+        run.sync()
+    for k in ("msa_out", "d_msa_in"):
+        a, b = to_np(getattr(row, k)), to_np(getattr(col, k)).transpose(1, 0, 2)
+        assert np.array_equal(a, b), (k, rel_err(a, b))
+    base = inp["msa"] if dtype == 1 else inp["msa"].astype(np.float32)
+    assert rel_err(to_np(row.msa_out), base) > 1e-2      # the attention does take part
+
+
 @pytest.mark.parametrize("h_msa,d_msa,s,r,dtype", [(4, 32, 257, 33, 1), (2, 24, 65, 65, 1), (4, 16, 97, 31, 1), (4, 8, 31, 34, 1), (4, 32, 290, 7, 0)])
 def test_attention_tiles_and_head_dimensions(h_msa, d_msa, s, r, dtype):
     """Head dimensions of one and two contraction steps, one key more than a staged chunk, a ragged last tile, an odd last batch row."""
