@@ -184,6 +184,11 @@ __global__ __launch_bounds__(512, 2) void gemm_deep_kernel(Operand A, Operand B,
 // (225 tiles, 0.88) 191 -> 109; 5120 x 5120, K 1024 (400 tiles, 0.78) 102 -> 75.  k-contiguous A: 2048 x 8192, K 8192 (256 tiles) 352 ->
 // 256 and (B x-contiguous) 404 -> 243; 1024 x 9600, K 9600 (152 tiles, 0.59) 273 -> 257 and 300 -> 241; 1024 x 8192 (128 tiles, 0.5) 183 ->
 // 214 and 204 -> 203; 512 x 12288 (96 tiles) 262 -> 322 and 293 -> 311.
+// The share counts outputs, not tiles: in a tile wider than the output most products are of repeated rows (N 64, K 256, the input
+// cotangent of a transition over 64 channels, gemm64_kernel -> this one: M 44000 10.5 -> 17.2, 262144 33 -> 60, 1966080 232 -> 432), so an
+// output narrower than a tile is never taken.
+// Beside another branch's kernels the same line holds (whole calls without -> with this kernel there: s 512, r 384 forward 2416 ->
+// 2377, step 8624 -> 8542; s 400, r 256 forward 1172 -> 1155; extra-MSA forward at s 1024, r 256 1065 -> 1021).
 static inline bool deep_fits(const Operand& A, bool a_kc, const Operand& B, bool b_kc, const GemmShape& sh) {
   if (sh.batch != 1 || sh.k_chunk > 0 || sh.n_rows != sh.N) return false;
   if (A.x_in < (1 << 30) || A.k_in < (1 << 30) || B.x_in < (1 << 30) || B.k_in < (1 << 30)) return false;
@@ -191,9 +196,9 @@ static inline bool deep_fits(const Operand& A, bool a_kc, const Operand& B, bool
     return false;      // byte offsets of 32 bits
   if ((a_kc || b_kc) && sh.K % 8) return false;
   if ((!a_kc && sh.M % 8) || (!b_kc && sh.N % 8)) return false;
-  if (sh.K < 256) return false;
+  if (sh.K < 256 || sh.M < DeepCfg::BM || sh.N < DeepCfg::BM) return false;
   const long long tiles = (long long)((sh.M + 255) / 256) * ((sh.N + 255) / 256), rounds = (tiles + 255) / 256;
-  return tiles < (1 << 20) && tiles * 20 >= rounds * 256 * 11;
+  return tiles < (1 << 20) && (long long)sh.M * sh.N * 20 >= rounds * 256 * 11 * (DeepCfg::BM * DeepCfg::BM);
 }
 template <class Epi>
 static inline bool launch_gemm_deep(hipStream_t st, const Operand& A, bool a_kc, const Operand& B, bool b_kc, const GemmShape& sh, const Epi& epi) {

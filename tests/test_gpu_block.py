@@ -684,6 +684,30 @@ def test_outer_product_over_many_rows():
     _assert(errs, worst, tol, stats)
 
 
+def _kernels_by_label(run, branches=3, backward=True):
+    """Label -> the kernels that its launches take, of a forward (and backward) pass of the given branches."""
+    run.h.set_option(1, branches)      # PE_OPT_BRANCHES
+    run.h.set_option(3, 1)             # PE_OPT_KERNEL_TIMING
+    run.fwd(use_ctx=backward)
+    if backward:
+        run.bwd()
+    run.sync()
+    out = {}
+    for e in run.h.timing_collect():
+        out.setdefault(e["name"], set()).add(e["kernel"])
+    return out
+
+
+def test_narrow_outputs_keep_their_tiles():
+    """A transition over 64 channels: the cotangent of its input has 64 columns and a contraction over 256, which 256 x 256 tiles would
+    fill to a quarter (36096 rows are 141 of them, as many as their rule asks for); it stays on the 64-row tiles, while
+    the outer product of the same block (3072 x 3072) is on the large ones."""
+    dims, table, inp = _case("extra_msa", s=376, r=96)
+    names = _kernels_by_label(BlockRun(dims, inp, two_streams=False), branches=1)
+    assert names["trans dxhat"] == {"gemm64_kernel<EpiGeneric,F=0>"}, names["trans dxhat"]
+    assert names["opm outer"] == {"gemm_deep_kernel<xc,xc>"}, names["opm outer"]
+
+
 @pytest.mark.slow
 def test_extra_msa_bf16():
     """Config 3: extra-MSA-stack block (s=1024, r=256, c_m=64, global column attention), bf16."""
