@@ -198,24 +198,49 @@ __global__ __launch_bounds__(512, KS <= 8 ? 4 : 2) void gemm_rows_kernel(Operand
   }
 }
 
-// Operands and sizes the kernel takes (the epilogue is checked by the launcher).  Measured alone on the chip, gemm_kernel or
-// gemm64_kernel -> this one (us), head-major output unless stated: K = 256, N = 1024: M 8192 12.3 -> 13.2, 12416 18.3 -> 14.4,
-// 32768 31 -> 23, 196608 210 -> 126 (4.0 TB/s), ReLU bits on the way in, M 32768: 33.6 -> 23.8; K = 128, N = 512: M 1089
-// 6.5 -> 5.5, 9409 8.6 -> 6.7, 65536 22.3 -> 16.1 (5.2 TB/s), 147456 61 -> 42, ReLU bits, M 65536: 26.2 -> 17.7; K = 128, N = 1024,
-// M 65536: 58 -> 49; K = 128, N = 128, M 65536: 9.0 -> 8.4; K = 64, N = 256: M 32768 8.1 -> 8.4, 262144 43 -> 34, 1966080 290 -> 243.
+// Operands the kernel takes (the epilogue is checked by the launcher).
 // Beside another branch's kernels (sh.beside) the waves and the LDS it keeps are room that the other stream's workgroups would
-// have filled: K >= 128 pays there only where the launch is long (s 128, r 256, two streams: step 2338 -> 2390 us with all of
-// them; s 512, r 384, forward: 2915 -> 2675), so outputs of more than 2^26 elements.
-// At K = 256 the first block waits for a panel of 128 KB: the row blocks of all panels have to fill more than half of the 2048
-// wave slots.  Epilogues that read a tensor of the output's size gain nothing (N = K = 256 with a residual, M 196608: 63.6 ->
-// 67.4), nor do outputs of 64 columns (M 262144, K 256: 39.6 -> 41.8): not taken.
+// have filled: K >= 128 pays there only where the launch is long, so outputs of more than 2^26 elements.  Whole calls, none -> these:
+// s 512, r 384 step 8868 -> 8542 us, forward 2627 -> 2377; s 400, r 200 step 3347 -> 3265; s 400, r 256 4364 -> 4207.  (From 2^25: s 256, r 256
+// 3227 -> 3138, but s 128, r 256, of which every GEMM is below, 2338 -> 2390 with all of them.)  K = 64 pays beside as it does alone: extra-MSA
+// step at s 1024, r 256 3379 -> 3344, s 2000, r 70 1467 -> 1449.
+// Epilogues that read a tensor of the output's size gain nothing (N = K = 256 with a residual, M 196608: 63.6 -> 67.4), nor do outputs
+// of 64 columns (M 262144, K 256: 39.6 -> 41.8): not taken.
 static inline bool rows_operands_ok(const Operand& A, const Operand& B, const GemmShape& sh) {
   if (sh.batch != 1 || sh.k_chunk > 0 || sh.n_rows != sh.N) return false;
   if (sh.K != 64 && sh.K != 128 && sh.K != 256) return false;
   if (sh.N % 128 || B.x_in < (1 << 30) || B.k_in < (1 << 30) || B.x_stride < sh.K) return false;
   if (A.k_in < (1 << 30) && A.k_in != 8 && A.k_in % 32) return false;
   if (sh.beside && sh.K >= 128 && (long long)sh.M * sh.N <= (1LL << 26)) return false;
-  if (sh.K == 256 && (sh.N % 256 || (sh.M + 31) / 32 * (long long)(sh.N / 256) < 1280)) return false;
+  return sh.K != 256 || sh.N % 256 == 0;
+}
+// Launches alone on the chip, gemm_kernel or gemm64_kernel -> this one (us; plain = head-major projections, act = activation, mask = decisions
+// on the way in): K 256, N 1024: plain M 12800 22.6 -> 17.6, 32768 34 -> 28, 196608 232 -> 142 (4.0 TB/s), act 12800 25.0 -> 19.9, 32768 38 -> 34,
+// mask 10240 18.4 -> 17.8, 32768 45 -> 31.  K 128, N 512: plain M 2304 9.5 -> 8.6, 65536 28 -> 21, act 2304 10.7 -> 10.2, 33124 23.6 -> 18.1, mask 65536
+// 34 -> 24; N 1024: M 1024 10.6 -> 9.3, 65536 44 -> 32; N 128: plain M 65536 12.0 -> 10.9, 147456 18.5 -> 18.8.  K 64, N 256: plain M 24000 10.8 -> 10.2,
+// 65536 17.5 -> 13.2, 1966080 310 -> 250, act 51200 18.4 -> 15.3, 262144 49 -> 45, 1966080 354 -> 361 (without decisions 355 -> 329), mask 51200
+// 18.1 -> 13.8, 1966080 432 -> 312.
+// At K = 256 the first block waits for a panel of 128 KB: the row blocks of all panels have to fill more than half of the 2048 wave slots.
+// An activation on the way out lengthens a wave's life, and the kernel loses where the one it replaces needs a single round of workgroups
+// (768 of gemm_kernel are resident at once, as many of gemm64_kernel), or where its own waves need a second round that they hardly fill:
+//   K 64, panels of 256 columns, up to 768 tiles of 128 x 128: M 8192 9.9 -> 12.3, 32768 11.7 -> 14.0, 44800 13.3 -> 13.9 (whole forward passes 269.5 -> 272.0,
+//     359 -> 361.5, 408.7 -> 409.0); above: 51200 18.4 -> 15.3
+//   K 256, up to 768 tiles: N 1024 M 10240 18.0 -> 20.4, 12288 19.1 -> 20.4 (forward 313.5 -> 315.2, 319.0 -> 320.5); N 2048 M 5120 18.9 -> 20.1
+//   K 256, 2049 to 2560 waves: N 1024 M 18432 28.4 -> 31.4 (forward 385 -> 390), 20480 29.2 -> 31.2 (398 -> 401), 21120 (2640 waves) forward 413 -> 410; N 512
+//     M 34560 27.5 -> 31.7
+//   N 128 on gemm64_kernel (M from 32768), up to 768 of its 64-row tiles: K 128 M 33856 10.6 -> 11.2, 40000 11.2 -> 11.7 (forward 476.9 -> 480.9, 507.0 ->
+//     510.3); K 64 M 32768 8.6 -> 10.2; above: K 128 M 50176 12.5 -> 12.2
+// Plain outputs and masks were neutral or better in whole calls on both sides of these lines (within 0.2 %).
+static inline bool rows_pays(const GemmShape& sh, int features) {
+  const bool act = features & EF_ACT;
+  const int M = sh.M;
+  const long long tiles = (long long)((M + 127) / 128) * (sh.N / 128);      // gemm_kernel's workgroups
+  if (act && sh.K == 64 && sh.N % 256 == 0 && tiles <= 768) return false;
+  if (act && sh.N == 128 && M >= 128 * 256 && M <= 768 * 64) return false;
+  if (sh.K == 256) {
+    const long long waves = (long long)((M + 31) / 32) * (sh.N / 256);
+    if (waves < 1280 || (act && (tiles <= 768 || (waves > 2048 && waves <= 2560)))) return false;
+  }
   return true;
 }
 // NP: panel width in 32-column blocks.  K = 256: 128 KB of LDS, one workgroup per CU; else at most 50 KB and at most 128 registers,
@@ -230,7 +255,7 @@ static inline void launch_rows_np(hipStream_t st, const Operand& A, const Operan
 }
 template <int F>
 static inline bool launch_rows_f(hipStream_t st, const Operand& A, const Operand& B, const GemmShape& sh, const EpiGeneric<bf16>& epi) {
-  if (!RowsGeneric<F>::ok(epi, sh.N)) return false;
+  if (!RowsGeneric<F>::ok(epi, sh.N) || !rows_pays(sh, epi.features())) return false;
   if (sh.K == 256) launch_rows_np<F, 16, 8>(st, A, B, sh, epi);
   else if (sh.K == 128) launch_rows_np<F, 8, 4>(st, A, B, sh, epi);
   else if (sh.N % 256 == 0) launch_rows_np<F, 4, 8>(st, A, B, sh, epi);

@@ -708,6 +708,29 @@ def test_narrow_outputs_keep_their_tiles():
     assert names["opm outer"] == {"gemm_deep_kernel<xc,xc>"}, names["opm outer"]
 
 
+@pytest.mark.parametrize("name,s,r,branch,taken", [
+    ("extra_msa", 768, 64, 1, {"attn qkvg": 1, "trans 1": 0, "trans dh": 1}),      # K = 64, N = 256: 768 tiles of 128 x 128
+    ("extra_msa", 769, 64, 1, {"attn qkvg": 1, "trans 1": 1, "trans dh": 1}),      # 770
+    ("af2_initial", 159, 64, 1, {"attn qkvg": 0, "trans 1": 0, "trans dh": 0}),    # K = 256, N = 1024: 1272 waves
+    ("af2_initial", 192, 64, 1, {"attn qkvg": 1, "trans 1": 0, "trans dh": 1}),    # 768 tiles
+    ("af2_initial", 193, 64, 1, {"attn qkvg": 1, "trans 1": 1, "trans dh": 1}),    # 776
+    ("af2_initial", 256, 64, 1, {"attn qkvg": 1, "trans 1": 1, "trans dh": 1}),    # 2048 waves
+    ("af2_initial", 257, 64, 1, {"attn qkvg": 1, "trans 1": 0, "trans dh": 1}),    # 2056
+    ("af2_initial", 320, 64, 1, {"attn qkvg": 1, "trans 1": 0, "trans dh": 1}),    # 2560
+    ("af2_initial", 321, 64, 1, {"attn qkvg": 1, "trans 1": 1, "trans dh": 1}),    # 2568
+    ("af2_initial", 8, 181, 2, {"trimul gate": 1, "trimul dxhat_o": 1}),           # K = 128, N = 128: 32761 rows
+    ("af2_initial", 8, 182, 2, {"trimul gate": 0, "trimul dxhat_o": 1}),           # 33124, gemm64_kernel
+    ("af2_initial", 8, 221, 2, {"trimul gate": 0, "trimul dxhat_o": 1}),           # 48841: 764 of its workgroups
+    ("af2_initial", 8, 222, 2, {"trimul gate": 1, "trimul dxhat_o": 1}),           # 771
+])
+def test_row_streaming_gemms_where_they_pay(name, s, r, branch, taken):
+    """Which GEMMs of one branch go to the row-streaming kernel on either side of each line of its rule (rows_pays), alone on the chip."""
+    dims, table, inp = _case(name, s=s, r=r)
+    names = _kernels_by_label(BlockRun(dims, inp, two_streams=False), branches=branch)
+    got = {k: int(all(n.startswith("gemm_rows_kernel") for n in names[k])) for k in taken}
+    assert got == taken, {k: names[k] for k in taken}
+
+
 @pytest.mark.slow
 def test_extra_msa_bf16():
     """Config 3: extra-MSA-stack block (s=1024, r=256, c_m=64, global column attention), bf16."""
