@@ -62,7 +62,7 @@ int main(int argc, char** argv) {
   timeit("attn_fwd<bias>", reps, 6.0 * H * plane * e, 4.0 * ll * d, [&] { launch_attn_fwd<T>(0, a); });
   timeit("attn_fwd<nobias>", reps, 6.0 * H * plane * e, 4.0 * ll * d, [&] { AttnArgs an = a; an.biasQ = an.biasK = nullptr; launch_attn_fwd<T>(0, an); });
   timeit("attn_bwd_dq2", reps, 5.0 * H * plane * e + ll, 6.0 * ll * d, [&] { launch_attn_bwd_dq<T>(0, a); });
-  AttnArgs a0 = a; a0.dS = nullptr; a0.biasQ = a0.biasK = nullptr;   // the unbiased kernel would write one dS plane per batch row: the buffer holds half of them
+  AttnArgs a0 = a; a0.biasQ = a0.biasK = nullptr;
   timeit("attn_bwd_dq<nobias>", reps, 5.0 * H * plane * e, 6.0 * ll * d, [&] { launch_attn_bwd_dq<T>(0, a0); });
   timeit("attn_bwd_dkv<bias>", reps, 6.0 * H * plane * e, 8.0 * ll * d, [&] { launch_attn_bwd_dkv<T>(0, a); });
   timeit("attn_bwd_dkv<nobias>", reps, 6.0 * H * plane * e, 8.0 * ll * d, [&] { launch_attn_bwd_dkv<T>(0, a0); });

@@ -247,23 +247,10 @@ PE_DEV f32x16 splat16(float v) {
 // Bias values of one 32x32 tile for the lane that owns position `col` (clamped to L-1 by the caller) of the lane axis,
 // from the chunk-ordered plane of its head (bias_tile_kernel).  bf16: chunk c of lane group g holds positions
 // 16 c + 8 g + 0..7 of the other axis, i.e. the B operand of MFMA step c; fp32: accumulator order.  16-byte loads; a half
-// wave's 32 lanes read 512 contiguous bytes per load.
+// wave's 32 lanes read 512 contiguous bytes per load.  p: the lane's own address of chunk 0; chunks are 2 L lanes apart.
 template <typename T> struct BiasTile;
 template <> struct BiasTile<bf16> { bf16x8 v[2]; };
 template <> struct BiasTile<float> { float v[16]; };
-PE_DEV void attn_load_bias(const bf16* plane, int L, int tile, int col, int g, BiasTile<bf16>& b) {
-#pragma unroll
-  for (int c = 0; c < 2; c++) b.v[c] = *reinterpret_cast<const bf16x8*>(plane + bias_chunk_off<bf16>(tile, c, g, col, L));
-}
-PE_DEV void attn_load_bias(const float* plane, int L, int tile, int col, int g, BiasTile<float>& b) {
-#pragma unroll
-  for (int c = 0; c < 4; c++) {
-    const f32x4 v = *reinterpret_cast<const f32x4*>(plane + bias_chunk_off<float>(tile, c, g, col, L));
-#pragma unroll
-    for (int r = 0; r < 4; r++) b.v[c * 4 + r] = v[r];
-  }
-}
-// the same from the lane's own address of chunk 0: chunks are 2 L lanes apart
 PE_DEV void attn_load_bias_at(const bf16* p, int L, BiasTile<bf16>& b) {
 #pragma unroll
   for (int c = 0; c < 2; c++) b.v[c] = *reinterpret_cast<const bf16x8*>(p + (long long)c * 2 * L * BiasChunk<bf16>::CH);
@@ -332,9 +319,6 @@ template <> PE_DEV void attn_store_tile16_at<bf16>(bf16* p, int L, const float (
     for (int r = 0; r < 8; r++) o[r] = (bf16)v[c * 8 + r];
     __builtin_nontemporal_store(o, reinterpret_cast<bf16x8*>(p + (long long)c * 2 * L * BiasChunk<bf16>::CH));
   }
-}
-template <typename T> PE_DEV void attn_store_tile16(T* plane, int L, int tile, int col, int g, const float (&v)[16]) {
-  attn_store_tile16_at<T>(plane + bias_chunk_off<T>(tile, 0, g, col, L), L, v);
 }
 // number of 32-position tiles of an axis of length L
 PE_DEV int attn_tiles32(int L) { return (L + 31) >> 5; }
@@ -643,11 +627,11 @@ __global__ __launch_bounds__(256) void attn_bwd_pre_kernel(AttnArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// Backward, dQ (+ dS for the bias gradient).  Same tiling as the forward kernel.
+// Backward, dQ of an attention without a bias (one with a bias: attn_bwd_dq2_kernel).  Same tiling as the forward kernel.
 // ---------------------------------------------------------------------------
 // Capped at 128 registers (4 waves per SIMD instead of 3 at the 138 the compiler would take; three
 // dwords spill): measured 85 -> 77 us per biased attention at L = 256.
-template <typename T, bool HAS_BIAS, int NK = 0>
+template <typename T, int NK = 0>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) void attn_bwd_dq_kernel(AttnArgs a) {
   typedef AttnCfg<T> C;
   typedef Mma<T> MM;
@@ -684,13 +668,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
   const long long sidx = ((long long)b * a.H + h) * L + qi;
   const float lse2 = qok ? a.lse[sidx] * PE_LOG2E : 0.0f;
   const float Di = qok ? a.D[sidx] : 0.0f;
-  constexpr bool has_bias = HAS_BIAS;
-  const T* bplane = has_bias ? (const T*)a.biasQ + (long long)h * attn_tiles32(L) * L * 32 : nullptr;
-  const int bcolq = min(qi, L - 1);
-  // dS plane of this (b, h) in the layout of biasQ
-  T* dsplane = a.dS ? (T*)a.dS + ((long long)b * a.H + h) * attn_tiles32(L) * L * 32 : nullptr;
-  IdFrag<T> idf;
-  idf.init(l32, g);
 
   f32x16 dq;
 #pragma unroll
@@ -707,10 +684,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
     __syncthreads();
 #pragma unroll
     for (int jt = 0; jt < C::KT / 32; jt++) {
-      const int kt0 = j0 + jt * 32;
-      if (kt0 >= L) break;
-      BiasTile<T> bt;
-      if (has_bias) attn_load_bias(bplane, L, kt0 >> 5, bcolq, g, bt);
+      if (j0 + jt * 32 >= L) break;
       const int masked = __builtin_amdgcn_readfirstlane(lds_flag[jt]);
       const int off0 = (jt * 32 + l32) * C::RM + g * MM::KP;
       f32x16 sacc = splat16(0.0f), pacc = splat16(0.0f);
@@ -720,16 +694,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
           MM::mma(sacc, MM::load(lds_k + off0 + kk * MM::KSTEP), qf[kk]);      // S^T = K Q^T
           MM::mma(pacc, MM::load(lds_v + off0 + kk * MM::KSTEP), dof[kk]);     // dP^T = V dO^T
         }
-      if (has_bias) attn_add_bias(sacc, bt, idf);
       if (masked) attn_add_row_mask(sacc, lds_madd + jt * 32, g);
 #pragma unroll
       for (int e = 0; e < 16; e++) sacc[e] = fast_exp2(sacc[e] - lse2) * (pacc[e] - Di);     // dS = P (dP - D)
-      if (dsplane && qok) {
-        float v16[16];
-#pragma unroll
-        for (int e = 0; e < 16; e++) v16[e] = sacc[e];
-        attn_store_tile16<T>(dsplane, L, kt0 >> 5, qi, g, v16);
-      }
       if constexpr (TR) {
 #pragma unroll
         for (int u = 0; u < 2; u++) MM::mma(dq, lds_rfrag<C::RM>(lds_k, jt * 32 + 16 * u, l32, g), acc_to_frag<T>(sacc, u));
@@ -1020,7 +987,7 @@ static inline void launch_attn_bwd_dq(hipStream_t st, const AttnArgs& a) {
 #define PE_ATTN_DQ(NK)                                                                             \
   do {                                                                                             \
     if (a.biasQ) hipLaunchKernelGGL((attn_bwd_dq2_kernel<T, NK>), grid, dim3(512), 0, st, a);      \
-    else hipLaunchKernelGGL((attn_bwd_dq_kernel<T, false, NK>), grid, dim3(256), 0, st, a);        \
+    else hipLaunchKernelGGL((attn_bwd_dq_kernel<T, NK>), grid, dim3(256), 0, st, a);        \
   } while (0)
   if constexpr (sizeof(T) == 2) {
     if (a.d <= 16) PE_ATTN_DQ(1); else PE_ATTN_DQ(2);
@@ -1128,7 +1095,7 @@ __global__ __launch_bounds__(AttnWalk::THREADS) void attn_bwd_walk_kernel(AttnAr
       if (isk) mk = a.mask[(long long)(b) * a.mask_bs + (long long)(k0 + krow) * a.mask_ks];                         \
     }                                                                                                                \
   } while (0)
-// bias of query tile qt (uniform), as attn_load_bias
+// bias of query tile qt (uniform), as attn_load_bias_at
 #define PE_WALK_BIAS(qt)                                                                                             \
   do {                                                                                                               \
     const bf16* tp = bplane + (long long)(qt) * L * 32;                                                              \

@@ -1395,7 +1395,7 @@ template <typename T> struct Runner {
         const long long Bds = c.bias ? (gm.B + 1) / 2 : gm.B;
         prof_begin(st);
         launch_attn_bwd_dq<T>(st, a);
-        prof_end(st, gm.l_dq, c.bias ? "(attn_bwd_dq2_kernel<T>)" : "(attn_bwd_dq_kernel<T, false>)", 6.0 * gm.B * H * gm.L * gm.L * dh,
+        prof_end(st, gm.l_dq, c.bias ? "(attn_bwd_dq2_kernel<T>)" : "(attn_bwd_dq_kernel<T>)", 6.0 * gm.B * H * gm.L * gm.L * dh,
                  5.0 * M * HD * sizeof(T) + (c.bias ? 1.0 * Bds * H * gm.L * gm.L * sizeof(T) : 0.0));
         check(gm.l_dq);
         prof_begin(st);
