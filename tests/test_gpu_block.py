@@ -618,6 +618,38 @@ def test_attention_without_a_bias_is_one_with_a_zero_bias(h_msa, d_msa, s, r, dt
     assert rel_err(to_np(row.msa_out), base) > 1e-2      # the attention does take part
 
 
+@pytest.mark.parametrize("dtype,sign", [(1, -1.0), (1, 1.0), (0, -1.0)])
+def test_attention_with_a_large_log_sum_exp(dtype, sign):
+    """Every logit of the row and the column attention near -300 or 300, forward and backward: channel 0 of q and k is a
+    constant, exact in bf16, that adds the same to every logit (the softmax is indifferent to it, lse is not), the other
+    channels are as usual.  The constant comes from a normalised channel without gain, so the cotangent that reaches the MSA
+    does not see it; the parameters behind that channel are not compared (their exact gradients are sums that cancel)."""
+    dims, table, inp = _case("tiny", dtype=dtype, s=39, r=70, c_m=64, h_msa=2, d_msa=32)
+    table, n = param_table(dims)
+    inp = make_inputs(dims, table, n, ("random_residues", 0.1), 73)
+    for at, ln in (("row", "row.ln_m"), ("col", "col.ln")):
+        _entry(inp, table, ln + ".g")[0], _entry(inp, table, ln + ".b")[0] = 0.0, 1.0
+        for w, v in (("w_q", sign * 42.5), ("w_k", 40.0)):
+            m = _entry(inp, table, "%s.%s" % (at, w))      # [channel][head * 32 + position]
+            m[:, ::32] = 0.0
+            m[0, :] = 0.0
+            m[0, ::32] = v
+    for name in ("mtrans.w2", "mtrans.b2"):                # no ReLU decision reaches the cotangent
+        _entry(inp, table, name)[...] = 0.0
+    run = BlockRun(dims, inp)
+    run.fwd()
+    run.bwd()
+    run.sync()
+    for name in ("row.lse", "col.lse"):
+        lse = run.ctx_entry(name)
+        assert np.all((sign * lse > 250.0) | (lse == 0.0)) and np.mean(lse == 0.0) <= 0.1      # 0: no valid key (a masked residue's column)
+    args = (dims, inp["params"], inp["msa"], inp["pair"], inp["msa_mask"], inp["pair_mask"])
+    m, z, cache, _ = ev.block_fwd(*args)
+    dm, dz, _, _ = ev.block_bwd(dims, cache, inp["d_msa_out"], inp["d_pair_out"])
+    for got, ref in ((run.msa_out, m), (run.d_msa_in, dm)):
+        assert rel_err(to_np(got), ref) < TOL[dtype]
+
+
 @pytest.mark.parametrize("h_msa,d_msa,s,r,dtype", [(4, 32, 257, 33, 1), (2, 24, 65, 65, 1), (4, 16, 97, 31, 1), (4, 8, 31, 34, 1), (4, 32, 290, 7, 0)])
 def test_attention_tiles_and_head_dimensions(h_msa, d_msa, s, r, dtype):
     """Head dimensions of one and two contraction steps, one key more than a staged chunk, a ragged last tile, an odd last batch row."""
@@ -654,12 +686,36 @@ def test_forward_without_activations_is_the_same_forward(name, dtype, over):
         assert torch.equal(getattr(run, k), ref[k]), k
 
 
+@pytest.mark.parametrize("name,dtype,over", [("tiny", 0, {}), ("tiny", 1, {}), ("af2_initial", 1, dict(s=17, r=45)), ("extra_msa", 1, dict(s=70, r=40))])
+def test_forward_without_activations_into_unaligned_outputs(name, dtype, over):
+    """Outputs that are not 16-byte aligned: without a ctx the MSA stack works in msa_out where it is aligned, and copies
+    its result there where it is not.  The same bits, and nothing beside them."""
+    import torch
+    import paper_2211_00235_amd as pe
+    dims, table, inp = _case(name, dtype=dtype, **over)
+    run = BlockRun(dims, inp)
+    run.fwd(use_ctx=False)
+    run.sync()
+    n = run.msa_out.numel()
+    for shift in (1, 16 // run.msa_out.element_size() // 2):
+        buf = torch.full((n + 64,), 7.0, dtype=run.msa_out.dtype, device="cuda")
+        out = buf[16 + shift:16 + shift + n]
+        assert out.data_ptr() % 16
+        run.pair_out.zero_()
+        torch.cuda.synchronize()
+        pair = run.pair_out.clone()
+        pe.block_fwd(run.h, run.dims, run.msa, run.pair, run.msa_mask, run.pair_mask, run.params, out, pair, None, run.ws, run.sm, run.sp)
+        run.sync()
+        assert torch.equal(out, run.msa_out.reshape(-1))
+        assert bool((buf[:16 + shift] == 7.0).all()) and bool((buf[16 + shift + n:] == 7.0).all())
+
+
 @pytest.mark.parametrize("name,s,r,two_streams,ks", [("af2_initial", 81, 131, False, (256, 128)), ("af2_initial", 9, 33, False, (128,)),
                                                      ("extra_msa", 150, 47, True, (64,))])
 def test_row_streaming_gemms(name, s, r, two_streams, ks):
-    """The GEMMs whose waves walk through 32-row blocks (pe_rows.h) at each contraction length: a ragged last block, more
-    blocks than wave slots (81 x 131 rows over four panels) and fewer, head-major output of 8 and 32 channels, strided rows
-    (column attention, ending node), ReLU decisions on the way out and in."""
+    """The GEMMs whose waves walk through 32-row blocks (pe_rows.h) at each contraction length: a ragged last block, fewer
+    blocks than wave slots (more: the two tests below), head-major output of 8 and 32 channels, strided rows (column
+    attention, ending node), ReLU decisions on the way out and in."""
     dims, table, inp = _case(name, s=s, r=r)
     table, n = param_table(dims)
     inp = make_inputs(dims, table, n, ("random_residues", 0.1), s + r)
@@ -668,6 +724,73 @@ def test_row_streaming_gemms(name, s, r, two_streams, ks):
     assert {str(k) for k in ks} <= seen, seen
     errs, worst, tol, stats = check_case(dims, table, inp, two_streams=two_streams)
     _assert(errs, worst, tol, stats)
+
+
+def _rows_wave_slots(K, N):
+    """Row blocks of 32 that the row-streaming kernel's waves take at once, per panel (launch_rows_np): 256 or 512 workgroups
+    of eight waves, shared among the panels in groups of eight workgroups."""
+    panel = 128 if K == 128 else 256
+    return max(1, 256 * (1 if K == 256 else 2) // (N // panel) // 8) * 8 * 8
+
+
+def test_row_streaming_gemms_beyond_the_wave_slots():
+    """K = 256 and 128 with more row blocks than waves: a wave takes a second block, on the same piece of LDS, and a last one
+    that is ragged.  Two streams keep these GEMMs on the tiled kernels, which sum in the same order: outputs and cotangents are
+    the same bits."""
+    import torch
+    s, r = 161, 199
+    assert s * r > 32 * _rows_wave_slots(256, 1024) and r * r > 32 * _rows_wave_slots(128, 512)
+    dims, table, inp = _case("af2_initial", s=s, r=r)
+    one, two = BlockRun(dims, inp, two_streams=False), BlockRun(dims, inp, two_streams=True)
+    seen = {k for k in _kernel_launches(one) if k.startswith("gemm_rows_kernel")}
+    for form in ("F=3073,K=256", "F=5,K=256", "F=8,K=256", "F=3073,K=128", "F=5,K=128", "F=8,K=128", "F=3136,K=128"):
+        assert "gemm_rows_kernel<%s>" % form in seen, (form, seen)
+    assert not any(k.startswith("gemm_rows_kernel") for k in _kernel_launches(two))
+    for k in ("msa_out", "pair_out", "d_msa_in", "d_pair_in"):
+        assert torch.equal(getattr(one, k), getattr(two, k)), k
+
+
+def test_row_streaming_gemms_beyond_the_wave_slots_at_64_channels():
+    """K = 64 with more row blocks than waves.  The transition alone (the other MSA sub-operations have no output), of whose rows
+    none knows another: an MSA of 1040 sequences against its two halves, whose rows every wave has one block of at most;
+    outputs and cotangents are the same bits.  The head-major projection of the row attention against PyTorch in fp32: bf16
+    results, so half a unit in the last place (2^-8 of the value) and the rounding of 64 fp32 products."""
+    import torch
+    s, r = 1040, 127
+    slots = 32 * _rows_wave_slots(64, 256)
+    assert s * r > slots >= s * r // 2
+    dims, table, inp = _case("extra_msa", s=s, r=r)
+    table, n = param_table(dims)
+    inp = make_inputs(dims, table, n, ("random_rows", 0.05), 71)
+    for name in ("row.w_o", "col.w_o", "opm.w_o"):
+        _entry(inp, table, name)[...] = 0.0
+    full = BlockRun(dims, inp)
+    names = _kernel_launches(full)
+    for form in ("F=3073,K=64", "F=5,K=64", "F=8,K=64"):
+        assert names.get("gemm_rows_kernel<%s>" % form, 0) > 0, (form, names)
+    for h in range(2):
+        sl = slice(h * s // 2, (h + 1) * s // 2)
+        half_inp = dict(inp, **{k: np.ascontiguousarray(inp[k][sl]) for k in ("msa", "msa_mask", "d_msa_out")})
+        half = BlockRun(dict(dims, s=s // 2), half_inp)
+        half.fwd()
+        half.bwd()
+        half.sync()
+        for k in ("msa_out", "d_msa_in"):
+            assert torch.equal(getattr(full, k)[sl], getattr(half, k)), (k, h)
+    H, d, c = dims["h_msa"], dims["d_msa"], dims["c_m"]
+    xhat = torch.from_numpy(full.ctx_entry("row.xhat").reshape(s * r, c)).float().cuda()
+    qkvg = torch.from_numpy(full.ctx_entry("row.qkvg").reshape(4, H, s * r, d)).float()
+    for k, name in enumerate(("row.w_q", "row.w_k", "row.w_v", "row.w_g")):
+        w = torch.from_numpy(_entry(inp, table, name)).float().cuda()
+        if k == 0:
+            w = w * (1.4426950408889634 / d ** 0.5)
+        ref = xhat @ w.to(torch.bfloat16).float()
+        if k == 3:
+            ref = ref + torch.from_numpy(_entry(inp, table, "row.b_g")).float().cuda()
+        ref = ref.reshape(s * r, H, d).permute(1, 0, 2).cpu()
+        excess = (qkvg[k] - ref).abs() - ref.abs() / 256
+        # the scaled query weight is rounded from an fp32 product that may differ in its last place: one bf16 unit of it, rarely
+        assert float(excess.max()) < (2e-2 if k == 0 else 1e-4), (name, float(excess.max()))
 
 
 def test_outer_product_over_many_rows():
