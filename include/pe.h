@@ -149,7 +149,7 @@ int pe_destroy(pe_handle* h);
  * saved activations (pe_stack_workspace_bytes_keep bytes of workspace: about
  * 1.3 GiB per main block at s=128, r=256, which 288 GB of HBM hold for the whole
  * trunk) and recomputes nothing; results are bit-identical to the default,
- * which saves block inputs only and recomputes each block's forward.
+ * which saves block inputs only and recomputes each block's forward but the last's.
  * PE_OPT_STACK_OVERLAP (default 0): 1 = with PE_OPT_STACK_KEEP_CTX and two distinct streams,
  * pe_stack_fwd_bwd enqueues the part of the NEXT block's forward that needs the new MSA
  * representation only (weight preparation of the MSA branch, LayerNorm and q / k / v / gate
@@ -269,8 +269,9 @@ int pe_block_bwd(pe_handle* h, const pe_dims* dims,
  * made of Evoformer blocks, 52 = 4 + 48.  Only the pair representation flows
  * from the extra blocks into the main blocks; the extra-MSA representation is
  * dropped (its output cotangent is zero).  Block inputs are saved in the
- * forward pass and each block's forward is recomputed in the backward pass
- * (with PE_OPT_STACK_KEEP_CTX every block's activations are kept instead).
+ * forward pass and each block's forward is recomputed in the backward pass,
+ * the last block's excepted, whose activations are still there (with
+ * PE_OPT_STACK_KEEP_CTX every block's activations are kept instead).
  *   params / d_params: the blocks' flat buffers back to back, extra first.
  *   msa_out, pair_out: final representations.  d_msa_out, d_pair_out: their
  *   cotangents.  d_extra_msa_in, d_msa_in, d_pair_in: overwritten.

@@ -19,8 +19,9 @@
 // partner lane (lane ^ 32).  Row max / row sum then need one cross-lane exchange, the
 // per-query softmax state is one scalar per lane, and the probability tile can be fed
 // straight back as an MFMA operand (the contraction index is permuted consistently on
-// both operands; the other operand is read from a transposed LDS copy of V / K / Q / dO).
-// Online softmax over key tiles of 64; K row-major and V transposed are staged in LDS.
+// both operands; the other operand, V / K / Q / dO with channels as rows, comes from the row-major LDS
+// tile by transposing reads in bf16, from a transposed LDS copy in fp32 and in the walking backward).
+// Online softmax over key tiles of 32 out of staged chunks.
 #pragma once
 #include "pe_common.h"
 #include "pe_elem.h"
@@ -384,7 +385,7 @@ PE_DEV void attn_chunk_store(const typename Vec16<T>::type (&r)[AttnChunk<T>::NV
 #endif
 // NK: contraction steps of the score products when known at compile time (bf16: 1 up to d = 16, 2 above), 0: from d.
 // What bounds it: the vector unit, about 9 instructions per logit at d = 32 of which one is an exponential of four times the
-// length.  Hence no transposed copy of V, the partner's maximum by a lane swap instead of through LDS, a bias pointer that
+// length (busy 0.51 of the time at L = 256, where a workgroup's life is short, 0.70 to 0.81 at 384 and 512, 0.88 at d = 8).  Hence no transposed copy of V, the partner's maximum by a lane swap instead of through LDS, a bias pointer that
 // steps by a constant; outputs and gate pass through LDS at the end (64-byte runs; a query per lane is a 16-byte access per row).
 template <typename T, bool HAS_BIAS, int NK = 0>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(PE_FWD_WAVES, PE_FWD_WAVES))) void attn_fwd_kernel(AttnArgs a) {

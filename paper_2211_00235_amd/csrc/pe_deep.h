@@ -1,11 +1,13 @@
 // GEMM for large outputs with a long contraction (bf16): the three contractions of the outer product mean with many
 // sequences, C[m][n] = scale2d( sum_k A[m][k] * B[n][k] ), operands k-contiguous or x-contiguous.
 //
-// What bounds gemm_kernel there is LDS bandwidth: a wave that owns 64 x 64 of a 128 x 128 tile reads 4 KB of fragments per
-// four MFMAs, 128 cycles of LDS against 128 cycles of MFMA per 16 k of a workgroup with the tile's stores still to come.
+// A wave of gemm_kernel, which owns 64 x 64 of a 128 x 128 tile, reads 4 KB of fragments per four MFMAs: 128 cycles of LDS against
+// 128 cycles of MFMA per 16 k of a workgroup, with the tile's stores still to come.
 // Here the tile is 256 x 256 and each of eight waves owns 128 x 64 of it: 6 KB per eight MFMAs.  One workgroup per CU, two
 // buffers of 64 KB: a k-step of 64 costs one barrier.  A tile is requested a whole step (64 MFMAs of each SIMD) before it is
 // stored to the other buffer, and the fragments of each 16 k are requested ahead of the products of the 16 k before them.
+// Counters: matrix unit busy 0.51 to 0.55 of the time at K = 5120 and 12288, LDS 0.33 to 0.35, 1.8 waves per SIMD: two waves per SIMD do not hide
+// the barrier of a step; 0.25 and 0.23 at K = 512, where the epilogue, which nothing overlaps, weighs more.
 // Products are summed in gemm_kernel's order: results are bit-identical to it.
 #pragma once
 #include "pe_gemm.h"

@@ -5,13 +5,15 @@
 // tensors) is memory traffic, mostly of the output; gemm_kernel reaches 2 to 3 TB/s on them because its workgroups pass
 // through load, multiply and store phases together, four k-steps each, with 16 KB of loads in flight per workgroup.  Here a
 // workgroup keeps a panel of B in LDS for its whole life and its eight waves walk through 32-row blocks of A independently of
-// each other, without a barrier: a wave loads its block (all of K, up to 16 KB) straight into MFMA fragments, multiplies it
-// with the panel and stores; with eight waves in different phases loads, MFMAs and stores overlap.
+// each other, without a barrier: a wave loads its block (all of K, up to 16 KB) into registers, turns it into MFMA fragments
+// through 2 KB of LDS of its own (RowsPiece; heads of 8 channels are loaded as fragments), multiplies it with the panel and
+// stores; with eight waves in different phases loads, MFMAs and stores overlap.  Counters at M 196608, K 256, N 1024: 384 MiB written and 114
+// fetched at 4.0 TB/s, matrix unit busy 0.32, LDS 0.35, vector unit 0.21 of the time.
 //
 // Products are computed transposed, D[n][m], weights as the A operand (from LDS, in fragment order: 1 KB contiguous per read)
 // and rows of A as the B operand, so a row of the output is a lane (and its partner lane ^ 32): after one exchange
 // of accumulator quads between the two lane halves (v_permlane32_swap) a lane holds 8 consecutive columns of its row, twice
-// per 32 columns, and the epilogue needs no LDS.
+// per 32 columns: the epilogue's arithmetic needs no LDS, its stores go through the wave's 2 KB once more.
 // The products are summed over k in gemm_kernel's order: results are bit-identical to it.
 #pragma once
 #include "pe_gemm.h"
