@@ -221,8 +221,8 @@ template <typename T> PE_DEV typename Mma<T>::frag gl_frag(const T* p, int kk, i
 //     tile, decided when the tile is staged);
 //   * in the dK / dV kernel, where -lse and -D of a tile's queries sit in LDS in accumulator order, they are the C
 //     operands of the S and dP products.
-// These kernels are bound by the length of a workgroup's life (memory round trips and dependent stages in a row at 3-4
-// waves per SIMD), not by any one unit: measured on MI355X, halving the vector instructions per logit changed the
+// At L = 256 these kernels are bound by the length of a workgroup's life (memory round trips and dependent stages in a row
+// at 3-4 waves per SIMD), not by any one unit: measured on MI355X, halving the vector instructions per logit changed the
 // forward kernel by 2 %, taking the exponentials out by 3 %, while its loads and stores add their full time to the
 // arithmetic's.  What helps is fewer round trips in a row (K / V staged 256 keys at a time in the forward kernel) and
 // registers kept at the 128 that four waves per SIMD allow.
