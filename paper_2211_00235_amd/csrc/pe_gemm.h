@@ -518,22 +518,69 @@ template <typename T> struct EpiTmGateBwd {
   }
 };
 
+// fp32 operands are multiplied as three bf16 terms each: v = hi + mid + lo, every term the rest rounded to 8 significant bits.
+// v_mfma_f32_32x32x2_f32 makes 64 flops per cycle and SIMD, the bf16 instruction 1024, so the six products that matter (hi hi,
+// hi mid, mid hi, mid mid, hi lo, lo hi) take 24 x 32 cycles per 64 x 64 of output and 16 of contraction instead of 32 x 64.  What is left
+// out, mid lo + lo mid + lo lo, is at most 2^-24 of |a b|.  One stream, s 128, r 256, us per launch: parameter gradients 90 -> 55,
+// head-major projections 131 -> 101, hidden layers 134 -> 107, cotangents with a LayerNorm 128 -> 103; the step 8522 -> 7260.
+// Against 64 bits (five blocks, s 37..1100, r 33..160) parameter gradients are at 0.53 to 0.70 of the error that fp32 MFMAs
+// left (16 products are summed per instruction instead of 2), outputs and cotangents at 0.42 to 0.84.
+// A value beyond the largest bf16 number, an infinity or a NaN has no such terms: see gemm_redo.
+PE_DEV void split3(const f32x4& v, bf16x4 (&t)[3]) {
+#pragma unroll
+  for (int e = 0; e < 4; e += 2) {
+    float r0 = v[e], r1 = v[e + 1];
+#pragma unroll
+    for (int p = 0; p < 3; p++) {
+      union { bf16x2 b; unsigned u; } w;
+      w.b[0] = (bf16)r0; w.b[1] = (bf16)r1;
+      asm("" : "+v"(w.u));      // or each half is converted a second time for its own widening
+      t[p][e] = w.b[0]; t[p][e + 1] = w.b[1];
+      r0 -= __uint_as_float(w.u << 16);
+      r1 -= __uint_as_float(w.u & 0xffff0000u);
+    }
+  }
+}
+
+// A tile in LDS is bf16: one plane (bf16 operands), or one per term (fp32).
 template <typename T> struct GemmCfg {
   static constexpr int VEC = Vec16<T>::N;
   static constexpr int BM = 128, BN = 128;
-  static constexpr int BK = 8 * VEC;        // 64 (bf16) or 32 (fp32): 128-byte rows
-  static constexpr int LDSS = BK + VEC;     // +16 bytes: conflict-free 16-byte fragment reads
-  // LDS element offset of (row, 16-byte chunk c of the row, element w inside the chunk) in the tile of a k-contiguous operand:
-  // the 16 rows that a fragment read touches at once fall on 16 different bank groups (row stride 144 bytes)
-  static PE_DEV int off(int row, int c, int w) { return row * LDSS + c * VEC + w; }
-  // The tile of an x-contiguous operand stays in memory order [k][128 rows] (16-byte stores of what was loaded).
-  // fp32: a fragment is one element per lane (32 rows at k, 32 rows at k + 1: 32 consecutive words per half wave on a
-  // read), the row index is XOR-ed by 32 at odd k: the two halves of a wave read disjoint banks.  With a transposing store
-  // the fp32 parameter-gradient GEMMs ran at 43 TFLOP/s (256 x 1024 x 32768: 301 us).
-  // bf16: fragments come from transposing reads (xmem_frag); the 32-byte unit of a row is XOR-ed by 2 (k % 4), so that the four
+  static constexpr int BK = 8 * VEC;        // 64 (bf16) or 32 (fp32): 128-byte rows in memory
+  static constexpr int TERMS = sizeof(T) == 4 ? 3 : 1;
+  static constexpr int LDSS = sizeof(T) == 4 ? BK : BK + VEC;   // row of a plane of a k-contiguous operand
+  static constexpr int tile(int rows) { return TERMS * rows * LDSS; }
+  // LDS element offset of (row, 16-byte chunk c of 8 k) in a plane of a k-contiguous operand.  bf16: 16 bytes of padding, the 16 rows
+  // that a fragment read touches at once fall on 16 different bank groups (row stride 144 bytes).  fp32 (64-byte rows): the chunk
+  // is XOR-ed instead, which leaves room for three workgroups per CU; 8 consecutive rows at a chunk fall on all 128 bytes, 16 on all 256.
+  static PE_DEV int off(int row, int c) {
+    return sizeof(T) == 4 ? row * LDSS + ((c ^ (((row >> 1) ^ (row >> 3)) & 3)) << 3) : row * LDSS + (c << 3);
+  }
+  // The tile of an x-contiguous operand stays in memory order [k][128 rows] (a thread's vector is stored as it was loaded) and its
+  // fragments come from transposing reads (xmem_frag); the 64-byte unit of a row is XOR-ed by k % 4, so that the four
   // rows of k and both halves of the 32 rows that a read touches cover every bank once.
-  static PE_DEV int xoff(int k, int row) {
-    return sizeof(T) == 4 ? k * 128 + (row ^ ((k & 1) << 5)) : k * 128 + (row ^ ((k & 3) << 5));
+  static PE_DEV int xoff(int k, int row) { return k * 128 + (row ^ ((k & 3) << 5)); }
+  // vector c (16 bytes of memory) of a row of a k-contiguous tile of ROWS rows
+  template <int ROWS> static PE_DEV void put(bf16* lds, int row, int c, const typename Vec16<T>::type& v) {
+    if constexpr (sizeof(T) == 4) {
+      bf16x4 t[3];
+      split3(v, t);
+#pragma unroll
+      for (int p = 0; p < 3; p++) *reinterpret_cast<bf16x4*>(lds + p * ROWS * LDSS + off(row, c >> 1) + (c & 1) * 4) = t[p];
+    } else {
+      *reinterpret_cast<bf16x8*>(lds + off(row, c)) = v;
+    }
+  }
+  // the vector from x on at row k of an x-contiguous tile
+  static PE_DEV void put_x(bf16* lds, int k, int x, const typename Vec16<T>::type& v) {
+    if constexpr (sizeof(T) == 4) {
+      bf16x4 t[3];
+      split3(v, t);
+#pragma unroll
+      for (int p = 0; p < 3; p++) *reinterpret_cast<bf16x4*>(lds + p * 128 * BK + xoff(k, x)) = t[p];
+    } else {
+      *reinterpret_cast<bf16x8*>(lds + xoff(k, x)) = v;
+    }
   }
 };
 // MFMA fragment (16 k from k0, 32 rows from r0, lane (l32, g)) of a bf16 tile in memory order
@@ -545,6 +592,90 @@ PE_DEV bf16x8 xmem_frag(const bf16* tile, int k0, int r0, int l32, int g) {
 #pragma unroll
   for (int e = 0; e < 4; e++) { f[e] = lo[e]; f[4 + e] = hi[e]; }
   return f;
+}
+
+// MFMA operand of 32 rows and 16 k: lane (l32, g) holds k = 8 g + 0..7 of row l32, of each term
+template <typename T> struct GemmFrag {
+  bf16x8 t[GemmCfg<T>::TERMS];
+  // row of a k-contiguous tile of ROWS rows, 16-byte chunk c
+  template <int ROWS> PE_DEV void get(const bf16* lds, int row, int c) {
+#pragma unroll
+    for (int p = 0; p < GemmCfg<T>::TERMS; p++) t[p] = *reinterpret_cast<const bf16x8*>(lds + p * ROWS * GemmCfg<T>::LDSS + GemmCfg<T>::off(row, c));
+  }
+  // 16 k from k0, 32 rows from r0 of an x-contiguous tile
+  PE_DEV void get_x(const bf16* lds, int k0, int r0, int l32, int g) {
+#pragma unroll
+    for (int p = 0; p < GemmCfg<T>::TERMS; p++) t[p] = xmem_frag(lds + p * 128 * GemmCfg<T>::BK, k0, r0, l32, g);
+  }
+};
+// acc[i][j] += a[i] b[j], 16 steps of the contraction.  fp32: hi hi goes to acc, the five smaller products to lo (gemm_sum adds them at
+// the end).  The instruction drops the bits of a product that lie below the accumulator's, towards minus infinity: with all six in one
+// accumulator the sums were as accurate as fp32 MFMAs' one by one, but off to one side, and the gradients of LayerNorm offsets, which
+// add up thousands of them, were 5 to 15 times further from 64 bits.
+template <typename T, int NI, int NJ>
+PE_DEV void gemm_mma(f32x16 (&acc)[NI][NJ], f32x16 (&lo)[NI][NJ], const GemmFrag<T> (&a)[NI], const GemmFrag<T> (&b)[NJ]) {
+  constexpr int TA[6] = {0, 1, 0, 1, 2, 0}, TB[6] = {0, 0, 1, 1, 0, 2};
+#pragma unroll
+  for (int p = 0; p < (sizeof(T) == 4 ? 6 : 1); p++)
+#pragma unroll
+    for (int i = 0; i < NI; i++)
+#pragma unroll
+      for (int j = 0; j < NJ; j++) {
+        f32x16& c = p ? lo[i][j] : acc[i][j];
+        c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i].t[TA[p]], b[j].t[TB[p]], c, 0, 0, 0);
+      }
+}
+template <int NI, int NJ> PE_DEV void gemm_zero(f32x16 (&acc)[NI][NJ]) {
+#pragma unroll
+  for (int i = 0; i < NI; i++)
+#pragma unroll
+    for (int j = 0; j < NJ; j++)
+#pragma unroll
+      for (int e = 0; e < 16; e++) acc[i][j][e] = 0.0f;
+}
+template <typename T, int NI, int NJ> PE_DEV void gemm_sum(f32x16 (&acc)[NI][NJ], const f32x16 (&lo)[NI][NJ]) {
+  if constexpr (sizeof(T) == 4) {
+#pragma unroll
+    for (int i = 0; i < NI; i++)
+#pragma unroll
+      for (int j = 0; j < NJ; j++)
+#pragma unroll
+        for (int e = 0; e < 16; e++) acc[i][j][e] += lo[i][j][e];
+  }
+}
+
+PE_DEV long long gemm_addr(const Operand& op, int x, int k) {
+  return (long long)((unsigned)x / (unsigned)op.x_in) * op.x_outer + (long long)((unsigned)x % (unsigned)op.x_in) * op.x_stride +
+         (long long)((unsigned)k / (unsigned)op.k_in) * op.k_outer + (long long)((unsigned)k % (unsigned)op.k_in) * op.k_stride;
+}
+// A wave whose fp32 sums are not all finite forms them again with fp32 MFMAs, element by element from memory: the terms of an infinity or
+// of a value that rounds to one in bf16 are not numbers, where the value's own products may be.  (Rows m, n are the wave's first ones.)
+template <typename T, int NI, int NJ>
+PE_DEV void gemm_redo(f32x16 (&acc)[NI][NJ], const T* pa, const Operand& A, int m, int M, const T* pb, const Operand& B, int n, int N, int kbeg,
+                      int kend, int l32, int g) {
+  if constexpr (sizeof(T) == 4) {
+    float t = 0.0f;
+#pragma unroll
+    for (int i = 0; i < NI; i++)
+#pragma unroll
+      for (int j = 0; j < NJ; j++)
+#pragma unroll
+        for (int e = 0; e < 16; e++) t = fmaf(acc[i][j][e], 0.0f, t);
+    if (!__any(t != 0.0f)) return;
+    gemm_zero(acc);
+#pragma unroll 1
+    for (int k = kbeg + g; k < kend + g; k += 2) {
+      float a[NI], b[NJ];
+#pragma unroll
+      for (int i = 0; i < NI; i++) { const int x = m + 32 * i + l32; a[i] = (x < M && k < kend) ? pa[gemm_addr(A, x, k)] : 0.0f; }
+#pragma unroll
+      for (int j = 0; j < NJ; j++) { const int x = n + 32 * j + l32; b[j] = (x < N && k < kend) ? pb[gemm_addr(B, x, k)] : 0.0f; }
+#pragma unroll
+      for (int i = 0; i < NI; i++)
+#pragma unroll
+        for (int j = 0; j < NJ; j++) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[j], acc[i][j], 0, 0, 0);
+    }
+  }
 }
 
 // element-wise (unaligned) variant of one 16-byte vector load: elements e = 0..VEC-1 along k (KC) or x
@@ -647,34 +778,28 @@ PE_DEV void gemm_load_tile(typename Vec16<T>::type (&regs)[4], const T* base, co
   }
 }
 
-template <typename T, bool KC>
-PE_DEV void gemm_store_tile(const typename Vec16<T>::type (&regs)[4], T* lds, int tid) {
+// 128 rows (of the tile's ROWS, from row r0 on) of a k-contiguous tile, or an x-contiguous tile
+template <typename T, bool KC, int ROWS = 128>
+PE_DEV void gemm_store_tile(const typename Vec16<T>::type (&regs)[4], bf16* lds, int tid, int r0 = 0) {
   constexpr int VEC = Vec16<T>::N;
-  constexpr int LDSS = GemmCfg<T>::LDSS;
-  typedef typename Vec16<T>::type V;
   if (KC) {
-    int kv = tid & 7;
 #pragma unroll
-    for (int i = 0; i < 4; i++) {
-      int row = (tid >> 3) + 32 * i;
-      *reinterpret_cast<V*>(lds + GemmCfg<T>::off(row, kv, 0)) = regs[i];
-    }
+    for (int i = 0; i < 4; i++) GemmCfg<T>::template put<ROWS>(lds, r0 + (tid >> 3) + 32 * i, tid & 7, regs[i]);
   } else {
     constexpr int XB = 128 / VEC;
     const int xb = tid % XB, kb = tid / XB;
 #pragma unroll
-    for (int j = 0; j < 4; j++) *reinterpret_cast<V*>(lds + GemmCfg<T>::xoff(kb * 4 + j, xb * VEC)) = regs[j];
+    for (int j = 0; j < 4; j++) GemmCfg<T>::put_x(lds, kb * 4 + j, xb * VEC, regs[j]);
   }
 }
 
 template <typename T, bool A_KC, bool B_KC, bool AL, bool VE, class Epi, int F = EF_ALL>
-__global__ __launch_bounds__(256) void gemm_kernel(Operand A, Operand B, GemmShape sh, Epi epi) {
+__global__ __launch_bounds__(256, sizeof(T) == 4 ? 2 : 1) void gemm_kernel(Operand A, Operand B, GemmShape sh, Epi epi) {
   typedef GemmCfg<T> C;
-  typedef Mma<T> MM;
   typedef typename Vec16<T>::type V;
-  __shared__ __attribute__((aligned(16))) T lds_all[(C::BM + C::BN) * C::LDSS];   // 36 KB
-  T* lds_a = lds_all;
-  T* lds_b = lds_all + C::BM * C::LDSS;
+  __shared__ __attribute__((aligned(16))) bf16 lds_all[C::tile(C::BM) + C::tile(C::BN)];   // 36 KB, fp32 48 KB
+  bf16* lds_a = lds_all;
+  bf16* lds_b = lds_all + C::tile(C::BM);
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int l32 = lane & 31, g = lane >> 5;
@@ -703,17 +828,15 @@ __global__ __launch_bounds__(256) void gemm_kernel(Operand A, Operand B, GemmSha
     pb += (long long)b * B.batch_stride;
   }
 
-  f32x16 acc[2][2];
-#pragma unroll
-  for (int i = 0; i < 2; i++)
-#pragma unroll
-    for (int j = 0; j < 2; j++)
-#pragma unroll
-      for (int e = 0; e < 16; e++) acc[i][j][e] = 0.0f;
+  f32x16 acc[2][2], lo[2][2];
+  gemm_zero(acc);
+  gemm_zero(lo);
   // column sums of B: for every (batch, n-tile) one of the m-tile workgroups adds up its B tiles
   bool do_cs = false;
   float cs = 0.0f;
-  if constexpr (Epi::HAS_COLSUM) do_cs = epi.colsum != nullptr && tid < C::BN && (m0 / C::BM) == (n0 / C::BN + b) % NTm;
+  constexpr bool CSF = sizeof(T) == 4;      // fp32: from the registers of the loads (cf), before the split
+  float cf[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+  if constexpr (Epi::HAS_COLSUM) do_cs = epi.colsum != nullptr && (CSF || tid < C::BN) && (m0 / C::BM) == (n0 / C::BN + b) % NTm;
 
   V ra[4], rb[4];
   RowAddr<T, A_KC> rowa;
@@ -728,46 +851,76 @@ __global__ __launch_bounds__(256) void gemm_kernel(Operand A, Operand B, GemmSha
     __syncthreads();  // previous tile fully consumed
     gemm_store_tile<T, A_KC>(ra, lds_a, tid);
     gemm_store_tile<T, B_KC>(rb, lds_b, tid);
+    if constexpr (Epi::HAS_COLSUM && CSF) {
+      if (do_cs) {
+#pragma unroll
+        for (int i = 0; i < 4; i++)
+#pragma unroll
+          for (int e = 0; e < 4; e++) cf[B_KC ? i : e] += rb[i][e];
+      }
+    }
     __syncthreads();
     if (k0 + C::BK < kend) {
       gemm_load_tile<T, A_KC, AL>(ra, pa, A, rowa, sh.M, k0 + C::BK, kend, tid);
       gemm_load_tile<T, B_KC, AL>(rb, pb, B, rowb, sh.n_rows, k0 + C::BK, kend, tid);
     }
-    if constexpr (Epi::HAS_COLSUM) {
+    if constexpr (Epi::HAS_COLSUM && !CSF) {
       if (do_cs && !B_KC) {
 #pragma unroll 8
         for (int k = 0; k < C::BK; k++) cs += to_f(lds_b[C::xoff(k, tid)]);
       } else if (do_cs) {
 #pragma unroll
         for (int ch = 0; ch < C::BK / C::VEC; ch++) {
-          V v = *reinterpret_cast<const V*>(lds_b + C::off(tid, ch, 0));
+          V v = *reinterpret_cast<const V*>(lds_b + C::off(tid, ch));
 #pragma unroll
           for (int e = 0; e < C::VEC; e++) cs += to_f(v[e]);
         }
       }
     }
 #pragma unroll
-    for (int kk = 0; kk < C::BK / MM::KSTEP; kk++) {
-      typename MM::frag af[2], bf[2];
+    for (int kk = 0; kk < C::BK / 16; kk++) {
+      GemmFrag<T> af[2], bf[2];
 #pragma unroll
       for (int t = 0; t < 2; t++) {
-        const int eo = kk * MM::KSTEP + g * MM::KP;
-        const int ar = wm * 64 + t * 32 + l32, br = wn * 64 + t * 32 + l32;
-        if constexpr (A_KC) af[t] = MM::load(lds_a + C::off(ar, eo / C::VEC, eo % C::VEC));
-        else if constexpr (sizeof(T) == 4) af[t] = MM::load(lds_a + C::xoff(eo, ar));
-        else af[t] = xmem_frag(lds_a, kk * MM::KSTEP, wm * 64 + t * 32, l32, g);
-        if constexpr (B_KC) bf[t] = MM::load(lds_b + C::off(br, eo / C::VEC, eo % C::VEC));
-        else if constexpr (sizeof(T) == 4) bf[t] = MM::load(lds_b + C::xoff(eo, br));
-        else bf[t] = xmem_frag(lds_b, kk * MM::KSTEP, wn * 64 + t * 32, l32, g);
+        const int ar = wm * 64 + t * 32, br = wn * 64 + t * 32;
+        if constexpr (A_KC) af[t].template get<C::BM>(lds_a, ar + l32, 2 * kk + g);
+        else af[t].get_x(lds_a, kk * 16, ar, l32, g);
+        if constexpr (B_KC) bf[t].template get<C::BN>(lds_b, br + l32, 2 * kk + g);
+        else bf[t].get_x(lds_b, kk * 16, br, l32, g);
       }
-#pragma unroll
-      for (int i = 0; i < 2; i++)
-#pragma unroll
-        for (int j = 0; j < 2; j++) MM::mma(acc[i][j], af[i], bf[j]);
+      gemm_mma<T>(acc, lo, af, bf);
     }
   }
+  gemm_sum<T>(acc, lo);
+  gemm_redo<T>(acc, pa, A, m0 + wm * 64, sh.M, pb, B, n0 + wn * 64, sh.n_rows, kbeg, kend, l32, g);
 
-  if constexpr (Epi::HAS_COLSUM) {
+  if constexpr (Epi::HAS_COLSUM && CSF) {
+    if (do_cs) {      // the same for the whole workgroup
+      float* red = reinterpret_cast<float*>(lds_all);      // x-contiguous: [8 groups of k][128]
+      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < 4; i++) {
+        if (B_KC) {
+          float t = cf[i];
+#pragma unroll
+          for (int o = 1; o < 8; o <<= 1) t += __shfl_xor(t, o, 64);
+          const int n = n0 + (tid >> 3) + 32 * i;
+          if ((tid & 7) == 0 && n < sh.N) epi.colsum[(long long)b * sh.N + n] = t;
+        } else {
+          red[(tid >> 5) * 128 + (tid & 31) * 4 + i] = cf[i];
+        }
+      }
+      if (!B_KC) {
+        __syncthreads();
+        if (tid < 128 && n0 + tid < sh.N) {
+          float t = 0.0f;
+#pragma unroll
+          for (int q = 0; q < 8; q++) t += red[q * 128 + tid];
+          epi.colsum[(long long)b * sh.N + n0 + tid] = t;
+        }
+      }
+    }
+  } else if constexpr (Epi::HAS_COLSUM) {
     if (do_cs && n0 + tid < sh.N) epi.colsum[(long long)b * sh.N + n0 + tid] = cs;
   }
   if (VE) {
@@ -777,7 +930,7 @@ __global__ __launch_bounds__(256) void gemm_kernel(Operand A, Operand B, GemmSha
     // operations of one wave execute in order, so the wave only needs the compiler to keep
     // the write and read phases apart.
     constexpr int WS = 64 + 4;
-    static_assert(4 * 32 * WS * sizeof(float) <= (C::BM + C::BN) * C::LDSS * sizeof(T), "stage tiles must fit");
+    static_assert(4 * 32 * WS * sizeof(float) <= sizeof(lds_all), "stage tiles must fit");
     float* stage = reinterpret_cast<float*>(lds_all) + wave * 32 * WS;
     const int c8 = (lane & 7) * 8, n = n0 + wn * 64 + c8;
     if constexpr (Epi::TM_GATE) {
@@ -968,23 +1121,20 @@ template <typename T> static inline bool gemm_operand_ok(const Operand& o, bool 
 template <typename T, class Epi, int F>
 __global__ __launch_bounds__(256) void gemm64_kernel(Operand A, Operand B, GemmShape sh, Epi epi) {
   typedef GemmCfg<T> C;
-  typedef Mma<T> MM;
   typedef typename Vec16<T>::type V;
   constexpr int BM = 64;
-  __shared__ __attribute__((aligned(16))) T lds_all[(BM + C::BN) * C::LDSS];   // 27 KB
-  T* lds_a = lds_all;
-  T* lds_b = lds_all + BM * C::LDSS;
+  __shared__ __attribute__((aligned(16))) bf16 lds_all[C::tile(BM) + C::tile(C::BN)];   // 27 KB, fp32 36 KB
+  bf16* lds_a = lds_all;
+  bf16* lds_b = lds_all + C::tile(BM);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int l32 = lane & 31, g = lane >> 5;
   const int m0 = blockIdx.x * BM;
   const T* pa = (const T*)A.ptr;
   const T* pb = (const T*)B.ptr;
 
-  f32x16 acc[2];
-#pragma unroll
-  for (int i = 0; i < 2; i++)
-#pragma unroll
-    for (int e = 0; e < 16; e++) acc[i][e] = 0.0f;
+  f32x16 acc[2][1], lo[2][1];
+  gemm_zero(acc);
+  gemm_zero(lo);
 
   // per-thread addressing: k-vector kv = tid % 8, rows tid / 8 + 32 i (2 rows of A, 4 of B)
   const int kv = tid & 7;
@@ -1020,7 +1170,7 @@ __global__ __launch_bounds__(256) void gemm64_kernel(Operand A, Operand B, GemmS
   for (int k0 = 0; k0 < sh.K; k0 += C::BK) {
     __syncthreads();  // previous tile fully consumed
 #pragma unroll
-    for (int i = 0; i < 2; i++) *reinterpret_cast<V*>(lds_a + C::off((tid >> 3) + 32 * i, kv, 0)) = ra[i];
+    for (int i = 0; i < 2; i++) C::template put<BM>(lds_a, (tid >> 3) + 32 * i, kv, ra[i]);
     gemm_store_tile<T, true>(rb, lds_b, tid);
     __syncthreads();
     if (k0 + C::BK < sh.K) {
@@ -1028,18 +1178,20 @@ __global__ __launch_bounds__(256) void gemm64_kernel(Operand A, Operand B, GemmS
       gemm_load_tile<T, true, true>(rb, pb, B, rowb, sh.N, k0 + C::BK, sh.K, tid);
     }
 #pragma unroll
-    for (int kk = 0; kk < C::BK / MM::KSTEP; kk++) {
-      const int eo = kk * MM::KSTEP + g * MM::KP;
-      typename MM::frag bf = MM::load(lds_b + C::off(wave * 32 + l32, eo / C::VEC, eo % C::VEC));
+    for (int kk = 0; kk < C::BK / 16; kk++) {
+      GemmFrag<T> af[2], bf[1];
+      bf[0].template get<C::BN>(lds_b, wave * 32 + l32, 2 * kk + g);
 #pragma unroll
-      for (int t = 0; t < 2; t++)
-        MM::mma(acc[t], MM::load(lds_a + C::off(t * 32 + l32, eo / C::VEC, eo % C::VEC)), bf);
+      for (int t = 0; t < 2; t++) af[t].template get<BM>(lds_a, t * 32 + l32, 2 * kk + g);
+      gemm_mma<T>(acc, lo, af, bf);
     }
   }
+  gemm_sum<T>(acc, lo);
+  gemm_redo<T>(acc, pa, A, m0, sh.M, pb, B, wave * 32, sh.N, 0, sh.K, l32, g);
 
   // wave-private staging of the 32 x 32 sub-tiles, then 8 consecutive columns per lane
   constexpr int WS = 32 + 4;
-  static_assert(4 * 32 * WS * sizeof(float) <= (BM + C::BN) * C::LDSS * sizeof(T), "stage tiles must fit");
+  static_assert(4 * 32 * WS * sizeof(float) <= sizeof(lds_all), "stage tiles must fit");
   float* stage = reinterpret_cast<float*>(lds_all) + wave * 32 * WS;
   const int c8 = (lane & 3) * 8, n = wave * 32 + c8;
   typename Epi::ColV cv;
@@ -1055,7 +1207,7 @@ __global__ __launch_bounds__(256) void gemm64_kernel(Operand A, Operand B, GemmS
 #pragma unroll
   for (int i = 0; i < 2; i++) {
 #pragma unroll
-    for (int a = 0; a < 16; a++) stage[acc_row(g, a) * WS + l32] = acc[i][a];
+    for (int a = 0; a < 16; a++) stage[acc_row(g, a) * WS + l32] = acc[i][0][a];
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -1114,10 +1266,9 @@ template <typename T> struct RowLn {
 template <typename T, int F, int MODE, int HB = 0, bool G2 = false>
 __global__ __launch_bounds__(256) void gemm64r_kernel(Operand A, Operand B, GemmShape sh, EpiGeneric<T> epi, RowLn<T> ln) {
   typedef GemmCfg<T> C;
-  typedef Mma<T> MM;
   typedef typename Vec16<T>::type V;
   constexpr int BM = 64, CH = 128;
-  __shared__ __attribute__((aligned(16))) T lds_all[(BM + C::BN) * C::LDSS];   // 27 KB
+  __shared__ __attribute__((aligned(16))) bf16 lds_all[C::tile(BM) + C::tile(C::BN)];   // 27 KB, fp32 36 KB
   __shared__ __attribute__((aligned(16))) float wbl[HB > 0 ? HB * CH : 4];      // w_bias as [h][c], zero beyond H
   if constexpr (HB > 0) {
     for (int i = threadIdx.x; i < HB * CH; i += 256) {
@@ -1125,19 +1276,17 @@ __global__ __launch_bounds__(256) void gemm64r_kernel(Operand A, Operand B, Gemm
       wbl[i] = hh < ln.H ? ln.w_bias[c * ln.H + hh] : 0.0f;
     }
   }
-  T* lds_a = lds_all;
-  T* lds_b = lds_all + BM * C::LDSS;
+  bf16* lds_a = lds_all;
+  bf16* lds_b = lds_all + C::tile(BM);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int l32 = lane & 31, g = lane >> 5;
   const int m0 = blockIdx.x * BM;
   const T* pa = (const T*)A.ptr;
   const T* pb = (const T*)B.ptr;
 
-  f32x16 acc[2];
-#pragma unroll
-  for (int i = 0; i < 2; i++)
-#pragma unroll
-    for (int e = 0; e < 16; e++) acc[i][e] = 0.0f;
+  f32x16 acc[2][1], lo[2][1];
+  gemm_zero(acc);
+  gemm_zero(lo);
 
   const int kv = tid & 7;
   long long aa[2];
@@ -1171,7 +1320,7 @@ __global__ __launch_bounds__(256) void gemm64r_kernel(Operand A, Operand B, Gemm
   for (int k0 = 0; k0 < sh.K; k0 += C::BK) {
     __syncthreads();  // previous tile fully consumed
 #pragma unroll
-    for (int i = 0; i < 2; i++) *reinterpret_cast<V*>(lds_a + C::off((tid >> 3) + 32 * i, kv, 0)) = ra[i];
+    for (int i = 0; i < 2; i++) C::template put<BM>(lds_a, (tid >> 3) + 32 * i, kv, ra[i]);
     gemm_store_tile<T, true>(rb, lds_b, tid);
     __syncthreads();
     if (k0 + C::BK < sh.K) {
@@ -1179,19 +1328,21 @@ __global__ __launch_bounds__(256) void gemm64r_kernel(Operand A, Operand B, Gemm
       gemm_load_tile<T, true, true>(rb, pb, B, rowb, sh.N, k0 + C::BK, sh.K, tid);
     }
 #pragma unroll
-    for (int kk = 0; kk < C::BK / MM::KSTEP; kk++) {
-      const int eo = kk * MM::KSTEP + g * MM::KP;
-      typename MM::frag bf = MM::load(lds_b + C::off(wave * 32 + l32, eo / C::VEC, eo % C::VEC));
+    for (int kk = 0; kk < C::BK / 16; kk++) {
+      GemmFrag<T> af[2], bf[1];
+      bf[0].template get<C::BN>(lds_b, wave * 32 + l32, 2 * kk + g);
 #pragma unroll
-      for (int t = 0; t < 2; t++)
-        MM::mma(acc[t], MM::load(lds_a + C::off(t * 32 + l32, eo / C::VEC, eo % C::VEC)), bf);
+      for (int t = 0; t < 2; t++) af[t].template get<BM>(lds_a, t * 32 + l32, 2 * kk + g);
+      gemm_mma<T>(acc, lo, af, bf);
     }
   }
+  gemm_sum<T>(acc, lo);
+  gemm_redo<T>(acc, pa, A, m0, sh.M, pb, B, wave * 32, sh.N, 0, sh.K, l32, g);
 
   // wave-private staging of the 32 x 32 sub-tiles; lane -> 8 consecutive columns of the rows
   // rloc(q) = 32 (q / 2) + 16 (q % 2) + lane / 4, q = 0..3
   constexpr int WS = 32 + 4;
-  static_assert((4 * 32 * WS + 4 * BM * 2) * sizeof(float) <= (BM + C::BN) * C::LDSS * sizeof(T), "stage tiles and row sums must fit");
+  static_assert((4 * 32 * WS + 4 * BM * 2) * sizeof(float) <= sizeof(lds_all), "stage tiles and row sums must fit");
   float* stage = reinterpret_cast<float*>(lds_all) + wave * 32 * WS;
   float* rowred = reinterpret_cast<float*>(lds_all) + 4 * 32 * WS;   // [wave][row][2]
   const int c8 = (lane & 3) * 8, n = wave * 32 + c8;
@@ -1249,7 +1400,7 @@ __global__ __launch_bounds__(256) void gemm64r_kernel(Operand A, Operand B, Gemm
 #pragma unroll
   for (int i = 0; i < 2; i++) {
 #pragma unroll
-    for (int a = 0; a < 16; a++) stage[acc_row(g, a) * WS + l32] = acc[i][a];
+    for (int a = 0; a < 16; a++) stage[acc_row(g, a) * WS + l32] = acc[i][0][a];
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -1463,27 +1614,22 @@ __global__ __launch_bounds__(256) void gemm64r_kernel(Operand A, Operand B, Gemm
 // the 128 x 128 kernel they replace, and the forward GEMMs are the ones that run at its full rate): not kept.
 // ---------------------------------------------------------------------------
 template <typename T>
-__global__ __launch_bounds__(256) void gemm64w_kernel(Operand A, Operand B, GemmShape sh, RowLn<T> ln) {
+__global__ __launch_bounds__(256, sizeof(T) == 4 ? 2 : 1) void gemm64w_kernel(Operand A, Operand B, GemmShape sh, RowLn<T> ln) {
   typedef GemmCfg<T> C;
-  typedef Mma<T> MM;
   typedef typename Vec16<T>::type V;
   constexpr int BM = 64, CH = 256;
-  __shared__ __attribute__((aligned(16))) T lds_all[(BM + CH) * C::LDSS];   // 45 KB
-  T* lds_a = lds_all;
-  T* lds_b = lds_all + BM * C::LDSS;
+  __shared__ __attribute__((aligned(16))) bf16 lds_all[C::tile(BM) + C::tile(CH)];   // 45 KB, fp32 60 KB
+  bf16* lds_a = lds_all;
+  bf16* lds_b = lds_all + C::tile(BM);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int l32 = lane & 31, g = lane >> 5;
   const int m0 = blockIdx.x * BM;
   const T* pa = (const T*)A.ptr;
   const T* pb = (const T*)B.ptr;
 
-  f32x16 acc[2][2];
-#pragma unroll
-  for (int i = 0; i < 2; i++)
-#pragma unroll
-    for (int j = 0; j < 2; j++)
-#pragma unroll
-      for (int e = 0; e < 16; e++) acc[i][j][e] = 0.0f;
+  f32x16 acc[2][2], lo[2][2];
+  gemm_zero(acc);
+  gemm_zero(lo);
 
   const int kv = tid & 7;
   long long aa[2];
@@ -1519,9 +1665,9 @@ __global__ __launch_bounds__(256) void gemm64w_kernel(Operand A, Operand B, Gemm
   for (int k0 = 0; k0 < sh.K; k0 += C::BK) {
     __syncthreads();  // previous tile fully consumed
 #pragma unroll
-    for (int i = 0; i < 2; i++) *reinterpret_cast<V*>(lds_a + C::off((tid >> 3) + 32 * i, kv, 0)) = ra[i];
-    gemm_store_tile<T, true>(rb0, lds_b, tid);
-    gemm_store_tile<T, true>(rb1, lds_b + 128 * C::LDSS, tid);
+    for (int i = 0; i < 2; i++) C::template put<BM>(lds_a, (tid >> 3) + 32 * i, kv, ra[i]);
+    gemm_store_tile<T, true, CH>(rb0, lds_b, tid);
+    gemm_store_tile<T, true, CH>(rb1, lds_b, tid, 128);
     __syncthreads();
     if (k0 + C::BK < sh.K) {
       load_a(k0 + C::BK);
@@ -1529,23 +1675,21 @@ __global__ __launch_bounds__(256) void gemm64w_kernel(Operand A, Operand B, Gemm
       gemm_load_tile<T, true, true>(rb1, pb, B, rowb1, sh.N, k0 + C::BK, sh.K, tid);
     }
 #pragma unroll
-    for (int kk = 0; kk < C::BK / MM::KSTEP; kk++) {
-      const int eo = kk * MM::KSTEP + g * MM::KP;
-      typename MM::frag af[2], bf[2];
+    for (int kk = 0; kk < C::BK / 16; kk++) {
+      GemmFrag<T> af[2], bf[2];
 #pragma unroll
       for (int t = 0; t < 2; t++) {
-        af[t] = MM::load(lds_a + C::off(t * 32 + l32, eo / C::VEC, eo % C::VEC));
-        bf[t] = MM::load(lds_b + C::off(wave * 64 + t * 32 + l32, eo / C::VEC, eo % C::VEC));
+        af[t].template get<BM>(lds_a, t * 32 + l32, 2 * kk + g);
+        bf[t].template get<CH>(lds_b, wave * 64 + t * 32 + l32, 2 * kk + g);
       }
-#pragma unroll
-      for (int i = 0; i < 2; i++)
-#pragma unroll
-        for (int j = 0; j < 2; j++) MM::mma(acc[i][j], af[i], bf[j]);
+      gemm_mma<T>(acc, lo, af, bf);
     }
   }
+  gemm_sum<T>(acc, lo);
+  gemm_redo<T>(acc, pa, A, m0, sh.M, pb, B, wave * 64, sh.N, 0, sh.K, l32, g);
 
   constexpr int WS = 64 + 4;
-  static_assert((4 * 32 * WS + 2 * 4 * 32 * 2) * sizeof(float) <= (BM + CH) * C::LDSS * sizeof(T), "stage tiles and row sums must fit");
+  static_assert((4 * 32 * WS + 2 * 4 * 32 * 2) * sizeof(float) <= sizeof(lds_all), "stage tiles and row sums must fit");
   float* stage = reinterpret_cast<float*>(lds_all) + wave * 32 * WS;
   float* rowred_all = reinterpret_cast<float*>(lds_all) + 4 * 32 * WS;   // [half][wave][row][2]
   const int c8 = (lane & 7) * 8, n = wave * 64 + c8;
