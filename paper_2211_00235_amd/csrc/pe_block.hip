@@ -853,6 +853,11 @@ template <typename T> struct Runner {
     // fp32: two workgroups per CU, one splits its operands into terms while the other multiplies (the 18 launches
     // of a step at s 128, r 256: 75.6 -> 54.7 us each), where a split keeps at least four k-tiles
     if (sizeof(T) == 4 && K >= 2LL * want * 128) want *= 2;
+    // bf16: 256 workgroups are one per CU and half the bytes in flight that the memory system takes, but a split costs its partial sums
+    // twice: two per CU where a split keeps 2048 positions.  Step at s 5120, r 384 (extra-MSA widths) 20326 -> 19644 us, s 512, r 384 with
+    // recomputation 11155 -> 10927, extra-MSA s 1024, r 256 3429 -> 3399, s 300, r 256 on one stream 3982 -> 3946; below that (from 1024 on) s 128, r 256 2341 ->
+    // 2402 (three per CU there).  Three per CU from 2048 on are no faster than two.
+    if (sizeof(T) == 2 && K >= 2LL * want * 2048) want *= 2;
     const int BK = GemmCfg<T>::BK;
     long long kc = (K + want - 1) / want;
     kc = (kc + BK - 1) / BK * BK;
