@@ -18,6 +18,7 @@
 #include "pe_gcol.h"
 #include "pe_gemm.h"
 #include "pe_layout.h"
+#include "pe_pipe.h"
 #include "pe_rows.h"
 #include "pe_small.h"
 
@@ -700,6 +701,7 @@ template <typename T> struct Runner {
     char kn[64] = "";
     if (!timed()) {}
     else if (g_gemm_last_small) snprintf(kn, sizeof(kn), "gemm_small_kernel<%s,%s>", akc ? "kc" : "xc", bkc ? "kc" : "xc");
+    else if (g_gemm_last_pipe) snprintf(kn, sizeof(kn), "gemm_pipe_kernel<EpiGeneric,F=%d>", g_gemm_last_features);
     else if (g_gemm_last_deep) snprintf(kn, sizeof(kn), "gemm_deep_kernel<%s,%s>", akc ? "kc" : "xc", bkc ? "kc" : "xc");
     else if (g_gemm_last_rows) snprintf(kn, sizeof(kn), "gemm_rows_kernel<F=%d,K=%d>", g_gemm_last_features, K);
     else if (narrow) snprintf(kn, sizeof(kn), "gemm64_kernel<EpiGeneric,F=%d>", g_gemm_last_features);
@@ -781,7 +783,7 @@ template <typename T> struct Runner {
       GemmShape sh{(int)M, Cc, K, 1, 0, 0};
       return launch_gemm64r<T, 2>(st, A, B, sh, epi_plain<T>(dxh, Cc), ln, false);
     }
-    const long long gridf = (M + 63) / 64;
+    const long long gridf = (M + 31) / 32;      // at most: workgroups take 64 rows or 32
     const int plen = 2 * Cc + (bias_db ? Cc * bias_H : 0);
     // sized by bias_H whether or not the bias path is taken: the planning pass must not depend on pointer values
     float* part = (Cc == 128 || Cc == 256) ? (float*)part_arena(ar).alloc((size_t)gridf * (2 * Cc + Cc * bias_H) * sizeof(float)) : nullptr;
@@ -803,7 +805,8 @@ template <typename T> struct Runner {
       GemmShape sh{(int)M, Cc, K, 1, 0, 0};
       join_side(st);   // gout may alias a buffer the side stream is still reading
       prof_begin(st);
-      if (launch_gemm64r<T, 2>(st, A, B, sh, e, ln)) {
+      int tiles = 0;
+      if (launch_gemm64r<T, 2>(st, A, B, sh, e, ln, true, &tiles)) {
         char kn[64] = "";
         if (!timed()) {}
         else if (Cc == 256) snprintf(kn, sizeof(kn), "gemm64w_kernel<F=0,MODE=2>");
@@ -812,7 +815,7 @@ template <typename T> struct Runner {
                  ((double)M * K + (double)Cc * K + (gin ? 3.0 : 2.0) * M * Cc + (acc ? 1.0 : 0.0) * M * Cc) * sizeof(T));
         check(what);
         ReduceSeg sg[3] = {{0, Cc, g_off, 0}, {Cc, Cc, b_off, 0}, {2 * Cc, Cc * bias_H, w_bias_off, 0}};
-        reduce_to(ar, part, (int)gridf, plen, 1, plen, bias_db ? 3 : 2, sg);
+        reduce_to(ar, part, tiles, plen, 1, plen, bias_db ? 3 : 2, sg);
         if (fin) fin_done = true;
         return bias_db != nullptr;
       }
@@ -1368,7 +1371,7 @@ template <typename T> struct Runner {
         prof_begin(st);
         bool al = false, narrow = false;
         int rc = launch_gemm<T, EpiAttnPre<T>>(st, A, true, B, true, sh, ep, &al, &narrow);
-        prof_end(st, "attn dog+pre", narrow ? "gemm64_kernel<EpiAttnPre>" : "gemm_kernel<kc,kc,vec,EpiAttnPre>", 2.0 * M * HD * Cc,
+        prof_end(st, "attn dog+pre", g_gemm_last_pipe ? "gemm_pipe_kernel<EpiAttnPre>" : narrow ? "gemm64_kernel<EpiAttnPre>" : "gemm_kernel<kc,kc,vec,EpiAttnPre>", 2.0 * M * HD * Cc,
                  ((double)M * Cc + (double)HD * Cc + 4.0 * M * HD) * sizeof(T));
         if (rc == -1) { err = PE_ERR_DIMS; if (h) h->last_error = "gemm operand alignment: attn dog"; }
         else check("attn dog+pre");
@@ -1556,7 +1559,7 @@ template <typename T> struct Runner {
         const double fl = 2.0 * r * r * r * ct, by = (2.0 * r * r + 5.0 * r * r) * ct * sizeof(T);
         prof_begin(st);
         int rc = launch_gemm<T, EpiTmGateBwd<T>>(st, A1, a1k, B1, b1k, sh, ga);
-        prof_end(st, "trimul da+gate", a1k && b1k ? "gemm_kernel<kc,kc,vec,EpiTmGateBwd>" : "gemm_kernel<kc,xc,vec,EpiTmGateBwd>", fl, by);
+        prof_end(st, "trimul da+gate", g_gemm_last_pipe ? "gemm_pipe_kernel<EpiTmGateBwd>" : a1k && b1k ? "gemm_kernel<kc,kc,vec,EpiTmGateBwd>" : "gemm_kernel<kc,xc,vec,EpiTmGateBwd>", fl, by);
         if (rc == -1) { err = PE_ERR_DIMS; if (h) h->last_error = "gemm operand alignment: trimul da+gate"; }
         else check("trimul da+gate");
         if (!err) {

@@ -678,6 +678,103 @@ PE_DEV void gemm_redo(f32x16 (&acc)[NI][NJ], const T* pa, const Operand& A, int 
   }
 }
 
+// ---------------------------------------------------------------------------
+// Tiles of k-contiguous bf16 operands straight from memory to LDS (gemm_pipe_kernel of pe_pipe.h, the row-complete kernels below):
+// global_load_lds moves 1 KB (eight rows of 64 k) per wave instruction; a lane's place in LDS is fixed and it picks the chunk of memory
+// that belongs there, so the XOR of the tile layout costs nothing.  A ring of S tiles per operand: one barrier per step, behind which
+// every wave's part of step t's tiles is there and its last fragments of step t - 1 are read, whose buffers are requested for step
+// t + S - 1.  Products are summed in the order of the register-staged loops: results are bit-identical to theirs.
+// ---------------------------------------------------------------------------
+// 16 bytes per lane from base + off to the lane's 16 bytes from LDS address l on (l: the same for all lanes).  The compiler does not count
+// these: lds_dma_barrier waits for them.
+PE_DEV void lds_dma16(const char* base, unsigned off, unsigned l) {
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "s"(l) : "memory");
+}
+// all but this wave's last N vector memory operations are done, in every wave of the workgroup
+template <int N> PE_DEV void lds_dma_barrier() { asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory"); }
+
+// Main loop of four waves, WM x (4 / WM), on a BM x BN tile with a ring of S stages.
+template <int BM, int BN, int WM, int S> struct PipeLoop {
+  static constexpr int WN = 4 / WM, TM = BM / WM, TN = BN / WN, NI = TM / 32, NJ = TN / 32;
+  static constexpr int STAGE = (BM + BN) * 64, LDS = S * STAGE;      // elements
+  // element offset of 16-byte chunk c of a row of 64 k: 8 consecutive rows at a chunk fall on all 128 bytes, 16 on all 256
+  static PE_DEV int off(int row, int c) { return row * 64 + ((c ^ (row & 7) ^ ((row >> 3) & 1)) << 3); }
+
+  // one operand's requests of a wave: rows (wave P + p) 8 + lane / 8, p = 0..P-1, of each tile
+  template <int P> struct Side {
+    const char* base;
+    long long step;       // bytes from a tile to the next
+    unsigned o[P], l;     // byte offsets, LDS address of the wave's first row
+    PE_DEV void init(const Operand& op, const void* p0, int x0, int X, int wave, int lane, unsigned lds) {
+      base = (const char*)p0;
+      step = op.k_in >= (1 << 30) ? 128 : 128LL / op.k_in * op.k_outer;
+      l = lds + wave * P * 1024;
+#pragma unroll
+      for (int p = 0; p < P; p++) {
+        const int row = (wave * P + p) * 8 + (lane >> 3), c = (lane & 7) ^ (row & 7) ^ ((row >> 3) & 1);
+        const unsigned x = (unsigned)min(x0 + row, X - 1);      // rows beyond the operand repeat the last one (their products are not stored)
+        unsigned k = c * 8;
+        if (op.k_in < (1 << 30)) { const unsigned q = k / (unsigned)op.k_in; k += q * (unsigned)(op.k_outer - op.k_in); }
+        o[p] = 2u * (k + (op.x_in >= (1 << 30) ? x * (unsigned)op.x_stride
+                                               : x / (unsigned)op.x_in * (unsigned)op.x_outer + x % (unsigned)op.x_in * (unsigned)op.x_stride));
+      }
+    }
+    PE_DEV void issue(int t, int slot) const {
+      const char* b = base + t * step;
+      const unsigned ls = __builtin_amdgcn_readfirstlane(l + slot * 2 * STAGE);
+#pragma unroll
+      for (int p = 0; p < P; p++) lds_dma16(b, o[p], ls + p * 1024);
+    }
+  };
+  // A from row m0 on (M rows), B from row n0 on (N rows); nothing is in flight and no fragment unread in any wave when it returns
+  static PE_DEV void run(f32x16 (&acc)[NI][NJ], bf16* lds, const Operand& A, const void* pa, int m0, int M, const Operand& B, const void* pb, int n0,
+                         int N, int K) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l32 = lane & 31, g = lane >> 5;
+    const int wm = (wave / WN) * TM, wn = (wave % WN) * TN, nt = K / 64;
+    const unsigned l0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) bf16*)lds;
+    Side<BM / 32> sa;
+    Side<BN / 32> sb;
+    sa.init(A, pa, m0, M, wave, lane, l0);
+    sb.init(B, pb, n0, N, wave, lane, l0 + BM * 128);
+    gemm_zero(acc);
+    // beyond the contraction the last tile is requested again, for buffers that are not read any more
+#pragma unroll
+    for (int s = 0; s < S - 1; s++) { sa.issue(min(s, nt - 1), s); sb.issue(min(s, nt - 1), s); }
+    int s = 0;
+    for (int t = 0; t < nt; t++) {
+      lds_dma_barrier<(S - 2) * (BM + BN) / 32>();
+      const bf16* la = lds + s * STAGE;
+      const bf16* lb = la + BM * 64;
+      const int tn = min(t + S - 1, nt - 1), sn = s == 0 ? S - 1 : s - 1;
+      sa.issue(tn, sn);
+      sb.issue(tn, sn);
+#pragma unroll
+      for (int kk = 0; kk < 4; kk++) {
+        bf16x8 af[NI], bf[NJ];
+#pragma unroll
+        for (int i = 0; i < NI; i++) af[i] = *reinterpret_cast<const bf16x8*>(la + off(wm + i * 32 + l32, 2 * kk + g));
+#pragma unroll
+        for (int j = 0; j < NJ; j++) bf[j] = *reinterpret_cast<const bf16x8*>(lb + off(wn + j * 32 + l32, 2 * kk + g));
+#pragma unroll
+        for (int i = 0; i < NI; i++)
+#pragma unroll
+          for (int j = 0; j < NJ; j++) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[i], bf[j], acc[i][j], 0, 0, 0);
+      }
+      s = s + 1 == S ? 0 : s + 1;
+    }
+    lds_dma_barrier<0>();
+  }
+};
+
+// operand of the main loop (on top of gemm_operand_ok): a tile of 64 k is a whole number of groups of the two-level k map; byte
+// offsets of a row and of a tile's chunks take 32 bits
+static inline bool pipe_operand_ok(const Operand& o, int X, int K) {
+  if (K % 64 || (o.k_in < (1 << 30) && (64 % o.k_in || o.k_in % 8))) return false;
+  if (o.x_stride < 0 || o.x_outer < 0 || o.k_outer < 0) return false;
+  const long long rows = o.x_in >= (1 << 30) ? (X - 1LL) * o.x_stride : (X - 1LL) / o.x_in * o.x_outer + std::min(X - 1, o.x_in - 1) * o.x_stride;
+  return 2 * (rows + (o.k_in < (1 << 30) ? 64 / o.k_in * o.k_outer : 0) + 64) < (1LL << 32);
+}
+
 // element-wise (unaligned) variant of one 16-byte vector load: elements e = 0..VEC-1 along k (KC) or x
 template <typename T, bool KC>
 PE_DEV typename Vec16<T>::type gemm_load_slow(const T* base, const Operand& op, int x, int X, int k, int kend) {
@@ -1263,12 +1360,15 @@ template <typename T> struct RowLn {
 
 // (asking for three waves per SIMD, which the variant with the bias path misses at 174 registers, makes the pair
 // stack 0.7 % faster alone and the two-stream step 0.4 % slower: not asked for)
-template <typename T, int F, int MODE, int HB = 0, bool G2 = false>
+// S > 0: tiles by DMA with a ring of S stages (bf16) and BM = 64 or 32 rows, 0: through registers
+template <typename T, int F, int MODE, int HB = 0, bool G2 = false, int S = 0, int BM = 64>
 __global__ __launch_bounds__(256) void gemm64r_kernel(Operand A, Operand B, GemmShape sh, EpiGeneric<T> epi, RowLn<T> ln) {
   typedef GemmCfg<T> C;
   typedef typename Vec16<T>::type V;
-  constexpr int BM = 64, CH = 128;
-  __shared__ __attribute__((aligned(16))) bf16 lds_all[C::tile(BM) + C::tile(C::BN)];   // 27 KB, fp32 36 KB
+  constexpr int CH = 128, NQ = BM / 16;      // NQ: row groups of a lane
+  static_assert(BM == 64 || (BM == 32 && S > 0), "rows of a tile");
+  typedef PipeLoop<BM, CH, 1, S> PL;
+  __shared__ __attribute__((aligned(16))) bf16 lds_all[S ? PL::LDS : C::tile(BM) + C::tile(C::BN)];   // 48 or 72 KB; 27 KB, fp32 36 KB
   __shared__ __attribute__((aligned(16))) float wbl[HB > 0 ? HB * CH : 4];      // w_bias as [h][c], zero beyond H
   if constexpr (HB > 0) {
     for (int i = threadIdx.x; i < HB * CH; i += 256) {
@@ -1284,10 +1384,13 @@ __global__ __launch_bounds__(256) void gemm64r_kernel(Operand A, Operand B, Gemm
   const T* pa = (const T*)A.ptr;
   const T* pb = (const T*)B.ptr;
 
-  f32x16 acc[2][1], lo[2][1];
+  f32x16 acc[BM / 32][1];
+  if constexpr (S > 0) {
+    PL::run(acc, lds_all, A, pa, m0, sh.M, B, pb, 0, sh.N, sh.K);
+  } else {
+  f32x16 lo[2][1];
   gemm_zero(acc);
   gemm_zero(lo);
-
   const int kv = tid & 7;
   long long aa[2];
   bool aok[2];
@@ -1338,34 +1441,35 @@ __global__ __launch_bounds__(256) void gemm64r_kernel(Operand A, Operand B, Gemm
   }
   gemm_sum<T>(acc, lo);
   gemm_redo<T>(acc, pa, A, m0, sh.M, pb, B, wave * 32, sh.N, 0, sh.K, l32, g);
+  }
 
   // wave-private staging of the 32 x 32 sub-tiles; lane -> 8 consecutive columns of the rows
-  // rloc(q) = 32 (q / 2) + 16 (q % 2) + lane / 4, q = 0..3
+  // rloc(q) = 32 (q / 2) + 16 (q % 2) + lane / 4, q = 0..NQ-1
   constexpr int WS = 32 + 4;
   static_assert((4 * 32 * WS + 4 * BM * 2) * sizeof(float) <= sizeof(lds_all), "stage tiles and row sums must fit");
   float* stage = reinterpret_cast<float*>(lds_all) + wave * 32 * WS;
   float* rowred = reinterpret_cast<float*>(lds_all) + 4 * 32 * WS;   // [wave][row][2]
   const int c8 = (lane & 3) * 8, n = wave * 32 + c8;
-  float vals[4][8];
+  float vals[NQ][8];
   // every global load of the epilogue is issued here, before the accumulators go through LDS (raw registers)
   float gm[8];
 #pragma unroll
   for (int e = 0; e < 8; e++) gm[e] = ln.gamma[n + e];
   typename EpiGeneric<T>::ColV cv;
-  typename EpiGeneric<T>::Pre8 pre[MODE == 1 ? 4 : 1];
-  Raw8<T> xr[MODE == 2 ? 4 : 1], pr[MODE == 2 ? 4 : 1], gr[MODE == 2 ? 4 : 1], g2[G2 ? 4 : 1];   // G2: the kernel takes gin2
-  float mean[MODE == 2 ? 4 : 1], rstd[MODE == 2 ? 4 : 1];
-  float dbv[HB > 0 ? 4 : 1][HB > 0 ? HB : 1];
+  typename EpiGeneric<T>::Pre8 pre[MODE == 1 ? NQ : 1];
+  Raw8<T> xr[MODE == 2 ? NQ : 1], pr[MODE == 2 ? NQ : 1], gr[MODE == 2 ? NQ : 1], g2[G2 ? NQ : 1];   // G2: the kernel takes gin2
+  float mean[MODE == 2 ? NQ : 1], rstd[MODE == 2 ? NQ : 1];
+  float dbv[HB > 0 ? NQ : 1][HB > 0 ? HB : 1];
   if constexpr (MODE == 1) {
     epi.template colv<F>(n, cv);
 #pragma unroll
-    for (int q = 0; q < 4; q++) {
+    for (int q = 0; q < NQ; q++) {
       const int m = m0 + (q >> 1) * 32 + (q & 1) * 16 + (lane >> 2);
       if (m < sh.M) epi.template pre8<F>(0, m, n, cv, pre[q]);
     }
   } else {
 #pragma unroll
-    for (int q = 0; q < 4; q++) {
+    for (int q = 0; q < NQ; q++) {
       const int m = m0 + (q >> 1) * 32 + (q & 1) * 16 + (lane >> 2);
       xr[q].zero(); pr[q].zero(); gr[q].zero();
       if constexpr (G2) g2[q].zero();
@@ -1398,7 +1502,7 @@ __global__ __launch_bounds__(256) void gemm64r_kernel(Operand A, Operand B, Gemm
   }
   __syncthreads();   // all waves are done with the operand tiles
 #pragma unroll
-  for (int i = 0; i < 2; i++) {
+  for (int i = 0; i < BM / 32; i++) {
 #pragma unroll
     for (int a = 0; a < 16; a++) stage[acc_row(g, a) * WS + l32] = acc[i][0][a];
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -1421,9 +1525,9 @@ __global__ __launch_bounds__(256) void gemm64r_kernel(Operand A, Operand B, Gemm
     return (rowred[(0 * BM + rloc) * 2 + j] + rowred[(1 * BM + rloc) * 2 + j]) + (rowred[(2 * BM + rloc) * 2 + j] + rowred[(3 * BM + rloc) * 2 + j]);
   };
   if constexpr (MODE == 1) {
-    float mu[4];
+    float mu[NQ];
 #pragma unroll
-    for (int q = 0; q < 4; q++) {
+    for (int q = 0; q < NQ; q++) {
       const int rloc = (q >> 1) * 32 + (q & 1) * 16 + (lane >> 2), m = m0 + rloc;
       float s = 0.0f;
       if (m < sh.M) {
@@ -1436,7 +1540,7 @@ __global__ __launch_bounds__(256) void gemm64r_kernel(Operand A, Operand B, Gemm
     }
     __syncthreads();
 #pragma unroll
-    for (int q = 0; q < 4; q++) {
+    for (int q = 0; q < NQ; q++) {
       const int rloc = (q >> 1) * 32 + (q & 1) * 16 + (lane >> 2);
       mu[q] = row_total(rloc, 0) * (1.0f / CH);
       float s = 0.0f;
@@ -1450,7 +1554,7 @@ __global__ __launch_bounds__(256) void gemm64r_kernel(Operand A, Operand B, Gemm
 #pragma unroll
     for (int e = 0; e < 8; e++) bt[e] = ln.beta[n + e];
 #pragma unroll
-    for (int q = 0; q < 4; q++) {
+    for (int q = 0; q < NQ; q++) {
       const int rloc = (q >> 1) * 32 + (q & 1) * 16 + (lane >> 2), m = m0 + rloc;
       if (m < sh.M) {
         const float rstd = rsqrtf(row_total(rloc, 1) * (1.0f / CH) + ln.eps);
@@ -1481,10 +1585,10 @@ __global__ __launch_bounds__(256) void gemm64r_kernel(Operand A, Operand B, Gemm
       static_assert(4 * BM * HB <= 4 * 32 * WS, "bias row sums must fit in the staging area");
       const float* brd = reinterpret_cast<const float*>(lds_all);
       __syncthreads();
-      const int row = tid & 63, m = m0 + row;
+      const int row = tid & (BM - 1), m = m0 + row;
       if (m < sh.M) {
 #pragma unroll
-        for (int hh = tid >> 6; hh < HB; hh += 4)
+        for (int hh = tid / BM; hh < HB; hh += 256 / BM)
           if (hh < ln.H)
             ln.bias_out[(long long)hh * sh.M + m] = (brd[(0 * BM + row) * HB + hh] + brd[(1 * BM + row) * HB + hh]) +
                                                     (brd[(2 * BM + row) * HB + hh] + brd[(3 * BM + row) * HB + hh]);
@@ -1495,7 +1599,7 @@ __global__ __launch_bounds__(256) void gemm64r_kernel(Operand A, Operand B, Gemm
 #pragma unroll
     for (int e = 0; e < 8; e++) { dgs[e] = 0.0f; dbs[e] = 0.0f; }
 #pragma unroll
-    for (int q = 0; q < 4; q++) {
+    for (int q = 0; q < NQ; q++) {
       const int rloc = (q >> 1) * 32 + (q & 1) * 16 + (lane >> 2), m = m0 + rloc;
       float s1 = 0.0f, s2 = 0.0f;
       if (m < sh.M) {
@@ -1529,7 +1633,7 @@ __global__ __launch_bounds__(256) void gemm64r_kernel(Operand A, Operand B, Gemm
     }
     __syncthreads();
 #pragma unroll
-    for (int q = 0; q < 4; q++) {
+    for (int q = 0; q < NQ; q++) {
       const int rloc = (q >> 1) * 32 + (q & 1) * 16 + (lane >> 2), m = m0 + rloc;
       if (m < sh.M) {
         const float s1 = row_total(rloc, 0) * (1.0f / CH), s2 = row_total(rloc, 1) * (1.0f / CH);
@@ -1547,7 +1651,7 @@ __global__ __launch_bounds__(256) void gemm64r_kernel(Operand A, Operand B, Gemm
         store8<T>(ln.gout + (long long)m * CH + n, o);
       }
     }
-    // column sums over the workgroup's 64 rows: the 16 lanes of a wave with the same columns, rows in a fixed order
+    // column sums over the workgroup's rows: the 16 lanes of a wave with the same columns, rows in a fixed order
 #pragma unroll
     for (int e = 0; e < 8; e++) {
 #pragma unroll
@@ -1560,7 +1664,7 @@ __global__ __launch_bounds__(256) void gemm64r_kernel(Operand A, Operand B, Gemm
       store8<float>(pp + CH + n, dbs);
     }
     if constexpr (HB > 0) {
-      // bias weight: sum over the 64 rows of y[row][c] db[h][row], 32 rows at a time through LDS (y in fp32 where the
+      // bias weight: sum over the rows of y[row][c] db[h][row], 32 rows at a time through LDS (y in fp32 where the
       // accumulator staging was): thread -> channel c = tid % 128 and HB / 2 heads, rows in order
       constexpr int YL = CH + 4, HH2 = HB / 2;
       static_assert(32 * YL + 32 * HB <= 4 * 32 * WS, "y tile and db rows must fit in the staging area");
@@ -1573,7 +1677,7 @@ __global__ __launch_bounds__(256) void gemm64r_kernel(Operand A, Operand B, Gemm
       for (int j = 0; j < HH2; j++) accw[j] = 0.0f;
       const int cc = tid & 127, h0 = (tid >> 7) * HH2;
 #pragma unroll
-      for (int half = 0; half < 2; half++) {
+      for (int half = 0; half < BM / 32; half++) {
         __syncthreads();   // half 0: every wave is past its row-sum reads; half 1: the first half's tile has been read
 #pragma unroll
         for (int qq = 0; qq < 2; qq++) {
@@ -1613,12 +1717,14 @@ __global__ __launch_bounds__(256) void gemm64r_kernel(Operand A, Operand B, Gemm
 // alone 9 us faster, the two-stream step 18 us slower (64-row tiles take in 25 % more operand bytes per flop than
 // the 128 x 128 kernel they replace, and the forward GEMMs are the ones that run at its full rate): not kept.
 // ---------------------------------------------------------------------------
-template <typename T>
+template <typename T, int S = 0, int BM = 64>
 __global__ __launch_bounds__(256, sizeof(T) == 4 ? 2 : 1) void gemm64w_kernel(Operand A, Operand B, GemmShape sh, RowLn<T> ln) {
   typedef GemmCfg<T> C;
   typedef typename Vec16<T>::type V;
-  constexpr int BM = 64, CH = 256;
-  __shared__ __attribute__((aligned(16))) bf16 lds_all[C::tile(BM) + C::tile(CH)];   // 45 KB, fp32 60 KB
+  constexpr int CH = 256;
+  static_assert(BM == 64 || (BM == 32 && S > 0), "rows of a tile");
+  typedef PipeLoop<BM, CH, 1, S> PL;
+  __shared__ __attribute__((aligned(16))) bf16 lds_all[S ? PL::LDS : C::tile(BM) + C::tile(CH)];   // 80 KB; 45 KB, fp32 60 KB
   bf16* lds_a = lds_all;
   bf16* lds_b = lds_all + C::tile(BM);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -1627,10 +1733,13 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 2 : 1) void gemm64w_kernel(Op
   const T* pa = (const T*)A.ptr;
   const T* pb = (const T*)B.ptr;
 
-  f32x16 acc[2][2], lo[2][2];
+  f32x16 acc[BM / 32][2];
+  if constexpr (S > 0) {
+    PL::run(acc, lds_all, A, pa, m0, sh.M, B, pb, 0, sh.N, sh.K);
+  } else {
+  f32x16 lo[2][2];
   gemm_zero(acc);
   gemm_zero(lo);
-
   const int kv = tid & 7;
   long long aa[2];
   bool aok[2];
@@ -1687,6 +1796,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 2 : 1) void gemm64w_kernel(Op
   }
   gemm_sum<T>(acc, lo);
   gemm_redo<T>(acc, pa, A, m0, sh.M, pb, B, wave * 64, sh.N, 0, sh.K, l32, g);
+  }
 
   constexpr int WS = 64 + 4;
   static_assert((4 * 32 * WS + 2 * 4 * 32 * 2) * sizeof(float) <= sizeof(lds_all), "stage tiles and row sums must fit");
@@ -1702,7 +1812,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 2 : 1) void gemm64w_kernel(Op
   for (int e = 0; e < 8; e++) { dgs[e] = 0.0f; dbs[e] = 0.0f; }
   __syncthreads();   // all waves are done with the operand tiles
 #pragma unroll
-  for (int i = 0; i < 2; i++) {
+  for (int i = 0; i < BM / 32; i++) {
     float* rowred = rowred_all + i * 4 * 32 * 2;
     auto row_total = [&](int r, int j) {
       return (rowred[(0 * 32 + r) * 2 + j] + rowred[(1 * 32 + r) * 2 + j]) + (rowred[(2 * 32 + r) * 2 + j] + rowred[(3 * 32 + r) * 2 + j]);
@@ -1783,7 +1893,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 2 : 1) void gemm64w_kernel(Op
     }
   }
   {
-    // column sums over the workgroup's 64 rows: the 8 lanes of a wave with the same columns
+    // column sums over the workgroup's rows: the 8 lanes of a wave with the same columns
 #pragma unroll
     for (int e = 0; e < 8; e++) {
 #pragma unroll
@@ -1805,12 +1915,18 @@ static thread_local int g_gemm_last_features = EF_ALL;
 // epilogue, one of the feature sets below); false: nothing was launched and the caller takes the separate kernels
 template <typename T, int MODE>
 static inline bool launch_gemm64r(hipStream_t st, const Operand& A, const Operand& B, const GemmShape& sh, const EpiGeneric<T>& epi,
-                                  const RowLn<T>& ln, bool launch = true) {
+                                  const RowLn<T>& ln, bool launch = true, int* tiles = nullptr) {
   if ((sh.N != 128 && sh.N != 256) || sh.M <= 0 || sh.batch != 1 || sh.k_chunk != 0) return false;
   if (A.k_stride != 1 || B.k_stride != 1) return false;
   if (!gemm_operand_ok<T>(A, true, sh.M, sh) || !gemm_operand_ok<T>(B, true, sh.N, sh)) return false;
   auto p16 = [](const void* p) { return ((uintptr_t)p) % 16 == 0; };
-  dim3 grid((unsigned)((sh.M + 63) / 64)), block(256);
+  const bool pipe = std::is_same<T, bf16>::value && pipe_operand_ok(A, sh.M, sh.K) && pipe_operand_ok(B, sh.N, sh.K);
+  constexpr int SP = std::is_same<T, bf16>::value ? 2 : 0;
+  // Up to one round of 64-row tiles over the CUs: 32-row ones, twice the workgroups and half the epilogue in each (one stream, s 90, r 112 step 1217 ->
+  // 1189 us, s 40, r 60 845 -> 804; s 128, r 97 forward 351 -> 342).  Two streams: 871 and 871; to two rounds s 128, r 256 2316 -> 2334.
+  const int bm = pipe && (sh.M + 63) / 64 <= 256 ? 32 : 64;
+  if (tiles) *tiles = (sh.M + bm - 1) / bm;
+  const dim3 grid((unsigned)((sh.M + bm - 1) / bm)), block(256);
   if (sh.N == 256) {   // the 256-channel kernel: LayerNorm backward only, without the options
     if constexpr (MODE == 1) {
       return false;
@@ -1818,37 +1934,48 @@ static inline bool launch_gemm64r(hipStream_t st, const Operand& A, const Operan
       if (ln.prev || ln.db || ln.gin2) return false;
       if (!p16(ln.x) || !p16(ln.gout) || (ln.gin && !p16(ln.gin)) || !p16(ln.partial)) return false;
       if (!launch) return true;
-      hipLaunchKernelGGL((gemm64w_kernel<T>), grid, block, 0, st, A, B, sh, ln);
+      constexpr int BS = std::is_same<T, bf16>::value ? 32 : 64;
+      if (pipe && bm == 32) hipLaunchKernelGGL((gemm64w_kernel<T, SP, BS>), grid, block, 0, st, A, B, sh, ln);
+      else if (pipe) hipLaunchKernelGGL((gemm64w_kernel<T, SP>), grid, block, 0, st, A, B, sh, ln);
+      else hipLaunchKernelGGL((gemm64w_kernel<T>), grid, block, 0, st, A, B, sh, ln);
       g_gemm_last_features = 0;
       return true;
     }
   }
   if constexpr (MODE == 1) {
+    constexpr int BS = std::is_same<T, bf16>::value ? 32 : 64;
     if (!epi.vec_ok(sh.N) || !p16(ln.y)) return false;
     const int f = epi.features();
     if (ln.bias_out && (ln.H < 1 || ln.H > 8 || !ln.w_bias)) return false;
     if (!launch) return (f & ~(EF_BIASN | EF_AUX | EF_MUL | EF_RES)) == 0;
+#define PE_GEMM64R_1(S, R, BM) {                                                                                           \
+      if (!ln.bias_out) hipLaunchKernelGGL((gemm64r_kernel<T, (S), 1, 0, false, R, BM>), grid, block, 0, st, A, B, sh, epi, ln); \
+      else if (ln.H <= 4) hipLaunchKernelGGL((gemm64r_kernel<T, (S), 1, 4, false, R, BM>), grid, block, 0, st, A, B, sh, epi, ln);   \
+      else hipLaunchKernelGGL((gemm64r_kernel<T, (S), 1, 8, false, R, BM>), grid, block, 0, st, A, B, sh, epi, ln); }
 #define PE_GEMM64R_SPEC(S)                                                                                             \
     if ((f & ~(S)) == 0) {                                                                                             \
-      if (!ln.bias_out) hipLaunchKernelGGL((gemm64r_kernel<T, (S), 1, 0>), grid, block, 0, st, A, B, sh, epi, ln);     \
-      else if (ln.H <= 4) hipLaunchKernelGGL((gemm64r_kernel<T, (S), 1, 4>), grid, block, 0, st, A, B, sh, epi, ln);   \
-      else hipLaunchKernelGGL((gemm64r_kernel<T, (S), 1, 8>), grid, block, 0, st, A, B, sh, epi, ln);                  \
+      if (pipe && bm == 32) PE_GEMM64R_1(S, SP, BS) else if (pipe) PE_GEMM64R_1(S, SP, 64) else PE_GEMM64R_1(S, 0, 64)                                                       \
       g_gemm_last_features = (S);                                                                                      \
       return true;                                                                                                     \
     }
     PE_GEMM64R_SPEC(EF_BIASN | EF_RES)
     PE_GEMM64R_SPEC(EF_BIASN | EF_AUX | EF_MUL | EF_RES)
 #undef PE_GEMM64R_SPEC
+#undef PE_GEMM64R_1
     return false;
   } else {
     if (!p16(ln.x) || !p16(ln.gout) || (ln.gin && !p16(ln.gin)) || (ln.gin2 && !p16(ln.gin2)) || (ln.prev && !p16(ln.prev)) || !p16(ln.partial)) return false;
     if (ln.db && (ln.H < 1 || ln.H > 8 || !ln.w_bias || !ln.beta)) return false;
     if (ln.gin2 && ln.db) return false;   // no instantiation with both
     if (!launch) return true;
-    if (ln.gin2) hipLaunchKernelGGL((gemm64r_kernel<T, 0, 2, 0, true>), grid, block, 0, st, A, B, sh, epi, ln);
-    else if (!ln.db) hipLaunchKernelGGL((gemm64r_kernel<T, 0, 2, 0>), grid, block, 0, st, A, B, sh, epi, ln);
-    else if (ln.H <= 4) hipLaunchKernelGGL((gemm64r_kernel<T, 0, 2, 4>), grid, block, 0, st, A, B, sh, epi, ln);
-    else hipLaunchKernelGGL((gemm64r_kernel<T, 0, 2, 8>), grid, block, 0, st, A, B, sh, epi, ln);
+    constexpr int BS = std::is_same<T, bf16>::value ? 32 : 64;
+#define PE_GEMM64R_2(R, BM) {                                                                                               \
+      if (ln.gin2) hipLaunchKernelGGL((gemm64r_kernel<T, 0, 2, 0, true, R, BM>), grid, block, 0, st, A, B, sh, epi, ln);     \
+      else if (!ln.db) hipLaunchKernelGGL((gemm64r_kernel<T, 0, 2, 0, false, R, BM>), grid, block, 0, st, A, B, sh, epi, ln); \
+      else if (ln.H <= 4) hipLaunchKernelGGL((gemm64r_kernel<T, 0, 2, 4, false, R, BM>), grid, block, 0, st, A, B, sh, epi, ln); \
+      else hipLaunchKernelGGL((gemm64r_kernel<T, 0, 2, 8, false, R, BM>), grid, block, 0, st, A, B, sh, epi, ln); }
+    if (pipe && bm == 32) PE_GEMM64R_2(SP, BS) else if (pipe) PE_GEMM64R_2(SP, 64) else PE_GEMM64R_2(0, 64)
+#undef PE_GEMM64R_2
     g_gemm_last_features = 0;
     return true;
   }
@@ -2335,6 +2462,10 @@ static thread_local bool g_gemm_last_rows = false;
 template <class Epi>
 static inline bool launch_gemm_deep(hipStream_t st, const Operand& A, bool a_kc, const Operand& B, bool b_kc, const GemmShape& sh, const Epi& epi);
 static thread_local bool g_gemm_last_deep = false;
+// few tiles of k-contiguous operands (pe_pipe.h): false = not launched
+template <class Epi> static inline bool launch_gemm_pipe(hipStream_t st, const Operand& A, const Operand& B, const GemmShape& sh, const Epi& epi);
+static inline bool pipe_over_small(const GemmShape& sh);
+static thread_local bool g_gemm_last_pipe = false;
 
 // Operands that break the 16-byte vector rules (odd leading dimensions) take the
 // element-wise loader and the per-element epilogue: same tiles, same arithmetic, slower.
@@ -2353,21 +2484,25 @@ static inline int launch_gemm(hipStream_t st, const Operand& A, bool a_kc, const
   g_gemm_last_small = false;
   g_gemm_last_rows = false;
   g_gemm_last_deep = false;
+  g_gemm_last_pipe = false;
+  bool ve = al && epi.vec_ok(sh.N);
+  if (used_vec) *used_vec = ve;
+  if (used_narrow) *used_narrow = false;
   if constexpr (!Epi::TM_GATE) {
     const bool sve = epi.vec_ok(sh.N);
     // bf16 parameter gradients have a kernel that is faster even there (gemm_dwx_kernel)
     const bool dwx = std::is_same<Epi, EpiPartial>::value && std::is_same<T, bf16>::value && wave_groups && !a_kc && !b_kc;
     if (!dwx && (sve || Epi::ELEM) && small_gemm_fits<T>(sh.M, sh.N, sh.k_chunk > 0 ? sh.k_chunk : sh.K, sh.batch, a_kc, b_kc)) {
-      launch_gemm_small<T, Epi>(st, A, a_kc, B, b_kc, sh, epi);
-      g_gemm_last_small = true;
-      if (used_vec) *used_vec = sve;
-      if (used_narrow) *used_narrow = false;
+      if constexpr (std::is_same<T, bf16>::value)
+        g_gemm_last_pipe = ve && a_kc && b_kc && pipe_over_small(sh) && launch_gemm_pipe<Epi>(st, A, B, sh, epi);
+      if (!g_gemm_last_pipe) {
+        launch_gemm_small<T, Epi>(st, A, a_kc, B, b_kc, sh, epi);
+        g_gemm_last_small = true;
+        if (used_vec) *used_vec = sve;
+      }
       return hipGetLastError() == hipSuccess ? 0 : -2;
     }
   }
-  bool ve = al && epi.vec_ok(sh.N);
-  if (used_vec) *used_vec = ve;
-  if (used_narrow) *used_narrow = false;
   if constexpr (std::is_same<T, bf16>::value) {
     if (ve && a_kc && b_kc && launch_gemm_rows<Epi>(st, A, B, sh, epi)) {
       g_gemm_last_rows = true;
@@ -2375,6 +2510,10 @@ static inline int launch_gemm(hipStream_t st, const Operand& A, bool a_kc, const
     }
     if (ve && launch_gemm_deep<Epi>(st, A, a_kc, B, b_kc, sh, epi)) {
       g_gemm_last_deep = true;
+      return hipGetLastError() == hipSuccess ? 0 : -2;
+    }
+    if (ve && a_kc && b_kc && launch_gemm_pipe<Epi>(st, A, B, sh, epi)) {
+      g_gemm_last_pipe = true;
       return hipGetLastError() == hipSuccess ? 0 : -2;
     }
   }

@@ -754,6 +754,33 @@ def test_row_streaming_gemms(name, s, r, two_streams, ks):
     _assert(errs, worst, tol, stats)
 
 
+@pytest.mark.parametrize("name,s,r,two_streams,labels", [
+    ("af2_initial", 45, 67, False, ("attn out", "trans 2", "attn dog+pre", "opm project")),      # ragged rows, head-major and [(i,p)][(j,q)] operands
+    ("af2_initial", 131, 33, True, ("attn out", "attn dog+pre")),                                # strided rows (column attention)
+    ("extra_msa", 260, 33, False, ("trans 1", "trans dh")),                                      # one k-step (K = 64), ReLU decisions out and in
+    ("af2_initial", 9, 64, False, ("trimul out", "trimul da+gate")),                             # a batch of 64 x 64 contractions, one tile each
+])
+def test_few_tile_gemms(name, s, r, two_streams, labels):
+    """GEMMs of few 64 x 64 tiles with operands by DMA (pe_pipe.h): remainders in rows, one k-step and more, two-level index maps of both
+    kinds, a batch, each epilogue that has a kernel there; against the oracle at the path's tolerance."""
+    dims, table, inp = _case(name, s=s, r=r)
+    table, n = param_table(dims)
+    inp = make_inputs(dims, table, n, ("random_residues", 0.1), s + r)
+    names = _kernels_by_label(BlockRun(dims, inp, two_streams=two_streams))
+    for k in labels:
+        assert any(v.startswith("gemm_pipe_kernel") for v in names[k]), (k, names[k])
+    errs, worst, tol, stats = check_case(dims, table, inp, two_streams=two_streams)
+    _assert(errs, worst, tol, stats)
+
+
+@pytest.mark.parametrize("s,r", [(5, 127), (5, 128), (5, 129), (129, 127)])
+def test_row_complete_epilogues_on_32_and_64_rows(s, r):
+    """The row-complete kernels at the line between 32-row tiles (up to 16384 rows) and 64-row tiles, and with remainders in both."""
+    dims, table, inp = _case("af2_initial", s=s, r=r)
+    errs, worst, tol, stats = check_case(dims, table, inp, two_streams=False)
+    _assert(errs, worst, tol, stats)
+
+
 def _rows_wave_slots(K, N):
     """Row blocks of 32 that the row-streaming kernel's waves take at once, per panel (launch_rows_np): 256 or 512 workgroups
     of eight waves, shared among the panels in groups of eight workgroups."""
