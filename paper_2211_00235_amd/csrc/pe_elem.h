@@ -1428,22 +1428,41 @@ __global__ __launch_bounds__(256) void add2x8_kernel(const T* a, const T* b, T* 
 }
 // ---------------------------------------------------------------------------
 // Outer product mean normaliser: inv_norm[i][j] = 1 / (eps + sum_s mask[s][i] mask[s][j])
+// A workgroup has a 32 x 32 tile of residue pairs on the fp32 matrix unit (products of 0 / 1 masks and their sums are exact); its waves, one
+// for every 16 sequences up to eight, take 16 sequences at a time in turn and add up through LDS.  With a thread per pair, walking
+// through all sequences alone, the launch was a chain of memory round trips (us, then -> now): s 90, r 112 11.1 -> 5.0; s 128, r 97
+// 5.4 -> 4.4; s 24, r 48 4.8 -> 4.0; s 512, r 384 46 -> 20; s 5120, r 384 251 -> 77 (sixteen waves 56 there, but 57 at s 512 beside the pair
+// branch, where their workgroups wait for a whole CU).
 // ---------------------------------------------------------------------------
-__global__ void opm_norm_kernel(const float* mask, float* inv_norm, int s, int r, float eps) {
-  long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= (long long)r * r) return;
-  int i = idx / r, j = idx % r;
-  float acc = 0.0f;   // 0/1 products: any summation order gives the same (exact) count
-  int t = 0;
-  for (; t + 32 <= s; t += 32) {   // 64 independent loads in flight per thread: the loop is a chain of memory round trips
-    float a[32], b[32];
+__global__ __launch_bounds__(512) void opm_norm_kernel(const float* mask, float* inv_norm, int s, int r, float eps) {
+  __shared__ float part[8][1024];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6, l32 = lane & 31, g = lane >> 5;
+  const int i0 = blockIdx.y * 32, j0 = blockIdx.x * 32;
+  const float* pi = mask + min(i0 + l32, r - 1);
+  const float* pj = mask + min(j0 + l32, r - 1);
+  f32x16 acc;
 #pragma unroll
-    for (int u = 0; u < 32; u++) { a[u] = mask[(long long)(t + u) * r + i]; b[u] = mask[(long long)(t + u) * r + j]; }
+  for (int e = 0; e < 16; e++) acc[e] = 0.0f;
+  for (int t0 = wave * 16; t0 < s; t0 += nw * 16) {
+    float a[8], b[8];
 #pragma unroll
-    for (int u = 0; u < 32; u++) acc += a[u] * b[u];
+    for (int u = 0; u < 8; u++) {
+      const int t = t0 + 2 * u + g;
+      a[u] = t < s ? pi[(long long)t * r] : 0.0f;
+      b[u] = t < s ? pj[(long long)t * r] : 0.0f;
+    }
+#pragma unroll
+    for (int u = 0; u < 8; u++) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[u], b[u], acc, 0, 0, 0);
   }
-  for (; t < s; t++) acc += mask[(long long)t * r + i] * mask[(long long)t * r + j];
-  inv_norm[idx] = 1.0f / (eps + acc);
+#pragma unroll
+  for (int e = 0; e < 16; e++) part[wave][acc_row(g, e) * 32 + l32] = acc[e];
+  __syncthreads();
+  for (int q = threadIdx.x; q < 1024; q += blockDim.x) {
+    const int i = i0 + (q >> 5), j = j0 + (q & 31);
+    float t = 0.0f;
+    for (int w = 0; w < nw; w++) t += part[w][q];
+    if (i < r && j < r) inv_norm[(long long)i * r + j] = 1.0f / (eps + t);
+  }
 }
 
 // zero n 16-byte words (buffers are 256-byte multiples)

@@ -754,6 +754,21 @@ def test_row_streaming_gemms(name, s, r, two_streams, ks):
     _assert(errs, worst, tol, stats)
 
 
+@pytest.mark.parametrize("s,r", [(1, 33), (15, 32), (17, 31), (33, 65), (257, 33), (300, 8)])
+def test_outer_product_normaliser(s, r):
+    """Counts of sequences per residue pair on 32 x 32 tiles, up to eight waves of 16 sequences: remainders in residues, in a wave's
+    sequences and in the waves' rounds; masks that leave some pairs few sequences."""
+    dims, table, inp = _case("tiny", dtype=0, s=s, r=r)
+    rng = np.random.default_rng(s * 1000 + r)
+    inp["msa_mask"] = (rng.random((s, r)) < 0.6).astype(inp["msa_mask"].dtype)
+    inp["msa_mask"][0, :] = 1.0
+    _, z0, _, _ = ev.block_fwd(dims, inp["params"], inp["msa"], inp["pair"], inp["msa_mask"], inp["pair_mask"], want_cache=False)
+    run = BlockRun(dims, inp)
+    run.fwd(use_ctx=True)
+    run.sync()
+    assert rel_err(to_np(run.pair_out), z0) <= TOL[0]
+
+
 @pytest.mark.parametrize("name,s,r,two_streams,labels", [
     ("af2_initial", 45, 67, False, ("attn out", "trans 2", "attn dog+pre", "opm project")),      # ragged rows, head-major and [(i,p)][(j,q)] operands
     ("af2_initial", 131, 33, True, ("attn out", "attn dog+pre")),                                # strided rows (column attention)
