@@ -25,16 +25,19 @@
  *  - Calls only ENQUEUE work.  At entry stream_pair is made to wait for the
  *    work already queued on stream_msa (inputs have to be ready with respect
  *    to stream_msa); at return both streams are joined, so outputs may be
- *    consumed on either stream.  stream_msa == stream_pair is allowed and
- *    serialises the branches.
+ *    consumed on either stream.  stream_msa == stream_pair is allowed: the
+ *    call is then ordered like any other work on that stream, and inside it
+ *    the pair branch runs beside the MSA branch on a stream of the handle
+ *    (one after the other for the smallest blocks, one branch, the AF2
+ *    ordering, under PE_OPT_KERNEL_TIMING, PE_OPT_SYNC_DEBUG or
+ *    PE_OPT_SIDE_STREAMS, and in a capture that is the handle's first
+ *    one-stream call).
  *  - Results are deterministic: no atomics, every reduction in a fixed order.
- *    A call that has the device to itself (stream_msa == stream_pair, one
- *    branch selected with PE_OPT_BRANCHES, or PE_VARIANT_AF2, whose data flow
- *    is serial) takes a parameter-gradient kernel
- *    that sums the contraction index in another fixed order than the
- *    two-stream call does: outputs and input cotangents are bit-identical
- *    between the two modes, bf16-path parameter gradients agree to fp32
- *    rounding.
+ *    A call whose branches run one after the other (see above) takes a
+ *    parameter-gradient kernel that sums the contraction index in another
+ *    fixed order than a call whose branches run side by side does: outputs
+ *    and input cotangents are bit-identical between the two modes, bf16-path
+ *    parameter gradients agree to fp32 rounding.
  *  - Return value 0 = PE_OK, negative = error (see pe_strerror).  Arguments
  *    are validated before anything is launched.
  */
@@ -121,7 +124,9 @@ typedef struct pe_ctx_entry {
 } pe_ctx_entry;
 
 /* Handle: owns a few hipEvents used to fork/join the streams and, once
- * PE_OPT_SIDE_STREAMS has been set, two side streams (default priority).
+ * PE_OPT_SIDE_STREAMS has been set, two side streams, and after the first
+ * call with one stream the pair branch's stream (all of default priority;
+ * pe_destroy waits for the work on the last).
  * Host state only.  Not thread safe: one handle per host thread; calls on one
  * handle must not overlap.  The compute calls may be captured into a HIP
  * graph by the caller (they allocate nothing, never synchronise the host and

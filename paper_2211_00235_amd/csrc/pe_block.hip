@@ -48,6 +48,8 @@ struct pe_handle {
   hipStream_t side[2];              // side stream of the MSA branch / of the pair branch
   hipEvent_t side_ev[32];           // ring of fork/join events
   int side_ev_next;
+  hipStream_t pair;                 // the pair branch's stream of calls with one stream (pair_stream), created by the first of them
+  hipEvent_t pair_ev;
   std::vector<ProfRec> recs;        // one per timed launch since the last collect
   std::vector<hipEvent_t> ev_pool;  // reusable timing events
   std::string last_error;
@@ -737,7 +739,7 @@ template <typename T> struct Runner {
       memset(&ln, 0, sizeof(ln));
       ln.gamma = P(nxt.g_off); ln.beta = P(nxt.b_off); ln.y = nxt.y; ln.stats = nxt.stats; ln.eps = d.ln_eps;
       if (nxt.direct) { ln.bias_out = nxt.direct; ln.stats2 = nxt.zstats; ln.w_bias = P(nxt.w_bias_off); ln.H = nxt.H; }
-      GemmShape sh{M, N, K, 1, 0, 0};
+      GemmShape sh{M, N, K, 1, 0, 0, 0, alone() ? 0 : 1};
       prof_begin(st);
       if (launch_gemm64r<T, 1>(st, A, B, sh, e, ln)) {
         char kn[64] = "";
@@ -802,7 +804,7 @@ template <typename T> struct Runner {
         ln.gin2 = fin_add; ln.gout = fin_out;
       }
       EpiGeneric<T> e = epi_plain<T>(dxh, Cc);
-      GemmShape sh{(int)M, Cc, K, 1, 0, 0};
+      GemmShape sh{(int)M, Cc, K, 1, 0, 0, 0, alone() ? 0 : 1};
       join_side(st);   // gout may alias a buffer the side stream is still reading
       prof_begin(st);
       int tiles = 0;
@@ -2207,6 +2209,8 @@ int pe_create(pe_handle** out) {
   h->stack_overlap = 0;
   h->side[0] = h->side[1] = nullptr;
   h->side_ev_next = 0;
+  h->pair = nullptr;
+  h->pair_ev = nullptr;
   for (int i = 0; i < 32; i++) h->side_ev[i] = nullptr;
   for (int i = 0; i < 6; i++) {
     if (hipEventCreateWithFlags(&h->ev[i], hipEventDisableTiming) != hipSuccess) {
@@ -2225,6 +2229,11 @@ int pe_destroy(pe_handle* h) {
   for (auto e : h->ev_pool) (void)hipEventDestroy(e);
   for (int i = 0; i < 2; i++) if (h->side[i]) (void)hipStreamDestroy(h->side[i]);
   for (int i = 0; i < 32; i++) if (h->side_ev[i]) (void)hipEventDestroy(h->side_ev[i]);
+  if (h->pair) {
+    (void)hipStreamSynchronize(h->pair);      // work of the last call may still be on it
+    (void)hipStreamDestroy(h->pair);
+    (void)hipEventDestroy(h->pair_ev);
+  }
   delete h;
   return PE_OK;
 }
@@ -2307,6 +2316,43 @@ size_t pe_workspace_bytes(const pe_dims* d, int with_ctx) {
   return plan_for(*d).total(with_ctx != 0);
 }
 
+// The stream of the pair branch.  A caller that passes one stream gets the branches side by side all the same, the pair branch on a
+// stream of the handle: every call makes stream_pair wait for stream_msa at its entry and joins the two before it returns, so for
+// the caller the work stays in the order of its own stream.  Half of the launches of a short protein leave most CUs idle and the other
+// branch's fill them.  One after the other -> side by side, us: forward s 128, r 97 334 -> 270, s 16, r 33 216 -> 189; step s 90, r 112 1186 -> 892, s 300, r 256
+// 3950 -> 3546, extra-MSA s 300, r 80 1000 -> 626, fp32 s 128, r 128 2900 -> 2600; small widths s 24, r 48 548 -> 519.
+// Two streams cost the host: 40 launches take it 190 us there.  A forward pass over narrow channels (up to 32) that is done earlier stays on one (s 24, r 48 175
+// against 191, s 64, r 64 183 against 190), as do the smallest steps (s 8, r 16 510 against 529).
+// As before for the AlphaFold2 ordering, whose data flow is serial, one branch alone, and calls that time or check
+// kernel by kernel.  The stream is created by the first such call, on the handle's device and not while the caller's stream is captured.
+static bool branches_pay(const pe_dims& d, bool forward) {
+  if (d.variant == PE_VARIANT_AF2) return false;
+  return std::max(d.c_m, d.c_z) > 32 || (long long)d.r * ((long long)d.s * d.c_m + (long long)d.r * d.c_z) >= (forward ? 1 << 18 : 1 << 14);
+}
+static hipStream_t pair_stream(pe_handle* h, hipStream_t sm, hipStream_t sp, bool pays) {
+  if (sm != sp || !pays || h->branches != 3 || h->timing || h->sync_debug || h->side_streams) return sp;
+  int dev = -1;
+  if (hipGetDevice(&dev) != hipSuccess || dev != h->device) return sp;
+  if (!h->pair) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(sm, &cap) != hipSuccess) { (void)hipGetLastError(); return sp; }
+    if (cap != hipStreamCaptureStatusNone) return sp;
+    if (hipEventCreateWithFlags(&h->pair_ev, hipEventDisableTiming) != hipSuccess) { (void)hipGetLastError(); return sp; }
+    if (hipStreamCreateWithFlags(&h->pair, hipStreamNonBlocking) != hipSuccess) {
+      (void)hipGetLastError();
+      (void)hipEventDestroy(h->pair_ev);
+      h->pair = nullptr;
+      return sp;
+    }
+  }
+  return h->pair;
+}
+// a call that failed on the way may have left work on the handle's stream: the caller's waits for it
+static int pair_done(pe_handle* h, hipStream_t sm, hipStream_t sp, int rc) {
+  if (rc != PE_OK && sp == h->pair && sp != sm && hipEventRecord(h->pair_ev, sp) == hipSuccess) (void)hipStreamWaitEvent(sm, h->pair_ev, 0);
+  return rc;
+}
+
 static int block_fwd_call(pe_handle* h, const pe_dims* dims, const void* msa_in, const void* pair_in, const float* msa_mask,
                           const float* pair_mask, const float* params, void* msa_out, void* pair_out, void* ctx, void* workspace,
                           size_t workspace_bytes, void* stream_msa, void* stream_pair, bool forward_only) {
@@ -2325,11 +2371,12 @@ static int block_fwd_call(pe_handle* h, const pe_dims* dims, const void* msa_in,
     if (any_alias(rg, (int)(sizeof(rg) / sizeof(rg[0])))) return PE_ERR_ALIAS;
   }
   if (((uintptr_t)workspace) % 256 || (ctx && ((uintptr_t)ctx) % 256)) return PE_ERR_ARG;
+  const hipStream_t sm = (hipStream_t)stream_msa, sp = pair_stream(h, sm, (hipStream_t)stream_pair, branches_pay(*dims, true));
   if (dims->dtype == PE_BF16)
-    return block_fwd_impl<bf16>(h, *dims, msa_in, pair_in, msa_mask, pair_mask, params, msa_out, pair_out, ctx, workspace,
-                                workspace_bytes, (hipStream_t)stream_msa, (hipStream_t)stream_pair, ctx == nullptr, false, nullptr, forward_only);
-  return block_fwd_impl<float>(h, *dims, msa_in, pair_in, msa_mask, pair_mask, params, msa_out, pair_out, ctx, workspace,
-                               workspace_bytes, (hipStream_t)stream_msa, (hipStream_t)stream_pair, ctx == nullptr, false, nullptr, forward_only);
+    return pair_done(h, sm, sp, block_fwd_impl<bf16>(h, *dims, msa_in, pair_in, msa_mask, pair_mask, params, msa_out, pair_out, ctx, workspace,
+                                workspace_bytes, sm, sp, ctx == nullptr, false, nullptr, forward_only));
+  return pair_done(h, sm, sp, block_fwd_impl<float>(h, *dims, msa_in, pair_in, msa_mask, pair_mask, params, msa_out, pair_out, ctx, workspace,
+                               workspace_bytes, sm, sp, ctx == nullptr, false, nullptr, forward_only));
 }
 int pe_block_fwd(pe_handle* h, const pe_dims* dims, const void* msa_in, const void* pair_in, const float* msa_mask,
                  const float* pair_mask, const float* params, void* msa_out, void* pair_out, void* ctx, void* workspace,
@@ -2387,13 +2434,12 @@ int pe_block_bwd(pe_handle* h, const pe_dims* dims, const void* msa_in, const vo
     if (any_alias(rg, (int)(sizeof(rg) / sizeof(rg[0])))) return PE_ERR_ALIAS;
   }
   if (((uintptr_t)workspace) % 256 || (ctx && ((uintptr_t)ctx) % 256)) return PE_ERR_ARG;
+  const hipStream_t sm = (hipStream_t)stream_msa, sp = pair_stream(h, sm, (hipStream_t)stream_pair, branches_pay(*dims, false));
   if (dims->dtype == PE_BF16)
-    return block_bwd_impl<bf16>(h, *dims, msa_in, pair_in, msa_mask, pair_mask, params, d_msa_out, d_pair_out, d_msa_in,
-                                d_pair_in, d_params, ctx, workspace, workspace_bytes, (hipStream_t)stream_msa,
-                                (hipStream_t)stream_pair);
-  return block_bwd_impl<float>(h, *dims, msa_in, pair_in, msa_mask, pair_mask, params, d_msa_out, d_pair_out, d_msa_in,
-                               d_pair_in, d_params, ctx, workspace, workspace_bytes, (hipStream_t)stream_msa,
-                               (hipStream_t)stream_pair);
+    return pair_done(h, sm, sp, block_bwd_impl<bf16>(h, *dims, msa_in, pair_in, msa_mask, pair_mask, params, d_msa_out, d_pair_out, d_msa_in,
+                                d_pair_in, d_params, ctx, workspace, workspace_bytes, sm, sp));
+  return pair_done(h, sm, sp, block_bwd_impl<float>(h, *dims, msa_in, pair_in, msa_mask, pair_mask, params, d_msa_out, d_pair_out, d_msa_in,
+                               d_pair_in, d_params, ctx, workspace, workspace_bytes, sm, sp));
 }
 
 size_t pe_stack_workspace_bytes(int n_extra, const pe_dims* extra, int n_main, const pe_dims* main_) {
@@ -2442,14 +2488,16 @@ int pe_stack_fwd_bwd(pe_handle* h, int n_extra, const pe_dims* extra, int n_main
                          {workspace, sp.total, true}};
     if (any_alias(rg, (int)(sizeof(rg) / sizeof(rg[0])))) return PE_ERR_ALIAS;
   }
+  const bool pays = (!n_main || branches_pay(*main_, false)) && (!n_extra || branches_pay(*extra, false));
+  const hipStream_t sm = (hipStream_t)stream_msa, st_pair = pair_stream(h, sm, (hipStream_t)stream_pair, pays);
   const int dt = n_main ? main_->dtype : extra->dtype;
   if (dt == PE_BF16)
-    return stack_impl<bf16>(h, n_extra, extra, n_main, main_, sp, extra_msa_in, msa_in, pair_in, extra_msa_mask, msa_mask,
+    return pair_done(h, sm, st_pair, stack_impl<bf16>(h, n_extra, extra, n_main, main_, sp, extra_msa_in, msa_in, pair_in, extra_msa_mask, msa_mask,
                             pair_mask, params, d_msa_out, d_pair_out, msa_out, pair_out, d_extra_msa_in, d_msa_in,
-                            d_pair_in, d_params, (char*)workspace, (hipStream_t)stream_msa, (hipStream_t)stream_pair);
-  return stack_impl<float>(h, n_extra, extra, n_main, main_, sp, extra_msa_in, msa_in, pair_in, extra_msa_mask, msa_mask,
+                            d_pair_in, d_params, (char*)workspace, sm, st_pair));
+  return pair_done(h, sm, st_pair, stack_impl<float>(h, n_extra, extra, n_main, main_, sp, extra_msa_in, msa_in, pair_in, extra_msa_mask, msa_mask,
                            pair_mask, params, d_msa_out, d_pair_out, msa_out, pair_out, d_extra_msa_in, d_msa_in,
-                           d_pair_in, d_params, (char*)workspace, (hipStream_t)stream_msa, (hipStream_t)stream_pair);
+                           d_pair_in, d_params, (char*)workspace, sm, st_pair));
 }
 
 int pe_timing_collect(pe_handle* h, pe_timing_entry* out, int cap) {

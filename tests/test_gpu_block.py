@@ -1000,6 +1000,61 @@ def test_extra_msa_finetune_depth_by_replication():
     assert errs[worst] < tol, (worst, errs[worst])
 
 
+@pytest.mark.parametrize("name,s,r,variant", [("af2_initial", 17, 45, 0), ("extra_msa", 40, 35, 2), ("tiny", 40, 50, 0)])
+def test_one_stream_calls_keep_the_order_of_their_stream(name, s, r, variant):
+    """A call with one stream runs its branches side by side, the pair branch on the handle's own stream: inputs written on the caller's stream
+    right before a call are what both branches read, and outputs copied on it right after are complete, three times without a host
+    synchronisation; equal to the two-stream call's.  Then the same calls captured into a graph on that stream, by a handle that has its own
+    stream by then and by one that does not: three replays each with eager work in between."""
+    import torch
+    dims, table, inp = _case(name, dtype=1, s=s, r=r, variant=variant)
+    outs = ("msa_out", "pair_out", "d_msa_in", "d_pair_in", "d_params")
+    two = BlockRun(dims, inp)
+    two.fwd()
+    two.bwd()
+    two.sync()
+    ref = {k: getattr(two, k).clone() for k in outs}
+    run, fresh = BlockRun(dims, inp, two_streams=False), BlockRun(dims, inp, two_streams=False)
+    src = {k: getattr(run, k).clone() for k in ("msa", "pair", "params")}
+    run.sync()
+    got = []
+    with torch.cuda.stream(run.sm):
+        for _ in range(3):
+            for k in src:
+                getattr(run, k).zero_()
+            for k in outs:
+                getattr(run, k).zero_()
+            for k in src:
+                getattr(run, k).copy_(src[k])
+            run.fwd()
+            run.bwd()
+            got.append({k: getattr(run, k).clone() for k in outs})
+    run.sync()
+    for g in got:
+        for k in outs:
+            assert torch.equal(g[k], ref[k]), k
+    for r_ in (run, fresh):
+        r_.sm = r_.sp = torch.cuda.Stream()      # (the default stream cannot be captured)
+        graph = torch.cuda.CUDAGraph()
+        r_.d_params.zero_()
+        r_.sync()
+        torch.cuda.synchronize()
+        with torch.cuda.graph(graph, stream=r_.sm):
+            r_.fwd()
+            r_.bwd()
+        for rep in range(3):
+            for k in outs:
+                getattr(r_, k).zero_()
+            r_.ctx.zero_()
+            two.fwd()
+            two.bwd()
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            for k in outs[:4] if r_ is fresh else outs:      # serial branches sum parameter gradients in another order
+                assert torch.equal(getattr(r_, k), ref[k]), (rep, k)
+
+
 def test_hip_graph_capture_and_replay():
     """The calls only enqueue work on the caller's streams (no allocation, no host synchronisation,
     no memset nodes), so a caller can capture forward + backward into a HIP graph: three replays,
