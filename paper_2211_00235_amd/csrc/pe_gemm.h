@@ -2467,7 +2467,6 @@ static inline bool launch_gemm_deep(hipStream_t st, const Operand& A, bool a_kc,
 static thread_local bool g_gemm_last_deep = false;
 // few tiles of k-contiguous operands (pe_pipe.h): false = not launched
 template <class Epi> static inline bool launch_gemm_pipe(hipStream_t st, const Operand& A, const Operand& B, const GemmShape& sh, const Epi& epi);
-static inline bool pipe_over_small(const GemmShape& sh);
 static thread_local bool g_gemm_last_pipe = false;
 
 // Operands that break the 16-byte vector rules (odd leading dimensions) take the
@@ -2496,13 +2495,9 @@ static inline int launch_gemm(hipStream_t st, const Operand& A, bool a_kc, const
     // bf16 parameter gradients have a kernel that is faster even there (gemm_dwx_kernel)
     const bool dwx = std::is_same<Epi, EpiPartial>::value && std::is_same<T, bf16>::value && wave_groups && !a_kc && !b_kc;
     if (!dwx && (sve || Epi::ELEM) && small_gemm_fits<T>(sh.M, sh.N, sh.k_chunk > 0 ? sh.k_chunk : sh.K, sh.batch, a_kc, b_kc)) {
-      if constexpr (std::is_same<T, bf16>::value)
-        g_gemm_last_pipe = ve && a_kc && b_kc && pipe_over_small(sh) && launch_gemm_pipe<Epi>(st, A, B, sh, epi);
-      if (!g_gemm_last_pipe) {
-        launch_gemm_small<T, Epi>(st, A, a_kc, B, b_kc, sh, epi);
-        g_gemm_last_small = true;
-        if (used_vec) *used_vec = sve;
-      }
+      launch_gemm_small<T, Epi>(st, A, a_kc, B, b_kc, sh, epi);
+      g_gemm_last_small = true;
+      if (used_vec) *used_vec = sve;
       return hipGetLastError() == hipSuccess ? 0 : -2;
     }
   }

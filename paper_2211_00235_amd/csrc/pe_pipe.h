@@ -103,9 +103,3 @@ static inline bool launch_gemm_pipe(hipStream_t st, const Operand& A, const Oper
     }
   }
 }
-// Instead of gemm_small_kernel too, where a tile is filled and enough of them share a long contraction (small -> this, us): 1000 x 1024,
-// K 256 10.1 -> 7.4; 2048 x 256, K 1024 13.6 -> 10.0, K 256 8.2 -> 7.0; 4096 x 128, K 512 9.6 -> 8.1; 256 x 256, K 256 7.4 -> 6.9; but 1000 x 256, K 1024 (64 tiles)
-// 9.6 -> 9.8.
-static inline bool pipe_over_small(const GemmShape& sh) {
-  return sh.M >= PIPE_TILE && sh.N >= PIPE_TILE && (sh.K <= 512 || pipe_tiles(sh) >= 128);
-}
