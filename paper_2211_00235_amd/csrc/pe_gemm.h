@@ -119,6 +119,7 @@ enum : int { EF_BIASN = 1, EF_BIASM = 2, EF_ACT = 4, EF_RELUMASK = 8, EF_AUX = 1
 template <typename T> struct EpiGeneric {
   static constexpr bool HAS_COLSUM = false;
   static constexpr bool TM_GATE = false;
+  static constexpr bool SPLIT = false;    // fp32 operands in bf16 terms (GemmCfg)
   static constexpr bool ELEM = true;      // has an element-wise path
   T* out; long long out_batch;
   int om_in;
@@ -328,6 +329,7 @@ template <typename T> static inline EpiGeneric<T> epi_plain(void* out, long long
 struct EpiPartial {
   static constexpr bool HAS_COLSUM = true;
   static constexpr bool TM_GATE = false;
+  static constexpr bool SPLIT = true;
   static constexpr bool ELEM = true;      // has an element-wise path
   float* out; long long mn; int ldn;
   float* colsum;   // nullable: [batch][N] sums over k of the B operand (bias gradients ride on the dW GEMM)
@@ -362,6 +364,7 @@ struct EpiPartial {
 template <typename T> struct EpiAttnPre {
   static constexpr bool HAS_COLSUM = false;
   static constexpr bool TM_GATE = false;
+  static constexpr bool SPLIT = true;
   static constexpr bool ELEM = false;      // has an element-wise path
   const T* gate;       // gate pre-activation plane group: qkvg + 3*H*plane
   const T* o;
@@ -433,6 +436,7 @@ template <typename T> struct EpiAttnPre {
 template <typename T> struct EpiTmGate {
   static constexpr bool HAS_COLSUM = false;
   static constexpr bool TM_GATE = true;
+  static constexpr bool SPLIT = false;
   static constexpr bool ELEM = false;      // has an element-wise path
   T* proj_t; T* a_t; T* b_t;   // proj_t nullptr: not stored (no backward pass follows)
   const float* bias;     // [4 ct] in the order of proj_t's rows
@@ -466,6 +470,7 @@ template <typename T> struct EpiTmGate {
 template <typename T> struct EpiTmGateBwd {
   static constexpr bool HAS_COLSUM = false;
   static constexpr bool TM_GATE = false;
+  static constexpr bool SPLIT = true;
   static constexpr bool ELEM = false;      // has an element-wise path
   const T* proj_t; const float* mask; T* dproj_t;
   int ct, r, side; long long Mz;   // Mz = r * pitch
@@ -518,13 +523,14 @@ template <typename T> struct EpiTmGateBwd {
   }
 };
 
-// fp32 operands are multiplied as three bf16 terms each: v = hi + mid + lo, every term the rest rounded to 8 significant bits.
-// v_mfma_f32_32x32x2_f32 makes 64 flops per cycle and SIMD, the bf16 instruction 1024, so the six products that matter (hi hi,
-// hi mid, mid hi, mid mid, hi lo, lo hi) take 24 x 32 cycles per 64 x 64 of output and 16 of contraction instead of 32 x 64.  What is left
-// out, mid lo + lo mid + lo lo, is at most 2^-24 of |a b|.  One stream, s 128, r 256, us per launch: parameter gradients 90 -> 55,
-// head-major projections 131 -> 101, hidden layers 134 -> 107, cotangents with a LayerNorm 128 -> 103; the step 8522 -> 7260.
-// Against 64 bits (five blocks, s 37..1100, r 33..160) parameter gradients are at 0.53 to 0.70 of the error that fp32 MFMAs
-// left (16 products are summed per instruction instead of 2), outputs and cotangents at 0.42 to 0.84.
+// fp32 operands of the backward pass are multiplied as three bf16 terms each (SPLIT): v = hi + mid + lo, every term the rest rounded
+// to 8 significant bits.  v_mfma_f32_32x32x2_f32 makes 64 flops per cycle and SIMD, the bf16 instruction 1024, so the six products that matter
+// (hi hi, hi mid, mid hi, mid mid, hi lo, lo hi) take 24 x 32 cycles per 64 x 64 of output and 16 of contraction instead of 32 x 64.  What is
+// left out, mid lo + lo mid + lo lo, is at most 2^-24 of |a b|.  One stream, s 128, r 256, us per launch: parameter gradients 90 -> 55, cotangents with
+// a LayerNorm 128 -> 103.  Against 64 bits parameter gradients are at 0.80 to 0.90 of the error that fp32 MFMAs left (16 products are summed per
+// instruction instead of 2).
+// The forward pass, and what has the same epilogue in the backward pass, stays with fp32 MFMAs: its last bits decide which hidden units are on, and
+// two fp32 paths that differ there differ by whole rows of some cotangents.
 // A value beyond the largest bf16 number, an infinity or a NaN has no such terms: see gemm_redo.
 PE_DEV void split3(const f32x4& v, bf16x4 (&t)[3]) {
 #pragma unroll
@@ -542,42 +548,47 @@ PE_DEV void split3(const f32x4& v, bf16x4 (&t)[3]) {
   }
 }
 
-// A tile in LDS is bf16: one plane (bf16 operands), or one per term (fp32).
-template <typename T> struct GemmCfg {
+// A tile in LDS: one plane of what memory holds, or (fp32, SPLIT) a bf16 plane per term.  Sizes and plane offsets are in bf16 elements.
+template <typename T, bool SPLIT = false> struct GemmCfg {
   static constexpr int VEC = Vec16<T>::N;
   static constexpr int BM = 128, BN = 128;
   static constexpr int BK = 8 * VEC;        // 64 (bf16) or 32 (fp32): 128-byte rows in memory
-  static constexpr int TERMS = sizeof(T) == 4 ? 3 : 1;
-  static constexpr int LDSS = sizeof(T) == 4 ? BK : BK + VEC;   // row of a plane of a k-contiguous operand
+  static constexpr int TERMS = SPLIT ? 3 : 1;
+  static constexpr int LDSS = SPLIT ? BK : 72;   // row of a plane of a k-contiguous operand
   static constexpr int tile(int rows) { return TERMS * rows * LDSS; }
-  // LDS element offset of (row, 16-byte chunk c of 8 k) in a plane of a k-contiguous operand.  bf16: 16 bytes of padding, the 16 rows
-  // that a fragment read touches at once fall on 16 different bank groups (row stride 144 bytes).  fp32 (64-byte rows): the chunk
+  // offset of (row, 16-byte chunk c) in a plane of a k-contiguous operand.  One plane: 16 bytes of padding, the 16 rows
+  // that a fragment read touches at once fall on 16 different bank groups (row stride 144 bytes).  Terms (64-byte rows): the chunk
   // is XOR-ed instead, which leaves room for three workgroups per CU; 8 consecutive rows at a chunk fall on all 128 bytes, 16 on all 256.
   static PE_DEV int off(int row, int c) {
-    return sizeof(T) == 4 ? row * LDSS + ((c ^ (((row >> 1) ^ (row >> 3)) & 3)) << 3) : row * LDSS + (c << 3);
+    return SPLIT ? row * LDSS + ((c ^ (((row >> 1) ^ (row >> 3)) & 3)) << 3) : row * LDSS + (c << 3);
   }
-  // The tile of an x-contiguous operand stays in memory order [k][128 rows] (a thread's vector is stored as it was loaded) and its
-  // fragments come from transposing reads (xmem_frag); the 64-byte unit of a row is XOR-ed by k % 4, so that the four
+  // The tile of an x-contiguous operand stays in memory order [k][128 rows] (a thread's vector is stored as it was loaded).
+  // bf16: its fragments come from transposing reads (xmem_frag); the 64-byte unit of a row is XOR-ed by k % 4, so that the four
   // rows of k and both halves of the 32 rows that a read touches cover every bank once.
   static PE_DEV int xoff(int k, int row) { return k * 128 + (row ^ ((k & 3) << 5)); }
+  // fp32 in one plane (elements): a fragment is one element per lane (32 rows at k, 32 rows at k + 1); the row index is XOR-ed by 32 at odd k:
+  // the two halves of a wave read disjoint banks
+  static PE_DEV int xoff32(int k, int row) { return k * 128 + (row ^ ((k & 1) << 5)); }
   // vector c (16 bytes of memory) of a row of a k-contiguous tile of ROWS rows
   template <int ROWS> static PE_DEV void put(bf16* lds, int row, int c, const typename Vec16<T>::type& v) {
-    if constexpr (sizeof(T) == 4) {
+    if constexpr (SPLIT) {
       bf16x4 t[3];
       split3(v, t);
 #pragma unroll
       for (int p = 0; p < 3; p++) *reinterpret_cast<bf16x4*>(lds + p * ROWS * LDSS + off(row, c >> 1) + (c & 1) * 4) = t[p];
     } else {
-      *reinterpret_cast<bf16x8*>(lds + off(row, c)) = v;
+      *reinterpret_cast<typename Vec16<T>::type*>(lds + off(row, c)) = v;
     }
   }
   // the vector from x on at row k of an x-contiguous tile
   static PE_DEV void put_x(bf16* lds, int k, int x, const typename Vec16<T>::type& v) {
-    if constexpr (sizeof(T) == 4) {
+    if constexpr (SPLIT) {
       bf16x4 t[3];
       split3(v, t);
 #pragma unroll
       for (int p = 0; p < 3; p++) *reinterpret_cast<bf16x4*>(lds + p * 128 * BK + xoff(k, x)) = t[p];
+    } else if constexpr (sizeof(T) == 4) {
+      *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(lds) + xoff32(k, x)) = v;
     } else {
       *reinterpret_cast<bf16x8*>(lds + xoff(k, x)) = v;
     }
@@ -594,35 +605,53 @@ PE_DEV bf16x8 xmem_frag(const bf16* tile, int k0, int r0, int l32, int g) {
   return f;
 }
 
-// MFMA operand of 32 rows and 16 k: lane (l32, g) holds k = 8 g + 0..7 of row l32, of each term
-template <typename T> struct GemmFrag {
-  bf16x8 t[GemmCfg<T>::TERMS];
-  // row of a k-contiguous tile of ROWS rows, 16-byte chunk c
-  template <int ROWS> PE_DEV void get(const bf16* lds, int row, int c) {
+// MFMA operand of 32 rows and 16 k: lane (l32, g) holds k = 8 g + 0..7 of row l32, of each term; fp32 in one plane: k = 2 i + g, i = 0..7
+template <typename T, bool SPLIT> struct GemmFrag {
+  typedef GemmCfg<T, SPLIT> C;
+  static constexpr bool F32 = sizeof(T) == 4 && !SPLIT;
+  bf16x8 t[F32 ? 1 : C::TERMS];
+  float f[F32 ? 8 : 1];
+  // row of a k-contiguous tile of ROWS rows, 16 k number kk
+  template <int ROWS> PE_DEV void get(const bf16* lds, int row, int kk, int g) {
+    if constexpr (F32) {
 #pragma unroll
-    for (int p = 0; p < GemmCfg<T>::TERMS; p++) t[p] = *reinterpret_cast<const bf16x8*>(lds + p * ROWS * GemmCfg<T>::LDSS + GemmCfg<T>::off(row, c));
+      for (int i = 0; i < 8; i++) f[i] = reinterpret_cast<const float*>(lds + C::off(row, 0))[kk * 16 + 2 * i + g];
+    } else {
+#pragma unroll
+      for (int p = 0; p < C::TERMS; p++) t[p] = *reinterpret_cast<const bf16x8*>(lds + p * ROWS * C::LDSS + C::off(row, 2 * kk + g));
+    }
   }
   // 16 k from k0, 32 rows from r0 of an x-contiguous tile
   PE_DEV void get_x(const bf16* lds, int k0, int r0, int l32, int g) {
+    if constexpr (F32) {
 #pragma unroll
-    for (int p = 0; p < GemmCfg<T>::TERMS; p++) t[p] = xmem_frag(lds + p * 128 * GemmCfg<T>::BK, k0, r0, l32, g);
+      for (int i = 0; i < 8; i++) f[i] = reinterpret_cast<const float*>(lds)[C::xoff32(k0 + 2 * i + g, r0 + l32)];
+    } else {
+#pragma unroll
+      for (int p = 0; p < C::TERMS; p++) t[p] = xmem_frag(lds + p * 128 * C::BK, k0, r0, l32, g);
+    }
   }
 };
-// acc[i][j] += a[i] b[j], 16 steps of the contraction.  fp32: hi hi goes to acc, the five smaller products to lo (gemm_sum adds them at
+// acc[i][j] += a[i] b[j], 16 steps of the contraction.  SPLIT: hi hi goes to acc, the five smaller products to lo (gemm_sum adds them at
 // the end).  The instruction drops the bits of a product that lie below the accumulator's, towards minus infinity: with all six in one
 // accumulator the sums were as accurate as fp32 MFMAs' one by one, but off to one side, and the gradients of LayerNorm offsets, which
 // add up thousands of them, were 5 to 15 times further from 64 bits.
-template <typename T, int NI, int NJ>
-PE_DEV void gemm_mma(f32x16 (&acc)[NI][NJ], f32x16 (&lo)[NI][NJ], const GemmFrag<T> (&a)[NI], const GemmFrag<T> (&b)[NJ]) {
+template <typename T, bool SPLIT, int NI, int NJ>
+PE_DEV void gemm_mma(f32x16 (&acc)[NI][NJ], f32x16 (&lo)[NI][NJ], const GemmFrag<T, SPLIT> (&a)[NI], const GemmFrag<T, SPLIT> (&b)[NJ]) {
   constexpr int TA[6] = {0, 1, 0, 1, 2, 0}, TB[6] = {0, 0, 1, 1, 0, 2};
+  constexpr bool F32 = sizeof(T) == 4 && !SPLIT;
 #pragma unroll
-  for (int p = 0; p < (sizeof(T) == 4 ? 6 : 1); p++)
+  for (int p = 0; p < (F32 ? 8 : SPLIT ? 6 : 1); p++)
 #pragma unroll
     for (int i = 0; i < NI; i++)
 #pragma unroll
       for (int j = 0; j < NJ; j++) {
-        f32x16& c = p ? lo[i][j] : acc[i][j];
-        c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i].t[TA[p]], b[j].t[TB[p]], c, 0, 0, 0);
+        if constexpr (F32) {
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i].f[p], b[j].f[p], acc[i][j], 0, 0, 0);
+        } else {
+          f32x16& c = p ? lo[i][j] : acc[i][j];
+          c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i].t[TA[p]], b[j].t[TB[p]], c, 0, 0, 0);
+        }
       }
 }
 template <int NI, int NJ> PE_DEV void gemm_zero(f32x16 (&acc)[NI][NJ]) {
@@ -633,8 +662,8 @@ template <int NI, int NJ> PE_DEV void gemm_zero(f32x16 (&acc)[NI][NJ]) {
 #pragma unroll
       for (int e = 0; e < 16; e++) acc[i][j][e] = 0.0f;
 }
-template <typename T, int NI, int NJ> PE_DEV void gemm_sum(f32x16 (&acc)[NI][NJ], const f32x16 (&lo)[NI][NJ]) {
-  if constexpr (sizeof(T) == 4) {
+template <bool SPLIT, int NI, int NJ> PE_DEV void gemm_sum(f32x16 (&acc)[NI][NJ], const f32x16 (&lo)[NI][NJ]) {
+  if constexpr (SPLIT) {
 #pragma unroll
     for (int i = 0; i < NI; i++)
 #pragma unroll
@@ -650,10 +679,10 @@ PE_DEV long long gemm_addr(const Operand& op, int x, int k) {
 }
 // A wave whose fp32 sums are not all finite forms them again with fp32 MFMAs, element by element from memory: the terms of an infinity or
 // of a value that rounds to one in bf16 are not numbers, where the value's own products may be.  (Rows m, n are the wave's first ones.)
-template <typename T, int NI, int NJ>
+template <bool SPLIT, typename T, int NI, int NJ>
 PE_DEV void gemm_redo(f32x16 (&acc)[NI][NJ], const T* pa, const Operand& A, int m, int M, const T* pb, const Operand& B, int n, int N, int kbeg,
                       int kend, int l32, int g) {
-  if constexpr (sizeof(T) == 4) {
+  if constexpr (SPLIT) {
     float t = 0.0f;
 #pragma unroll
     for (int i = 0; i < NI; i++)
@@ -876,25 +905,26 @@ PE_DEV void gemm_load_tile(typename Vec16<T>::type (&regs)[4], const T* base, co
 }
 
 // 128 rows (of the tile's ROWS, from row r0 on) of a k-contiguous tile, or an x-contiguous tile
-template <typename T, bool KC, int ROWS = 128>
+template <typename T, bool SPLIT, bool KC, int ROWS = 128>
 PE_DEV void gemm_store_tile(const typename Vec16<T>::type (&regs)[4], bf16* lds, int tid, int r0 = 0) {
   constexpr int VEC = Vec16<T>::N;
   if (KC) {
 #pragma unroll
-    for (int i = 0; i < 4; i++) GemmCfg<T>::template put<ROWS>(lds, r0 + (tid >> 3) + 32 * i, tid & 7, regs[i]);
+    for (int i = 0; i < 4; i++) GemmCfg<T, SPLIT>::template put<ROWS>(lds, r0 + (tid >> 3) + 32 * i, tid & 7, regs[i]);
   } else {
     constexpr int XB = 128 / VEC;
     const int xb = tid % XB, kb = tid / XB;
 #pragma unroll
-    for (int j = 0; j < 4; j++) GemmCfg<T>::put_x(lds, kb * 4 + j, xb * VEC, regs[j]);
+    for (int j = 0; j < 4; j++) GemmCfg<T, SPLIT>::put_x(lds, kb * 4 + j, xb * VEC, regs[j]);
   }
 }
 
 template <typename T, bool A_KC, bool B_KC, bool AL, bool VE, class Epi, int F = EF_ALL>
-__global__ __launch_bounds__(256, sizeof(T) == 4 ? 2 : 1) void gemm_kernel(Operand A, Operand B, GemmShape sh, Epi epi) {
-  typedef GemmCfg<T> C;
+__global__ __launch_bounds__(256, sizeof(T) == 4 && Epi::SPLIT ? 2 : 1) void gemm_kernel(Operand A, Operand B, GemmShape sh, Epi epi) {
+  constexpr bool SPLIT = sizeof(T) == 4 && Epi::SPLIT;
+  typedef GemmCfg<T, SPLIT> C;
   typedef typename Vec16<T>::type V;
-  __shared__ __attribute__((aligned(16))) bf16 lds_all[C::tile(C::BM) + C::tile(C::BN)];   // 36 KB, fp32 48 KB
+  __shared__ __attribute__((aligned(16))) bf16 lds_all[C::tile(C::BM) + C::tile(C::BN)];   // 36 KB, in terms 48 KB
   bf16* lds_a = lds_all;
   bf16* lds_b = lds_all + C::tile(C::BM);
 
@@ -946,8 +976,8 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 2 : 1) void gemm_kernel(Opera
   }
   for (int k0 = kbeg; k0 < kend; k0 += C::BK) {
     __syncthreads();  // previous tile fully consumed
-    gemm_store_tile<T, A_KC>(ra, lds_a, tid);
-    gemm_store_tile<T, B_KC>(rb, lds_b, tid);
+    gemm_store_tile<T, SPLIT, A_KC>(ra, lds_a, tid);
+    gemm_store_tile<T, SPLIT, B_KC>(rb, lds_b, tid);
     if constexpr (Epi::HAS_COLSUM && CSF) {
       if (do_cs) {
 #pragma unroll
@@ -976,20 +1006,20 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 2 : 1) void gemm_kernel(Opera
     }
 #pragma unroll
     for (int kk = 0; kk < C::BK / 16; kk++) {
-      GemmFrag<T> af[2], bf[2];
+      GemmFrag<T, SPLIT> af[2], bf[2];
 #pragma unroll
       for (int t = 0; t < 2; t++) {
         const int ar = wm * 64 + t * 32, br = wn * 64 + t * 32;
-        if constexpr (A_KC) af[t].template get<C::BM>(lds_a, ar + l32, 2 * kk + g);
+        if constexpr (A_KC) af[t].template get<C::BM>(lds_a, ar + l32, kk, g);
         else af[t].get_x(lds_a, kk * 16, ar, l32, g);
-        if constexpr (B_KC) bf[t].template get<C::BN>(lds_b, br + l32, 2 * kk + g);
+        if constexpr (B_KC) bf[t].template get<C::BN>(lds_b, br + l32, kk, g);
         else bf[t].get_x(lds_b, kk * 16, br, l32, g);
       }
-      gemm_mma<T>(acc, lo, af, bf);
+      gemm_mma<T, SPLIT>(acc, lo, af, bf);
     }
   }
-  gemm_sum<T>(acc, lo);
-  gemm_redo<T>(acc, pa, A, m0 + wm * 64, sh.M, pb, B, n0 + wn * 64, sh.n_rows, kbeg, kend, l32, g);
+  gemm_sum<SPLIT>(acc, lo);
+  gemm_redo<SPLIT>(acc, pa, A, m0 + wm * 64, sh.M, pb, B, n0 + wn * 64, sh.n_rows, kbeg, kend, l32, g);
 
   if constexpr (Epi::HAS_COLSUM && CSF) {
     if (do_cs) {      // the same for the whole workgroup
@@ -1217,10 +1247,11 @@ template <typename T> static inline bool gemm_operand_ok(const Operand& o, bool 
 // ---------------------------------------------------------------------------
 template <typename T, class Epi, int F>
 __global__ __launch_bounds__(256) void gemm64_kernel(Operand A, Operand B, GemmShape sh, Epi epi) {
-  typedef GemmCfg<T> C;
+  constexpr bool SPLIT = sizeof(T) == 4 && Epi::SPLIT;
+  typedef GemmCfg<T, SPLIT> C;
   typedef typename Vec16<T>::type V;
   constexpr int BM = 64;
-  __shared__ __attribute__((aligned(16))) bf16 lds_all[C::tile(BM) + C::tile(C::BN)];   // 27 KB, fp32 36 KB
+  __shared__ __attribute__((aligned(16))) bf16 lds_all[C::tile(BM) + C::tile(C::BN)];   // 27 KB, in terms 36 KB
   bf16* lds_a = lds_all;
   bf16* lds_b = lds_all + C::tile(BM);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -1268,7 +1299,7 @@ __global__ __launch_bounds__(256) void gemm64_kernel(Operand A, Operand B, GemmS
     __syncthreads();  // previous tile fully consumed
 #pragma unroll
     for (int i = 0; i < 2; i++) C::template put<BM>(lds_a, (tid >> 3) + 32 * i, kv, ra[i]);
-    gemm_store_tile<T, true>(rb, lds_b, tid);
+    gemm_store_tile<T, SPLIT, true>(rb, lds_b, tid);
     __syncthreads();
     if (k0 + C::BK < sh.K) {
       load_a(k0 + C::BK);
@@ -1276,15 +1307,15 @@ __global__ __launch_bounds__(256) void gemm64_kernel(Operand A, Operand B, GemmS
     }
 #pragma unroll
     for (int kk = 0; kk < C::BK / 16; kk++) {
-      GemmFrag<T> af[2], bf[1];
-      bf[0].template get<C::BN>(lds_b, wave * 32 + l32, 2 * kk + g);
+      GemmFrag<T, SPLIT> af[2], bf[1];
+      bf[0].template get<C::BN>(lds_b, wave * 32 + l32, kk, g);
 #pragma unroll
-      for (int t = 0; t < 2; t++) af[t].template get<BM>(lds_a, t * 32 + l32, 2 * kk + g);
-      gemm_mma<T>(acc, lo, af, bf);
+      for (int t = 0; t < 2; t++) af[t].template get<BM>(lds_a, t * 32 + l32, kk, g);
+      gemm_mma<T, SPLIT>(acc, lo, af, bf);
     }
   }
-  gemm_sum<T>(acc, lo);
-  gemm_redo<T>(acc, pa, A, m0, sh.M, pb, B, wave * 32, sh.N, 0, sh.K, l32, g);
+  gemm_sum<SPLIT>(acc, lo);
+  gemm_redo<SPLIT>(acc, pa, A, m0, sh.M, pb, B, wave * 32, sh.N, 0, sh.K, l32, g);
 
   // wave-private staging of the 32 x 32 sub-tiles, then 8 consecutive columns per lane
   constexpr int WS = 32 + 4;
@@ -1363,12 +1394,13 @@ template <typename T> struct RowLn {
 // S > 0: tiles by DMA with a ring of S stages (bf16) and BM = 64 or 32 rows, 0: through registers
 template <typename T, int F, int MODE, int HB = 0, bool G2 = false, int S = 0, int BM = 64>
 __global__ __launch_bounds__(256) void gemm64r_kernel(Operand A, Operand B, GemmShape sh, EpiGeneric<T> epi, RowLn<T> ln) {
-  typedef GemmCfg<T> C;
+  constexpr bool SPLIT = sizeof(T) == 4 && MODE == 2;
+  typedef GemmCfg<T, SPLIT> C;
   typedef typename Vec16<T>::type V;
   constexpr int CH = 128, NQ = BM / 16;      // NQ: row groups of a lane
   static_assert(BM == 64 || (BM == 32 && S > 0), "rows of a tile");
   typedef PipeLoop<BM, CH, 1, S> PL;
-  __shared__ __attribute__((aligned(16))) bf16 lds_all[S ? PL::LDS : C::tile(BM) + C::tile(C::BN)];   // 48 or 72 KB; 27 KB, fp32 36 KB
+  __shared__ __attribute__((aligned(16))) bf16 lds_all[S ? PL::LDS : C::tile(BM) + C::tile(C::BN)];   // 48 or 72 KB; 27 KB, in terms 36 KB
   __shared__ __attribute__((aligned(16))) float wbl[HB > 0 ? HB * CH : 4];      // w_bias as [h][c], zero beyond H
   if constexpr (HB > 0) {
     for (int i = threadIdx.x; i < HB * CH; i += 256) {
@@ -1424,7 +1456,7 @@ __global__ __launch_bounds__(256) void gemm64r_kernel(Operand A, Operand B, Gemm
     __syncthreads();  // previous tile fully consumed
 #pragma unroll
     for (int i = 0; i < 2; i++) C::template put<BM>(lds_a, (tid >> 3) + 32 * i, kv, ra[i]);
-    gemm_store_tile<T, true>(rb, lds_b, tid);
+    gemm_store_tile<T, SPLIT, true>(rb, lds_b, tid);
     __syncthreads();
     if (k0 + C::BK < sh.K) {
       load_a(k0 + C::BK);
@@ -1432,15 +1464,15 @@ __global__ __launch_bounds__(256) void gemm64r_kernel(Operand A, Operand B, Gemm
     }
 #pragma unroll
     for (int kk = 0; kk < C::BK / 16; kk++) {
-      GemmFrag<T> af[2], bf[1];
-      bf[0].template get<C::BN>(lds_b, wave * 32 + l32, 2 * kk + g);
+      GemmFrag<T, SPLIT> af[2], bf[1];
+      bf[0].template get<C::BN>(lds_b, wave * 32 + l32, kk, g);
 #pragma unroll
-      for (int t = 0; t < 2; t++) af[t].template get<BM>(lds_a, t * 32 + l32, 2 * kk + g);
-      gemm_mma<T>(acc, lo, af, bf);
+      for (int t = 0; t < 2; t++) af[t].template get<BM>(lds_a, t * 32 + l32, kk, g);
+      gemm_mma<T, SPLIT>(acc, lo, af, bf);
     }
   }
-  gemm_sum<T>(acc, lo);
-  gemm_redo<T>(acc, pa, A, m0, sh.M, pb, B, wave * 32, sh.N, 0, sh.K, l32, g);
+  gemm_sum<SPLIT>(acc, lo);
+  gemm_redo<SPLIT>(acc, pa, A, m0, sh.M, pb, B, wave * 32, sh.N, 0, sh.K, l32, g);
   }
 
   // wave-private staging of the 32 x 32 sub-tiles; lane -> 8 consecutive columns of the rows
@@ -1719,12 +1751,13 @@ __global__ __launch_bounds__(256) void gemm64r_kernel(Operand A, Operand B, Gemm
 // ---------------------------------------------------------------------------
 template <typename T, int S = 0, int BM = 64>
 __global__ __launch_bounds__(256, sizeof(T) == 4 ? 2 : 1) void gemm64w_kernel(Operand A, Operand B, GemmShape sh, RowLn<T> ln) {
-  typedef GemmCfg<T> C;
+  constexpr bool SPLIT = sizeof(T) == 4;
+  typedef GemmCfg<T, SPLIT> C;
   typedef typename Vec16<T>::type V;
   constexpr int CH = 256;
   static_assert(BM == 64 || (BM == 32 && S > 0), "rows of a tile");
   typedef PipeLoop<BM, CH, 1, S> PL;
-  __shared__ __attribute__((aligned(16))) bf16 lds_all[S ? PL::LDS : C::tile(BM) + C::tile(CH)];   // 80 KB; 45 KB, fp32 60 KB
+  __shared__ __attribute__((aligned(16))) bf16 lds_all[S ? PL::LDS : C::tile(BM) + C::tile(CH)];   // 80 KB; 45 KB, in terms 60 KB
   bf16* lds_a = lds_all;
   bf16* lds_b = lds_all + C::tile(BM);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -1775,8 +1808,8 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 2 : 1) void gemm64w_kernel(Op
     __syncthreads();  // previous tile fully consumed
 #pragma unroll
     for (int i = 0; i < 2; i++) C::template put<BM>(lds_a, (tid >> 3) + 32 * i, kv, ra[i]);
-    gemm_store_tile<T, true, CH>(rb0, lds_b, tid);
-    gemm_store_tile<T, true, CH>(rb1, lds_b, tid, 128);
+    gemm_store_tile<T, SPLIT, true, CH>(rb0, lds_b, tid);
+    gemm_store_tile<T, SPLIT, true, CH>(rb1, lds_b, tid, 128);
     __syncthreads();
     if (k0 + C::BK < sh.K) {
       load_a(k0 + C::BK);
@@ -1785,17 +1818,17 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 2 : 1) void gemm64w_kernel(Op
     }
 #pragma unroll
     for (int kk = 0; kk < C::BK / 16; kk++) {
-      GemmFrag<T> af[2], bf[2];
+      GemmFrag<T, SPLIT> af[2], bf[2];
 #pragma unroll
       for (int t = 0; t < 2; t++) {
-        af[t].template get<BM>(lds_a, t * 32 + l32, 2 * kk + g);
-        bf[t].template get<CH>(lds_b, wave * 64 + t * 32 + l32, 2 * kk + g);
+        af[t].template get<BM>(lds_a, t * 32 + l32, kk, g);
+        bf[t].template get<CH>(lds_b, wave * 64 + t * 32 + l32, kk, g);
       }
-      gemm_mma<T>(acc, lo, af, bf);
+      gemm_mma<T, SPLIT>(acc, lo, af, bf);
     }
   }
-  gemm_sum<T>(acc, lo);
-  gemm_redo<T>(acc, pa, A, m0, sh.M, pb, B, wave * 64, sh.N, 0, sh.K, l32, g);
+  gemm_sum<SPLIT>(acc, lo);
+  gemm_redo<SPLIT>(acc, pa, A, m0, sh.M, pb, B, wave * 64, sh.N, 0, sh.K, l32, g);
   }
 
   constexpr int WS = 64 + 4;
