@@ -785,7 +785,7 @@ template <typename T> struct Runner {
       GemmShape sh{(int)M, Cc, K, 1, 0, 0};
       return launch_gemm64r<T, 2>(st, A, B, sh, epi_plain<T>(dxh, Cc), ln, false);
     }
-    const long long gridf = (M + 31) / 32;      // at most: workgroups take 64 rows or 32
+    const long long gridf = sizeof(T) == 2 && (M + 63) / 64 <= 256 ? (M + 31) / 32 : (M + 63) / 64;      // 32-row tiles or 64 (launch_gemm64r): at most
     const int plen = 2 * Cc + (bias_db ? Cc * bias_H : 0);
     // sized by bias_H whether or not the bias path is taken: the planning pass must not depend on pointer values
     float* part = (Cc == 128 || Cc == 256) ? (float*)part_arena(ar).alloc((size_t)gridf * (2 * Cc + Cc * bias_H) * sizeof(float)) : nullptr;

@@ -1953,7 +1953,7 @@ static inline bool launch_gemm64r(hipStream_t st, const Operand& A, const Operan
   if (A.k_stride != 1 || B.k_stride != 1) return false;
   if (!gemm_operand_ok<T>(A, true, sh.M, sh) || !gemm_operand_ok<T>(B, true, sh.N, sh)) return false;
   auto p16 = [](const void* p) { return ((uintptr_t)p) % 16 == 0; };
-  // Up to one round of 64-row tiles over the CUs: 32-row ones, twice the workgroups and half the epilogue in each (one stream, s 90, r 112 step 1217 ->
+  // Up to one round of 64-row tiles over the CUs: 32-row ones, twice the workgroups and half the epilogue in each (branches one after the other, s 90, r 112 step 1217 ->
   // 1189 us, s 40, r 60 845 -> 804; s 128, r 97 forward 351 -> 342).  Two streams: 871 and 871; to two rounds s 128, r 256 2316 -> 2334.
   const bool rows32 = (sh.M + 63) / 64 <= 256;
   // 64-row tiles by DMA only where nothing runs beside them (the AlphaFold2 ordering at s 128, r 256 2666 -> 2649): twice the LDS is room

@@ -5,7 +5,8 @@
 // k-step waits for its loads, stores them to LDS and passes two barriers, and nothing else on the CU fills the gaps; four to fourteen
 // such steps with half of the CUs idle.  Here a step passes one barrier and finds its operands there, and four times the tiles
 // fill the chip.  Per launch (us, gemm_kernel -> this): 10080 x 256, K 1024 22.7 -> 14.6, K 256 12.0 -> 8.6; 9408 x 128, K 1024 21.8 -> 11.7, K 512
-// 14.7 -> 8.6, K 128 9.5 -> 6.8; 3000 x 256, K 1024 21.4 -> 9.8.  One stream, s 128, r 97 forward 378 -> 352, s 90, r 112 392 -> 358, step 1300 -> 1236.
+// 14.7 -> 8.6, K 128 9.5 -> 6.8; 3000 x 256, K 1024 21.4 -> 9.8.  Branches one after the other, s 128, r 97 forward 378 -> 352, s 90, r 112 392 -> 358, step
+// 1300 -> 1236; side by side the step 909 -> 879.
 #pragma once
 #include "pe_gemm.h"
 

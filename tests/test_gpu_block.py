@@ -763,10 +763,11 @@ def test_outer_product_normaliser(s, r):
 
 
 @pytest.mark.parametrize("name,s,r,two_streams,labels", [
-    ("af2_initial", 45, 67, False, ("attn out", "trans 2", "attn dog+pre", "opm project")),      # ragged rows, head-major and [(i,p)][(j,q)] operands
+    ("af2_initial", 131, 67, False, ("attn out", "trans 2", "attn dog+pre", "opm project")),     # ragged rows, head-major and [(i,p)][(j,q)] operands
     ("af2_initial", 131, 33, True, ("attn out", "attn dog+pre")),                                # strided rows (column attention)
-    ("extra_msa", 260, 33, False, ("trans 1", "trans dh")),                                      # one k-step (K = 64), ReLU decisions out and in
-    ("af2_initial", 9, 64, False, ("trimul out", "trimul da+gate")),                             # a batch of 64 x 64 contractions, one tile each
+    ("af2_initial", 60, 50, False, ("attn qkvg", "trans 1", "trans dh")),                        # head-major output, ReLU decisions out and in
+    ("extra_msa", 260, 33, False, ("trans 1",)),                                                 # one k-step (K = 64)
+    ("af2_initial", 5, 128, False, ("trimul out", "trimul da+gate")),                            # a batch of 128 x 128 contractions
 ])
 def test_few_tile_gemms(name, s, r, two_streams, labels):
     """GEMMs of few 64 x 64 tiles with operands by DMA (pe_pipe.h): remainders in rows, one k-step and more, two-level index maps of both
