@@ -671,17 +671,18 @@ template <typename T> struct Runner {
       if (dry || err) return;
       if (!e.vec_ok(N)) { err = PE_ERR_DIMS; if (h) h->last_error = std::string("split-K epilogue alignment: ") + what; return; }
       GemmShape sh{M, N, K, nsplit, (int)kc};
-      EpiPartial ep{part, (long long)M * N, N};
+      typedef std::conditional_t<sizeof(T) == 4, EpiPartialF32, EpiPartial> EP;
+      const EP ep{EpiPartial{part, (long long)M * N, N}};
       prof_begin(st);
       bool al = false, dwx = false;
       int depth = 0;
-      int rc = launch_gemm<T, EpiPartial>(st, A, akc, B, bkc, sh, ep, &al, &dwx, dw_groups(), &depth);
+      int rc = launch_gemm<T, EP>(st, A, akc, B, bkc, sh, ep, &al, &dwx, dw_groups(), &depth);
       char kn[64] = "";
       if (!timed()) {}
       else if (g_gemm_last_small) snprintf(kn, sizeof(kn), "gemm_small_kernel<%s,%s>", akc ? "kc" : "xc", bkc ? "kc" : "xc");
       else if (dwx && depth) snprintf(kn, sizeof(kn), "gemm_dwp_kernel<%d>", depth);
       else if (dwx) snprintf(kn, sizeof(kn), "gemm_dwx_kernel<%d>", dw_groups());
-      else snprintf(kn, sizeof(kn), "gemm_kernel<%s,%s,%s,EpiPartial>", akc ? "kc" : "xc", bkc ? "kc" : "xc", al ? "vec" : "elem");
+      else snprintf(kn, sizeof(kn), "gemm_kernel<%s,%s,%s,EpiPartial%s>", akc ? "kc" : "xc", bkc ? "kc" : "xc", al ? "vec" : "elem", sizeof(T) == 4 ? "F32" : "");
       prof_end(st, what, kn, 2.0 * M * N * K, ((double)M * K + (double)N * K) * sizeof(T));
       if (rc == -1) { err = PE_ERR_DIMS; if (h) h->last_error = std::string("gemm operand alignment: ") + what; return; }
       check(what);

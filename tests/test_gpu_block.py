@@ -428,6 +428,14 @@ def test_fp32_values_beyond_the_largest_bf16_number(s, r):
     _assert(errs, worst, tol, stats)
 
 
+def test_fp32_outer_product_cotangents_on_fp32_mfmas():
+    """The outer product's cotangents are not split into bf16 terms (LayerNorm gradients below them lose accuracy)."""
+    dims, table, inp = _case("extra_msa", dtype=0, s=300, r=64)
+    names = _kernels_by_label(BlockRun(dims, inp))
+    assert names["opm da"] == {"gemm_kernel<kc,kc,vec,EpiPartialF32>"}, names["opm da"]
+    assert names["opm db"] == {"gemm_kernel<kc,xc,vec,EpiPartialF32>"}, names["opm db"]
+
+
 @pytest.mark.parametrize("dtype", [0, 1])
 def test_large_magnitude_inputs(dtype):
     """Inputs drawn 8 times wider (N(0, 64)): LayerNorm inputs of large magnitude and, through the un-normalised
