@@ -529,16 +529,21 @@ template <typename T> struct EpiTmGateBwd {
 // to 8 significant bits.  v_mfma_f32_32x32x2_f32 makes 64 flops per cycle and SIMD, the bf16 instruction 1024, so the six products that matter
 // (hi hi, hi mid, mid hi, mid mid, hi lo, lo hi) take 24 x 32 cycles per 64 x 64 of output and 16 of contraction instead of 32 x 64.  What is
 // left out, mid lo + lo mid + lo lo, is at most 2^-24 of |a b|.  One stream, s 128, r 256, us per launch: parameter gradients 90 -> 55, cotangents with
-// a LayerNorm 128 -> 103.  Against 64 bits parameter gradients are at 0.80 to 0.90 of the error that fp32 MFMAs left (16 products are summed per
-// instruction instead of 2).
+// a LayerNorm 128 -> 103; the step 7900 -> 7320.  Against 64 bits, geometric means of the errors of all gradients over those of fp32 MFMAs (16 products are
+// summed per instruction instead of 2): 0.75 at s 128, r 256, 0.81 at s 64, r 160, 0.89 to 0.90 at extra-MSA widths; no single tensor's is larger (16 seeds).
 // The forward pass, and what has the same epilogue in the backward pass, stays with fp32 MFMAs: its last bits decide which hidden units are on, and
 // two fp32 paths that differ there differ by whole rows of some cotangents.  So do the outer product's cotangents (EpiPartialF32): in bf16 terms the gradients
 // of the global column attention's LayerNorm below them were 1.15 times further from 64 bits (s 300, r 64 and s 1100, r 33).
-// A value beyond the largest bf16 number, an infinity or a NaN has no such terms: see gemm_redo.
-PE_DEV void split3(const f32x4& v, bf16x4 (&t)[3]) {
+// A value beyond the largest bf16 number, an infinity or a NaN has no such terms, and one below 2^-102 has lost bits at bf16's least
+// number, 2^-133: see gemm_redo.
+// What a thread has split: the least 2 |v| - 1 as integers (a zero is the largest one) and the largest |v|
+struct SplitRange { unsigned lo = ~0u; float hi = 0.0f; };
+PE_DEV void split3(const f32x4& v, bf16x4 (&t)[3], SplitRange& rg) {
 #pragma unroll
   for (int e = 0; e < 4; e += 2) {
     float r0 = v[e], r1 = v[e + 1];
+    rg.lo = min(rg.lo, min(2 * __float_as_uint(r0) - 1, 2 * __float_as_uint(r1) - 1));
+    asm("v_max3_f32 %0, %0, |%1|, |%2|" : "+v"(rg.hi) : "v"(r0), "v"(r1));
 #pragma unroll
     for (int p = 0; p < 3; p++) {
       union { bf16x2 b; unsigned u; } w;
@@ -573,10 +578,10 @@ template <typename T, bool SPLIT = false> struct GemmCfg {
   // the two halves of a wave read disjoint banks
   static PE_DEV int xoff32(int k, int row) { return k * 128 + (row ^ ((k & 1) << 5)); }
   // vector c (16 bytes of memory) of a row of a k-contiguous tile of ROWS rows
-  template <int ROWS> static PE_DEV void put(bf16* lds, int row, int c, const typename Vec16<T>::type& v) {
+  template <int ROWS> static PE_DEV void put(bf16* lds, int row, int c, const typename Vec16<T>::type& v, SplitRange& rg) {
     if constexpr (SPLIT) {
       bf16x4 t[3];
-      split3(v, t);
+      split3(v, t, rg);
 #pragma unroll
       for (int p = 0; p < 3; p++) *reinterpret_cast<bf16x4*>(lds + p * ROWS * LDSS + off(row, c >> 1) + (c & 1) * 4) = t[p];
     } else {
@@ -584,10 +589,10 @@ template <typename T, bool SPLIT = false> struct GemmCfg {
     }
   }
   // the vector from x on at row k of an x-contiguous tile
-  static PE_DEV void put_x(bf16* lds, int k, int x, const typename Vec16<T>::type& v) {
+  static PE_DEV void put_x(bf16* lds, int k, int x, const typename Vec16<T>::type& v, SplitRange& rg) {
     if constexpr (SPLIT) {
       bf16x4 t[3];
-      split3(v, t);
+      split3(v, t, rg);
 #pragma unroll
       for (int p = 0; p < 3; p++) *reinterpret_cast<bf16x4*>(lds + p * 128 * BK + xoff(k, x)) = t[p];
     } else if constexpr (sizeof(T) == 4) {
@@ -636,9 +641,9 @@ template <typename T, bool SPLIT> struct GemmFrag {
   }
 };
 // acc[i][j] += a[i] b[j], 16 steps of the contraction.  SPLIT: hi hi goes to acc, the five smaller products to lo (gemm_sum adds them at
-// the end).  The instruction drops the bits of a product that lie below the accumulator's, towards minus infinity: with all six in one
-// accumulator the sums were as accurate as fp32 MFMAs' one by one, but off to one side, and the gradients of LayerNorm offsets, which
-// add up thousands of them, were 5 to 15 times further from 64 bits.
+// the end).  The instruction keeps products to 2^-31 of the accumulator and rounds to nearest, but where the products are the larger ones it drops the
+// accumulator's bits below 2^-24 of the largest product, towards minus infinity: hi hi on top of smaller sums (one accumulator for all six, or
+// the smaller five first) left the gradients of LayerNorm offsets, which add up thousands of results, 5 to 20 times further from 64 bits.
 template <typename T, bool SPLIT, int NI, int NJ>
 PE_DEV void gemm_mma(f32x16 (&acc)[NI][NJ], f32x16 (&lo)[NI][NJ], const GemmFrag<T, SPLIT> (&a)[NI], const GemmFrag<T, SPLIT> (&b)[NJ]) {
   constexpr int TA[6] = {0, 1, 0, 1, 2, 0}, TB[6] = {0, 0, 1, 1, 0, 2};
@@ -680,20 +685,34 @@ PE_DEV long long gemm_addr(const Operand& op, int x, int k) {
   return (long long)((unsigned)x / (unsigned)op.x_in) * op.x_outer + (long long)((unsigned)x % (unsigned)op.x_in) * op.x_stride +
          (long long)((unsigned)k / (unsigned)op.k_in) * op.k_outer + (long long)((unsigned)k % (unsigned)op.k_in) * op.k_stride;
 }
-// A wave whose fp32 sums are not all finite forms them again with fp32 MFMAs, element by element from memory: the terms of an infinity or
-// of a value that rounds to one in bf16 are not numbers, where the value's own products may be.  (Rows m, n are the wave's first ones.)
+// The workgroup's waves share what they have split.  A wave forms its sums again with fp32 MFMAs, element by element from memory, where
+//  - they are not all finite: the terms of an infinity or of a value that rounds to one in bf16 are not numbers, where the value's own products may be;
+//  - a value below 2^-102 was among the operands and it may show: its terms may miss 2^-134, times the other operand.  Below 2^16 on the other
+//    side and over up to 2^20 steps that is at most 2^-98, a fp32 rounding (2^-24) of a sum of 2^-64 or more even by a factor of 2^10.
+// (Keeping the range, and the outer product's cotangents on fp32 MFMAs, cost 3 % of a step at s 128, r 256, 7090 -> 7310 us.  Rows m, n are the
+// wave's first ones.)
+constexpr unsigned SPLIT_TINY = 0x0C800000u;      // 2^-102
+constexpr float SPLIT_HUGE = 65536.0f, SPLIT_LEAST = 5.421010862e-20f;      // 2^16, 2^-64
 template <bool SPLIT, typename T, int NI, int NJ>
 PE_DEV void gemm_redo(f32x16 (&acc)[NI][NJ], const T* pa, const Operand& A, int m, int M, const T* pb, const Operand& B, int n, int N, int kbeg,
-                      int kend, int l32, int g) {
+                      int kend, int l32, int g, const SplitRange& rg) {
   if constexpr (SPLIT) {
-    float t = 0.0f;
+    __shared__ int seen[4];      // per wave: bit 0 a value below SPLIT_TINY, bit 1 one of SPLIT_HUGE or more
+    const int mine = (__any(rg.lo < 2 * SPLIT_TINY - 1) ? 1 : 0) | (__any(rg.hi >= SPLIT_HUGE) ? 2 : 0);
+    seen[threadIdx.x >> 6] = mine;
+    __syncthreads();
+    const int all = seen[0] | seen[1] | seen[2] | seen[3];
+    float t = 0.0f, least = 1.0f;
 #pragma unroll
     for (int i = 0; i < NI; i++)
 #pragma unroll
       for (int j = 0; j < NJ; j++)
 #pragma unroll
-        for (int e = 0; e < 16; e++) t = fmaf(acc[i][j][e], 0.0f, t);
-    if (!__any(t != 0.0f)) return;
+        for (int e = 0; e < 16; e++) {
+          t = fmaf(acc[i][j][e], 0.0f, t);
+          least = fminf(least, fabsf(acc[i][j][e]));
+        }
+    if (!__any(t != 0.0f || ((all & 1) && ((all & 2) || least < SPLIT_LEAST)))) return;
     gemm_zero(acc);
 #pragma unroll 1
     for (int k = kbeg + g; k < kend + g; k += 2) {
@@ -909,16 +928,16 @@ PE_DEV void gemm_load_tile(typename Vec16<T>::type (&regs)[4], const T* base, co
 
 // 128 rows (of the tile's ROWS, from row r0 on) of a k-contiguous tile, or an x-contiguous tile
 template <typename T, bool SPLIT, bool KC, int ROWS = 128>
-PE_DEV void gemm_store_tile(const typename Vec16<T>::type (&regs)[4], bf16* lds, int tid, int r0 = 0) {
+PE_DEV void gemm_store_tile(const typename Vec16<T>::type (&regs)[4], bf16* lds, int tid, SplitRange& rg, int r0 = 0) {
   constexpr int VEC = Vec16<T>::N;
   if (KC) {
 #pragma unroll
-    for (int i = 0; i < 4; i++) GemmCfg<T, SPLIT>::template put<ROWS>(lds, r0 + (tid >> 3) + 32 * i, tid & 7, regs[i]);
+    for (int i = 0; i < 4; i++) GemmCfg<T, SPLIT>::template put<ROWS>(lds, r0 + (tid >> 3) + 32 * i, tid & 7, regs[i], rg);
   } else {
     constexpr int XB = 128 / VEC;
     const int xb = tid % XB, kb = tid / XB;
 #pragma unroll
-    for (int j = 0; j < 4; j++) GemmCfg<T, SPLIT>::put_x(lds, kb * 4 + j, xb * VEC, regs[j]);
+    for (int j = 0; j < 4; j++) GemmCfg<T, SPLIT>::put_x(lds, kb * 4 + j, xb * VEC, regs[j], rg);
   }
 }
 
@@ -961,6 +980,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 && Epi::SPLIT ? 2 : 1) void gem
   f32x16 acc[2][2], lo[2][2];
   gemm_zero(acc);
   gemm_zero(lo);
+  SplitRange rg;
   // column sums of B: for every (batch, n-tile) one of the m-tile workgroups adds up its B tiles
   bool do_cs = false;
   float cs = 0.0f;
@@ -979,8 +999,8 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 && Epi::SPLIT ? 2 : 1) void gem
   }
   for (int k0 = kbeg; k0 < kend; k0 += C::BK) {
     __syncthreads();  // previous tile fully consumed
-    gemm_store_tile<T, SPLIT, A_KC>(ra, lds_a, tid);
-    gemm_store_tile<T, SPLIT, B_KC>(rb, lds_b, tid);
+    gemm_store_tile<T, SPLIT, A_KC>(ra, lds_a, tid, rg);
+    gemm_store_tile<T, SPLIT, B_KC>(rb, lds_b, tid, rg);
     if constexpr (Epi::HAS_COLSUM && CSF) {
       if (do_cs) {
 #pragma unroll
@@ -1022,7 +1042,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 && Epi::SPLIT ? 2 : 1) void gem
     }
   }
   gemm_sum<SPLIT>(acc, lo);
-  gemm_redo<SPLIT>(acc, pa, A, m0 + wm * 64, sh.M, pb, B, n0 + wn * 64, sh.n_rows, kbeg, kend, l32, g);
+  gemm_redo<SPLIT>(acc, pa, A, m0 + wm * 64, sh.M, pb, B, n0 + wn * 64, sh.n_rows, kbeg, kend, l32, g, rg);
 
   if constexpr (Epi::HAS_COLSUM && CSF) {
     if (do_cs) {      // the same for the whole workgroup
@@ -1266,6 +1286,7 @@ __global__ __launch_bounds__(256) void gemm64_kernel(Operand A, Operand B, GemmS
   f32x16 acc[2][1], lo[2][1];
   gemm_zero(acc);
   gemm_zero(lo);
+  SplitRange rg;
 
   // per-thread addressing: k-vector kv = tid % 8, rows tid / 8 + 32 i (2 rows of A, 4 of B)
   const int kv = tid & 7;
@@ -1301,8 +1322,8 @@ __global__ __launch_bounds__(256) void gemm64_kernel(Operand A, Operand B, GemmS
   for (int k0 = 0; k0 < sh.K; k0 += C::BK) {
     __syncthreads();  // previous tile fully consumed
 #pragma unroll
-    for (int i = 0; i < 2; i++) C::template put<BM>(lds_a, (tid >> 3) + 32 * i, kv, ra[i]);
-    gemm_store_tile<T, SPLIT, true>(rb, lds_b, tid);
+    for (int i = 0; i < 2; i++) C::template put<BM>(lds_a, (tid >> 3) + 32 * i, kv, ra[i], rg);
+    gemm_store_tile<T, SPLIT, true>(rb, lds_b, tid, rg);
     __syncthreads();
     if (k0 + C::BK < sh.K) {
       load_a(k0 + C::BK);
@@ -1318,7 +1339,7 @@ __global__ __launch_bounds__(256) void gemm64_kernel(Operand A, Operand B, GemmS
     }
   }
   gemm_sum<SPLIT>(acc, lo);
-  gemm_redo<SPLIT>(acc, pa, A, m0, sh.M, pb, B, wave * 32, sh.N, 0, sh.K, l32, g);
+  gemm_redo<SPLIT>(acc, pa, A, m0, sh.M, pb, B, wave * 32, sh.N, 0, sh.K, l32, g, rg);
 
   // wave-private staging of the 32 x 32 sub-tiles, then 8 consecutive columns per lane
   constexpr int WS = 32 + 4;
@@ -1426,6 +1447,7 @@ __global__ __launch_bounds__(256) void gemm64r_kernel(Operand A, Operand B, Gemm
   f32x16 lo[2][1];
   gemm_zero(acc);
   gemm_zero(lo);
+  SplitRange rg;
   const int kv = tid & 7;
   long long aa[2];
   bool aok[2];
@@ -1458,8 +1480,8 @@ __global__ __launch_bounds__(256) void gemm64r_kernel(Operand A, Operand B, Gemm
   for (int k0 = 0; k0 < sh.K; k0 += C::BK) {
     __syncthreads();  // previous tile fully consumed
 #pragma unroll
-    for (int i = 0; i < 2; i++) C::template put<BM>(lds_a, (tid >> 3) + 32 * i, kv, ra[i]);
-    gemm_store_tile<T, SPLIT, true>(rb, lds_b, tid);
+    for (int i = 0; i < 2; i++) C::template put<BM>(lds_a, (tid >> 3) + 32 * i, kv, ra[i], rg);
+    gemm_store_tile<T, SPLIT, true>(rb, lds_b, tid, rg);
     __syncthreads();
     if (k0 + C::BK < sh.K) {
       load_a(k0 + C::BK);
@@ -1475,7 +1497,7 @@ __global__ __launch_bounds__(256) void gemm64r_kernel(Operand A, Operand B, Gemm
     }
   }
   gemm_sum<SPLIT>(acc, lo);
-  gemm_redo<SPLIT>(acc, pa, A, m0, sh.M, pb, B, wave * 32, sh.N, 0, sh.K, l32, g);
+  gemm_redo<SPLIT>(acc, pa, A, m0, sh.M, pb, B, wave * 32, sh.N, 0, sh.K, l32, g, rg);
   }
 
   // wave-private staging of the 32 x 32 sub-tiles; lane -> 8 consecutive columns of the rows
@@ -1776,6 +1798,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 2 : 1) void gemm64w_kernel(Op
   f32x16 lo[2][2];
   gemm_zero(acc);
   gemm_zero(lo);
+  SplitRange rg;
   const int kv = tid & 7;
   long long aa[2];
   bool aok[2];
@@ -1810,9 +1833,9 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 2 : 1) void gemm64w_kernel(Op
   for (int k0 = 0; k0 < sh.K; k0 += C::BK) {
     __syncthreads();  // previous tile fully consumed
 #pragma unroll
-    for (int i = 0; i < 2; i++) C::template put<BM>(lds_a, (tid >> 3) + 32 * i, kv, ra[i]);
-    gemm_store_tile<T, SPLIT, true, CH>(rb0, lds_b, tid);
-    gemm_store_tile<T, SPLIT, true, CH>(rb1, lds_b, tid, 128);
+    for (int i = 0; i < 2; i++) C::template put<BM>(lds_a, (tid >> 3) + 32 * i, kv, ra[i], rg);
+    gemm_store_tile<T, SPLIT, true, CH>(rb0, lds_b, tid, rg);
+    gemm_store_tile<T, SPLIT, true, CH>(rb1, lds_b, tid, rg, 128);
     __syncthreads();
     if (k0 + C::BK < sh.K) {
       load_a(k0 + C::BK);
@@ -1831,7 +1854,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 2 : 1) void gemm64w_kernel(Op
     }
   }
   gemm_sum<SPLIT>(acc, lo);
-  gemm_redo<SPLIT>(acc, pa, A, m0, sh.M, pb, B, wave * 64, sh.N, 0, sh.K, l32, g);
+  gemm_redo<SPLIT>(acc, pa, A, m0, sh.M, pb, B, wave * 64, sh.N, 0, sh.K, l32, g, rg);
   }
 
   constexpr int WS = 64 + 4;

@@ -2,6 +2,7 @@
 import numpy as np
 import pytest
 
+import paper_2211_00235_amd as pe
 from oracle import evoformer as ev
 from oracle.params import param_table
 from pe_inputs import make_inputs, dims_for
@@ -434,6 +435,110 @@ def test_fp32_outer_product_cotangents_on_fp32_mfmas():
     names = _kernels_by_label(BlockRun(dims, inp))
     assert names["opm da"] == {"gemm_kernel<kc,kc,vec,EpiPartialF32>"}, names["opm da"]
     assert names["opm db"] == {"gemm_kernel<kc,xc,vec,EpiPartialF32>"}, names["opm db"]
+
+
+def _tensor(table, flat, name):
+    e = [x for x in table if x["name"] == name][0]
+    return flat[e["offset"]:e["offset"] + int(np.prod(e["shape"]))].reshape(e["shape"])
+
+
+def _param_grads(dims, inp):
+    """Flat parameter gradients of the HIP path and of the oracle under the path's (validated) ReLU decisions."""
+    args = (dims, inp["params"], inp["msa"], inp["pair"], inp["msa_mask"], inp["pair_mask"])
+    _, _, _, inter = ev.block_fwd(*args, want_cache=False)
+    run = BlockRun(dims, inp)
+    run.fwd(use_ctx=True)
+    run.sync()
+    on, stats, _ = relu_decisions(dims, run, inter)
+    assert all(st["flips_outside"] == 0 for st in stats.values()), stats
+    _, _, cache, _ = ev.block_fwd(*args, relu_on=on)
+    _, _, ref, _ = ev.block_bwd(dims, cache, inp["d_msa_out"], inp["d_pair_out"])
+    run.bwd()
+    run.sync()
+    return to_np(run.d_params), ref
+
+
+def test_fp32_cotangents_too_small_for_three_bf16_terms():
+    """Cotangents of a hidden unit of about 2e-38 (outgoing weights 1e-39) against a weight of 1e38: three bf16 terms hold 13 bits of them
+    (bf16 ends at 2^-133), the products are of order one and make up the gradients of the LayerNorm offset and gain."""
+    dims, table, inp = _case("af2_initial", dtype=0, s=40, r=41)
+    for t in ("mtrans", "ptrans"):
+        _tensor(table, inp["params"], t + ".ln.g")[0] = 0.0
+        _tensor(table, inp["params"], t + ".ln.b")[0] = 2e-38
+        _tensor(table, inp["params"], t + ".w1")[0, 0] = 1e38
+        _tensor(table, inp["params"], t + ".w2")[0, :] = np.float32(1e-39)
+    errs, worst, tol, stats = check_case(dims, table, inp)
+    _assert(errs, worst, tol, stats)
+
+
+@pytest.mark.parametrize("value,scale", [(2.0123e-38, 1.0), (3.4e38, 1e-4)])
+def test_fp32_activations_without_three_bf16_terms(value, scale):
+    """A LayerNorm output channel of 2e-38 (bf16 terms hold 9 bits) or 3.4e38 (infinity in bf16) in every position: that row of the first
+    transition weight's gradient, split along an odd number of positions, rows fewer than a tile's, against float64."""
+    dims, table, inp = _case("extra_msa", dtype=0, s=41, r=53)
+    inp["d_msa_out"] *= scale
+    inp["d_pair_out"] *= scale
+    value = float(np.float32(value))
+    for t in ("mtrans", "ptrans"):
+        _tensor(table, inp["params"], t + ".ln.g")[0] = 0.0
+        _tensor(table, inp["params"], t + ".ln.b")[0] = value
+        if value > 1:
+            _tensor(table, inp["params"], t + ".w1")[0, :] *= 1e-38
+    names = _kernels_by_label(BlockRun(dims, inp))
+    assert names["trans dW1"] == {"gemm_kernel<xc,xc,vec,EpiPartial>"}, names["trans dW1"]
+    got, ref = _param_grads(dims, inp)
+    for t in ("mtrans", "ptrans"):
+        a, b = _tensor(table, got, t + ".w1")[0], _tensor(table, ref, t + ".w1")[0]
+        assert np.linalg.norm(a - b) <= TOL[0] * np.linalg.norm(b), (t, np.linalg.norm(a - b) / np.linalg.norm(b))
+
+
+def test_fp32_weights_beyond_the_largest_bf16_number():
+    """Attention output weights and triangle operands of 3.4e38 against values of 1e-38 on their other side: the attention and triangle
+    cotangents that go through bf16 terms, in every kernel that has them, with ragged tiles."""
+    dims, table, inp = _case("af2_initial", dtype=0, s=46, r=183)
+    inp["d_msa_out"] *= 1e-6
+    inp["d_pair_out"] *= 1e-6
+    for t in ("row", "col", "tas", "tae"):
+        _tensor(table, inp["params"], t + ".w_v")[:, 0] *= 1e-38
+        w = _tensor(table, inp["params"], t + ".w_o")
+        w[0, :] = np.where(w[0, :] < 0, -3.4e38, 3.4e38)
+    for t in ("tmo", "tmi"):
+        _tensor(table, inp["params"], t + ".w_ap")[:, 0] *= 1e-38
+        _tensor(table, inp["params"], t + ".b_ap")[0] = 0.0
+        _tensor(table, inp["params"], t + ".w_bp")[:, 0] = 0.0
+        _tensor(table, inp["params"], t + ".b_bp")[0] = 3.4e38
+        _tensor(table, inp["params"], t + ".w_bg")[:, 0] = 0.0
+        _tensor(table, inp["params"], t + ".b_bg")[0] = 200.0
+    names = _kernels_by_label(BlockRun(dims, inp))
+    assert names["attn dog+pre"] == {"gemm_kernel<kc,kc,vec,EpiAttnPre>", "gemm64_kernel<EpiAttnPre>"}, names["attn dog+pre"]
+    assert all(k.endswith("EpiTmGateBwd>") for k in names["trimul da+gate"]), names["trimul da+gate"]
+    errs, worst, tol, stats = check_case(dims, table, inp)
+    _assert(errs, worst, tol, stats)
+
+
+def test_fp32_long_contraction_of_one_sign():
+    """The second transition weight's gradient over 3072 positions per split of non-negative operands (hidden units, cotangents made
+    positive): its error against float64 has no side.  Half a bit to one side per 16 positions would be 96 x 2^-24 = 6e-6 of every element on average;
+    a rounding per 16 positions and per split of the sum that adds the 32 splits up is at most 224 x 2^-24 = 1.3e-5."""
+    import torch
+    dims, table, inp = _case("af2_initial", dtype=0, s=256, r=384)
+    inp["d_msa_out"] = np.abs(inp["d_msa_out"])
+    inp["d_pair_out"] = np.zeros_like(inp["d_pair_out"])
+    run = BlockRun(dims, inp)
+    run.fwd(use_ctx=True)
+    run.bwd()
+    run.sync()
+    e = [x for x in pe.ctx_table(dims) if x["name"] == "mtrans.h"][0]
+    h = run.ctx[e["offset_bytes"]:e["offset_bytes"] + 4 * e["count"]].view(torch.float32).reshape(256 * 384, -1)
+    g = run.d_msa_out.reshape(256 * 384, -1)
+    ref = torch.zeros(h.shape[1], g.shape[1], dtype=torch.float64, device="cuda")
+    for i in range(0, 256 * 384, 8192):
+        ref += h[i:i + 8192].double().t().contiguous() @ g[i:i + 8192].double()
+    got = torch.from_numpy(_tensor(table, to_np(run.d_params), "mtrans.w2")).cuda()
+    err = (got - ref) / ref.abs().clamp_min(1e-300)
+    mean, rms = float(err.mean()), float((err * err).mean().sqrt())
+    print("mean %.3e rms %.3e max %.3e" % (mean, rms, float(err.abs().max())))
+    assert abs(mean) <= 1e-6 and float(err.abs().max()) <= 1.3e-5, (mean, rms)
 
 
 @pytest.mark.parametrize("dtype", [0, 1])
