@@ -30,8 +30,8 @@
  *    the pair branch runs beside the MSA branch on a stream of the handle
  *    (one after the other for the smallest blocks, one branch, the AF2
  *    ordering, under PE_OPT_KERNEL_TIMING, PE_OPT_SYNC_DEBUG or
- *    PE_OPT_SIDE_STREAMS, and in a capture that is the handle's first
- *    one-stream call).
+ *    PE_OPT_SIDE_STREAMS, and while a capture that has not ended holds another
+ *    call of the handle with one stream and not this one).
  *  - Results are deterministic: no atomics, every reduction in a fixed order.
  *    A call whose branches run one after the other (see above) takes a
  *    parameter-gradient kernel that sums the contraction index in another
@@ -124,9 +124,10 @@ typedef struct pe_ctx_entry {
 } pe_ctx_entry;
 
 /* Handle: owns a few hipEvents used to fork/join the streams and, once
- * PE_OPT_SIDE_STREAMS has been set, two side streams, and after the first
- * call with one stream the pair branch's stream (all of default priority;
- * pe_destroy waits for the work on the last).
+ * PE_OPT_SIDE_STREAMS has been set, two side streams, and the stream of the
+ * pair branch of calls with one stream (all of default priority; the last is
+ * the handle's alone from pe_create to pe_destroy, which gives it back with
+ * the work that is still on it; idle ones are kept, up to eight per device).
  * Host state only.  Not thread safe: one handle per host thread; calls on one
  * handle must not overlap.  The compute calls may be captured into a HIP
  * graph by the caller (they allocate nothing, never synchronise the host and

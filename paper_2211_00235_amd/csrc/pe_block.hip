@@ -48,8 +48,7 @@ struct pe_handle {
   hipStream_t side[2];              // side stream of the MSA branch / of the pair branch
   hipEvent_t side_ev[32];           // ring of fork/join events
   int side_ev_next;
-  hipStream_t pair;                 // the pair branch's stream of calls with one stream (pair_stream), created by the first of them
-  hipEvent_t pair_ev;
+  hipStream_t pair;                 // the pair branch's stream of calls with one stream (pair_stream); null: there is none
   std::vector<ProfRec> recs;        // one per timed launch since the last collect
   std::vector<hipEvent_t> ev_pool;  // reusable timing events
   std::string last_error;
@@ -2174,6 +2173,45 @@ static bool any_alias(const Region* r, int n) {
   return false;
 }
 
+// Streams of the pair branch (pair_stream).  A handle takes one for itself when it is created and gives it back when it is destroyed, with what is
+// queued on it, so that neither waits for the device and a compute call creates nothing (a stream costs 120 us, almost half of a
+// short protein's forward pass; waiting in pe_destroy cost 50).  Up to PAIR_KEPT idle ones are kept per device until the process ends.
+constexpr size_t PAIR_KEPT = 8;
+static std::mutex g_pair_mutex;
+static std::vector<hipStream_t>& pair_kept(int dev) {
+  static std::vector<hipStream_t>* v = new std::vector<hipStream_t>[PE_MAX_DEVICES];      // never destroyed: the HIP runtime may be gone by then
+  return v[dev];
+}
+static bool pair_capturing(hipStream_t st) {
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &cap) != hipSuccess) { (void)hipGetLastError(); return true; }
+  return cap != hipStreamCaptureStatusNone;
+}
+static hipStream_t pair_take(int dev) {
+  {
+    std::lock_guard<std::mutex> lock(g_pair_mutex);
+    std::vector<hipStream_t>& v = pair_kept(dev);
+    for (size_t i = 0; i < v.size(); i++)      // the one that was given back first; not one whose capture has not ended
+      if (!pair_capturing(v[i])) {
+        hipStream_t st = v[i];
+        v.erase(v.begin() + i);
+        return st;
+      }
+  }
+  hipStream_t st = nullptr;
+  if (hipStreamCreateWithFlags(&st, hipStreamNonBlocking) != hipSuccess) { (void)hipGetLastError(); return nullptr; }
+  return st;
+}
+static void pair_give(int dev, hipStream_t st) {
+  {
+    std::lock_guard<std::mutex> lock(g_pair_mutex);
+    std::vector<hipStream_t>& v = pair_kept(dev);
+    if (v.size() < PAIR_KEPT || pair_capturing(st)) { v.push_back(st); return; }
+  }
+  (void)hipStreamSynchronize(st);
+  (void)hipStreamDestroy(st);
+}
+
 extern "C" {
 
 int pe_destroy(pe_handle* h);
@@ -2211,7 +2249,6 @@ int pe_create(pe_handle** out) {
   h->side[0] = h->side[1] = nullptr;
   h->side_ev_next = 0;
   h->pair = nullptr;
-  h->pair_ev = nullptr;
   for (int i = 0; i < 32; i++) h->side_ev[i] = nullptr;
   for (int i = 0; i < 6; i++) {
     if (hipEventCreateWithFlags(&h->ev[i], hipEventDisableTiming) != hipSuccess) {
@@ -2220,6 +2257,7 @@ int pe_create(pe_handle** out) {
       return PE_ERR_HIP;
     }
   }
+  h->pair = pair_take(h->device);
   *out = h;
   return PE_OK;
 }
@@ -2230,11 +2268,7 @@ int pe_destroy(pe_handle* h) {
   for (auto e : h->ev_pool) (void)hipEventDestroy(e);
   for (int i = 0; i < 2; i++) if (h->side[i]) (void)hipStreamDestroy(h->side[i]);
   for (int i = 0; i < 32; i++) if (h->side_ev[i]) (void)hipEventDestroy(h->side_ev[i]);
-  if (h->pair) {
-    (void)hipStreamSynchronize(h->pair);      // work of the last call may still be on it
-    (void)hipStreamDestroy(h->pair);
-    (void)hipEventDestroy(h->pair_ev);
-  }
+  if (h->pair) pair_give(h->device, h->pair);
   delete h;
   return PE_OK;
 }
@@ -2324,8 +2358,8 @@ size_t pe_workspace_bytes(const pe_dims* d, int with_ctx) {
 // 3950 -> 3546, extra-MSA s 300, r 80 1000 -> 626, fp32 s 128, r 128 2900 -> 2600; small widths s 24, r 48 548 -> 519.
 // Two streams cost the host: 40 launches take it 190 us there.  A forward pass over narrow channels (up to 32) that is done earlier stays on one (s 24, r 48 175
 // against 191, s 64, r 64 183 against 190), as do the smallest steps (s 8, r 16 510 against 529).
-// As before for the AlphaFold2 ordering, whose data flow is serial, one branch alone, and calls that time or check
-// kernel by kernel.  The stream is created by the first such call, on the handle's device and not while the caller's stream is captured.
+// As before for the AlphaFold2 ordering, whose data flow is serial, one branch alone, calls that time or check kernel by kernel, on another device than the
+// handle's, and while a capture that has not ended holds the handle's stream and this call is not part of it.
 static bool branches_pay(const pe_dims& d, bool forward) {
   if (d.variant == PE_VARIANT_AF2) return false;
   return std::max(d.c_m, d.c_z) > 32 || (long long)d.r * ((long long)d.s * d.c_m + (long long)d.r * d.c_z) >= (forward ? 1 << 18 : 1 << 14);
@@ -2334,23 +2368,20 @@ static hipStream_t pair_stream(pe_handle* h, hipStream_t sm, hipStream_t sp, boo
   if (sm != sp || !pays || h->branches != 3 || h->timing || h->sync_debug || h->side_streams) return sp;
   int dev = -1;
   if (hipGetDevice(&dev) != hipSuccess || dev != h->device) return sp;
-  if (!h->pair) {
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(sm, &cap) != hipSuccess) { (void)hipGetLastError(); return sp; }
-    if (cap != hipStreamCaptureStatusNone) return sp;
-    if (hipEventCreateWithFlags(&h->pair_ev, hipEventDisableTiming) != hipSuccess) { (void)hipGetLastError(); return sp; }
-    if (hipStreamCreateWithFlags(&h->pair, hipStreamNonBlocking) != hipSuccess) {
-      (void)hipGetLastError();
-      (void)hipEventDestroy(h->pair_ev);
-      h->pair = nullptr;
-      return sp;
-    }
+  if (!h->pair || h->pair == sm) return sp;
+  hipStreamCaptureStatus cp = hipStreamCaptureStatusNone, cm = hipStreamCaptureStatusNone;
+  unsigned long long ip = 0, im = 0;
+  hipError_t e = hipStreamGetCaptureInfo(h->pair, &cp, &ip);
+  if (e == hipSuccess && cp != hipStreamCaptureStatusNone) {
+    e = hipStreamGetCaptureInfo(sm, &cm, &im);
+    if (e == hipSuccess && (cm != cp || im != ip)) return sp;
   }
+  if (e != hipSuccess) { (void)hipGetLastError(); return sp; }
   return h->pair;
 }
 // a call that failed on the way may have left work on the handle's stream: the caller's waits for it
 static int pair_done(pe_handle* h, hipStream_t sm, hipStream_t sp, int rc) {
-  if (rc != PE_OK && sp == h->pair && sp != sm && hipEventRecord(h->pair_ev, sp) == hipSuccess) (void)hipStreamWaitEvent(sm, h->pair_ev, 0);
+  if (rc != PE_OK && sp == h->pair && sp != sm && hipEventRecord(h->ev[5], sp) == hipSuccess) (void)hipStreamWaitEvent(sm, h->ev[5], 0);
   return rc;
 }
 

@@ -1162,6 +1162,131 @@ def test_one_stream_calls_keep_the_order_of_their_stream(name, s, r, variant):
                 assert torch.equal(getattr(r_, k), ref[k]), (rep, k)
 
 
+OUTS = ("msa_out", "pair_out", "d_msa_in", "d_pair_in", "d_params")
+
+
+def _two_stream_outputs(dims, inp):
+    run = BlockRun(dims, inp)
+    run.fwd()
+    run.bwd()
+    run.sync()
+    return {k: getattr(run, k).clone() for k in OUTS}
+
+
+def _clear(run):
+    for k in OUTS:
+        getattr(run, k).zero_()
+
+
+def _one_stream_run(dims, inp):
+    import torch
+    run = BlockRun(dims, inp, two_streams=False)
+    run.sm = run.sp = torch.cuda.Stream()      # (the default stream cannot be captured)
+    return run
+
+
+@pytest.mark.parametrize("first", [True, False])
+def test_first_call_of_a_handle_in_a_capture(first):
+    """A handle whose first one-stream calls are captured gives the bits of any other: three replays with eager work in between.  Handles made
+    and destroyed while the capture is on leave it whole."""
+    import torch
+    dims, table, inp = _case("af2_initial", dtype=1, s=64, r=96)
+    ref = _two_stream_outputs(dims, inp)
+    run, other = _one_stream_run(dims, inp), BlockRun(dims, inp)
+    if not first:
+        run.fwd()
+    graph = torch.cuda.CUDAGraph()
+    _clear(run)
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=run.sm):
+        pe.Handle()
+        run.fwd()
+        run.bwd()
+    for rep in range(3):
+        _clear(run)
+        run.ctx.zero_()
+        other.fwd()
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        for k in OUTS:
+            assert torch.equal(getattr(run, k), ref[k]), (rep, k)
+
+
+def test_one_stream_calls_on_another_stream_during_a_capture():
+    """A handle with a call in a capture that has not ended takes an eager call on another stream, which stays out of the capture."""
+    import torch
+    dims, table, inp = _case("af2_initial", dtype=1, s=17, r=45)
+    ref = _two_stream_outputs(dims, inp)
+    run, eager = _one_stream_run(dims, inp), _one_stream_run(dims, inp)
+    graph = torch.cuda.CUDAGraph()
+    for r in (run, eager):
+        _clear(r)
+    torch.cuda.synchronize()
+    eager.h = run.h
+    with torch.cuda.graph(graph, stream=run.sm):
+        run.fwd()
+        eager.fwd()
+        run.bwd()
+        eager.bwd()
+    eager.sync()
+    for k in OUTS[:4]:      # (branches one after the other sum parameter gradients in another order)
+        assert torch.equal(getattr(eager, k), ref[k]), k
+    _clear(eager)
+    torch.cuda.synchronize()
+    eager.fwd()      # the capture has ended: side by side again
+    eager.bwd()
+    eager.sync()
+    for k in OUTS:
+        assert torch.equal(getattr(eager, k), ref[k]), k
+    for rep in range(3):
+        _clear(run)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        for k in OUTS:
+            assert torch.equal(getattr(run, k), ref[k]), (rep, k)
+
+
+def test_handles_made_and_destroyed_with_work_pending():
+    """Threads that make a handle, call it on a stream of their own and destroy it without waiting, over and over: a handle's stream is passed
+    on with the work that is still on it."""
+    import threading
+    import torch
+    dims, table, inp = _case("extra_msa", dtype=1, s=40, r=35)
+    ref = _two_stream_outputs(dims, inp)
+    runs = [_one_stream_run(dims, inp) for _ in range(4)]
+    got, failed = [[] for _ in runs], []
+
+    def work(i):
+        try:
+            run = runs[i]
+            with torch.cuda.stream(run.sm):
+                for _ in range(6):
+                    run.h = pe.Handle()
+                    _clear(run)
+                    run.fwd()
+                    run.bwd()
+                    run.h = None
+                    got[i].append({k: getattr(run, k).clone() for k in OUTS})
+        except Exception as e:      # noqa: BLE001
+            failed.append(e)
+
+    torch.cuda.synchronize()
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(len(runs))]
+    for th in threads:
+        th.start()
+    for th in threads:
+        th.join()
+    torch.cuda.synchronize()
+    assert not failed, failed
+    for g in got:
+        assert len(g) == 6
+        for o in g:
+            for k in OUTS:
+                assert torch.equal(o[k], ref[k]), k
+
+
 def test_hip_graph_capture_and_replay():
     """The calls only enqueue work on the caller's streams (no allocation, no host synchronisation,
     no memset nodes), so a caller can capture forward + backward into a HIP graph: three replays,
