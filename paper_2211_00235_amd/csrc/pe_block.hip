@@ -49,6 +49,7 @@ struct pe_handle {
   hipEvent_t side_ev[32];           // ring of fork/join events
   int side_ev_next;
   hipStream_t pair;                 // the pair branch's stream of calls with one stream (pair_stream); null: there is none
+  bool pair_forked;                 // the call that is running has forked it from the caller's stream
   std::vector<ProfRec> recs;        // one per timed launch since the last collect
   std::vector<hipEvent_t> ev_pool;  // reusable timing events
   std::string last_error;
@@ -1838,7 +1839,9 @@ static bool hip_ok(pe_handle* h, hipError_t e, const char* what) {
 // `to` waits for everything queued on `from` so far
 static bool ev_link(pe_handle* h, int e, hipStream_t from, hipStream_t to) {
   if (from == to) return true;
-  return hip_ok(h, hipEventRecord(h->ev[e], from), "event record") && hip_ok(h, hipStreamWaitEvent(to, h->ev[e], 0), "stream wait");
+  if (!hip_ok(h, hipEventRecord(h->ev[e], from), "event record") || !hip_ok(h, hipStreamWaitEvent(to, h->ev[e], 0), "stream wait")) return false;
+  if (to == h->pair) h->pair_forked = true;
+  return true;
 }
 
 // Forward schedule of one block (Figure 1).  At entry stream_pair has been forked from stream_msa.
@@ -2249,6 +2252,7 @@ int pe_create(pe_handle** out) {
   h->side[0] = h->side[1] = nullptr;
   h->side_ev_next = 0;
   h->pair = nullptr;
+  h->pair_forked = false;
   for (int i = 0; i < 32; i++) h->side_ev[i] = nullptr;
   for (int i = 0; i < 6; i++) {
     if (hipEventCreateWithFlags(&h->ev[i], hipEventDisableTiming) != hipSuccess) {
@@ -2365,6 +2369,7 @@ static bool branches_pay(const pe_dims& d, bool forward) {
   return std::max(d.c_m, d.c_z) > 32 || (long long)d.r * ((long long)d.s * d.c_m + (long long)d.r * d.c_z) >= (forward ? 1 << 18 : 1 << 14);
 }
 static hipStream_t pair_stream(pe_handle* h, hipStream_t sm, hipStream_t sp, bool pays) {
+  h->pair_forked = false;
   if (sm != sp || !pays || h->branches != 3 || h->timing || h->sync_debug || h->side_streams) return sp;
   int dev = -1;
   if (hipGetDevice(&dev) != hipSuccess || dev != h->device) return sp;
@@ -2379,9 +2384,10 @@ static hipStream_t pair_stream(pe_handle* h, hipStream_t sm, hipStream_t sp, boo
   if (e != hipSuccess) { (void)hipGetLastError(); return sp; }
   return h->pair;
 }
-// a call that failed on the way may have left work on the handle's stream: the caller's waits for it
+// a call that failed after the fork may have left work on the handle's stream: the caller's waits for it
 static int pair_done(pe_handle* h, hipStream_t sm, hipStream_t sp, int rc) {
-  if (rc != PE_OK && sp == h->pair && sp != sm && hipEventRecord(h->ev[5], sp) == hipSuccess) (void)hipStreamWaitEvent(sm, h->ev[5], 0);
+  if (rc != PE_OK && h->pair_forked && sp == h->pair && sp != sm &&
+      (hipEventRecord(h->ev[5], sp) != hipSuccess || hipStreamWaitEvent(sm, h->ev[5], 0) != hipSuccess)) (void)hipGetLastError();
   return rc;
 }
 

@@ -1188,19 +1188,28 @@ def _one_stream_run(dims, inp):
 @pytest.mark.parametrize("first", [True, False])
 def test_first_call_of_a_handle_in_a_capture(first):
     """A handle whose first one-stream calls are captured gives the bits of any other: three replays with eager work in between.  Handles made
-    and destroyed while the capture is on leave it whole."""
+    and destroyed, and a call refused for its workspace, while the capture is on leave it whole."""
     import torch
     dims, table, inp = _case("af2_initial", dtype=1, s=64, r=96)
     ref = _two_stream_outputs(dims, inp)
     run, other = _one_stream_run(dims, inp), BlockRun(dims, inp)
     if not first:
         run.fwd()
+    ws = run.ws
     graph = torch.cuda.CUDAGraph()
     _clear(run)
     torch.cuda.synchronize()
     with torch.cuda.graph(graph, stream=run.sm):
+        run.ws = ws[:256]
+        with pytest.raises(pe.PEError):
+            run.fwd()
+        run.ws = ws
         pe.Handle()
         run.fwd()
+        run.ws = ws[:256]
+        with pytest.raises(pe.PEError):
+            run.bwd()
+        run.ws = ws
         run.bwd()
     for rep in range(3):
         _clear(run)
@@ -1246,6 +1255,29 @@ def test_one_stream_calls_on_another_stream_during_a_capture():
         torch.cuda.synchronize()
         for k in OUTS:
             assert torch.equal(getattr(run, k), ref[k]), (rep, k)
+
+
+def test_refused_calls_leave_no_error_behind():
+    """A refused call with a stream and the default stream (NULL), which a handle without a stream of its own once took for its own, and one
+    with one stream; a valid call follows each."""
+    import torch
+    dims, table, inp = _case("tiny", dtype=1, s=40, r=50)
+    ref = _two_stream_outputs(dims, inp)
+    for streams in ("null", "one"):
+        run = _one_stream_run(dims, inp)
+        if streams == "null":
+            run.sp = torch.cuda.default_stream()
+        ws, run.ws = run.ws, run.ws[:256]
+        with pytest.raises(pe.PEError):
+            run.fwd()
+        with pytest.raises(pe.PEError):
+            run.bwd()
+        run.ws = ws
+        run.fwd()
+        run.bwd()
+        run.sync()
+        for k in OUTS:
+            assert torch.equal(getattr(run, k), ref[k]), (streams, k)
 
 
 def test_handles_made_and_destroyed_with_work_pending():
