@@ -30,8 +30,9 @@
  *    the pair branch runs beside the MSA branch on a stream of the handle
  *    (one after the other for the smallest blocks, one branch, the AF2
  *    ordering, under PE_OPT_KERNEL_TIMING, PE_OPT_SYNC_DEBUG or
- *    PE_OPT_SIDE_STREAMS, and while a capture that has not ended holds another
- *    call of the handle with one stream and not this one).
+ *    PE_OPT_SIDE_STREAMS, on a stream of another priority or with a CU mask,
+ *    and while a capture that has not ended holds another call of the handle
+ *    with one stream and not this one).
  *  - Results are deterministic: no atomics, every reduction in a fixed order.
  *    A call whose branches run one after the other (see above) takes a
  *    parameter-gradient kernel that sums the contraction index in another

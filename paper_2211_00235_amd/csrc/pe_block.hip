@@ -2363,17 +2363,28 @@ size_t pe_workspace_bytes(const pe_dims* d, int with_ctx) {
 // Two streams cost the host: 40 launches take it 190 us there.  A forward pass over narrow channels (up to 32) that is done earlier stays on one (s 24, r 48 175
 // against 191, s 64, r 64 183 against 190), as do the smallest steps (s 8, r 16 510 against 529).
 // As before for the AlphaFold2 ordering, whose data flow is serial, one branch alone, calls that time or check kernel by kernel, on another device than the
-// handle's, and while a capture that has not ended holds the handle's stream and this call is not part of it.
+// handle's, for a caller's stream of another priority or with other compute units than the handle's (half of the work would leave them), and while a
+// capture that has not ended holds the handle's stream and this call is not part of it.
 static bool branches_pay(const pe_dims& d, bool forward) {
   if (d.variant == PE_VARIANT_AF2) return false;
   return std::max(d.c_m, d.c_z) > 32 || (long long)d.r * ((long long)d.s * d.c_m + (long long)d.r * d.c_z) >= (forward ? 1 << 18 : 1 << 14);
+}
+static bool same_attributes(hipStream_t a, hipStream_t b) {
+  int pa = 0, pb = 0;
+  uint32_t ma[32] = {}, mb[32] = {};
+  if (hipStreamGetPriority(a, &pa) != hipSuccess || hipStreamGetPriority(b, &pb) != hipSuccess || hipExtStreamGetCUMask(a, 32, ma) != hipSuccess ||
+      hipExtStreamGetCUMask(b, 32, mb) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return pa == pb && memcmp(ma, mb, sizeof(ma)) == 0;
 }
 static hipStream_t pair_stream(pe_handle* h, hipStream_t sm, hipStream_t sp, bool pays) {
   h->pair_forked = false;
   if (sm != sp || !pays || h->branches != 3 || h->timing || h->sync_debug || h->side_streams) return sp;
   int dev = -1;
   if (hipGetDevice(&dev) != hipSuccess || dev != h->device) return sp;
-  if (!h->pair || h->pair == sm) return sp;
+  if (!h->pair || h->pair == sm || !same_attributes(h->pair, sm)) return sp;
   hipStreamCaptureStatus cp = hipStreamCaptureStatusNone, cm = hipStreamCaptureStatusNone;
   unsigned long long ip = 0, im = 0;
   hipError_t e = hipStreamGetCaptureInfo(h->pair, &cp, &ip);

@@ -1319,6 +1319,37 @@ def test_handles_made_and_destroyed_with_work_pending():
                 assert torch.equal(o[k], ref[k]), k
 
 
+def test_one_stream_calls_stay_on_the_callers_compute_units():
+    """A stream with a CU mask keeps the whole call: its branches run one after the other (the parameter gradients are those of a timed
+    call, which sums them in the order of a call that runs alone)."""
+    import ctypes as C
+    import torch
+    dims, table, inp = _case("af2_initial", dtype=1, s=64, r=96)
+    serial = _one_stream_run(dims, inp)
+    serial.h.set_option(3, 1)             # PE_OPT_KERNEL_TIMING
+    serial.fwd()
+    serial.bwd()
+    serial.sync()
+    beside = _two_stream_outputs(dims, inp)
+    assert not torch.equal(serial.d_params, beside["d_params"])
+    st, mask = C.c_void_p(), (C.c_uint32 * 8)(*([0xffffffff] * 4 + [0] * 4))
+    L = pe.lib()
+    assert L.hipExtStreamCreateWithCUMask(C.byref(st), 8, mask) == 0
+    run = BlockRun(dims, inp, two_streams=False)
+    run.sm = run.sp = torch.cuda.ExternalStream(st.value)
+    run.fwd()
+    run.bwd()
+    run.sync()
+    for k in OUTS:
+        assert torch.equal(getattr(run, k), getattr(serial, k)), k
+    plain = BlockRun(dims, inp, two_streams=False)      # the default stream has no mask
+    plain.fwd()
+    plain.bwd()
+    plain.sync()
+    assert torch.equal(plain.d_params, beside["d_params"])
+    assert L.hipStreamDestroy(st) == 0
+
+
 def test_hip_graph_capture_and_replay():
     """The calls only enqueue work on the caller's streams (no allocation, no host synchronisation,
     no memset nodes), so a caller can capture forward + backward into a HIP graph: three replays,
