@@ -739,7 +739,7 @@ PE_DEV void gemm_redo(f32x16 (&acc)[NI][NJ], const T* pa, const Operand& A, int 
 // 16 bytes per lane from base + off to the lane's 16 bytes from LDS address l on (l: the same for all lanes).  The compiler does not count
 // these: lds_dma_barrier waits for them.
 PE_DEV void lds_dma16(const char* base, unsigned off, unsigned l) {
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "s"(l) : "memory");
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "s"(l) : "memory", "m0");
 }
 // all but this wave's last N vector memory operations are done, in every wave of the workgroup
 template <int N> PE_DEV void lds_dma_barrier() { asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory"); }
