@@ -1246,7 +1246,7 @@ template <typename T> struct Runner {
       gemm_ln(sm, x, PL.opm.ln_g, PL.opm.ln_b, C.opm.mhat, C.opm.stats, Mm, d.c_m, op_plain(W.opm.wt_ab, d.c_m), 2 * co, e, "opm ab");
     }
     if (!dry && !err) {
-      PE_LAUNCH("opm_norm", 2.0 * Mz * d.s, 4.0 * (Mz + Mm), sm, opm_norm_kernel, dim3((r + 31) / 32, (r + 31) / 32), dim3(64 * std::max(1, std::min(8, (d.s + 15) / 16))), 0, msa_mask,
+      PE_LAUNCH("opm_norm", 2.0 * Mz * d.s, 4.0 * (Mz + Mm), sm, opm_norm_kernel, dim3((r + 31) / 32, (r + 31) / 32), dim3(64 * std::max(4, std::min(8, (d.s + 15) / 16))), 0, msa_mask,
                 C.opm.inv_norm, d.s, r, d.opm_eps);
     }
     {

@@ -1428,15 +1428,16 @@ __global__ __launch_bounds__(256) void add2x8_kernel(const T* a, const T* b, T* 
 }
 // ---------------------------------------------------------------------------
 // Outer product mean normaliser: inv_norm[i][j] = 1 / (eps + sum_s mask[s][i] mask[s][j])
-// A workgroup has a 32 x 32 tile of residue pairs on the fp32 matrix unit (products of 0 / 1 masks and their sums are exact); its waves, one
-// for every 16 sequences up to eight, take 16 sequences at a time in turn and add up through LDS.  With a thread per pair, walking
-// through all sequences alone, the launch was a chain of memory round trips (us, then -> now): s 90, r 112 11.1 -> 5.0; s 128, r 97
-// 5.4 -> 4.4; s 24, r 48 4.8 -> 4.0; s 512, r 384 46 -> 20; s 5120, r 384 251 -> 77 (sixteen waves 56 there, but 57 at s 512 beside the pair
-// branch, where their workgroups wait for a whole CU).
+// A workgroup has a 32 x 32 tile of residue pairs on the fp32 matrix unit (products of 0 / 1 masks and their sums are exact); its four to eight waves
+// take 16 sequences at a time in turn and add up through LDS.  With a thread per pair, walking
+// through all sequences alone, the launch was a chain of memory round trips (us, then -> now): s 8, r 16 2.1 -> 2.4; s 16, r 33 3.6 -> 2.9; s 24, r 48 4.4 -> 3.1; s 90, r 112
+// 10.3 -> 4.0; s 512, r 384 46 -> 20; s 5120, r 384 251 -> 77 (sixteen waves 56 there, but 57 at s 512 beside the pair
+// branch, where their workgroups wait for a whole CU).  One wave per 16 sequences, which up to 16 adds and stores 1024 pairs alone: 3.9 at s 8, r 16, 4.9 at s 16, r 33.
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(512) void opm_norm_kernel(const float* mask, float* inv_norm, int s, int r, float eps) {
   __shared__ float part[8][1024];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6, l32 = lane & 31, g = lane >> 5;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l32 = lane & 31, g = lane >> 5;
+  const int nw = min((int)blockDim.x >> 6, (s + 15) >> 4);      // waves that have sequences
   const int i0 = blockIdx.y * 32, j0 = blockIdx.x * 32;
   const float* pi = mask + min(i0 + l32, r - 1);
   const float* pj = mask + min(j0 + l32, r - 1);
@@ -1454,8 +1455,10 @@ __global__ __launch_bounds__(512) void opm_norm_kernel(const float* mask, float*
 #pragma unroll
     for (int u = 0; u < 8; u++) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[u], b[u], acc, 0, 0, 0);
   }
+  if (wave < nw) {
 #pragma unroll
-  for (int e = 0; e < 16; e++) part[wave][acc_row(g, e) * 32 + l32] = acc[e];
+    for (int e = 0; e < 16; e++) part[wave][acc_row(g, e) * 32 + l32] = acc[e];
+  }
   __syncthreads();
   for (int q = threadIdx.x; q < 1024; q += blockDim.x) {
     const int i = i0 + (q >> 5), j = j0 + (q & 31);
