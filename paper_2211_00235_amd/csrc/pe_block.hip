@@ -744,7 +744,7 @@ template <typename T> struct Runner {
       prof_begin(st);
       if (launch_gemm64r<T, 1>(st, A, B, sh, e, ln)) {
         char kn[64] = "";
-        if (timed()) snprintf(kn, sizeof(kn), "gemm64r_kernel<F=%d,MODE=1,HB=%d>", g_gemm_last_features, nxt.direct ? (nxt.H <= 4 ? 4 : 8) : 0);
+        if (timed()) snprintf(kn, sizeof(kn), "gemm64r_kernel<F=%d,MODE=1,HB=%d,DMA=%d>", g_gemm_last_features, nxt.direct ? (nxt.H <= 4 ? 4 : 8) : 0, g_gemm64r_dma);
         prof_end(st, what, kn, 2.0 * M * N * K, ((double)M * K + (double)N * K + 2.0 * M * N) * sizeof(T));
         check(what);
         ln_done_set(nxt.y);
@@ -812,8 +812,8 @@ template <typename T> struct Runner {
       if (launch_gemm64r<T, 2>(st, A, B, sh, e, ln, true, &tiles)) {
         char kn[64] = "";
         if (!timed()) {}
-        else if (Cc == 256) snprintf(kn, sizeof(kn), "gemm64w_kernel<F=0,MODE=2>");
-        else snprintf(kn, sizeof(kn), "gemm64r_kernel<F=0,MODE=2,HB=%d,G2=%d>", bias_db ? (bias_H <= 4 ? 4 : 8) : 0, fin ? 1 : 0);
+        else if (Cc == 256) snprintf(kn, sizeof(kn), "gemm64w_kernel<F=0,MODE=2,DMA=%d>", g_gemm64r_dma);
+        else snprintf(kn, sizeof(kn), "gemm64r_kernel<F=0,MODE=2,HB=%d,G2=%d,DMA=%d>", bias_db ? (bias_H <= 4 ? 4 : 8) : 0, fin ? 1 : 0, g_gemm64r_dma);
         prof_end(st, what, kn, 2.0 * M * Cc * K,
                  ((double)M * K + (double)Cc * K + (gin ? 3.0 : 2.0) * M * Cc + (acc ? 1.0 : 0.0) * M * Cc) * sizeof(T));
         check(what);

@@ -1969,6 +1969,8 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 2 : 1) void gemm64w_kernel(Op
 // feature mask of the kernel instantiation that the last launch_gemm call of this host thread took (EF_ALL = the
 // general kernel); read by the caller to label the launch with the exact kernel symbol
 static thread_local int g_gemm_last_features = EF_ALL;
+// rows of the tiles by DMA of this host thread's last launch_gemm64r, 0: through registers
+static thread_local int g_gemm64r_dma = 0;
 
 // launches the row-complete kernel when its conditions hold (N == 128, k-contiguous aligned operands, the vector
 // epilogue, one of the feature sets below); false: nothing was launched and the caller takes the separate kernels
@@ -1988,6 +1990,7 @@ static inline bool launch_gemm64r(hipStream_t st, const Operand& A, const Operan
   constexpr int SP = std::is_same<T, bf16>::value ? 2 : 0;
   const int bm = pipe && rows32 ? 32 : 64;
   if (tiles) *tiles = (sh.M + bm - 1) / bm;
+  g_gemm64r_dma = pipe ? bm : 0;
   const dim3 grid((unsigned)((sh.M + bm - 1) / bm)), block(256);
   if (sh.N == 256) {   // the 256-channel kernel: LayerNorm backward only, without the options
     if constexpr (MODE == 1) {

@@ -79,11 +79,15 @@ def relu_decisions(dims, run, inter):
     return out, stats, errs
 
 
-def check_case(dims, table, inp, two_streams=True, use_ctx=True, verbose=False, plain_backward=False):
+def check_case(dims, table, inp, two_streams=True, use_ctx=True, verbose=False, plain_backward=False, timed=False):
+    """timed: under PE_OPT_KERNEL_TIMING, which with one stream runs the branches one after the other, each with the chip to itself;
+    stats["kernels"] then has the kernels that each label of this very run took."""
     tol = TOL[dims["dtype"]]
     args = (dims, inp["params"], inp["msa"], inp["pair"], inp["msa_mask"], inp["pair_mask"])
     m0, z0, cache0, inter0 = ev.block_fwd(*args, want_cache=plain_backward)
     run = BlockRun(dims, inp, two_streams=two_streams)
+    if timed:
+        run.h.set_option(3, 1)
     run.fwd(use_ctx=True)
     run.sync()
     errs = {}
@@ -113,6 +117,10 @@ def check_case(dims, table, inp, two_streams=True, use_ctx=True, verbose=False, 
     errs["d_msa_in"] = rel_err(got["d_msa_in"], dm)
     errs["d_pair_in"] = rel_err(got["d_pair_in"], dz)
     errs.update({"d_params." + k: v for k, v in param_errors(got["d_params"], g, table).items()})
+    if timed:
+        stats["kernels"] = {}
+        for e in run.h.timing_collect():
+            stats["kernels"].setdefault(e["name"], set()).add(e["kernel"])
     stats["sizes"] = {"d_params." + e["name"]: int(np.prod(e["shape"])) for e in table}
     worst = max(errs, key=errs.get)
     plain = {}
@@ -125,5 +133,5 @@ def check_case(dims, table, inp, two_streams=True, use_ctx=True, verbose=False, 
     if verbose:
         for k, v in list(errs.items()) + list(plain.items()):
             print("  %-32s %.3e" % (k, v))
-        print("  relu:", {k: v for k, v in stats.items() if k not in ("plain", "sizes")})
+        print("  relu:", {k: v for k, v in stats.items() if k not in ("plain", "sizes", "kernels")})
     return errs, worst, tol, stats

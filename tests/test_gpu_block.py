@@ -292,10 +292,13 @@ def test_af2_initial_bf16():
 
 
 def test_af2_initial_bf16_one_stream():
-    """Config 2 with both branches on one stream: a call that has the chip to itself takes the
-    parameter-gradient GEMM with two wave groups; every output element against the oracle."""
+    """Config 2 on one stream, side by side on the handle's own, and one branch after the other: a branch that has the chip to
+    itself takes the parameter-gradient GEMM with two wave groups; every output element against the oracle."""
     dims, table, inp = _case("af2_initial")
     _assert(*check_case(dims, table, inp, two_streams=False))
+    errs, worst, tol, stats = check_case(dims, table, inp, two_streams=False, timed=True)
+    assert any("gemm_dwx_kernel<2>" in v for v in stats["kernels"].values()), stats["kernels"]
+    _assert(errs, worst, tol, stats)
 
 
 def test_ragged_shapes_one_stream_bf16():
@@ -304,7 +307,8 @@ def test_ragged_shapes_one_stream_bf16():
                              d_pair=8, c_tri=24, c_opm=16, n_trans=2)
     table, n = param_table(dims)
     inp = make_inputs(dims, table, n, ("random_residues", 0.07), 5)
-    errs, worst, tol, stats = check_case(dims, table, inp, two_streams=False)
+    errs, worst, tol, stats = check_case(dims, table, inp, two_streams=False, timed=True)
+    assert any("gemm_dwx_kernel<2>" in v for v in stats["kernels"].values()), stats["kernels"]
     _assert_small(errs, tol, stats)
 
 
@@ -312,7 +316,7 @@ def test_ragged_shapes_one_stream_bf16():
 def test_random_small_shapes_fp32(two_streams):
     """Six seeded random draws of every size parameter (sequences 3..69, residues 8..200, channel widths, head
     counts and dimensions, hidden sizes, block ordering), fp32 path at 1e-4, with the branches on two streams and
-    on one (the call that runs alone takes other parameter-gradient kernels)."""
+    on one (side by side on the handle's own stream but for the smallest)."""
     rng = np.random.default_rng(123)
     for i in range(6):
         dims, _, _ = dims_for("tiny")
@@ -336,8 +340,8 @@ def test_af2_initial_fp32():
 def test_recompute_and_single_stream_match():
     """Backward with ctx == NULL (internal recompute), both branches on one stream, and the
     parameter-gradient kernels on library-owned side streams (PE_OPT_SIDE_STREAMS) give
-    bit-identical results to the two-stream, saved-ctx run.  One exception: on one stream the bf16
-    parameter-gradient GEMMs split their k range over two wave groups, so their fp32 sums are taken
+    bit-identical results to the two-stream, saved-ctx run.  One exception: where one stream's branches run one after the
+    other (a timed call), the bf16 parameter-gradient GEMMs split their k range over two wave groups, so their fp32 sums are taken
     in another order there: parameter gradients agree to fp32 rounding instead."""
     import torch
     from tests.gpu_util import BlockRun
@@ -345,9 +349,11 @@ def test_recompute_and_single_stream_match():
     table, n = param_table(dims)
     inp = make_inputs(dims, table, n, ("last_residues", 5), 9)
     outs = []
-    for two, use_ctx, side in ((True, True, False), (False, True, False), (True, False, False), (True, True, True),
-                               (True, False, True)):
+    for two, use_ctx, side, timed in ((True, True, False, False), (False, True, False, True), (True, False, False, False),
+                                      (True, True, True, False), (True, False, True, False), (False, True, False, False)):
         run = BlockRun(dims, inp, two_streams=two)
+        if timed:
+            run.h.set_option(3, 1)
         if side:
             run.h.set_option(4, 1)
         run.fwd()
@@ -361,7 +367,7 @@ def test_recompute_and_single_stream_match():
     for idx, other in enumerate(outs[1:], 1):
         for a, b in zip(outs[0][:4], other[:4]):
             assert torch.equal(a, b)
-        if idx == 1:    # the one-stream run
+        if idx == 1:    # one branch after the other
             scale = outs[0][4].abs().max().item()
             assert (outs[0][4] - other[4]).abs().max().item() <= 1e-5 * scale
         else:
@@ -853,10 +859,10 @@ def test_row_streaming_gemms(name, s, r, two_streams, ks):
     dims, table, inp = _case(name, s=s, r=r)
     table, n = param_table(dims)
     inp = make_inputs(dims, table, n, ("random_residues", 0.1), s + r)
-    run = BlockRun(dims, inp, two_streams=two_streams)
-    seen = {k.split("K=")[1].rstrip(">") for k in _kernel_launches(run) if k.startswith("gemm_rows_kernel")}
+    errs, worst, tol, stats = check_case(dims, table, inp, two_streams=two_streams, timed=True)
+    kernels = set().union(*stats["kernels"].values())
+    seen = {k.split("K=")[1].rstrip(">") for k in kernels if k.startswith("gemm_rows_kernel")}
     assert {str(k) for k in ks} <= seen, seen
-    errs, worst, tol, stats = check_case(dims, table, inp, two_streams=two_streams)
     _assert(errs, worst, tol, stats)
 
 
@@ -888,18 +894,23 @@ def test_few_tile_gemms(name, s, r, two_streams, labels):
     dims, table, inp = _case(name, s=s, r=r)
     table, n = param_table(dims)
     inp = make_inputs(dims, table, n, ("random_residues", 0.1), s + r)
-    names = _kernels_by_label(BlockRun(dims, inp, two_streams=two_streams))
+    errs, worst, tol, stats = check_case(dims, table, inp, two_streams=two_streams, timed=True)
     for k in labels:
-        assert any(v.startswith("gemm_pipe_kernel") for v in names[k]), (k, names[k])
-    errs, worst, tol, stats = check_case(dims, table, inp, two_streams=two_streams)
+        assert any(v.startswith("gemm_pipe_kernel") for v in stats["kernels"][k]), (k, stats["kernels"][k])
     _assert(errs, worst, tol, stats)
 
 
-@pytest.mark.parametrize("s,r", [(5, 127), (5, 128), (5, 129), (129, 127)])
-def test_row_complete_epilogues_on_32_and_64_rows(s, r):
-    """The row-complete kernels at the line between 32-row tiles (up to 16384 rows) and 64-row tiles, and with remainders in both."""
+@pytest.mark.parametrize("s,r,msa,pair", [(5, 127, 32, 32), (5, 128, 32, 32), (5, 129, 32, 64), (129, 127, 32, 32), (129, 131, 64, 64)])
+def test_row_complete_epilogues_on_32_and_64_rows(s, r, msa, pair):
+    """The row-complete kernels by DMA, which a branch that runs alone takes on every size, at the line between 32-row tiles (up to 16384
+    rows) and 64-row tiles, and with remainders in both: LayerNorm forward (pair stack), LayerNorm backward on 128 and 256 channels, with the
+    bias path and with the last sum of the pair gradient."""
     dims, table, inp = _case("af2_initial", s=s, r=r)
-    errs, worst, tol, stats = check_case(dims, table, inp, two_streams=False)
+    errs, worst, tol, stats = check_case(dims, table, inp, two_streams=False, timed=True)
+    seen = {k for v in stats["kernels"].values() for k in v if k.startswith("gemm64r") or k.startswith("gemm64w")}
+    assert {k.rsplit("DMA=", 1)[-1] for k in seen if k.startswith("gemm64w")} == {"%d>" % msa}, seen
+    assert {k.rsplit("DMA=", 1)[-1] for k in seen if k.startswith("gemm64r")} == {"%d>" % pair}, seen
+    assert {k.split(",")[1] for k in seen if k.startswith("gemm64r")} == {"MODE=1", "MODE=2"}, seen
     _assert(errs, worst, tol, stats)
 
 
