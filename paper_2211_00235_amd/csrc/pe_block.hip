@@ -2358,16 +2358,22 @@ size_t pe_workspace_bytes(const pe_dims* d, int with_ctx) {
 // The stream of the pair branch.  A caller that passes one stream gets the branches side by side all the same, the pair branch on a
 // stream of the handle: every call makes stream_pair wait for stream_msa at its entry and joins the two before it returns, so for
 // the caller the work stays in the order of its own stream.  Half of the launches of a short protein leave most CUs idle and the other
-// branch's fill them.  One after the other -> side by side, us: forward s 128, r 97 334 -> 270, s 16, r 33 216 -> 189; step s 90, r 112 1186 -> 892, s 300, r 256
-// 3950 -> 3546, extra-MSA s 300, r 80 1000 -> 626, fp32 s 128, r 128 2900 -> 2600; small widths s 24, r 48 548 -> 519.
+// branch's fill them.  One after the other -> side by side, us: forward s 128, r 97 334 -> 270, s 16, r 33 224 -> 189, s 128, r 256 777 -> 696, s 512, r 384 2483 ->
+// 2367, extra-MSA s 5120, r 384 6414 -> 6346; step s 90, r 112 1186 -> 885, s 300, r 256 3950 -> 3546, s 512, r 384 8859 -> 8410 (recomputed 11246 -> 10788),
+// extra-MSA s 300, r 80 1000 -> 626, s 1024, r 256 3669 -> 3302, s 5120, r 384 19839 -> 19432, fp32 s 128, r 256 7509 -> 6958; small widths s 24, r 48 561 -> 490:
+// nothing large enough to lose was found.
 // Two streams cost the host: 40 launches take it 190 us there.  A forward pass over narrow channels (up to 32) that is done earlier stays on one (s 24, r 48 175
-// against 191, s 64, r 64 183 against 190), as do the smallest steps (s 8, r 16 510 against 529).
+// against 191, s 64, r 64 183 against 190), as do the smallest steps (s 8, r 16 510 against 529), and narrow steps of the multimer ordering, which have more to wait for
+// in the host's shadow: a program that calls three handles in turn goes from stream to stream (s 8, r 59 594 one after the other, 616 side by side; s 64, r 64 581 and
+// 571 to 583; with one handle 564 and 499, 581 and 545).
 // As before for the AlphaFold2 ordering, whose data flow is serial, one branch alone, calls that time or check kernel by kernel, on another device than the
 // handle's, for a caller's stream of another priority or with other compute units than the handle's (half of the work would leave them), and while a
 // capture that has not ended holds the handle's stream and this call is not part of it.
 static bool branches_pay(const pe_dims& d, bool forward) {
   if (d.variant == PE_VARIANT_AF2) return false;
-  return std::max(d.c_m, d.c_z) > 32 || (long long)d.r * ((long long)d.s * d.c_m + (long long)d.r * d.c_z) >= (forward ? 1 << 18 : 1 << 14);
+  const bool narrow = std::max(d.c_m, d.c_z) <= 32;
+  if (narrow && !forward && d.variant == PE_VARIANT_MULTIMER) return false;
+  return !narrow || (long long)d.r * ((long long)d.s * d.c_m + (long long)d.r * d.c_z) >= (forward ? 1 << 18 : 1 << 14);
 }
 static bool same_attributes(hipStream_t a, hipStream_t b) {
   int pa = 0, pb = 0;
