@@ -1429,10 +1429,10 @@ __global__ __launch_bounds__(256) void add2x8_kernel(const T* a, const T* b, T* 
 // ---------------------------------------------------------------------------
 // Outer product mean normaliser: inv_norm[i][j] = 1 / (eps + sum_s mask[s][i] mask[s][j])
 // A workgroup has a 32 x 32 tile of residue pairs on the fp32 matrix unit (products of 0 / 1 masks and their sums are exact); its four to eight waves
-// take 16 sequences at a time in turn and add up through LDS.  With a thread per pair, walking
-// through all sequences alone, the launch was a chain of memory round trips (us, then -> now): s 8, r 16 2.1 -> 2.4; s 16, r 33 3.6 -> 2.9; s 24, r 48 4.4 -> 3.1; s 90, r 112
-// 10.3 -> 4.0; s 512, r 384 46 -> 20; s 5120, r 384 251 -> 77 (sixteen waves 56 there, but 57 at s 512 beside the pair
-// branch, where their workgroups wait for a whole CU).  One wave per 16 sequences, which up to 16 adds and stores 1024 pairs alone: 3.9 at s 8, r 16, 4.9 at s 16, r 33.
+// take 16 sequences at a time in turn and add up through LDS, up to 16 sequences all of them, without LDS.  With a thread per pair, walking
+// through all sequences alone, the launch was a chain of memory round trips (us, then -> now): s 8, r 16 2.1 -> 2.1; s 16, r 33 3.8 -> 2.5; s 24, r 48 4.6 -> 3.1; s 90,
+// r 112 10.5 -> 4.0; s 512, r 384 46 -> 20; s 5120, r 384 251 -> 77 (sixteen waves 56 there, but 57 at s 512 beside the pair
+// branch, where their workgroups wait for a whole CU).  One wave per 16 sequences, which up to 16 adds and stores 1024 pairs alone: 3.9 at s 8, r 16, 4.8 at s 16, r 33.
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(512) void opm_norm_kernel(const float* mask, float* inv_norm, int s, int r, float eps) {
   __shared__ float part[8][1024];
@@ -1444,7 +1444,7 @@ __global__ __launch_bounds__(512) void opm_norm_kernel(const float* mask, float*
   f32x16 acc;
 #pragma unroll
   for (int e = 0; e < 16; e++) acc[e] = 0.0f;
-  for (int t0 = wave * 16; t0 < s; t0 += nw * 16) {
+  for (int t0 = nw == 1 ? 0 : wave * 16; t0 < s; t0 += nw * 16) {
     float a[8], b[8];
 #pragma unroll
     for (int u = 0; u < 8; u++) {
@@ -1454,6 +1454,18 @@ __global__ __launch_bounds__(512) void opm_norm_kernel(const float* mask, float*
     }
 #pragma unroll
     for (int u = 0; u < 8; u++) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[u], b[u], acc, 0, 0, 0);
+  }
+  if (nw == 1) {      // four waves with the same sums: each stores a quarter of the rows
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+      if (wave != q) continue;
+#pragma unroll
+      for (int e = 4 * q; e < 4 * q + 4; e++) {
+        const int i = i0 + acc_row(g, e), j = j0 + l32;
+        if (i < r && j < r) inv_norm[(long long)i * r + j] = 1.0f / (eps + acc[e]);
+      }
+    }
+    return;
   }
   if (wave < nw) {
 #pragma unroll
