@@ -1984,9 +1984,12 @@ static inline bool launch_gemm64r(hipStream_t st, const Operand& A, const Operan
   // Up to one round of 64-row tiles over the CUs: 32-row ones, twice the workgroups and half the epilogue in each (branches one after the other, s 90, r 112 step 1217 ->
   // 1189 us, s 40, r 60 845 -> 804; s 128, r 97 forward 351 -> 342).  Two streams: 871 and 871; to two rounds s 128, r 256 2316 -> 2334.
   const bool rows32 = (sh.M + 63) / 64 <= 256;
-  // 64-row tiles by DMA only where nothing runs beside them (the AlphaFold2 ordering at s 128, r 256 2666 -> 2649): twice the LDS is room
-  // that the other branch's workgroups would have filled (s 128, r 256 on two streams 2325 -> 2332)
-  const bool pipe = std::is_same<T, bf16>::value && (rows32 || !sh.beside) && pipe_operand_ok(A, sh.M, sh.K) && pipe_operand_ok(B, sh.N, sh.K);
+  // 64-row tiles by DMA only where nothing runs beside them: twice the LDS is room that the other branch's workgroups would have filled (s 128, r 256 on
+  // two streams 2325 -> 2332).  LayerNorm forward (MODE 1) only up to 768 tiles, three per CU, which is what the LDS holds: through registers all 1024
+  // tiles of r = 256 are there at once.  AlphaFold2 ordering, through registers -> by DMA -> this rule: forward s 128, r 256 766 -> 780 -> 764, s 121, r 237 734 -> 746 ->
+  // 731; step s 128, r 256 2588 -> 2593 -> 2574, s 200, r 200 2688 -> 2656 -> 2657, s 300, r 256 3871 -> 3854 -> 3837.  The same line for the LayerNorm
+  // backward: 2580, 2681 and 3878.
+  const bool pipe = std::is_same<T, bf16>::value && (rows32 || (!sh.beside && (MODE == 2 || (sh.M + 63) / 64 <= 768))) && pipe_operand_ok(A, sh.M, sh.K) && pipe_operand_ok(B, sh.N, sh.K);
   constexpr int SP = std::is_same<T, bf16>::value ? 2 : 0;
   const int bm = pipe && rows32 ? 32 : 64;
   if (tiles) *tiles = (sh.M + bm - 1) / bm;
