@@ -29,8 +29,9 @@
  *    call is then ordered like any other work on that stream, and inside it
  *    the pair branch runs beside the MSA branch on a stream of the handle
  *    (one after the other for the smallest blocks, backward calls of narrow
- *    blocks in the multimer ordering, one branch, the AF2 ordering, under PE_OPT_KERNEL_TIMING, PE_OPT_SYNC_DEBUG or
- *    PE_OPT_SIDE_STREAMS, on a stream of another priority or with a CU mask,
+ *    blocks in the multimer ordering, one branch, the AF2 ordering, under
+ *    PE_OPT_KERNEL_TIMING, PE_OPT_SYNC_DEBUG or PE_OPT_SIDE_STREAMS,
+ *    on a stream of another priority or with a CU mask,
  *    and while a capture that has not ended holds another call of the handle
  *    with one stream and not this one).
  *  - Results are deterministic: no atomics, every reduction in a fixed order.
